@@ -364,6 +364,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
                 st.s[jb] = mfma(*reinterpret_cast<const bf16x8*>(kbuf0 + st.rm[kk] + jb * 32 * D * 2), st.qf[kk], st.s[jb]);
         }
         st.tnext = n_tiles_w > 0 ? lane_max(st.s) : -INFINITY;
+        // iteration 0 issues K(2) into the buffer that S^T(0) has just been read from: every wave must be done with it (a
+        // wave whose rows lie past the end of the chunk reads nothing here and would otherwise run ahead with its copies)
+        if (n_tiles > 2) __syncthreads();
 
         // iteration kt: K(kt+1) in kbuf[(kt+1) & 1], V(kt) in vbuf[kt & 1]; issues K(kt+2) -> kbuf[kt & 1] and
         // V(kt+1) -> vbuf[(kt+1) & 1], both free since the barrier at the top
