@@ -249,7 +249,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
     constexpr int kTileBytes = G::kTileBytes;
     // K tiles kt+1 / kt+2 and V tiles kt / kt+1: two buffers each
     __shared__ __attribute__((aligned(1024))) char lds[4 * kTileBytes];
-    __shared__ int next_slot;
+    // the slot handed round after an item, double-buffered: between two hand-overs there is one barrier, and with a single
+    // word the leader could overwrite it before a late wave has read it (items that only write zeros pass no other barrier)
+    __shared__ int next_slot[2];
     char* const kbuf0 = lds;
     char* const vbuf0 = lds + 2 * kTileBytes;
     const uint32_t kdst0 = lds_address(lds), vdst0 = kdst0 + 2 * kTileBytes;   // the same buffers as copy destinations
@@ -460,13 +462,13 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
 
     // ---- the persistent loop: the first item is the workgroup's own slot, the others are drawn from its queue
     int slot = blockIdx.x;
-    for (;;) {
+    for (int turn = 0;; turn ^= 1) {
         const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, slot);
         if (item.tile < 0) break;          // padding at the end of the queue: nothing left
         run_item(item);
-        if (tid == 0) next_slot = drawn;
-        __syncthreads();                   // publishes next_slot; every wave has left the item's LDS areas
-        slot = __builtin_amdgcn_readfirstlane(next_slot);
+        if (tid == 0) next_slot[turn] = drawn;
+        __syncthreads();                   // publishes the slot; every wave has left the item's LDS areas
+        slot = __builtin_amdgcn_readfirstlane(next_slot[turn]);
         if (slot >= p.num_items) break;
     }
     if (tid == 0) queue.leave();
