@@ -254,11 +254,12 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
                 offset[kind] = offset[HSPMD_LIST_FWD];
                 continue;
             }
-            const std::vector<hspmd_work_item> list = hspmd::build_work_list(
+            std::vector<hspmd_work_item> list = hspmd::build_work_list(
                 (hspmd_list_kind)kind, cu, num_seqs, plan->q_heads, plan->kv_heads, hspmd::kNumXcd, plan->order);
             count[kind] = (int64_t)list.size();
             offset[kind] = all.size();
-            all.insert(all.end(), list.begin(), list.end());
+            if (all.empty()) all = std::move(list);
+            else all.insert(all.end(), list.begin(), list.end());
         }
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
@@ -298,11 +299,12 @@ hspmd_status fill_block_plan(hspmd_attn_plan* plan, const int32_t* cu_q, const i
                 offset[kind] = offset[HSPMD_LIST_FWD];
                 continue;
             }
-            const std::vector<hspmd_block_item> list = hspmd::build_block_list(
+            std::vector<hspmd_block_item> list = hspmd::build_block_list(
                 (hspmd_list_kind)kind, cu_q, cu_k, q_pos, k_pos, num_seqs, plan->q_heads, plan->kv_heads, hspmd::kNumXcd);
             count[kind] = (int64_t)list.size();
             offset[kind] = all.size();
-            all.insert(all.end(), list.begin(), list.end());
+            if (all.empty()) all = std::move(list);
+            else all.insert(all.end(), list.begin(), list.end());
         }
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");

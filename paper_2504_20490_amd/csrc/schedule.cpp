@@ -21,7 +21,6 @@
 
 #include <algorithm>
 #include <numeric>
-#include <queue>
 
 namespace hspmd {
 
@@ -49,79 +48,125 @@ int64_t item_cost(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t g
     return ceil_div(last_key, kFwdKTile);
 }
 
-// Steps 2-5 of the placement, shared by the packed and the block lists: cut chains into segments, assign the
-// segments to queues by the longest-processing-time rule, order each queue, interleave the queues.
-template <typename Item, typename Cost>
-static std::vector<Item> place_chains(std::vector<std::vector<Item>>& chains, int64_t total_cost, int32_t num_queues,
-                                      Cost cost_of, Item pad) {
-    struct Seg {
-        int64_t cost = 0;
-        int64_t first_cost = 0;
-        int64_t order = 0;                 // creation index: keeps ties deterministic
-        std::vector<Item> items;
-    };
-    if (chains.empty()) return {};
-    // 2. cut chains into segments no heavier than 1/(4 * queues) of the total
+// The placement, shared by the packed and the block lists: chains are cut into segments, segments are assigned to queues
+// by the longest-processing-time rule, each queue is ordered, the queues are interleaved.
+//
+// The list is rebuilt for every pack, on the host, ahead of that pack's first kernel, so its cost counts.  Two facts keep
+// it at a few nanoseconds per item: the kv heads of a sequence have equal chains, so costs and cuts are computed once per
+// sequence and not per head; and nothing but segment descriptors is sorted, items are generated once, straight into their
+// slots.  A whole refill (two lists and their upload), against chains held as vectors of items: 57 sequences of 32 .. 506
+// tokens, 16 heads (2 x 2496 items) 231 -> 38 us; 14 sequences, 32 heads on 8 (16576 + 4144 items) 167 -> 67 us.
+namespace {
+
+// A run of items of one sequence's chain; the chains of all `copies` kv heads of the sequence hold it.
+struct SegmentClass {
+    int64_t cost, first_cost;   // of the whole run; of its first (most expensive) item
+    int64_t order0, stride;     // creation index of kv head g's copy: order0 + g * stride
+    int32_t seq, first, count;
+};
+
+// Walks the segments of all kv heads in the order (key descending, creation index ascending): `visit(class, kv head)`.
+// Copies of one class carry consecutive heads and classes of one sequence alternate head by head, so only the classes are
+// sorted and runs of equal keys within a sequence are walked head-first.
+template <typename Key, typename Visit>
+void walk_segments(const std::vector<SegmentClass>& classes, int32_t copies, Key key, Visit visit) {
+    std::vector<int32_t> by_key(classes.size());
+    std::iota(by_key.begin(), by_key.end(), 0);
+    std::stable_sort(by_key.begin(), by_key.end(), [&](int32_t a, int32_t b) { return key(classes[a]) > key(classes[b]); });
+    for (size_t i = 0; i < by_key.size();) {
+        size_t end = i + 1;
+        while (end < by_key.size() && key(classes[by_key[end]]) == key(classes[by_key[i]]) &&
+               classes[by_key[end]].seq == classes[by_key[i]].seq)
+            ++end;
+        for (int32_t g = 0; g < copies; ++g)
+            for (size_t j = i; j < end; ++j) visit(classes[by_key[j]], g);
+        i = end;
+    }
+}
+
+// chain_len(s): items of one kv head's chain of sequence s, most expensive first; cost_of(s, i): of its i-th item;
+// make(s, g, i): that item for kv head g.
+template <typename Item, typename ChainLen, typename Cost, typename Make>
+std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_queues, ChainLen chain_len, Cost cost_of,
+                               Make make, Item pad) {
+    int64_t total_cost = 0;
+    for (int32_t s = 0; s < num_seqs; ++s) {
+        const int32_t n = chain_len(s);
+        for (int32_t i = 0; i < n; ++i) total_cost += cost_of(s, i);
+    }
+    total_cost *= kv_heads;
+
+    // cut chains into segments no heavier than 1/(4 * queues) of the total
     const int64_t cap = std::max<int64_t>(1, total_cost / ((int64_t)num_queues * 4));
-    std::vector<Seg> segments;
-    for (auto& chain : chains) {
-        Seg seg;
-        for (const auto& it : chain) {
+    std::vector<SegmentClass> classes;
+    int64_t segments = 0;
+    for (int32_t s = 0; s < num_seqs; ++s) {
+        const int32_t n = chain_len(s);
+        if (n <= 0) continue;
+        const size_t first_class = classes.size();
+        SegmentClass seg{0, 0, 0, 0, s, 0, 0};
+        for (int32_t i = 0; i < n; ++i) {
             // an item that only writes zeros (block variant) still occupies a workgroup slot: weight 1, so that
             // such items spread over the queues instead of piling up in one
-            const int64_t c = std::max<int64_t>(1, cost_of(it));
-            if (!seg.items.empty() && seg.cost + c > cap) {
-                seg.order = (int64_t)segments.size();
-                segments.push_back(std::move(seg));
-                seg = Seg();
+            const int64_t c = std::max<int64_t>(1, cost_of(s, i));
+            if (seg.count > 0 && seg.cost + c > cap) {
+                classes.push_back(seg);
+                seg = SegmentClass{0, 0, 0, 0, s, i, 0};
             }
-            if (seg.items.empty()) seg.first_cost = c;
-            seg.items.push_back(it);
+            if (seg.count == 0) seg.first_cost = c;
+            ++seg.count;
             seg.cost += c;
         }
-        if (!seg.items.empty()) {
-            seg.order = (int64_t)segments.size();
-            segments.push_back(std::move(seg));
+        classes.push_back(seg);
+        const int64_t per_head = (int64_t)(classes.size() - first_class);
+        for (int64_t k = 0; k < per_head; ++k) {
+            classes[first_class + k].order0 = segments + k;
+            classes[first_class + k].stride = per_head;
         }
+        segments += per_head * kv_heads;
     }
+    if (classes.empty()) return {};
 
-    // 3. longest-processing-time assignment of segments to queues
-    std::vector<size_t> by_cost(segments.size());
-    std::iota(by_cost.begin(), by_cost.end(), 0);
-    std::stable_sort(by_cost.begin(), by_cost.end(),
-                     [&](size_t a, size_t b) { return segments[a].cost > segments[b].cost; });
-    using Load = std::pair<int64_t, int32_t>;  // (load, queue)
-    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> loads;
-    for (int32_t x = 0; x < num_queues; ++x) loads.push({0, x});
-    std::vector<std::vector<size_t>> queue_segments(num_queues);
-    for (size_t idx : by_cost) {
-        Load l = loads.top();
-        loads.pop();
-        queue_segments[l.second].push_back(idx);
-        l.first += segments[idx].cost;
-        loads.push(l);
-    }
+    // longest-processing-time assignment: each segment, heaviest first, goes to the least loaded queue (the lowest index
+    // among equals).  The loads are a binary heap whose root is replaced, never popped and pushed.
+    struct Load {
+        int64_t load;
+        int32_t queue;
+        bool before(const Load& o) const { return load != o.load ? load < o.load : queue < o.queue; }
+    };
+    std::vector<Load> heap((size_t)num_queues);
+    for (int32_t x = 0; x < num_queues; ++x) heap[x] = Load{0, x};   // sorted, hence a heap
+    std::vector<int32_t> queue_of((size_t)segments);
+    std::vector<int64_t> length((size_t)num_queues, 0);
+    walk_segments(classes, kv_heads, [](const SegmentClass& c) { return c.cost; }, [&](const SegmentClass& c, int32_t g) {
+        Load root = heap[0];
+        queue_of[(size_t)(c.order0 + g * c.stride)] = root.queue;
+        length[(size_t)root.queue] += c.count;
+        root.load += c.cost;
+        size_t at = 0;
+        for (size_t child = 1; child < heap.size(); child = 2 * at + 1) {
+            if (child + 1 < heap.size() && heap[child + 1].before(heap[child])) ++child;
+            if (!heap[child].before(root)) break;
+            heap[at] = heap[child];
+            at = child;
+        }
+        heap[at] = root;
+    });
 
-    // 4. inside a queue: segments by their most expensive item, then creation order
-    std::vector<std::vector<Item>> queues(num_queues);
-    size_t longest = 0;
-    for (int32_t x = 0; x < num_queues; ++x) {
-        auto& segs = queue_segments[x];
-        std::stable_sort(segs.begin(), segs.end(), [&](size_t a, size_t b) {
-            if (segments[a].first_cost != segments[b].first_cost) return segments[a].first_cost > segments[b].first_cost;
-            return segments[a].order < segments[b].order;
-        });
-        for (size_t idx : segs)
-            queues[x].insert(queues[x].end(), segments[idx].items.begin(), segments[idx].items.end());
-        longest = std::max(longest, queues[x].size());
-    }
-
-    // 5. interleave: slot p belongs to queue p % num_queues; pad short queues
-    std::vector<Item> out(longest * (size_t)num_queues, pad);
-    for (int32_t x = 0; x < num_queues; ++x)
-        for (size_t i = 0; i < queues[x].size(); ++i) out[i * (size_t)num_queues + (size_t)x] = queues[x][i];
+    // inside a queue: segments by their most expensive item, then creation order; slot p belongs to queue
+    // p % num_queues, short queues are padded at their end
+    const int64_t longest = *std::max_element(length.begin(), length.end());
+    std::vector<Item> out((size_t)(longest * num_queues), pad);
+    std::vector<int64_t> cursor((size_t)num_queues);
+    std::iota(cursor.begin(), cursor.end(), (int64_t)0);
+    walk_segments(classes, kv_heads, [](const SegmentClass& c) { return c.first_cost; }, [&](const SegmentClass& c, int32_t g) {
+        int64_t& slot = cursor[(size_t)queue_of[(size_t)(c.order0 + g * c.stride)]];
+        for (int32_t i = c.first; i < c.first + c.count; ++i, slot += num_queues) out[(size_t)slot] = make(c.seq, g, i);
+    });
     return out;
 }
+
+}  // namespace
 
 // The two orders without placement: used only to measure what the default order buys.
 static std::vector<hspmd_work_item> build_plain_list(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs,
@@ -150,27 +195,24 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
     const int32_t group = hq / hkv;
     const int tile_rows = (kind == HSPMD_LIST_DKV) ? kDkvKTile : kFwdQTile;
 
-    // 1. chains: all items that share one (sequence, kv head), most expensive first
-    std::vector<std::vector<hspmd_work_item>> chains;
-    int64_t total_cost = 0;
-    for (int32_t s = 0; s < num_seqs; ++s) {
-        const int32_t len = cu[s + 1] - cu[s];
-        if (len <= 0) continue;
-        const int32_t n_tiles = (int32_t)ceil_div(len, tile_rows);
-        for (int32_t g = 0; g < hkv; ++g) {
-            std::vector<hspmd_work_item> chain;
-            if (kind == HSPMD_LIST_DKV) {
-                for (int32_t t = 0; t < n_tiles; ++t) chain.push_back({cu[s], len, t, g});
-            } else {
-                for (int32_t t = n_tiles - 1; t >= 0; --t)
-                    for (int32_t h = g * group; h < (g + 1) * group; ++h) chain.push_back({cu[s], len, t, h});
-            }
-            for (const auto& it : chain) total_cost += item_cost(kind, it.seq_len, it.tile, group);
-            chains.push_back(std::move(chain));
-        }
-    }
+    // a chain: all items that share one (sequence, kv head), most expensive first
+    auto tile_of = [=](int32_t len, int32_t i) {
+        return kind == HSPMD_LIST_DKV ? i : (int32_t)ceil_div(len, tile_rows) - 1 - i / group;
+    };
     return place_chains<hspmd_work_item>(
-        chains, total_cost, num_queues, [&](const hspmd_work_item& it) { return item_cost(kind, it.seq_len, it.tile, group); },
+        num_seqs, hkv, num_queues,
+        [&](int32_t s) {
+            const int32_t n_tiles = (int32_t)ceil_div(cu[s + 1] - cu[s], tile_rows);
+            return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
+        },
+        [&](int32_t s, int32_t i) {
+            const int32_t len = cu[s + 1] - cu[s];
+            return item_cost(kind, len, tile_of(len, i), group);
+        },
+        [&](int32_t s, int32_t g, int32_t i) {
+            const int32_t len = cu[s + 1] - cu[s];
+            return hspmd_work_item{cu[s], len, tile_of(len, i), kind == HSPMD_LIST_DKV ? g : g * group + i % group};
+        },
         hspmd_work_item{0, 0, -1, 0});
 }
 
@@ -244,36 +286,22 @@ std::vector<hspmd_block_item> build_block_list(hspmd_list_kind kind, const int32
                                                const int32_t* q_pos, const int32_t* k_pos, int32_t num_seqs,
                                                int32_t hq, int32_t hkv, int32_t num_queues) {
     const int32_t group = hq / hkv;
-    std::vector<std::vector<hspmd_block_item>> chains;
-    int64_t total_cost = 0;
-    for (int32_t s = 0; s < num_seqs; ++s) {
-        const int32_t q_len = cu_q[s + 1] - cu_q[s], k_len = cu_k[s + 1] - cu_k[s];
-        const int32_t rows = (kind == HSPMD_LIST_DKV) ? k_len : q_len;     // rows of the outputs the list owns
-        if (rows <= 0) continue;
-        const int tile_rows = (kind == HSPMD_LIST_DKV) ? kDkvKTile : kFwdQTile;
-        const int32_t n_tiles = (int32_t)ceil_div(rows, tile_rows);
-        const hspmd_block_item proto{cu_q[s], q_len, cu_k[s], k_len, q_pos[s] - k_pos[s], 0, 0, q_pos[s]};
-        for (int32_t g = 0; g < hkv; ++g) {
-            std::vector<hspmd_block_item> chain;
-            auto add = [&](int32_t tile, int32_t head) {
-                hspmd_block_item it = proto;
-                it.tile = tile;
-                it.head = head;
-                chain.push_back(it);
-            };
-            if (kind == HSPMD_LIST_DKV) {
-                for (int32_t t = 0; t < n_tiles; ++t) add(t, g);
-            } else {
-                for (int32_t t = n_tiles - 1; t >= 0; --t)
-                    for (int32_t h = g * group; h < (g + 1) * group; ++h) add(t, h);
-            }
-            // most expensive first inside a chain (with a shift the cost is still monotone in the tile index)
-            for (const auto& it : chain) total_cost += block_item_cost(kind, it, group);
-            chains.push_back(std::move(chain));
-        }
-    }
+    const int tile_rows = (kind == HSPMD_LIST_DKV) ? kDkvKTile : kFwdQTile;
+    auto rows_of = [&](int32_t s) { return (kind == HSPMD_LIST_DKV) ? cu_k[s + 1] - cu_k[s] : cu_q[s + 1] - cu_q[s]; };
+    auto make = [&](int32_t s, int32_t g, int32_t i) {
+        hspmd_block_item it{cu_q[s], cu_q[s + 1] - cu_q[s], cu_k[s], cu_k[s + 1] - cu_k[s], q_pos[s] - k_pos[s], 0, 0, q_pos[s]};
+        it.tile = kind == HSPMD_LIST_DKV ? i : (int32_t)ceil_div(rows_of(s), tile_rows) - 1 - i / group;
+        it.head = kind == HSPMD_LIST_DKV ? g : g * group + i % group;
+        return it;
+    };
+    // most expensive first inside a chain (with a shift the cost is still monotone in the tile index)
     return place_chains<hspmd_block_item>(
-        chains, total_cost, num_queues, [&](const hspmd_block_item& it) { return block_item_cost(kind, it, group); },
+        num_seqs, hkv, num_queues,
+        [&](int32_t s) {
+            const int32_t n_tiles = (int32_t)ceil_div(rows_of(s), tile_rows);   // rows of the outputs the list owns
+            return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
+        },
+        [&](int32_t s, int32_t i) { return block_item_cost(kind, make(s, 0, i), group); }, make,
         hspmd_block_item{0, 0, 0, 0, 0, -1, 0, 0});
 }
 
