@@ -92,6 +92,13 @@ struct DkvTileLoad {
             global_to_lds<4>(stat, (uint32_t)lane * 4u, stat_dst);
         }
     }
+    // the same with the index as an argument that is constant after unrolling
+    __device__ __forceinline__ void piece_at(int n) const {
+        if (n < Copy::kPerWave) qcopy->issue_full_one_at(n, stage, q_row, wave);
+        else if (n < 2 * Copy::kPerWave)
+            docopy->issue_full_one_at(n - Copy::kPerWave, stage + DkvGeom<D>::kTileBytes, do_row, wave);
+        else if (n == 2 * Copy::kPerWave) global_to_lds<4>(stat, (uint32_t)lane * 4u, stat_dst);
+    }
 };
 
 __device__ __forceinline__ bf16x8 lds_read128(const char* lds, int addr) {
@@ -108,20 +115,25 @@ __device__ __forceinline__ bf16x8 lds_read_tr(const char* lds, int a0, int a1) {
     return u.v;
 }
 
-// One pipelined iteration on block i (RB = i & 1 is its position inside its 64-row tile).
+// One pipelined iteration on block i (RB = i & 1 selects the accumulator pair that holds its S' / dP').
 //   `cur`: addresses in the stage of block i's tile; `ahead`: addresses in the stage of block i+1's tile.
+//   WHOLE: the wave takes both 32-row blocks of every tile in turn, so RB is also block i's position inside its tile and
+//   block i+1 sits at the other one (of the next tile when RB == 1).  Otherwise the wave takes the same block of every
+//   tile and the position is part of the addresses.
 // dkey = my_key - (first row of block i) - 4 * (lane / 32): element e of an accumulator fragment is a
 // masked (row < key) pair iff 8 * (e / 4) + e % 4 < dkey.
 // SPREAD: the iteration also issues its share of the copies of a later tile (`load`), one instruction at a
 // time at fixed places among its LDS reads (the copies are ordered against LDS accesses, the reads are tied
-// to the MFMAs by the scheduling hints): pieces 0-3 in the first iteration of a tile, 4-8 in the second.
-template <int D, int KD, int RB, bool MASK, bool SPREAD>
+// to the MFMAs by the scheduling hints): pieces 0-3 in the first iteration of a tile, 4-8 in the second; all of them
+// when a tile has one iteration (!WHOLE).
+template <int D, int KD, int RB, bool MASK, bool SPREAD, bool WHOLE>
 __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D>& ahead,
                                               const DkvAddr<D>& cur, int dkey, float c, const DkvTileLoad<D>& load) {
     using G = DkvGeom<D, KD>;
     constexpr int KK = G::KK, DB = G::DB, K1 = G::K1;
-    constexpr int NRB = RB ^ 1;   // block i+1 sits at the other position (of the next tile when RB == 1)
-    constexpr int P0 = RB == 0 ? 0 : 4;   // first piece of this iteration
+    constexpr int NRB = RB ^ 1;
+    constexpr int CUR = WHOLE ? RB : 0, AHEAD = WHOLE ? NRB : 0;   // positions of blocks i and i+1 beyond the addresses
+    constexpr int P0 = RB == 0 ? 0 : 4;   // first piece of this iteration (WHOLE)
 
     // element e of an accumulator fragment -> packed bf16 pair index; one half = 8 elements = one B operand
     auto softmax_half = [&](int half, u32x4& pw, u32x4& dw) {
@@ -140,16 +152,18 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
     // statistics of block i+1 straight into its accumulators: rows 8 j + 4 (lane / 32) .. + 3 in registers 4 j .. 4 j + 3
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(lds + ahead.st + NRB * 128 + i4 * 32);
-        const f32x4 b = *reinterpret_cast<const f32x4*>(lds + ahead.st + NRB * 128 + i4 * 32 + 256);
+        const f32x4 a = *reinterpret_cast<const f32x4*>(lds + ahead.st + AHEAD * 128 + i4 * 32);
+        const f32x4 b = *reinterpret_cast<const f32x4*>(lds + ahead.st + AHEAD * 128 + i4 * 32 + 256);
 #pragma unroll
         for (int j = 0; j < 4; ++j) { st.s[NRB][4 * i4 + j] = a[j]; st.dp[NRB][4 * i4 + j] = b[j]; }
     }
 #pragma unroll
     for (int kk = 0; kk < K1; ++kk) {
-        st.qf[kk] = lds_read128(lds, ahead.rm[kk] + NRB * G::kBlockBytes);
-        st.dof[kk] = lds_read128(lds, ahead.rm[kk] + NRB * G::kBlockBytes + G::kTileBytes);
-        if constexpr (SPREAD) {
+        st.qf[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes);
+        st.dof[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes + G::kTileBytes);
+        if constexpr (SPREAD && !WHOLE) {
+            if (kk % 2 == 1) load.piece_at(kk / 2);
+        } else if constexpr (SPREAD) {
             if (kk == KK / 4 - 1) load.template piece<P0>();
             if (kk == 3 * KK / 4 - 1) load.template piece<P0 + 1>();
         }
@@ -175,10 +189,13 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
     for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
-            const int off = (RB * 2 + tt) * 16 * D * 2;   // 16 tile rows per k-step
+            const int off = (CUR * 2 + tt) * 16 * D * 2;   // 16 tile rows per k-step
             st.qtf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off, cur.tr[db][1] + off);
             st.dotf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off + G::kTileBytes, cur.tr[db][1] + off + G::kTileBytes);
-            if constexpr (SPREAD) {
+            if constexpr (SPREAD && !WHOLE) {
+                static_assert(K1 / 2 + KK >= DkvTileLoad<D>::kPieces, "a place for every piece");
+                load.piece_at(K1 / 2 + tt * DB + db);
+            } else if constexpr (SPREAD) {
                 if (tt == 0 && db == DB - 1) load.template piece<P0 + 2>();
                 if (tt == 1 && db == DB / 2 - 1) load.template piece<P0 + 3>();
                 if (RB == 1 && tt == 1 && db == DB - 1) load.template piece<P0 + 4>();
@@ -205,20 +222,30 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
 // Tile width 64: the accumulators are half as large, so two workgroups fit a compute unit (248 registers per wave, 2 x 68 KB
 // of LDS) and one hides the other's prologue, stores and waits.  Against one workgroup with 280 registers: 16384 tokens in
 // sequences of 32 .. 512, 16 heads: 98 -> 62 us; 8 x 2048, 32 heads: 396 -> 298 us; 2 x 8192, 8 heads on 2: 444 -> 413 us.
-template <int D, bool BLOCK, int KD = D / 16>
-__global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(BwdParams p) {
+//
+// SPLIT: a workgroup takes half an item, 64 keys; the waves are two pairs over the keys, and one pair takes the first
+// 32-row block of every tile, the other the second.  Same copies and LDS per tile, half the products, so a half item takes
+// about half the time: for packs whose longest item outlasts the rest of the pass (see launch_bwd_dkv).  The two
+// accumulator pairs of a key meet in LDS at the end, in one fixed order.
+template <int D, bool BLOCK, int KD, bool SPLIT>
+__global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv_kernel(BwdParams p) {
     using G = DkvGeom<D, KD>;
-    constexpr int BKV = kDkvKTile, BQ = kDkvQTile;
+    constexpr int BKV = SPLIT ? kDkvKTile / 2 : kDkvKTile, BQ = kDkvQTile;
     constexpr int KK = G::KK, DB = G::DB, K1 = G::K1;
     __shared__ __attribute__((aligned(1024))) char lds[G::kStages * G::kStageBytes];
 
-    const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, blockIdx.x);
+    // workgroups p and p + 8 of 16 take the halves of an item: like the item itself they belong to XCD p % 8
+    const int slot = SPLIT ? (int)(blockIdx.x / (2 * kQueues)) * kQueues + (int)(blockIdx.x % kQueues) : (int)blockIdx.x;
+    if (SPLIT && slot >= p.num_items) return;
+    const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, slot);
     if (item.tile < 0) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = item.q_len, Lk = item.k_len, shift = item.offset, g = item.head;   // L: rows of the chunk
-    const int key0 = item.tile * BKV;
-    const int wave_key0 = key0 + wave * 32;
+    const int key0 = item.tile * kDkvKTile + (SPLIT ? (int)(blockIdx.x / kQueues % 2) * BKV : 0);
+    if (SPLIT && key0 >= Lk) return;             // the last item of a sequence may have no second half
+    const int row_block = SPLIT ? wave >> 1 : 0;   // the 32-row block of every tile that is this wave's
+    const int wave_key0 = key0 + (SPLIT ? wave & 1 : wave) * 32;
     const int my_key = wave_key0 + (lane & 31);
     const int hh = lane >> 5;
     const bool valid = my_key < Lk;
@@ -236,7 +263,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
     const int n_tiles = per_head * p.group;
     if (BLOCK && per_head == 0) {
         // no row of the chunk sees these keys
-        if (valid) {
+        if (valid && row_block == 0) {
             const int64_t row_elem = ((int64_t)(item.k_start + my_key) * p.kv_heads + g) * hd;
 #pragma unroll
             for (int c4 = 0; c4 < D / 8; ++c4) {
@@ -317,6 +344,16 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
         }
     }
     off.st = 2 * G::kTileBytes + hh * 16;
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) off.rm[kk] += row_block * G::kBlockBytes;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            off.tr[db][0] += row_block * G::kBlockBytes;
+            off.tr[db][1] += row_block * G::kBlockBytes;
+        }
+        off.st += row_block * 128;
+    }
     // `off` holds the addresses of the current tile's stage and is moved from stage to stage by adding the
     // distance (one set of address registers instead of one per stage in use)
     auto shifted = [&](const DkvAddr<D>& a0, int bytes) {
@@ -362,8 +399,10 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
     // one: the ~400 live registers then meet at a join once per head, not once per iteration.
     int stage = 0;   // stage of tile u
     DkvTileLoad<D> no_load{};
-    auto tile_step = [&](int u, int qt, auto masked) {
+    // `par` (SPLIT, where a tile is one iteration): the accumulator pair that holds the tile's S' / dP'
+    auto tile_step = [&](int u, int qt, auto masked, auto par) {
         constexpr bool kMask = decltype(masked)::value;
+        constexpr int kPar = decltype(par)::value;
         if (u > 0) {
             // tile u+1 must have landed; the copies of tile u+2 (the newest kLoadsPerTile of this wave) may still fly
             if (u + 2 < n_tiles) wait_tile_loads_except<kLoadsPerTile>(); else wait_tile_loads();
@@ -375,9 +414,13 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
         // block 2u+2 lives in the next tile; the last tile has none: it re-reads itself (result unused)
         const int to_next = (stage1 - stage) * G::kStageBytes;
         const DkvAddr<D> next = shifted(off, u + 1 < n_tiles ? to_next : 0);
-        const int dkey0 = my_key - shift - qt * BQ - 4 * hh;
-        dkv_iteration<D, KD, 0, kMask, false>(st, lds, off, off, dkey0, c, no_load);
-        dkv_iteration<D, KD, 1, kMask, false>(st, lds, next, off, dkey0 - 32, c, no_load);
+        const int dkey0 = my_key - shift - qt * BQ - row_block * 32 - 4 * hh;
+        if constexpr (SPLIT) {
+            dkv_iteration<D, KD, kPar, kMask, false, false>(st, lds, next, off, dkey0, c, no_load);
+        } else {
+            dkv_iteration<D, KD, 0, kMask, false, true>(st, lds, off, off, dkey0, c, no_load);
+            dkv_iteration<D, KD, 1, kMask, false, true>(st, lds, next, off, dkey0 - 32, c, no_load);
+        }
         off = shifted(off, to_next);
         stage = stage1;
     };
@@ -385,7 +428,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
     // meanwhile (u + 3) belongs to the same head and is a whole tile, so its copies need no case distinction
     // and are issued from inside the two iterations.
     // `load` arrives pointing at the first rows of tile qt - 3 of the head and leaves pointing one tile lower.
-    auto tile_step_spread = [&](int u, int qt, DkvTileLoad<D>& load) {
+    auto tile_step_spread = [&](int u, int qt, DkvTileLoad<D>& load, auto par) {
+        constexpr int kPar = decltype(par)::value;
         if (u > 0) {
             wait_tile_loads_except<kLoadsPerTile>();   // u + 2 < n_tiles here
             __syncthreads();
@@ -396,9 +440,13 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
         load.stat_dst = load.stage + 2 * G::kTileBytes + (wave & 1) * 256;
         const int to_next = (stage1 - stage) * G::kStageBytes;
         const DkvAddr<D> next = shifted(off, to_next);
-        const int dkey0 = my_key - shift - qt * BQ - 4 * hh;
-        dkv_iteration<D, KD, 0, false, true>(st, lds, off, off, dkey0, c, load);
-        dkv_iteration<D, KD, 1, false, true>(st, lds, next, off, dkey0 - 32, c, load);
+        const int dkey0 = my_key - shift - qt * BQ - row_block * 32 - 4 * hh;
+        if constexpr (SPLIT) {
+            dkv_iteration<D, KD, kPar, false, true, false>(st, lds, next, off, dkey0, c, load);
+        } else {
+            dkv_iteration<D, KD, 0, false, true, true>(st, lds, off, off, dkey0, c, load);
+            dkv_iteration<D, KD, 1, false, true, true>(st, lds, next, off, dkey0 - 32, c, load);
+        }
         off = shifted(off, to_next);
         load.q_row -= (int64_t)BQ * p.q_stride;
         load.do_row -= (int64_t)BQ * p.q_heads * hd;
@@ -412,8 +460,12 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
     // q tiles that hold some (row, key) pair above the shifted diagonal for the keys of this workgroup:
     // qt BQ + shift < key0 + BKV - 1; the two nearest the diagonal when there is no shift
     const int n_masked = BLOCK ? (key0 + BKV - 2 - shift < 0 ? 0 : max(0, min(per_head, (key0 + BKV - 2 - shift) / BQ - first_qt + 1)))
-                               : min(2, per_head);
+                               : min(BKV / BQ, per_head);
     const int n_general = max(3, n_masked);   // tiles below this index (from the diagonal) take the general path
+    // SPLIT: tiles are walked in pairs, one per accumulator pair; after a single tile the pairs change places
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, 1>;
+    auto swap_pairs = [&] { st.s[0] = st.s[1]; st.dp[0] = st.dp[1]; };
     for (int h = 0, u = 0; h < p.group; ++h) {
         int j = per_head - 1;
         if (j >= n_general) {
@@ -427,10 +479,25 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
             load.stat = ((wave & 1) == 0 ? p.nlse : p.negd) + (int64_t)hq * p.total_tokens + row;
             load.wave = wave;
             load.lane = lane;
-            for (; j >= n_general; --j, ++u) tile_step_spread(u, first_qt + j, load);
+            if constexpr (SPLIT) {
+                for (; j > n_general; j -= 2, u += 2) {
+                    tile_step_spread(u, first_qt + j, load, Even{});
+                    tile_step_spread(u + 1, first_qt + j - 1, load, Odd{});
+                }
+            }
+            for (; j >= n_general; --j, ++u) {
+                tile_step_spread(u, first_qt + j, load, Even{});
+                if constexpr (SPLIT) swap_pairs();
+            }
         }
-        for (; j >= n_masked; --j, ++u) tile_step(u, first_qt + j, std::false_type{});
-        for (; j >= 0; --j, ++u) tile_step(u, first_qt + j, std::true_type{});
+        for (; j >= n_masked; --j, ++u) {
+            tile_step(u, first_qt + j, std::false_type{}, Even{});
+            if constexpr (SPLIT) swap_pairs();
+        }
+        for (; j >= 0; --j, ++u) {
+            tile_step(u, first_qt + j, std::true_type{}, Even{});
+            if constexpr (SPLIT) swap_pairs();
+        }
     }
 
     // epilogue: G2 of the last block
@@ -444,11 +511,45 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
     // whole rows per store instruction, staged through LDS (free once every wave has left the tile loop)
     const bool rope = p.rope_table != nullptr;
     __syncthreads();
-    char* wave_lds = lds + wave * (32 * D * 4);
+    constexpr int kWaveArea = 32 * D * 4;
+    static_assert(!SPLIT || 8 * kWaveArea <= G::kStages * G::kStageBytes, "exchange and staging areas");
+    char* wave_lds = lds + wave * kWaveArea;
+    if constexpr (SPLIT) {
+        // the waves of a key pair hold the two row blocks' shares: the first hands its dV over and stores dK, the second
+        // hands its dK over and stores dV
+        auto slot16 = [&](int w, int db, int i4) {
+            return reinterpret_cast<f32x4*>(lds + w * kWaveArea + ((db * 4 + i4) * 64 + lane) * 16);
+        };
+        auto hand_over = [&](const f32x16 (&x)[DB]) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4)
+                    *slot16(wave, db, i4) = f32x4{x[db][4 * i4], x[db][4 * i4 + 1], x[db][4 * i4 + 2], x[db][4 * i4 + 3]};
+        };
+        auto take_over = [&](f32x16 (&x)[DB]) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const f32x4 y = *slot16(wave ^ 2, db, i4);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[db][4 * i4 + j] += y[j];
+                }
+        };
+        if (row_block == 0) hand_over(st.dv);
+        else hand_over(st.dk);
+        __syncthreads();
+        if (row_block == 0) take_over(st.dk);
+        else take_over(st.dv);
+        wave_lds += 4 * kWaveArea;   // the partner may still read this wave's exchange area
+    }
+    const bool stores_dk = !SPLIT || row_block == 0, stores_dv = !SPLIT || row_block == 1;
     const int64_t row0_elem = ((int64_t)(item.k_start + wave_key0) * p.kv_heads + g) * hd;
     const int64_t row_stride = (int64_t)p.kv_heads * hd;
     const int rows = min(32, Lk - wave_key0);
-    if (rope) {
+    if (!stores_dk) {
+    } else if (rope) {
         // dK with respect to the keys before their rotary embedding; key positions inside the sequence
         store_tile_rope_transposed<D>(wave_lds, st.dk, p.scale, p.dk, row0_elem, p.grad_f32 != 0, row_stride, rows, hd,
                                       p.rope_table + (int64_t)(item.q_pos - item.offset + wave_key0) * hd, lane);
@@ -457,28 +558,38 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel(Bw
     } else {
         store_tile_bf16<D>(wave_lds, st.dk, p.scale, static_cast<uint16_t*>(p.dk) + row0_elem, row_stride, rows, hd, lane);
     }
-    if (p.grad_f32 != 0) {
+    if (!stores_dv) {
+    } else if (p.grad_f32 != 0) {
         store_tile_f32<D, false>(wave_lds, st.dv, 1.f, static_cast<float*>(p.dv) + row0_elem, row_stride, rows, hd, lane);
     } else {
         store_tile_bf16<D>(wave_lds, st.dv, 1.f, static_cast<uint16_t*>(p.dv) + row0_elem, row_stride, rows, hd, lane);
     }
 }
 
+namespace {
+
+template <int D, int KD>
+void launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream) {
+    const dim3 threads(kThreads);
+    if (split) {
+        const dim3 grid((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2));
+        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, true>), grid, threads, 0, stream, p);
+        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true>), grid, threads, 0, stream, p);
+    } else {
+        const dim3 grid((unsigned)num_items);
+        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
+        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
+    }
+}
+
+}  // namespace
+
 hipError_t launch_bwd_dkv(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
-    const dim3 grid((unsigned)num_items), threads(kThreads);
-    if (tile_width(head_dim) == 128) {
-        if (contraction_steps(head_dim) <= 7) {
-            if (block) hipLaunchKernelGGL((bwd_dkv_kernel<128, true, 7>), grid, threads, 0, stream, p);
-            else hipLaunchKernelGGL((bwd_dkv_kernel<128, false, 7>), grid, threads, 0, stream, p);
-        } else {
-            if (block) hipLaunchKernelGGL((bwd_dkv_kernel<128, true>), grid, threads, 0, stream, p);
-            else hipLaunchKernelGGL((bwd_dkv_kernel<128, false>), grid, threads, 0, stream, p);
-        }
-    } else {
-        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<64, true>), grid, threads, 0, stream, p);
-        else hipLaunchKernelGGL((bwd_dkv_kernel<64, false>), grid, threads, 0, stream, p);
-    }
+    const bool split = p.split != 0;
+    if (tile_width(head_dim) == 64) launch_dkv<64, 4>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) <= 7) launch_dkv<128, 7>(p, num_items, block, split, stream);
+    else launch_dkv<128, 8>(p, num_items, block, split, stream);
     return hipGetLastError();
 }
 

@@ -171,6 +171,7 @@ struct hspmd_attn_plan {
     int64_t total_tokens = 0;
     int32_t max_position = 0;      // positions inside a sequence that the plan's tokens occupy: 0 .. max_position-1
     int64_t count[3] = {0, 0, 0};
+    hspmd::PassLoad load[3];
     hspmd_work_item* items[3] = {nullptr, nullptr, nullptr};   // device; three views into the current slot
     hspmd_order order = HSPMD_ORDER_XCD_COST;
     // block variant (hspmd_attn_block_plan_create): total_tokens counts query tokens
@@ -241,6 +242,23 @@ hspmd_status install_lists(hspmd_attn_plan* plan, const void* host, size_t bytes
     return HSPMD_OK;
 }
 
+// Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass
+// takes as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs
+// 0.68 of the whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy
+// every Q / dO tile, and an item costs about eight steps beside its tiles.  Measured, whole and split (us): heaviest item 32
+// steps, 8.5 per slot (2 sequences, 8 heads) 50 and 41; 60 steps, 16 per slot (8 KV heads of 4) 85 and 61; 238 steps,
+// 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and 321; 3 steps, 168 items 17 and 23 (the
+// halves no longer fit the chip at once); 8 x 2048, 32 heads 652 and 826.
+bool split_dkv(const hspmd_attn_plan* plan) {
+    const double heaviest = (double)plan->load[HSPMD_LIST_DKV].heaviest, total = (double)plan->load[HSPMD_LIST_DKV].total;
+    const double items = (double)plan->count[HSPMD_LIST_DKV];
+    const double units = 256.0;   // compute units; whole items of tile width 64 fit a unit twice
+    const double slots = hspmd::tile_width(plan->head_dim) == 64 ? 2 * units : units;
+    const double whole = std::max(heaviest + 8, (total + 8 * items) / slots);
+    const double split = std::max(0.68 * heaviest + 8, (1.3 * total + 8 * 2 * items) / units);
+    return split < 0.9 * whole;
+}
+
 // Builds the three packed lists of a pack on the host (forward and dQ share one copy) and installs them.
 hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t num_seqs, bool first) {
     std::vector<hspmd_work_item> all;
@@ -277,6 +295,8 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
                                                        counters_at + kind * kCounterItems);
     plan->num_seqs = num_seqs;
     plan->total_tokens = cu[num_seqs];
+    for (int kind = 0; kind < 3; ++kind)
+        plan->load[kind] = hspmd::pass_load((hspmd_list_kind)kind, cu, num_seqs, plan->q_heads, plan->kv_heads);
     plan->max_position = 0;
     for (int32_t i = 0; i < num_seqs; ++i) plan->max_position = std::max(plan->max_position, cu[i + 1] - cu[i]);
     for (int kind = 0; kind < 3; ++kind) {
@@ -321,6 +341,9 @@ hspmd_status fill_block_plan(hspmd_attn_plan* plan, const int32_t* cu_q, const i
                                                        counters_at + kind * kCounterBlockItems);
     plan->num_seqs = num_seqs;
     plan->total_tokens = cu_q[num_seqs];
+    for (int kind = 0; kind < 3; ++kind)
+        plan->load[kind] = hspmd::block_pass_load((hspmd_list_kind)kind, cu_q, cu_k, q_pos, k_pos, num_seqs, plan->q_heads,
+                                                  plan->kv_heads);
     plan->total_kv_tokens = cu_k[num_seqs];
     plan->max_position = 0;
     for (int32_t i = 0; i < num_seqs; ++i)
@@ -586,6 +609,8 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     hipError_t e = timed ? timed_launch(2, s, dq_pass) : dq_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dQ launch");
     p.items = plan->items[HSPMD_LIST_DKV];
+    p.num_items = (int32_t)plan->count[HSPMD_LIST_DKV];
+    p.split = split_dkv(plan) ? 1 : 0;
     auto dkv_pass = [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], false, s); };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dK/dV launch");
@@ -921,6 +946,8 @@ static hspmd_status block_bwd(const hspmd_attn_plan* plan, const void* q, const 
     e = timed_launch(2, s, [&] { return hspmd::launch_bwd_dq(p, plan->head_dim, plan->count[HSPMD_LIST_DQ], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dQ launch");
     p.block_items = plan->block_items[HSPMD_LIST_DKV];
+    p.num_items = (int32_t)plan->count[HSPMD_LIST_DKV];
+    p.split = split_dkv(plan) ? 1 : 0;
     e = timed_launch(3, s, [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dK/dV launch");
     if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");

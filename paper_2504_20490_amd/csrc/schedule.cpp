@@ -216,6 +216,21 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
         hspmd_work_item{0, 0, -1, 0});
 }
 
+PassLoad pass_load(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv) {
+    const int tile_rows = (kind == HSPMD_LIST_DKV) ? kDkvKTile : kFwdQTile;
+    PassLoad load;
+    for (int32_t s = 0; s < num_seqs; ++s) {
+        const int32_t len = cu[s + 1] - cu[s], n_tiles = (int32_t)ceil_div(len, tile_rows);
+        for (int32_t t = 0; t < n_tiles; ++t) {
+            const int64_t c = item_cost(kind, len, t, hq / hkv);
+            load.total += c;
+            load.heaviest = std::max(load.heaviest, c);
+        }
+    }
+    load.total *= (kind == HSPMD_LIST_DKV) ? hkv : hq;
+    return load;
+}
+
 // ------------------------------------------------------------------------------ cost model
 // The paper's planner dispatches mixed-length sequences with a cost model evaluated on the CPU (Appendix
 // "Scenario-specific Planning", mixed-length case); this is the per-operator predictor for the attention
@@ -303,6 +318,23 @@ std::vector<hspmd_block_item> build_block_list(hspmd_list_kind kind, const int32
         },
         [&](int32_t s, int32_t i) { return block_item_cost(kind, make(s, 0, i), group); }, make,
         hspmd_block_item{0, 0, 0, 0, 0, -1, 0, 0});
+}
+
+PassLoad block_pass_load(hspmd_list_kind kind, const int32_t* cu_q, const int32_t* cu_k, const int32_t* q_pos,
+                         const int32_t* k_pos, int32_t num_seqs, int32_t hq, int32_t hkv) {
+    const int tile_rows = (kind == HSPMD_LIST_DKV) ? kDkvKTile : kFwdQTile;
+    PassLoad load;
+    for (int32_t s = 0; s < num_seqs; ++s) {
+        hspmd_block_item it{cu_q[s], cu_q[s + 1] - cu_q[s], cu_k[s], cu_k[s + 1] - cu_k[s], q_pos[s] - k_pos[s], 0, 0, q_pos[s]};
+        const int32_t n_tiles = (int32_t)ceil_div(kind == HSPMD_LIST_DKV ? it.k_len : it.q_len, tile_rows);
+        for (it.tile = 0; it.tile < n_tiles; ++it.tile) {
+            const int64_t c = block_item_cost(kind, it, hq / hkv);
+            load.total += c;
+            load.heaviest = std::max(load.heaviest, c);
+        }
+    }
+    load.total *= (kind == HSPMD_LIST_DKV) ? hkv : hq;
+    return load;
 }
 
 }  // namespace hspmd
