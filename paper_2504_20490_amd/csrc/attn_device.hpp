@@ -485,7 +485,12 @@ struct ItemQueue {
     }
     // one thread per workgroup, after its last draw
     __device__ __forceinline__ void leave() const {
-        const int gone = __hip_atomic_fetch_add(counters + kQueues, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        // Relaxed on purpose.  No data goes from one workgroup to another through the counters; all that is needed is that
+        // every draw has been performed before the reset, and each workgroup's last draw has returned its value (the
+        // workgroup acted on it) before this addition is issued.  Release and acquire at this scope write back and
+        // invalidate caches of the whole XCD, once per workgroup that leaves, while others still compute.
+        asm volatile("" ::: "memory");
+        const int gone = __hip_atomic_fetch_add(counters + kQueues, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (gone == (int)gridDim.x - 1) {
 #pragma unroll
             for (int i = 0; i <= kQueues; ++i)
