@@ -53,24 +53,31 @@ __global__ __launch_bounds__(kThreads) void bwd_dsum_kernel(BwdParams p) {
 // when head_dim ends before the tile width (the steps beyond it would multiply the zero padding of the Q / dO fragments)
 // Tile width 64 needs 168 registers per wave, so a third workgroup fits a compute unit (170 had kept it out):
 // sequences of 32 .. 512 tokens, 16 heads: 55 -> 48 us; 8 x 2048, 32 heads: 244 -> 230 us.
-template <int D, bool BLOCK, int KD = D / 16>
+// SPLIT: a workgroup takes half an item, 64 rows; two waves share each 32-row block, one takes the first 32-key block of
+// every tile, the other the second, and their sums meet in LDS at the end (as in the forward).
+template <int D, bool BLOCK, int KD, bool SPLIT>
 __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(BwdParams p) {
     static_assert(KD >= 1 && KD <= D / 16, "k-steps inside the tile width");
-    constexpr int BQ = kFwdQTile, BK = kFwdKTile;
+    constexpr int BQ = SPLIT ? kFwdQTile / 2 : kFwdQTile, BK = kFwdKTile;
     constexpr int KK = KD, DB = D / 32;
     constexpr int kTileBytes = BK * D * 2;
     __shared__ __attribute__((aligned(1024))) char lds[2 * 2 * kTileBytes];   // {K, V} x 2 stages
 
     // packed variant: this pass also produces the row statistics (see below); the constants that go with them
     if (!BLOCK && blockIdx.x == 0 && threadIdx.x < 16) p.ninf_pad[threadIdx.x] = -INFINITY;
-    const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, blockIdx.x);
+    // workgroups p and p + 8 of 16 take the halves of an item, the second, which sees more keys, before the first
+    const int slot = SPLIT ? (int)(blockIdx.x / (2 * kQueues)) * kQueues + (int)(blockIdx.x % kQueues) : (int)blockIdx.x;
+    if (SPLIT && slot >= p.num_items) return;
+    const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, slot);
     if (item.tile < 0) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Lq = item.q_len, L = item.k_len, off = item.offset;   // L: keys of the chunk (= rows when !BLOCK)
     const int h = item.head, hk = h / p.group;
-    const int q_row0 = item.tile * BQ;
-    const int wave_row0 = q_row0 + wave * 32;
+    const int q_row0 = item.tile * kFwdQTile + (SPLIT ? (1 - (int)(blockIdx.x / kQueues % 2)) * BQ : 0);
+    if (SPLIT && q_row0 >= Lq) return;   // the last item of a sequence may have no second half
+    const int row_block = SPLIT ? wave & 1 : wave, key_block = SPLIT ? wave >> 1 : 0;   // this wave's 32 rows; its keys of a tile
+    const int wave_row0 = q_row0 + row_block * 32;
     const int my_row = wave_row0 + (lane & 31);
     const int hh = lane >> 5;
     const bool valid = my_row < Lq;
@@ -89,7 +96,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
     const int n_tiles = (kv_end + BK - 1) / BK;
     if (BLOCK && n_tiles == 0) {
         // nothing visible: this block's share of dQ is zero
-        if (valid && !p.dq_accumulate) {
+        if (valid && key_block == 0 && !p.dq_accumulate) {
             float* row = static_cast<float*>(p.dq) + ((int64_t)(item.q_start + my_row) * p.q_heads + h) * hd;
 #pragma unroll
             for (int c4 = 0; c4 < D / 8; ++c4)
@@ -163,7 +170,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
         negd = -(d_part + partner32(d_part));            // the two half rows of lanes l and l + 32
         const float nlse = valid ? -stat_a / p.scale : -INFINITY;   // rows past the end get P = 0
         nlse2 = nlse * c;                                                // -LSE log2(e)
-        if (valid && hh == 0) {
+        if (valid && hh == 0 && key_block == 0) {
             p.negd[stat] = negd;
             p.nlse[stat] = nlse;
         }
@@ -192,6 +199,13 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
             tr[db][1] = tile_offset<D>(row + 8, col);
         }
     }
+    if constexpr (SPLIT) {
+        const int skip = key_block * 32 * D * 2;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) rm[kk] += skip;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) { tr[db][0] += skip; tr[db][1] += skip; }
+    }
 
     // One 32-key block, written step by step with a scheduling barrier after each step so that operand
     // fragments are requested kAhead MFMAs before their use:
@@ -199,13 +213,15 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
     //   VALU      : dS^T = exp2(S^T c - LSE log2e) (dP^T - D), with the first K^T fragments already requested
     //   2 DB steps: dQ^T += K^T dS^T                 (fragments by transpose read)
     // MASK: the block touches the diagonal.  SPREAD: step n of the first phase also issues copy instruction
-    // n / (2 KK / kPerWave) of a whole tile (K in block 0, V in block 1), see `piece`.
+    // n / (2 KK / kPerWave) of a whole tile (K in block 0, V in block 1; of both tiles when SPLIT), see `piece`.
     auto block = [&](const char* ktile, const char* vtile, int jb, int kb, auto masked, auto spread, auto&& piece) {
         constexpr bool kMask = decltype(masked)::value;
         constexpr bool kSpread = decltype(spread)::value;
         constexpr int kAhead = 4, kAheadT = 3;
         constexpr int N1 = 2 * KK, N2 = 2 * DB;
-        constexpr int every = N1 / TileCopy<D, BK>::kPerWave;
+        constexpr int kPieces = (SPLIT ? 2 : 1) * TileCopy<D, BK>::kPerWave;
+        constexpr int every = N1 / kPieces;
+        static_assert(every >= 1, "a step for every copy instruction");
         auto frag1 = [&](int n) {
             return *reinterpret_cast<const bf16x8*>((n < KK ? ktile : vtile) + rm[n % KK] + jb * 32 * D * 2);
         };
@@ -230,7 +246,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
             if (n < KK) sacc = mfma(q1[n % (kAhead + 1)], qf[n], sacc);
             else dp = mfma(q1[n % (kAhead + 1)], dof[n - KK], dp);
             if constexpr (kSpread) {
-                if (n % every == every - 1) piece(jb, n / every);
+                if (n % every == every - 1 && (!SPLIT || n / every < kPieces)) piece(jb, n / every);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -268,8 +284,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
         }
         auto none = [](int, int) {};
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-            const int kb = kt * BK + jb * 32;
+        for (int jb = 0; jb < (SPLIT ? 1 : 2); ++jb) {
+            const int kb = kt * BK + (SPLIT ? key_block : jb) * 32;
             if (!kMask || kb <= wave_limit) block(ktile, vtile, jb, kb, masked, std::false_type{}, none);
         }
     };
@@ -287,17 +303,22 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
         const uint16_t* k_row = kbase + (int64_t)(kt + 1) * BK * p.kv_stride;
         const uint16_t* v_row = vbase + (int64_t)(kt + 1) * BK * p.kv_stride;
         auto piece = [&](int jb, int i) {
-            if (jb == 0) kvcopy.issue_full_one_at(i, next, k_row, wave);
-            else kvcopy.issue_full_one_at(i, next + kTileBytes, v_row, wave);
+            constexpr int kPerTile = TileCopy<D, BK>::kPerWave;
+            if (SPLIT ? i < kPerTile : jb == 0) kvcopy.issue_full_one_at(i, next, k_row, wave);
+            else kvcopy.issue_full_one_at(SPLIT ? i - kPerTile : i, next + kTileBytes, v_row, wave);
         };
-        block(ktile, vtile, 0, kt * BK, std::false_type{}, std::true_type{}, piece);
-        block(ktile, vtile, 1, kt * BK + 32, std::false_type{}, std::true_type{}, piece);
+        if constexpr (SPLIT) {
+            block(ktile, vtile, 0, kt * BK + key_block * 32, std::false_type{}, std::true_type{}, piece);
+        } else {
+            block(ktile, vtile, 0, kt * BK, std::false_type{}, std::true_type{}, piece);
+            block(ktile, vtile, 1, kt * BK + 32, std::false_type{}, std::true_type{}, piece);
+        }
     };
     // separate loops instead of tests per tile: tiles wholly below the diagonal (with and without a whole
     // successor), then the (at most two) tiles on the diagonal
     // tiles whose every key exists and is visible to every row of this q tile (with the shift, keys past the end
     // of the chunk need the mask: the last, partial tile is never an interior one)
-    const int n_interior = BLOCK ? max(0, min(min(n_tiles, (q_row0 + off + 1) / BK), L / BK)) : min(n_tiles, 2 * item.tile);
+    const int n_interior = BLOCK ? max(0, min(min(n_tiles, (q_row0 + off + 1) / BK), L / BK)) : min(n_tiles, q_row0 / BK);
     const int n_spread = max(0, min(min(n_interior, n_tiles - 1), L / BK - 1));
     int kt = 0;
     // the long loop of a long sequence runs in pairs (even tile, odd tile) with constant stage offsets
@@ -309,10 +330,34 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
     for (; kt < n_interior; ++kt) step(kt, std::false_type{});
     for (; kt < n_tiles; ++kt) step(kt, std::true_type{});
 
+    if constexpr (SPLIT) {
+        __syncthreads();   // every wave has left the tile loop
+        char* const area = lds + 2 * kTileBytes + row_block * (32 * D * 4);
+        if (key_block == 1) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4)
+                    *reinterpret_cast<f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16) =
+                        f32x4{acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]};
+        }
+        __syncthreads();
+        if (key_block == 0) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const f32x4 y = *reinterpret_cast<const f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[db][4 * i4 + j] += y[j];
+                }
+        }
+    }
     if (p.rope_table != nullptr) {
         // dQ with respect to the queries before their rotary embedding; row positions inside the sequence
         __syncthreads();
-        char* wave_lds = lds + wave * (32 * D * 4);
+        char* wave_lds = lds + row_block * (32 * D * 4);
+        if (SPLIT && key_block == 1) return;
         const int64_t first_elem = ((int64_t)(item.q_start + wave_row0) * p.q_heads + h) * hd;
         const float* table_row0 = p.rope_table + (int64_t)(item.q_pos + wave_row0) * hd;
         if (BLOCK && p.dq_accumulate)
@@ -324,7 +369,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
     } else if (p.grad_f32 != 0) {
         // whole rows per store instruction, staged through LDS (free once every wave has left the tile loop)
         __syncthreads();
-        char* wave_lds = lds + wave * (32 * D * 4);
+        char* wave_lds = lds + row_block * (32 * D * 4);
+        if (SPLIT && key_block == 1) return;
         float* first_row = static_cast<float*>(p.dq) + ((int64_t)(item.q_start + wave_row0) * p.q_heads + h) * hd;
         const int rows = min(32, Lq - wave_row0);
         if (BLOCK && p.dq_accumulate)
@@ -333,7 +379,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
             store_tile_f32<D, false>(wave_lds, acc, p.scale, first_row, (int64_t)p.q_heads * hd, rows, hd, lane);
     } else {
         __syncthreads();
-        store_tile_bf16<D>(lds + wave * (32 * D * 2), acc, p.scale,
+        if (SPLIT && key_block == 1) return;
+        store_tile_bf16<D>(lds + row_block * (32 * D * 2), acc, p.scale,
                            static_cast<uint16_t*>(p.dq) + ((int64_t)(item.q_start + wave_row0) * p.q_heads + h) * hd,
                            (int64_t)p.q_heads * hd, min(32, Lq - wave_row0), hd, lane);
     }
@@ -353,21 +400,25 @@ hipError_t launch_bwd_dsum(const BwdParams& p, int head_dim, hipStream_t stream)
     return hipGetLastError();
 }
 
+namespace {
+
+template <int D, int KD>
+void launch_dq(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream) {
+    const dim3 grid((unsigned)(split ? (num_items + kQueues - 1) / kQueues * kQueues * 2 : num_items)), threads(kThreads);
+    if (block && split) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, true>), grid, threads, 0, stream, p);
+    else if (block) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
+    else if (split) hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, true>), grid, threads, 0, stream, p);
+    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
+}
+
+}  // namespace
+
 hipError_t launch_bwd_dq(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
-    const dim3 grid((unsigned)num_items), threads(kThreads);
-    if (tile_width(head_dim) == 128) {
-        if (contraction_steps(head_dim) <= 7) {
-            if (block) hipLaunchKernelGGL((bwd_dq_kernel<128, true, 7>), grid, threads, 0, stream, p);
-            else hipLaunchKernelGGL((bwd_dq_kernel<128, false, 7>), grid, threads, 0, stream, p);
-        } else {
-            if (block) hipLaunchKernelGGL((bwd_dq_kernel<128, true>), grid, threads, 0, stream, p);
-            else hipLaunchKernelGGL((bwd_dq_kernel<128, false>), grid, threads, 0, stream, p);
-        }
-    } else {
-        if (block) hipLaunchKernelGGL((bwd_dq_kernel<64, true>), grid, threads, 0, stream, p);
-        else hipLaunchKernelGGL((bwd_dq_kernel<64, false>), grid, threads, 0, stream, p);
-    }
+    const bool split = p.split != 0;
+    if (tile_width(head_dim) == 64) launch_dq<64, 4>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) <= 7) launch_dq<128, 7>(p, num_items, block, split, stream);
+    else launch_dq<128, 8>(p, num_items, block, split, stream);
     return hipGetLastError();
 }
 

@@ -32,12 +32,13 @@ struct FwdGeom {
     static constexpr int kTileBytes = kFwdKTile * D * 2;
 };
 
-template <int D, int KD>
+// NB: 32-key blocks of every tile that the wave takes: both, or one when two waves share the tile (SPLIT)
+template <int D, int KD, int NB>
 struct FwdState {
     using G = FwdGeom<D, KD>;
     bf16x8 qf[G::KK];      // this lane's query row (B operand of S^T = K Q^T)
     f32x16 acc[G::DB];     // O^T accumulator
-    f32x16 s[2];           // S^T of the current tile (two 32-key blocks)
+    f32x16 s[NB];          // S^T of the current tile, one fragment per 32-key block
     float m, l;            // running row max of the raw scores; this lane's share of the running row sum
     float tnext;           // this lane's maximum over s[] as it stands (all keys taken as visible)
     int rm[G::KK];         // per-lane LDS offsets of the K fragments (row-major read), block 0 of a tile
@@ -66,11 +67,12 @@ struct FwdTileLoad {
     }
 };
 
-// this lane's maximum over the 32 scores of a tile (v_max3: two scores per instruction)
-__device__ __forceinline__ float lane_max(const f32x16 (&s)[2]) {
+// this lane's maximum over its 16 NB scores of a tile (v_max3: two scores per instruction)
+template <int NB>
+__device__ __forceinline__ float lane_max(const f32x16 (&s)[NB]) {
     float t = fmaxf(s[0][0], s[0][1]);
 #pragma unroll
-    for (int e = 2; e < 32; ++e) t = fmaxf(t, s[e >> 4][e & 15]);   // a chain: pairs of steps become one v_max3
+    for (int e = 2; e < 16 * NB; ++e) t = fmaxf(t, s[e >> 4][e & 15]);   // a chain: pairs of steps become one v_max3
     return t;
 }
 
@@ -91,8 +93,10 @@ __device__ __forceinline__ float pair_max(float x) {
 // all waves queue up in front of the CU's one address unit.
 // BLOCK: a lane's row may have no visible key so far (its running max is still -inf): the maximum that the
 // exponentials are taken against is then replaced by 0, which keeps every weight and the rescale factor at 0.
-template <int D, int KD, bool MASK, bool LAST, bool SPREAD, bool BLOCK>
-__device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* kbuf, const char* vbuf, float c,
+// NB = 1: the wave's only 32-key block of the tile is part of the addresses; its eight score pairs all go under the
+// MFMAs of phase A, the copies too (two per step where the phase has fewer steps than copies).
+template <int D, int KD, int NB, bool MASK, bool LAST, bool SPREAD, bool BLOCK>
+__device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const char* kbuf, const char* vbuf, float c,
                                               int dkey /* my_row - key0 - 4 * (lane / 32) */,
                                               const FwdTileLoad<D>& load) {
     using G = FwdGeom<D, KD>;
@@ -103,7 +107,7 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
     if constexpr (MASK) {
         // element i of block jb is key 32 jb + 8 (i / 4) + i % 4 (+ 4 (lane / 32), folded into dkey)
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
+        for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
             for (int i = 0; i < 16; ++i)
                 if (32 * jb + 8 * (i >> 2) + (i & 3) > dkey) st.s[jb][i] = -INFINITY;
@@ -138,9 +142,9 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
     // ---------------- phase A: S^T(kt+1) on the MFMA, exp2 / row sum / bf16 pack of tile kt on the VALU.
     // Written out step by step with a scheduling barrier after each: step n issues the K fragment read of
     // MFMA n + kAheadK, MFMA n, and the softmax work on two scores.
-    f32x16 sn[2];
+    f32x16 sn[NB];
     float psum = 0.f;
-    union { u32x4 u; bf16x8 v; } pw[4];
+    union { u32x4 u; bf16x8 v; } pw[2 * NB];
     auto softmax_pair = [&](int n) {   // scores 2n, 2n+1 of the tile's 32 per lane -> one packed bf16 pair
         const int jb = n >> 3, i = (n & 7) * 2;
         const float e0 = fast_exp2(fmaf(st.s[jb][i], c, -mc));
@@ -154,8 +158,8 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
     };
     if constexpr (!LAST) {
         constexpr int kAheadK = 4;
-        constexpr int NM = 2 * KK;               // MFMAs of the phase
-        static_assert(2 * NP <= NM, "one copy instruction per MFMA step");
+        constexpr int NM = NB * KK;              // MFMAs of the phase
+        static_assert(NB == 1 || 2 * NP <= NM, "one copy instruction per MFMA step");
         auto k_frag = [&](int n) {
             return *reinterpret_cast<const bf16x8*>(kbuf + st.rm[n % KK] + (n / KK) * 32 * D * 2);
         };
@@ -163,14 +167,19 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
 #pragma unroll
         for (int n = 0; n < kAheadK; ++n) kq[n] = k_frag(n);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { sn[0][i] = 0.f; sn[1][i] = 0.f; }
+        for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sn[jb][i] = 0.f;
 #pragma unroll
         for (int n = 0; n < NM; ++n) {
             if (n + kAheadK < NM) kq[(n + kAheadK) % (kAheadK + 1)] = k_frag(n + kAheadK);
             sn[n / KK] = mfma(kq[n % (kAheadK + 1)], st.qf[n % KK], sn[n / KK]);
             // the first 8 of the 16 score pairs (key block 0, P fragments 0 and 1) spread over the NM MFMAs; the
             // other 8 go under the first P V MFMAs of phase B, which only need fragments 0 and 1
-            if constexpr (NM > 8) {
+            if constexpr (NB == 1) {
+#pragma unroll
+                for (int x = n * 8 / NM; x < (n + 1) * 8 / NM; ++x) softmax_pair(x);
+            } else if constexpr (NM > 8) {
                 // pairs 0 .. NM/2 - 1 at the even steps; with fewer than 16 steps the remaining ones at the last odd steps
                 if (n % 2 == 0) softmax_pair(n / 2);
                 else if (7 - (NM - 1 - n) / 2 >= NM / 2) softmax_pair(7 - (NM - 1 - n) / 2);
@@ -178,7 +187,13 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
                 static_assert(NM == 8, "eight score pairs over the steps of the phase");
                 softmax_pair(n);
             }
-            if constexpr (SPREAD) {
+            if constexpr (SPREAD && NB == 1) {
+#pragma unroll
+                for (int x = n * 2 * NP / NM; x < (n + 1) * 2 * NP / NM; ++x) {
+                    if (x < NP) load.k_piece(x);
+                    else load.v_piece(x - NP);
+                }
+            } else if constexpr (SPREAD) {
                 // all copies early in the iteration: both tiles are needed right after the next barrier
                 if (n < NP) load.k_piece(n);
                 else if (n < 2 * NP) load.v_piece(n - NP);
@@ -194,7 +209,7 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
     // ---------------- phase B: O^T += V(kt)^T P^T(kt), transpose reads kAheadV MFMAs ahead
     {
         constexpr int kAheadV = 3;
-        constexpr int NM = 4 * DB;
+        constexpr int NM = 2 * NB * DB;
         auto v_frag = [&](int n) {
             const int t = n / DB, db = n % DB;
             const int off = t * 16 * D * 2;
@@ -220,7 +235,9 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
             if (n + kAheadV < NM) vq[(n + kAheadV) % (kAheadV + 1)] = v_frag(n + kAheadV);
             st.acc[n % DB] = mfma(vq[n % (kAheadV + 1)], pw[n / DB].v, st.acc[n % DB]);
             // score pairs 8 .. 15 (key block 1, P fragments 2 and 3) under the MFMAs of fragments 0 and 1
-            if constexpr (DB == 4) {
+            if constexpr (NB == 1) {
+                if (!LAST) max_share(n * 16 / NM, 16 / NM);
+            } else if constexpr (DB == 4) {
                 if (n < 8) softmax_pair(8 + n);
                 else if (!LAST) max_share((n - 8) * 4, 4);
             } else {
@@ -234,17 +251,21 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD>& st, const char* k
     __builtin_amdgcn_s_setprio(0);
     st.l = st.l * alpha + psum;
     if constexpr (!LAST) {
-        st.s[0] = sn[0];
-        st.s[1] = sn[1];
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) st.s[jb] = sn[jb];
     }
 }
 
 }  // namespace
 
-template <int D, bool BLOCK, int KD = D / 16>
+// SPLIT: the unit of work is half an item, 64 rows; two waves share each 32-row block, one takes the first 32-key block of
+// every tile, the other the second, each with a running maximum and sum of its own, and their results meet in LDS at the
+// end.  Same copies and LDS per tile, half the products: for packs whose longest item outlasts the rest of the pass.
+template <int D, bool BLOCK, int KD, bool SPLIT>
 __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
     using G = FwdGeom<D, KD>;
-    constexpr int BQ = kFwdQTile, BK = kFwdKTile;
+    constexpr int BQ = SPLIT ? kFwdQTile / 2 : kFwdQTile, BK = kFwdKTile;
+    constexpr int NB = SPLIT ? 1 : 2;
     constexpr int KK = G::KK, DB = G::DB;
     constexpr int kTileBytes = G::kTileBytes;
     // K tiles kt+1 / kt+2 and V tiles kt / kt+1: two buffers each
@@ -252,12 +273,14 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
     // the slot handed round after an item, double-buffered: between two hand-overs there is one barrier, and with a single
     // word the leader could overwrite it before a late wave has read it (items that only write zeros pass no other barrier)
     __shared__ int next_slot[2];
+    __shared__ float2 row_stats[SPLIT ? 2 * 64 : 1];   // (maximum, sum) that the second wave of a row block hands to the first
     char* const kbuf0 = lds;
     char* const vbuf0 = lds + 2 * kTileBytes;
     const uint32_t kdst0 = lds_address(lds), vdst0 = kdst0 + 2 * kTileBytes;   // the same buffers as copy destinations
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row_block = SPLIT ? wave & 1 : wave, key_block = SPLIT ? wave >> 1 : 0;   // this wave's 32 rows; its keys of a tile
     const int hh = lane >> 5;
     const int hd = p.head_dim;   // elements per head in memory, <= D (columns hd .. D-1 exist only in LDS and registers)
     const float c = p.scale_log2;
@@ -278,12 +301,19 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
             tr[db][1] = tile_offset<D>(row + 8, col);
         }
     }
+    if constexpr (SPLIT) {
+        const int skip = key_block * 32 * D * 2;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) rm[kk] += skip;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) { tr[db][0] += skip; tr[db][1] += skip; }
+    }
 
     // ---- one work item: a 128-row q tile of one (sequence, q head)
     ItemQueue queue;
     queue.init(p.queue);
     int drawn = 0;
-    auto run_item = [&](const ItemGeom& item) {
+    auto run_item = [&](const ItemGeom& item, int half) {
         // The lane index as the item's own code sees it: an empty statement makes it a new value per item, so that what
         // the prologue and the epilogue derive from it (row numbers, addresses of the staged stores) is computed per
         // item.  Derived from the kernel-wide lane index, those values would be loop-invariant, would be moved out of
@@ -293,15 +323,19 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
         const int hh = lane >> 5;
         // the item's state is a new object: nothing of the previous item stays alive (a state kept across items would
         // hold the previous scores in registers through the prologue, wherever a wave might have no tile of its own)
-        FwdState<D, KD> st;
+        FwdState<D, KD, NB> st;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) st.rm[kk] = rm[kk];
 #pragma unroll
         for (int db = 0; db < DB; ++db) { st.tr[db][0] = tr[db][0]; st.tr[db][1] = tr[db][1]; }
         const int Lq = item.q_len, L = item.k_len, off = item.offset;   // L: keys of the chunk (= rows when !BLOCK)
         const int h = item.head, hk = h / p.group;
-        const int q_row0 = item.tile * BQ;
-        const int wave_row0 = q_row0 + wave * 32;
+        const int q_row0 = item.tile * kFwdQTile + (SPLIT ? half * BQ : 0);
+        if (SPLIT && q_row0 >= Lq) {   // the last item of a sequence may have no second half
+            if (tid == 0) drawn = queue.draw();
+            return;
+        }
+        const int wave_row0 = q_row0 + row_block * 32;
         const int my_row = wave_row0 + (lane & 31);
 
         const uint16_t* qbase = p.q + (int64_t)item.q_start * p.q_stride + (int64_t)h * hd;
@@ -317,11 +351,13 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
         // are visible to all of them (a wave whose rows lie past the end of the chunk computes nothing).  On the
         // diagonal the upper waves of a workgroup see fewer tiles than the lower ones.
         const int kv_end_w = wave_row0 < Lq ? max(0, min(L, min(Lq, wave_row0 + 32) + off)) : 0;
-        const int n_tiles_w = (kv_end_w + BK - 1) / BK;
-        const int n_interior_w = max(0, min(min(n_tiles_w, (wave_row0 + off + 1) / BK), L / BK));
+        // (SPLIT: tiles whose block of this wave holds such a key)
+        const int n_tiles_w = SPLIT ? (max(0, kv_end_w - key_block * 32) + BK - 1) / BK : (kv_end_w + BK - 1) / BK;
+        const int n_interior_w = SPLIT ? max(0, min(n_tiles_w, (min(wave_row0 + off + 1, L) - key_block * 32 + 32) / BK))
+                                       : max(0, min(min(n_tiles_w, (wave_row0 + off + 1) / BK), L / BK));
         if (BLOCK && n_tiles == 0) {
             // no key of the chunk is visible to any row of the tile: O = 0, LSE = -inf
-            if (my_row < Lq) {
+            if (my_row < Lq && key_block == 0) {
                 float* orow = p.o_f32 + ((int64_t)(item.q_start + my_row) * p.q_heads + h) * hd;
     #pragma unroll
                 for (int c4 = 0; c4 < D / 8; ++c4)
@@ -358,7 +394,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
         // S^T(0), not pipelined
         if (n_tiles_w > 0)
     #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
+        for (int jb = 0; jb < NB; ++jb) {
     #pragma unroll
             for (int i = 0; i < 16; ++i) st.s[jb][i] = 0.f;
     #pragma unroll
@@ -380,8 +416,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
             }
             if (kt + 2 < n_tiles) kvcopy.issue(kdst0 + (kt & 1) * kTileBytes, kbase, p.kv_stride, (kt + 2) * BK, L, wave, lane);
             if (kt + 1 < n_tiles) kvcopy.issue(vdst0 + ((kt + 1) & 1) * kTileBytes, vbase, p.kv_stride, (kt + 1) * BK, L, wave, lane);
-            fwd_iteration<D, KD, decltype(masked)::value, decltype(last)::value, false, BLOCK>(
-                st, kbuf0 + ((kt + 1) & 1) * kTileBytes, vbuf0 + (kt & 1) * kTileBytes, c, my_limit - kt * BK - 4 * hh, no_load);
+            fwd_iteration<D, KD, NB, decltype(masked)::value, decltype(last)::value, false, BLOCK>(
+                st, kbuf0 + ((kt + 1) & 1) * kTileBytes, vbuf0 + (kt & 1) * kTileBytes, c,
+                my_limit - kt * BK - key_block * 32 - 4 * hh, no_load);
         };
         // the same for an unmasked tile whose successors kt+1 and kt+2 are whole tiles: their copies need no case
         // distinction and are issued from inside the iteration
@@ -400,7 +437,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
             load.k_dst = kdst0 + par * kTileBytes;
             load.v_dst = vdst0 + (1 - par) * kTileBytes;
             load.wave = wave;
-            fwd_iteration<D, KD, false, false, true, BLOCK>(st, kbuf0 + (1 - par) * kTileBytes, vbuf0 + par * kTileBytes, c,
+            fwd_iteration<D, KD, NB, false, false, true, BLOCK>(st, kbuf0 + (1 - par) * kTileBytes, vbuf0 + par * kTileBytes, c,
                                                         my_limit - kt * BK - 4 * hh, load);
         };
         // a tile past this wave's own diagonal: the barrier and the wave's share of the copies, nothing else
@@ -436,10 +473,38 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
         // the next slot is requested when the tiles are done (not earlier: a slot reserved at the start of a long item
         // would wait for that item while other workgroups run out of work) and looked at after the stores
         if (tid == 0) drawn = queue.draw();
-        const float l_row = st.l + partner32(st.l);
+        float l_row = st.l + partner32(st.l);
         // O leaves through LDS (free once every wave has left the tile loop) so that every store instruction writes
         // whole rows; a row that saw no key (BLOCK only) has l = 0 and m = -inf: O = 0, LSE = -inf
         __syncthreads();
+        if constexpr (SPLIT) {
+            char* const area = vbuf0 + row_block * (32 * D * 4);
+            if (key_block == 1) {
+    #pragma unroll
+                for (int db = 0; db < DB; ++db)
+    #pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4)
+                        *reinterpret_cast<f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16) =
+                            f32x4{st.acc[db][4 * i4], st.acc[db][4 * i4 + 1], st.acc[db][4 * i4 + 2], st.acc[db][4 * i4 + 3]};
+                row_stats[row_block * 64 + lane] = make_float2(st.m, l_row);
+            }
+            __syncthreads();
+            if (key_block == 1) return;
+            // (a wave that met no key has m = -inf, l = 0, O = 0: its factor is exp2(-inf) = 0)
+            const float2 other = row_stats[row_block * 64 + lane];
+            const float m = fmaxf(st.m, other.x), m_ref = m == -INFINITY ? 0.f : m;
+            const float fa = fast_exp2((st.m - m_ref) * c), fb = fast_exp2((other.x - m_ref) * c);
+    #pragma unroll
+            for (int db = 0; db < DB; ++db)
+    #pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const f32x4 y = *reinterpret_cast<const f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16);
+    #pragma unroll
+                    for (int j = 0; j < 4; ++j) st.acc[db][4 * i4 + j] = st.acc[db][4 * i4 + j] * fa + y[j] * fb;
+                }
+            l_row = l_row * fa + other.y * fb;
+            st.m = m;
+        }
         const float inv = (!BLOCK || l_row > 0.f) ? 1.f / l_row : 0.f;
         const int rows = min(32, Lq - wave_row0);
         const int64_t row0_elem = ((int64_t)(item.q_start + wave_row0) * p.q_heads + h) * hd;
@@ -449,10 +514,10 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
     #pragma unroll
             for (int i = 0; i < 16; ++i) st.acc[db][i] *= inv;
         if constexpr (BLOCK) {
-            store_tile_f32<D, false>(lds + wave * (32 * D * 4), st.acc, 1.f, p.o_f32 + row0_elem, (int64_t)p.q_heads * hd, rows,
+            store_tile_f32<D, false>(lds + row_block * (32 * D * 4), st.acc, 1.f, p.o_f32 + row0_elem, (int64_t)p.q_heads * hd, rows,
                                      hd, lane);
         } else {
-            store_tile_bf16<D>(lds + wave * (32 * D * 2), st.acc, 1.f, p.o + row0_elem, (int64_t)p.q_heads * hd, rows, hd, lane);
+            store_tile_bf16<D>(lds + row_block * (32 * D * 2), st.acc, 1.f, p.o + row0_elem, (int64_t)p.q_heads * hd, rows, hd, lane);
         }
         if (my_row < Lq && hh == 0)
             p.lse[(int64_t)h * p.total_tokens + item.q_start + my_row] =
@@ -461,37 +526,44 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
     };
 
     // ---- the persistent loop: the first item is the workgroup's own slot, the others are drawn from its queue
+    // (SPLIT: the entries of a queue are half items, an item's second half, which sees more keys, before its first)
     int slot = blockIdx.x;
     for (int turn = 0;; turn ^= 1) {
-        const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, slot);
+        const int list_slot = SPLIT ? slot / (2 * kQueues) * kQueues + slot % kQueues : slot;
+        if (SPLIT && list_slot >= p.num_items) break;
+        const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, list_slot);
         if (item.tile < 0) break;          // padding at the end of the queue: nothing left
-        run_item(item);
+        run_item(item, 1 - slot / kQueues % 2);
         if (tid == 0) next_slot[turn] = drawn;
         __syncthreads();                   // publishes the slot; every wave has left the item's LDS areas
         slot = __builtin_amdgcn_readfirstlane(next_slot[turn]);
-        if (slot >= p.num_items) break;
+        if (!SPLIT && slot >= p.num_items) break;
     }
     if (tid == 0) queue.leave();
 }
 
+namespace {
+
+template <int D, int KD>
+void launch(const FwdParams& p, unsigned workgroups, bool block, bool split, hipStream_t stream) {
+    const dim3 grid(workgroups), threads(kThreads);
+    if (block && split) hipLaunchKernelGGL((fwd_kernel<D, true, KD, true>), grid, threads, 0, stream, p);
+    else if (block) hipLaunchKernelGGL((fwd_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
+    else if (split) hipLaunchKernelGGL((fwd_kernel<D, false, KD, true>), grid, threads, 0, stream, p);
+    else hipLaunchKernelGGL((fwd_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
+}
+
+}  // namespace
+
 hipError_t launch_fwd(const FwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
-    const int workgroups = persistent_grid(num_items, 2);
+    const bool split = p.split != 0;
+    const int workgroups = persistent_grid(split ? 2 * ((num_items + kQueues - 1) / kQueues * kQueues) : num_items, 2);
     if (workgroups <= 0) return hipErrorInvalidDevice;
-    const dim3 grid((unsigned)workgroups), threads(kThreads);
-    if (tile_width(head_dim) == 128) {
-        if (contraction_steps(head_dim) <= 7) {
-            // e.g. head_dim 104: the eighth 16-column step of the contraction over head_dim is all padding
-            if (block) hipLaunchKernelGGL((fwd_kernel<128, true, 7>), grid, threads, 0, stream, p);
-            else hipLaunchKernelGGL((fwd_kernel<128, false, 7>), grid, threads, 0, stream, p);
-        } else {
-            if (block) hipLaunchKernelGGL((fwd_kernel<128, true>), grid, threads, 0, stream, p);
-            else hipLaunchKernelGGL((fwd_kernel<128, false>), grid, threads, 0, stream, p);
-        }
-    } else {
-        if (block) hipLaunchKernelGGL((fwd_kernel<64, true>), grid, threads, 0, stream, p);
-        else hipLaunchKernelGGL((fwd_kernel<64, false>), grid, threads, 0, stream, p);
-    }
+    // e.g. head_dim 104: the eighth 16-column step of the contraction over head_dim is all padding
+    if (tile_width(head_dim) == 64) launch<64, 4>(p, (unsigned)workgroups, block, split, stream);
+    else if (contraction_steps(head_dim) <= 7) launch<128, 7>(p, (unsigned)workgroups, block, split, stream);
+    else launch<128, 8>(p, (unsigned)workgroups, block, split, stream);
     return hipGetLastError();
 }
 

@@ -242,6 +242,19 @@ hspmd_status install_lists(hspmd_attn_plan* plan, const void* host, size_t bytes
     return HSPMD_OK;
 }
 
+// Whether the forward and the dQ pass work on half items (64 rows, two waves of a workgroup sharing each 32-row block).  As
+// for the dK/dV pass below: a step of a half item takes about 0.6 of a whole item's (each tile is copied for half the rows),
+// so halves pay when the heaviest item is what the pass waits for: when it is at least twice as long as the work per slot
+// (two workgroups per compute unit), six steps of prologue and stores per half item included.  Measured, forward and dQ pass,
+// whole -> halves (us): heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot
+// 187 -> 145, 213 -> 131; 93 steps, 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 3 steps, 168
+// items 12.2 -> 14.4, 13.3 -> 15.0; 251 steps, 156 per slot 336 -> 376, 450 -> 445; 8 x 2048, 32 heads 304 -> 425, 450 -> 534.
+bool split_rows(const hspmd_attn_plan* plan, hspmd_list_kind kind) {
+    const double slots = 512.0;
+    const double per_slot = ((double)plan->load[kind].total + 6.0 * 2.0 * (double)plan->count[kind]) / slots;
+    return (double)plan->load[kind].heaviest + 6.0 >= 2.0 * per_slot;
+}
+
 // Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass
 // takes as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs
 // 0.68 of the whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy
@@ -550,6 +563,7 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
     p.scale_log2 = scale * 1.4426950408889634f;
     p.num_items = (int32_t)plan->count[HSPMD_LIST_FWD];
     p.queue = plan->queue[HSPMD_LIST_FWD];
+    p.split = split_rows(plan, HSPMD_LIST_FWD) ? 1 : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, plan->head_dim, plan->count[HSPMD_LIST_FWD], false, s); });
     if (e != hipSuccess) return fail_hip(e, "forward launch");
@@ -605,6 +619,8 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     hipStream_t s = static_cast<hipStream_t>(stream);
     // D = rowsum(dO * O) is computed by the dQ pass itself (every (row, head) belongs to exactly one of its items)
     p.items = plan->items[HSPMD_LIST_DQ];
+    p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
+    p.split = split_rows(plan, HSPMD_LIST_DQ) ? 1 : 0;
     auto dq_pass = [&] { return hspmd::launch_bwd_dq(p, plan->head_dim, plan->count[HSPMD_LIST_DQ], false, s); };
     hipError_t e = timed ? timed_launch(2, s, dq_pass) : dq_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dQ launch");
@@ -861,6 +877,7 @@ hspmd_status hspmd_attn_block_fwd(const hspmd_attn_plan* plan, const void* q, co
     p.scale_log2 = scale * 1.4426950408889634f;
     p.num_items = (int32_t)plan->count[HSPMD_LIST_FWD];
     p.queue = plan->queue[HSPMD_LIST_FWD];
+    p.split = split_rows(plan, HSPMD_LIST_FWD) ? 1 : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, plan->head_dim, plan->count[HSPMD_LIST_FWD], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block forward launch");
@@ -943,6 +960,8 @@ static hspmd_status block_bwd(const hspmd_attn_plan* plan, const void* q, const 
         if (e != hipSuccess) return fail_hip(e, "backward D launch");
     }
     p.block_items = plan->block_items[HSPMD_LIST_DQ];
+    p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
+    p.split = split_rows(plan, HSPMD_LIST_DQ) ? 1 : 0;
     e = timed_launch(2, s, [&] { return hspmd::launch_bwd_dq(p, plan->head_dim, plan->count[HSPMD_LIST_DQ], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dQ launch");
     p.block_items = plan->block_items[HSPMD_LIST_DKV];

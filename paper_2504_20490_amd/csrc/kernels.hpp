@@ -23,6 +23,7 @@ struct FwdParams {
     float scale_log2;              // softmax_scale * log2(e)
     int32_t num_items;             // slots of the work list (padding included)
     int32_t* queue;                // this pass's draw counters (ItemQueue), zero between launches
+    int32_t split;                 // the unit of work is half an item (decided from the plan's loads, see split_rows)
 };
 
 struct BwdParams {
@@ -52,7 +53,7 @@ struct BwdParams {
     float scale_log2;              // softmax_scale * log2(e)
     int32_t num_items;             // slots of the current pass's work list (padding included)
     int32_t* queue;                // the current pass's draw counters (ItemQueue), zero between launches
-    int32_t split;                 // dK/dV pass: two workgroups per item (decided from the plan's loads, see split_dkv)
+    int32_t split;                 // dK/dV pass: two workgroups per item (decided from the plan's loads, see split_rows, split_dkv)
 };
 
 // The kernels exist for tile widths 64 and 128 (LDS rows, MFMA contraction); a head_dim below the tile width runs
