@@ -263,13 +263,14 @@ __device__ __forceinline__ void store_grad4(void* base, int64_t elem, bool f32, 
 // FULL: all 32 rows and all D columns exist (decided per wave by the callers below).  Without the per-row test the
 // second loop is straight-line code: the LDS reads are issued together and the stores follow as the data arrives,
 // instead of one LDS round trip per store.
-template <int D, bool ACCUM, bool FULL>
-__device__ __forceinline__ void store_tile_f32_rows(char* wave_lds, const f32x16 (&acc)[D / 32], float mul, float* first_row,
+// DB: 32-column blocks that hold data (deduced): D / 32, or fewer for a head that ends before the tile's last block
+template <int D, bool ACCUM, bool FULL, int DB>
+__device__ __forceinline__ void store_tile_f32_rows(char* wave_lds, const f32x16 (&acc)[DB], float mul, float* first_row,
                                                     int64_t row_stride, int valid_rows, int head_dim, int lane) {
     constexpr int kChunks = D / 4;                // 16-byte chunks per row
     const int r = lane & 31, hh = lane >> 5;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
             const int chunk = (db * 32 + i4 * 8 + hh * 4) / 4;
@@ -295,23 +296,23 @@ __device__ __forceinline__ void store_tile_f32_rows(char* wave_lds, const f32x16
     }
 }
 
-template <int D, bool ACCUM>
-__device__ __forceinline__ void store_tile_f32(char* wave_lds, const f32x16 (&acc)[D / 32], float mul, float* first_row,
+template <int D, bool ACCUM, int DB>
+__device__ __forceinline__ void store_tile_f32(char* wave_lds, const f32x16 (&acc)[DB], float mul, float* first_row,
                                                int64_t row_stride, int valid_rows, int head_dim, int lane) {
-    if (valid_rows >= 32 && head_dim == D)
+    if (DB * 32 == D && valid_rows >= 32 && head_dim == D)
         store_tile_f32_rows<D, ACCUM, true>(wave_lds, acc, mul, first_row, row_stride, valid_rows, head_dim, lane);
     else
         store_tile_f32_rows<D, ACCUM, false>(wave_lds, acc, mul, first_row, row_stride, valid_rows, head_dim, lane);
 }
 
 // The same for a bf16 destination: rows of D bf16 in LDS (8-byte pieces in, 16-byte chunks out).
-template <int D, bool FULL>
-__device__ __forceinline__ void store_tile_bf16_rows(char* wave_lds, const f32x16 (&acc)[D / 32], float mul, uint16_t* first_row,
+template <int D, bool FULL, int DB>
+__device__ __forceinline__ void store_tile_bf16_rows(char* wave_lds, const f32x16 (&acc)[DB], float mul, uint16_t* first_row,
                                                      int64_t row_stride, int valid_rows, int head_dim, int lane) {
     constexpr int kChunks = D / 8;                // 16-byte chunks (8 bf16) per row
     const int r = lane & 31, hh = lane >> 5;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
             const int col = db * 32 + i4 * 8 + hh * 4;           // 4 elements = half a chunk
@@ -332,10 +333,10 @@ __device__ __forceinline__ void store_tile_bf16_rows(char* wave_lds, const f32x1
     }
 }
 
-template <int D>
-__device__ __forceinline__ void store_tile_bf16(char* wave_lds, const f32x16 (&acc)[D / 32], float mul, uint16_t* first_row,
+template <int D, int DB>
+__device__ __forceinline__ void store_tile_bf16(char* wave_lds, const f32x16 (&acc)[DB], float mul, uint16_t* first_row,
                                                 int64_t row_stride, int valid_rows, int head_dim, int lane) {
-    if (valid_rows >= 32 && head_dim == D)
+    if (DB * 32 == D && valid_rows >= 32 && head_dim == D)
         store_tile_bf16_rows<D, true>(wave_lds, acc, mul, first_row, row_stride, valid_rows, head_dim, lane);
     else
         store_tile_bf16_rows<D, false>(wave_lds, acc, mul, first_row, row_stride, valid_rows, head_dim, lane);
@@ -353,8 +354,8 @@ __device__ __forceinline__ void store_tile_bf16(char* wave_lds, const f32x16 (&a
 //   ACCUM: add to what the destination holds (fp32 only; the rotation is linear, so a sum of rotated shares is the
 //   rotated sum)
 //   FULL: all 32 rows and all D columns exist (straight-line code, see store_tile_f32_rows)
-template <int D, bool ACCUM, bool FULL>
-__device__ __forceinline__ void store_tile_rope_transposed_rows(char* wave_lds, const f32x16 (&acc)[D / 32], float mul, void* base,
+template <int D, bool ACCUM, bool FULL, int DB>
+__device__ __forceinline__ void store_tile_rope_transposed_rows(char* wave_lds, const f32x16 (&acc)[DB], float mul, void* base,
                                                                 int64_t first_elem, bool f32, int64_t row_stride, int valid_rows,
                                                                 int head_dim, const float* table_row0, int lane) {
     constexpr int kChunks = D / 4;             // 16-byte chunks per staged row
@@ -376,7 +377,7 @@ __device__ __forceinline__ void store_tile_rope_transposed_rows(char* wave_lds, 
     }
     const int r = lane & 31, hh = lane >> 5;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
             const int chunk = (db * 32 + i4 * 8 + hh * 4) / 4;
@@ -412,11 +413,11 @@ __device__ __forceinline__ void store_tile_rope_transposed_rows(char* wave_lds, 
     }
 }
 
-template <int D, bool ACCUM = false>
-__device__ __forceinline__ void store_tile_rope_transposed(char* wave_lds, const f32x16 (&acc)[D / 32], float mul, void* base,
+template <int D, bool ACCUM = false, int DB>
+__device__ __forceinline__ void store_tile_rope_transposed(char* wave_lds, const f32x16 (&acc)[DB], float mul, void* base,
                                                            int64_t first_elem, bool f32, int64_t row_stride, int valid_rows,
                                                            int head_dim, const float* table_row0, int lane) {
-    if (valid_rows >= 32 && head_dim == D)
+    if (DB * 32 == D && valid_rows >= 32 && head_dim == D)
         store_tile_rope_transposed_rows<D, ACCUM, true>(wave_lds, acc, mul, base, first_elem, f32, row_stride, valid_rows, head_dim,
                                                         table_row0, lane);
     else

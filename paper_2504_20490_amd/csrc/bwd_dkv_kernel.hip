@@ -32,13 +32,15 @@ namespace hspmd {
 namespace {
 
 // KD: 16-column steps of the contractions over head_dim (G1) that hold data: D / 16, or fewer when head_dim ends
-// before the tile width (the steps beyond it would multiply the zero padding of the K / V fragments)
+// before the tile width (the steps beyond it would multiply the zero padding of the K / V fragments); the products whose
+// output is head_dim wide (G2) take (KD + 1) / 2 blocks of 32 columns.  8 x 2048, 32 heads, head_dim 96: 6 steps and 3 blocks
+// instead of 7 and 4, 618 -> 527 us.
 template <int D, int KD = D / 16>
 struct DkvGeom {
     static_assert(KD >= 1 && KD <= D / 16, "k-steps inside the tile width");
-    static constexpr int KK = D / 16;                      // fragments per G2 operand (2 k-steps x D / 32 row blocks)
+    static constexpr int DB = (KD + 1) / 2;                // 32-row blocks of dK^T / dV^T that hold data
+    static constexpr int KK = 2 * DB;                      // fragments per G2 operand (2 k-steps x DB row blocks)
     static constexpr int K1 = KD;                          // k-steps over head_dim of G1
-    static constexpr int DB = D / 32;                      // 32-row blocks of dK^T / dV^T
     static constexpr int kTileBytes = kDkvQTile * D * 2;   // one 64-row tile
     static constexpr int kBlockBytes = 32 * D * 2;         // one 32-row block of it
     static constexpr int kStatBytes = 1024;                // -LSE/scale [64] at +0, -D [64] at +256
@@ -58,9 +60,9 @@ struct DkvState {
 };
 
 // per-lane LDS byte addresses (stage base included) of the operand fragments
-template <int D>
+template <int D, int KD>
 struct DkvAddr {
-    using G = DkvGeom<D>;
+    using G = DkvGeom<D, KD>;
     int rm[G::KK];         // row-major fragment kk of a 32-row block (Q tile; dO tile is + kTileBytes)
     int tr[G::DB][2];      // transposed fragment: column block db, 8-row part
     int st;                // statistics
@@ -127,8 +129,8 @@ __device__ __forceinline__ bf16x8 lds_read_tr(const char* lds, int a0, int a1) {
 // to the MFMAs by the scheduling hints): pieces 0-3 in the first iteration of a tile, 4-8 in the second; all of them
 // when a tile has one iteration (!WHOLE).
 template <int D, int KD, int RB, bool MASK, bool SPREAD, bool WHOLE>
-__device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D>& ahead,
-                                              const DkvAddr<D>& cur, int dkey, float c, const DkvTileLoad<D>& load) {
+__device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D, KD>& ahead,
+                                              const DkvAddr<D, KD>& cur, int dkey, float c, const DkvTileLoad<D>& load) {
     using G = DkvGeom<D, KD>;
     constexpr int KK = G::KK, DB = G::DB, K1 = G::K1;
     constexpr int NRB = RB ^ 1;
@@ -162,7 +164,7 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
         st.qf[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes);
         st.dof[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes + G::kTileBytes);
         if constexpr (SPREAD && !WHOLE) {
-            if (kk % 2 == 1) load.piece_at(kk / 2);
+            if (kk % 2 == 0) load.piece_at(kk / 2);
         } else if constexpr (SPREAD) {
             if (kk == KK / 4 - 1) load.template piece<P0>();
             if (kk == 3 * KK / 4 - 1) load.template piece<P0 + 1>();
@@ -193,8 +195,8 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
             st.qtf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off, cur.tr[db][1] + off);
             st.dotf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off + G::kTileBytes, cur.tr[db][1] + off + G::kTileBytes);
             if constexpr (SPREAD && !WHOLE) {
-                static_assert(K1 / 2 + KK >= DkvTileLoad<D>::kPieces, "a place for every piece");
-                load.piece_at(K1 / 2 + tt * DB + db);
+                static_assert((K1 + 1) / 2 + KK >= DkvTileLoad<D>::kPieces, "a place for every piece");
+                load.piece_at((K1 + 1) / 2 + tt * DB + db);
             } else if constexpr (SPREAD) {
                 if (tt == 0 && db == DB - 1) load.template piece<P0 + 2>();
                 if (tt == 1 && db == DB / 2 - 1) load.template piece<P0 + 3>();
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     const float c = p.scale_log2;
 
     // per-lane fragment offsets inside a stage
-    DkvAddr<D> off;
+    DkvAddr<D, KD> off;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) off.rm[kk] = tile_offset<D>(lane & 31, kk * 16 + hh * 8);
     {
@@ -356,8 +358,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     }
     // `off` holds the addresses of the current tile's stage and is moved from stage to stage by adding the
     // distance (one set of address registers instead of one per stage in use)
-    auto shifted = [&](const DkvAddr<D>& a0, int bytes) {
-        DkvAddr<D> a;
+    auto shifted = [&](const DkvAddr<D, KD>& a0, int bytes) {
+        DkvAddr<D, KD> a;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) a.rm[kk] = a0.rm[kk] + bytes;
 #pragma unroll
@@ -371,7 +373,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
 
     // prologue: G1(0) computed directly on top of block 0's statistics; P = dS = 0 for the non-existent block -1
     {
-        const DkvAddr<D>& a0 = off;   // stage 0
+        const DkvAddr<D, KD>& a0 = off;   // stage 0
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
             const f32x4 a = *reinterpret_cast<const f32x4*>(lds + a0.st + i4 * 32);
@@ -413,7 +415,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
         if (u + 3 < n_tiles) load_tile(u + 3, stage3);
         // block 2u+2 lives in the next tile; the last tile has none: it re-reads itself (result unused)
         const int to_next = (stage1 - stage) * G::kStageBytes;
-        const DkvAddr<D> next = shifted(off, u + 1 < n_tiles ? to_next : 0);
+        const DkvAddr<D, KD> next = shifted(off, u + 1 < n_tiles ? to_next : 0);
         const int dkey0 = my_key - shift - qt * BQ - row_block * 32 - 4 * hh;
         if constexpr (SPLIT) {
             dkv_iteration<D, KD, kPar, kMask, false, false>(st, lds, next, off, dkey0, c, no_load);
@@ -439,7 +441,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
         load.stage = lds0 + stage3 * G::kStageBytes;
         load.stat_dst = load.stage + 2 * G::kTileBytes + (wave & 1) * 256;
         const int to_next = (stage1 - stage) * G::kStageBytes;
-        const DkvAddr<D> next = shifted(off, to_next);
+        const DkvAddr<D, KD> next = shifted(off, to_next);
         const int dkey0 = my_key - shift - qt * BQ - row_block * 32 - 4 * hh;
         if constexpr (SPLIT) {
             dkv_iteration<D, KD, kPar, false, true, false>(st, lds, next, off, dkey0, c, load);
@@ -588,7 +590,9 @@ hipError_t launch_bwd_dkv(const BwdParams& p, int head_dim, int64_t num_items, b
     if (num_items == 0) return hipSuccess;
     const bool split = p.split != 0;
     if (tile_width(head_dim) == 64) launch_dkv<64, 4>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) <= 7) launch_dkv<128, 7>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) <= 5) launch_dkv<128, 5>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) == 6) launch_dkv<128, 6>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) == 7) launch_dkv<128, 7>(p, num_items, block, split, stream);
     else launch_dkv<128, 8>(p, num_items, block, split, stream);
     return hipGetLastError();
 }

@@ -50,7 +50,9 @@ __global__ __launch_bounds__(kThreads) void bwd_dsum_kernel(BwdParams p) {
 
 // --------------------------------------------------------------------------------- dQ pass
 // KD: 16-column steps of the contractions over head_dim (S^T = K Q^T, dP^T = V dO^T) that hold data: D / 16, or fewer
-// when head_dim ends before the tile width (the steps beyond it would multiply the zero padding of the Q / dO fragments)
+// when head_dim ends before the tile width (the steps beyond it would multiply the zero padding of the Q / dO fragments);
+// dQ^T += K^T dS^T takes (KD + 1) / 2 blocks of 32 columns.  8 x 2048, 32 heads, head_dim 96: 6 steps and 3 blocks instead of
+// 7 and 4, 402 -> 350 us.
 // Tile width 64 needs 168 registers per wave, so a third workgroup fits a compute unit (170 had kept it out):
 // sequences of 32 .. 512 tokens, 16 heads: 55 -> 48 us; 8 x 2048, 32 heads: 244 -> 230 us.
 // SPLIT: a workgroup takes half an item, 64 rows; two waves share each 32-row block, one takes the first 32-key block of
@@ -59,7 +61,7 @@ template <int D, bool BLOCK, int KD, bool SPLIT>
 __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(BwdParams p) {
     static_assert(KD >= 1 && KD <= D / 16, "k-steps inside the tile width");
     constexpr int BQ = SPLIT ? kFwdQTile / 2 : kFwdQTile, BK = kFwdKTile;
-    constexpr int KK = KD, DB = D / 32;
+    constexpr int KK = KD, DB = (KD + 1) / 2;   // DB: 32-column blocks of dQ that hold data
     constexpr int kTileBytes = BK * D * 2;
     __shared__ __attribute__((aligned(1024))) char lds[2 * 2 * kTileBytes];   // {K, V} x 2 stages
 
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
             if (n < KK) sacc = mfma(q1[n % (kAhead + 1)], qf[n], sacc);
             else dp = mfma(q1[n % (kAhead + 1)], dof[n - KK], dp);
             if constexpr (kSpread) {
-                if (n % every == every - 1 && (!SPLIT || n / every < kPieces)) piece(jb, n / every);
+                if (n % every == every - 1 && n / every < kPieces) piece(jb, n / every);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -417,7 +419,9 @@ hipError_t launch_bwd_dq(const BwdParams& p, int head_dim, int64_t num_items, bo
     if (num_items == 0) return hipSuccess;
     const bool split = p.split != 0;
     if (tile_width(head_dim) == 64) launch_dq<64, 4>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) <= 7) launch_dq<128, 7>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) <= 5) launch_dq<128, 5>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) == 6) launch_dq<128, 6>(p, num_items, block, split, stream);
+    else if (contraction_steps(head_dim) == 7) launch_dq<128, 7>(p, num_items, block, split, stream);
     else launch_dq<128, 8>(p, num_items, block, split, stream);
     return hipGetLastError();
 }

@@ -59,8 +59,9 @@ struct BwdParams {
 // The kernels exist for tile widths 64 and 128 (LDS rows, MFMA contraction); a head_dim below the tile width runs
 // on the next width up: register fragments are zero beyond head_dim, LDS pad columns repeat a valid chunk.
 inline int tile_width(int head_dim) { return head_dim <= 64 ? 64 : 128; }
-// 16-column steps of a contraction over head_dim that hold data; the kernels of tile width 128 also exist with 7
-// steps (head_dim 97 .. 112, such as the 104 of the paper's 32B model), which skip the step that is all padding
+// 16-column steps of a contraction over head_dim that hold data; the kernels of tile width 128 also exist with 5, 6 and 7
+// steps (head_dim up to 80, 96 and 112, such as the 104 of the paper's 32B model), which skip the steps, and with 5 and 6 the
+// 32-column block of the outputs, that are all padding
 inline int contraction_steps(int head_dim) { return (head_dim + 15) / 16; }
 
 // Workgroups that a persistent kernel starts: as many as the current device holds at once at `per_cu` workgroups per
