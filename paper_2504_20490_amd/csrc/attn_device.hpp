@@ -500,6 +500,44 @@ struct ItemQueue {
     }
 };
 
+// The item loop of a kernel that exists with and without one (dK/dV pass).  Without (false) everything here folds away.
+template <bool ON>
+struct PersistentLoop {
+    ItemQueue queue;
+    int drawn = 0, turn = 0;
+    __device__ __forceinline__ void init(int32_t* counters) {
+        if constexpr (ON) queue.init(counters);
+    }
+    // the lane index as a new value per item, so that what an item derives from it is not kept in registers across items
+    __device__ __forceinline__ int item_lane() const {
+        int lane = threadIdx.x & 63;
+        if constexpr (ON) asm volatile("" : "+v"(lane));
+        return lane;
+    }
+    __device__ __forceinline__ void draw() {
+        if constexpr (ON) {
+            if (threadIdx.x == 0) drawn = queue.draw();
+        }
+    }
+    // ends an item (every wave has left its LDS areas afterwards); false: no further item
+    __device__ __forceinline__ bool next(int& slot, int num_items) {
+        if constexpr (ON) {
+            __shared__ int next_slot[2];   // two words in turn: one barrier separates two hand-overs
+            if (threadIdx.x == 0) next_slot[turn] = drawn;
+            __syncthreads();
+            slot = __builtin_amdgcn_readfirstlane(next_slot[turn]);
+            turn ^= 1;
+            return slot < num_items;
+        }
+        return false;
+    }
+    __device__ __forceinline__ void leave() const {
+        if constexpr (ON) {
+            if (threadIdx.x == 0) queue.leave();
+        }
+    }
+};
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 }  // namespace hspmd

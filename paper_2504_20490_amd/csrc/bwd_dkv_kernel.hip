@@ -227,21 +227,27 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
 //
 // SPLIT: a workgroup takes half an item, 64 keys; the waves are two pairs over the keys, and one pair takes the first
 // 32-row block of every tile, the other the second.  Same copies and LDS per tile, half the products, so a half item takes
-// about half the time: for packs whose longest item outlasts the rest of the pass (see launch_bwd_dkv).  The two
+// 0.68 of the time: for packs whose longest item outlasts the rest of the pass.  The two
 // accumulator pairs of a key meet in LDS at the end, in one fixed order.
-template <int D, bool BLOCK, int KD, bool SPLIT>
+//
+// PERSIST: the workgroup draws items from its queue until none is left (as the forward does), for packs of many short items.
+template <int D, bool BLOCK, int KD, bool SPLIT, bool PERSIST = false>
 __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv_kernel(BwdParams p) {
+    static_assert(!PERSIST || (!BLOCK && !SPLIT), "whole items of packed plans only");
     using G = DkvGeom<D, KD>;
     constexpr int BKV = SPLIT ? kDkvKTile / 2 : kDkvKTile, BQ = kDkvQTile;
     constexpr int KK = G::KK, DB = G::DB, K1 = G::K1;
     __shared__ __attribute__((aligned(1024))) char lds[G::kStages * G::kStageBytes];
 
     // workgroups p and p + 8 of 16 take the halves of an item: like the item itself they belong to XCD p % 8
-    const int slot = SPLIT ? (int)(blockIdx.x / (2 * kQueues)) * kQueues + (int)(blockIdx.x % kQueues) : (int)blockIdx.x;
+    int slot = SPLIT ? (int)(blockIdx.x / (2 * kQueues)) * kQueues + (int)(blockIdx.x % kQueues) : (int)blockIdx.x;
     if (SPLIT && slot >= p.num_items) return;
+    PersistentLoop<PERSIST> loop;
+    loop.init(p.queue);
+    do {
     const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, slot);
-    if (item.tile < 0) return;
-    const int tid = threadIdx.x, lane = tid & 63;
+    if (item.tile < 0) break;
+    const int tid = threadIdx.x, lane = loop.item_lane();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = item.q_len, Lk = item.k_len, shift = item.offset, g = item.head;   // L: rows of the chunk
     const int key0 = item.tile * kDkvKTile + (SPLIT ? (int)(blockIdx.x / kQueues % 2) * BKV : 0);
@@ -502,6 +508,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
         }
     }
 
+    loop.draw();
     // epilogue: G2 of the last block
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
@@ -566,6 +573,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     } else {
         store_tile_bf16<D>(wave_lds, st.dv, 1.f, static_cast<uint16_t*>(p.dv) + row0_elem, row_stride, rows, hd, lane);
     }
+    } while (loop.next(slot, p.num_items));
+    loop.leave();
 }
 
 namespace {
@@ -579,6 +588,14 @@ void launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool split, h
         else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true>), grid, threads, 0, stream, p);
     } else {
         const dim3 grid((unsigned)num_items);
+        if constexpr (D == 128) {
+            if (!block && p.persist) {
+                const int workgroups = persistent_grid(num_items, 1);
+                if (workgroups > 0)   // (an error is sticky and reported by the caller's hipGetLastError)
+                    hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, true>), dim3((unsigned)workgroups), threads, 0, stream, p);
+                return;
+            }
+        }
         if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
         else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
     }

@@ -272,6 +272,18 @@ bool split_dkv(const hspmd_attn_plan* plan) {
     return split < 0.9 * whole;
 }
 
+// Whether the dK/dV pass draws its items in persistent workgroups (tile width 128, whole items, packed plans).  One workgroup
+// fits a compute unit there, so the time between two of them (about 5 us) is exposed: a large part of a short item.  Inside
+// the item loop, on the other hand, the compiler's schedule of the tile loop is 2-4 % slower.  Measured, one workgroup per
+// item and persistent (us), by mean steps per item: 4 (57 sequences of 32 .. 506 tokens, 16 heads, head_dim 96 / 128) 142 and
+// 124 / 168 and 156; 5 (32 x 512, 32 heads) 365 and 338; 9 (16 x 1024) 463 and 438; 13 558 and 552; 17 (8 x 2048) 676 and
+// 665, but the whole layer 1396 and 1402 under sustained load, where idle time comes back as clock; 33 (8 x 4096, 16 heads)
+// 1080 and 1098; 58 2850 and 2945; and with two items per unit 317 and 343.
+bool short_items(const hspmd_attn_plan* plan) {
+    const int64_t total = plan->load[HSPMD_LIST_DKV].total, items = plan->count[HSPMD_LIST_DKV];
+    return total <= 10 * items && items >= 4 * 256;
+}
+
 // Builds the three packed lists of a pack on the host (forward and dQ share one copy) and installs them.
 hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t num_seqs, bool first) {
     std::vector<hspmd_work_item> all;
@@ -627,6 +639,8 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     p.items = plan->items[HSPMD_LIST_DKV];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DKV];
     p.split = split_dkv(plan) ? 1 : 0;
+    p.persist = short_items(plan) ? 1 : 0;
+    p.queue = plan->queue[HSPMD_LIST_DKV];
     auto dkv_pass = [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], false, s); };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dK/dV launch");

@@ -54,6 +54,7 @@ struct BwdParams {
     int32_t num_items;             // slots of the current pass's work list (padding included)
     int32_t* queue;                // the current pass's draw counters (ItemQueue), zero between launches
     int32_t split;                 // dK/dV pass: two workgroups per item (decided from the plan's loads, see split_rows, split_dkv)
+    int32_t persist;               // dK/dV pass of a packed plan with whole items: persistent workgroups (see short_items)
 };
 
 // The kernels exist for tile widths 64 and 128 (LDS rows, MFMA contraction); a head_dim below the tile width runs
