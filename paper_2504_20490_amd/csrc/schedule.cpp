@@ -85,10 +85,10 @@ void walk_segments(const std::vector<SegmentClass>& classes, int32_t copies, Key
 }
 
 // chain_len(s): items of one kv head's chain of sequence s, most expensive first; cost_of(s, i): of its i-th item;
-// make(s, g, i): that item for kv head g.
+// make(s, g, i): that item for kv head g.  one_head: a chain holds one item per tile, not one per query head of a group.
 template <typename Item, typename ChainLen, typename Cost, typename Make>
-std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_queues, ChainLen chain_len, Cost cost_of,
-                               Make make, Item pad) {
+std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_queues, bool one_head, ChainLen chain_len,
+                               Cost cost_of, Make make, Item pad) {
     int64_t total_cost = 0;
     for (int32_t s = 0; s < num_seqs; ++s) {
         const int32_t n = chain_len(s);
@@ -96,8 +96,15 @@ std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_q
     }
     total_cost *= kv_heads;
 
-    // cut chains into segments no heavier than 1/(4 * queues) of the total
-    const int64_t cap = std::max<int64_t>(1, total_cost / ((int64_t)num_queues * 4));
+    // cut chains into segments no heavier than 1/(4 * queues) of the total; fewer than two chains per queue are cut finer:
+    // their few segments left the heaviest queue a tenth above the mean (5 heads: one document of 16001 tokens, forward 355 ->
+    // 345, dK/dV 612 -> 586 us; one of 24976 tokens 445 -> 416, dQ 592 -> 550, dK/dV 802 -> 749 us).  With more chains the
+    // coarse cut balances as well and keeps more of a chain's K and V in one L2.  (Chains with several query heads keep the coarse
+    // cut, so that a group's heads of one tile stay together.)
+    int64_t chains = 0;
+    for (int32_t s = 0; s < num_seqs; ++s) chains += chain_len(s) > 0 ? kv_heads : 0;
+    const int64_t parts = one_head && chains < 2 * (int64_t)num_queues ? 16 : 4;
+    const int64_t cap = std::max<int64_t>(1, total_cost / (num_queues * parts));
     std::vector<SegmentClass> classes;
     int64_t segments = 0;
     for (int32_t s = 0; s < num_seqs; ++s) {
@@ -200,7 +207,7 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
         return kind == HSPMD_LIST_DKV ? i : (int32_t)ceil_div(len, tile_rows) - 1 - i / group;
     };
     return place_chains<hspmd_work_item>(
-        num_seqs, hkv, num_queues,
+        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV || group == 1,
         [&](int32_t s) {
             const int32_t n_tiles = (int32_t)ceil_div(cu[s + 1] - cu[s], tile_rows);
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
@@ -311,7 +318,7 @@ std::vector<hspmd_block_item> build_block_list(hspmd_list_kind kind, const int32
     };
     // most expensive first inside a chain (with a shift the cost is still monotone in the tile index)
     return place_chains<hspmd_block_item>(
-        num_seqs, hkv, num_queues,
+        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV || group == 1,
         [&](int32_t s) {
             const int32_t n_tiles = (int32_t)ceil_div(rows_of(s), tile_rows);   // rows of the outputs the list owns
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
