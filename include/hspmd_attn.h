@@ -84,7 +84,7 @@ typedef enum {
     HSPMD_ORDER_COST = 2        /* one global list, most expensive item first, no XCD placement             */
 } hspmd_order;
 
-/* One unit of work for one workgroup.  tile < 0 marks a padding slot that does nothing. */
+/* One unit of work.  tile < 0 marks a padding slot that does nothing. */
 typedef struct {
     int32_t token_start;  /* first packed token of the sequence (cu_seqlens[seq])      */
     int32_t seq_len;      /* L of that sequence                                          */
@@ -134,7 +134,8 @@ hspmd_status hspmd_build_cu_seqlens(const int32_t* lengths, int32_t num_seqs, in
  * unit here is one tile of one sequence and head, its cost the number of tile
  * pairs it visits under the causal mask.
  *
- * Items are emitted in launch order: slot p is executed by workgroup p.  Slots
+ * Items are emitted in the order in which they are taken up (by one workgroup each, by
+ * persistent workgroups that take several, or by two that share an item).  Slots
  * p with equal p % num_queues form one queue; a queue keeps tiles that share
  * K/V (FWD, DQ) or Q/dO (DKV) together, queues are balanced by total cost and
  * each queue runs its expensive items first.  Shorter queues are padded with
@@ -321,7 +322,8 @@ hspmd_status hspmd_attn_block_bwd_rope(const hspmd_attn_plan* plan, const void* 
  * workgroups resident per XCD, and not less than its heaviest item; backward = dQ pass + dK/dV
  * pass.  The coefficients are fitted to measured kernel times
  * (paper_2504_20490_amd/fit_cost_model.py refits them): mean error 6-9 %, up to 15-29 % on packs
- * that take only about a hundred microseconds.  Host-side plan creation is not included.
+ * that take only about a hundred microseconds.  Packs whose longest items are shared by two
+ * workgroups are faster than predicted, by up to a third.  Host-side plan creation is not included.
  */
 hspmd_status hspmd_attn_estimate_ms(const int32_t* cu_seqlens, int32_t num_seqs, int32_t local_q_heads,
                                     int32_t local_kv_heads, int32_t head_dim, double* fwd_ms, double* bwd_ms);
