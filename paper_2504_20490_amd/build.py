@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIBRARY = os.path.join(HERE, "libhspmd_attn.so")
 SOURCES = ["hspmd_attn_api.hip", "schedule.cpp", "fwd_kernel.hip", "bwd_kernels.hip", "bwd_dkv_kernel.hip", "merge_kernel.hip", "probe.hip", "rope_kernel.hip"]
-HEADERS = ["attn_device.hpp", "kernels.hpp", "schedule.hpp", os.path.join("..", "..", "include", "hspmd_attn.h")]
+HEADERS = ["attn_device.hpp", "fwd_tiles.hpp", "kernels.hpp", "schedule.hpp", os.path.join("..", "..", "include", "hspmd_attn.h")]
 
 # Packed fp32 VALU forms are switched off for all device code of this library.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
@@ -16,7 +16,7 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 
 
 # what decides a kernel's HBM traffic: the attention kernels, their shared device code and the launch order
-KERNEL_SOURCES = ["fwd_kernel.hip", "bwd_kernels.hip", "bwd_dkv_kernel.hip", "attn_device.hpp", "kernels.hpp",
+KERNEL_SOURCES = ["fwd_kernel.hip", "bwd_kernels.hip", "bwd_dkv_kernel.hip", "attn_device.hpp", "fwd_tiles.hpp", "kernels.hpp",
                   "schedule.hpp", "schedule.cpp"]
 
 

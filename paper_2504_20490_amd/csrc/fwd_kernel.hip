@@ -15,6 +15,7 @@
 // query rows and the keys are separate chunks and the diagonal is shifted (one step of context-parallel
 // attention): partial O in fp32, LSE = -inf for rows that see no key.
 #include "attn_device.hpp"
+#include "fwd_tiles.hpp"
 #include "kernels.hpp"
 #include "schedule.hpp"
 
@@ -343,19 +344,10 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
         const uint16_t* kbase = p.k + (int64_t)item.k_start * p.kv_stride + (int64_t)hk * hd;
         const uint16_t* vbase = p.v + (int64_t)item.k_start * p.kv_stride + (int64_t)hk * hd;
 
-        // key j is visible to row r iff j <= r + off: the tile's last row sees keys 0 .. kv_end-1
-        const int kv_end = max(0, min(L, min(Lq, q_row0 + BQ) + off));
-        const int n_tiles = (kv_end + BK - 1) / BK;
-        // last key this lane's row may see, as an index into the chunk
+        // last key this lane's row may see (key j is visible to row r iff j <= r + off), as an index into the chunk
         const int my_limit = BLOCK ? min(my_row + off, L - 1) : my_row;
-        // this wave's own share: the tiles that hold a key visible to one of its 32 rows, and those among them that
-        // are visible to all of them (a wave whose rows lie past the end of the chunk computes nothing).  On the
-        // diagonal the upper waves of a workgroup see fewer tiles than the lower ones.
-        const int kv_end_w = wave_row0 < Lq ? max(0, min(L, min(Lq, wave_row0 + 32) + off)) : 0;
-        // (SPLIT: tiles whose block of this wave holds such a key)
-        const int n_tiles_w = SPLIT ? (max(0, kv_end_w - key_block * 32) + BK - 1) / BK : (kv_end_w + BK - 1) / BK;
-        const int n_interior_w = SPLIT ? max(0, min(n_tiles_w, (min(wave_row0 + off + 1, L) - key_block * 32 + 32) / BK))
-                                       : max(0, min(min(n_tiles_w, (wave_row0 + off + 1) / BK), L / BK));
+        const FwdTiles tiles = fwd_tiles(SPLIT, Lq, L, off, q_row0, row_block, key_block);
+        const int n_tiles = tiles.n_tiles, n_tiles_w = tiles.n_tiles_w;
         if (BLOCK && n_tiles == 0) {
             // no key of the chunk is visible to any row of the tile: O = 0, LSE = -inf
             if (my_row < Lq && key_block == 0) {
@@ -404,8 +396,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
         }
         st.tnext = n_tiles_w > 0 ? lane_max(st.s) : -INFINITY;
         // iteration 0 issues K(2) into the buffer that S^T(0) has just been read from: every wave must be done with it (a
-        // wave whose rows lie past the end of the chunk reads nothing here and would otherwise run ahead with its copies)
-        if (n_tiles > 2) __syncthreads();
+        // wave may run ahead of another: one whose rows lie past the end of the chunk reads nothing here, and the waves of the
+        // other resident workgroup hold some back)
+        if (tiles.reuses_first_k()) __syncthreads();
 
         // iteration kt: K(kt+1) in kbuf[(kt+1) & 1], V(kt) in vbuf[kt & 1]; issues K(kt+2) -> kbuf[kt & 1] and
         // V(kt+1) -> vbuf[(kt+1) & 1], both free since the barrier at the top
@@ -454,8 +447,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
         // tiles, and the wave's final tile (which has no successor to compute scores for); the large register state
         // then meets at a join once per loop, not per tile.  Every wave passes the barrier of every tile of the
         // workgroup, in whichever loop it happens to be.
-        const int n_plain = min(n_interior_w, n_tiles_w - 1);
-        const int n_spread = max(0, min(n_plain, L / BK - 2));   // tile kt+2 exists and is whole
+        const int n_plain = tiles.n_plain, n_spread = tiles.n_spread;
         int kt = 0;
         // the long loop of a long sequence runs in pairs (even tile, odd tile) with constant buffer offsets
         for (; kt + 1 < n_spread; kt += 2) {
