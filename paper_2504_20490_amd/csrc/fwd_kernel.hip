@@ -93,8 +93,9 @@ __device__ __forceinline__ float pair_max(float x) {
 // SPREAD: the iteration also issues this wave's share of the copies of K(kt+2) and V(kt+1), both whole
 // tiles, one instruction per MFMA step of phase A.  Issued back to back after the barrier, the copies of
 // all waves queue up in front of the CU's one address unit.
-// BLOCK: a lane's row may have no visible key so far (its running max is still -inf): the maximum that the
-// exponentials are taken against is then replaced by 0, which keeps every weight and the rescale factor at 0.
+// BLOCK and NB = 1: a lane's row may have no visible key so far, or, with half of the keys, none with a finite score (its
+// running max is still -inf): the maximum that the exponentials are taken against is then replaced by 0, which keeps every
+// weight and the rescale factor at 0.
 // NB = 1: the wave's only 32-key block of the tile is part of the addresses; its eight score pairs all go under the
 // MFMAs of phase A, the copies too (two per step where the phase has fewer steps than copies).
 template <int D, int KD, int NB, bool MASK, bool LAST, bool SPREAD, bool BLOCK>
@@ -126,7 +127,7 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const cha
     // becomes rare after the first tiles.  (-inf - -inf = NaN compares false: a row without a visible key keeps -inf.)
     constexpr float kMaxSlack = 8.f;
     const float m_new = (tmax - st.m) * c > kMaxSlack ? tmax : st.m;
-    const float m_ref = (BLOCK && m_new == -INFINITY) ? 0.f : m_new;
+    const float m_ref = ((BLOCK || NB == 1) && m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = fast_exp2((st.m - m_ref) * c);
     const float mc = m_ref * c;
     if (__any(m_new > st.m)) {      // wave-uniform: skip the accumulator rescale when no lane's max moved

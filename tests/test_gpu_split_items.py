@@ -3,8 +3,11 @@
 Packs whose longest item outlasts the rest of a pass: the items are then shared out to two workgroups.  Parity with the
 oracle where that split has its edges: a half without any key, a half of one key, one tile or an odd number of them per
 head, groups of query heads (whose tiles follow one another in one item), head_dim below the tile width."""
+import numpy as np
 import pytest
 
+import oracle
+from gpu_util import GpuRun, LSE_ABS, assert_close, default_scale, f64, make_case, magnitude_bound
 from test_gpu_parity import _full_check
 
 pytestmark = pytest.mark.gpu
@@ -23,3 +26,24 @@ def test_many_short_items(hq, hkv, d):
     """More than a thousand short dK/dV items: the pass then draws them in persistent workgroups, several per workgroup."""
     lengths = [1 + (i * 37) % 131 for i in range(150)]
     _full_check(lengths, hq, hkv, d, seed=950 + d, magnitude_slack=True, slack_roundings=2)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(2, 2, 128), (2, 1, 64), (2, 2, 96)])
+@pytest.mark.parametrize("first", [1, 32])
+def test_scores_below_the_range_of_fp32(first, hq, hkv, d):
+    """Keys `first` .. `first` + 31 of every 64 have scores of about -1e39, which fp32 holds as -inf: weight 0 in every row, as
+    long as the row sees one other key.  The wave that owns the second half of every tile (first = 32) then meets no finite
+    score at all."""
+    lengths = [200, 70, 129]
+    q, k, v, do = make_case(lengths, hq, hkv, d, seed=970 + d)
+    to_bits = lambda x: np.uint16(np.float32(x).view(np.uint32) >> 16)
+    position = np.concatenate([np.arange(n) for n in lengths])
+    q[:, :, 0] = to_bits(4.0)
+    k[(position % 64 >= first) & (position % 64 < first + 32), :, 0] = to_bits(-3e38)
+    run = GpuRun(lengths, q, k, v, do).run()
+    s = default_scale(d)
+    ro, rlse = oracle.attn_fwd(f64(q), f64(k), f64(v), lengths, s)
+    assert_close("O", run.host("o"), ro)
+    assert np.max(np.abs(run.host("lse") - rlse)) <= LSE_ABS
+    for name, ref in zip(("dq", "dk", "dv"), oracle.attn_bwd(f64(q), f64(k), f64(v), f64(do), lengths, s)):
+        assert_close(name, run.host(name), ref, max_abs=magnitude_bound(ref))
