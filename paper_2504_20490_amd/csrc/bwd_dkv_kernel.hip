@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
 namespace {
 
 template <int D, int KD>
-void launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream) {
+hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream) {
     const dim3 threads(kThreads);
     if (split) {
         const dim3 grid((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2));
@@ -591,14 +591,15 @@ void launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool split, h
         if constexpr (D == 128) {
             if (!block && p.persist) {
                 const int workgroups = persistent_grid(num_items, 1);
-                if (workgroups > 0)   // (an error is sticky and reported by the caller's hipGetLastError)
-                    hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, true>), dim3((unsigned)workgroups), threads, 0, stream, p);
-                return;
+                if (workgroups <= 0) return hipErrorInvalidDevice;
+                hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, true>), dim3((unsigned)workgroups), threads, 0, stream, p);
+                return hipGetLastError();
             }
         }
         if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
         else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
     }
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -606,12 +607,11 @@ void launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool split, h
 hipError_t launch_bwd_dkv(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
     const bool split = p.split != 0;
-    if (tile_width(head_dim) == 64) launch_dkv<64, 4>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) <= 5) launch_dkv<128, 5>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) == 6) launch_dkv<128, 6>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) == 7) launch_dkv<128, 7>(p, num_items, block, split, stream);
-    else launch_dkv<128, 8>(p, num_items, block, split, stream);
-    return hipGetLastError();
+    if (tile_width(head_dim) == 64) return launch_dkv<64, 4>(p, num_items, block, split, stream);
+    if (contraction_steps(head_dim) <= 5) return launch_dkv<128, 5>(p, num_items, block, split, stream);
+    if (contraction_steps(head_dim) == 6) return launch_dkv<128, 6>(p, num_items, block, split, stream);
+    if (contraction_steps(head_dim) == 7) return launch_dkv<128, 7>(p, num_items, block, split, stream);
+    return launch_dkv<128, 8>(p, num_items, block, split, stream);
 }
 
 }  // namespace hspmd
