@@ -318,12 +318,12 @@ hspmd_status hspmd_attn_block_bwd_rope(const hspmd_attn_plan* plan, const void* 
  * sequences to pipelines by a cost model evaluated on the CPU (Appendix "Scenario-specific Planning",
  * mixed-length case).  Host only, no GPU needed; costs about as much as building the work lists.
  * Model: each pass walks its work list; an item weighs (inner steps x a step time + a fixed time per
- * item), a pass takes a launch time plus the weight of its heaviest XCD queue divided by the
- * workgroups resident per XCD, and not less than its heaviest item; backward = dQ pass + dK/dV
- * pass.  The coefficients are fitted to measured kernel times
- * (paper_2504_20490_amd/fit_cost_model.py refits them): mean error 6-9 %, up to 15-29 % on packs
- * that take only about a hundred microseconds.  Packs whose longest items are shared by two
- * workgroups are faster than predicted, by up to a third.  Host-side plan creation is not included.
+ * item), a pass takes a launch time plus, smoothly joined, the longer of the weight of its heaviest XCD
+ * queue divided by the workgroups resident per XCD and the time of its heaviest item alone; passes that
+ * work on half items take a share of these; backward = dQ pass + dK/dV pass.  The coefficients are fitted
+ * per width class of head_dim (up to 64, 80, 96, 112, 128) to measured kernel times
+ * (paper_2504_20490_amd/fit_cost_model.py refits them): forward and backward have a mean error of 4-7 %,
+ * 95 % of the packs are within 18 %, all of them within 31 %.  Host-side plan creation is not included.
  */
 hspmd_status hspmd_attn_estimate_ms(const int32_t* cu_seqlens, int32_t num_seqs, int32_t local_q_heads,
                                     int32_t local_kv_heads, int32_t head_dim, double* fwd_ms, double* bwd_ms);

@@ -242,46 +242,8 @@ hspmd_status install_lists(hspmd_attn_plan* plan, const void* host, size_t bytes
     return HSPMD_OK;
 }
 
-// Whether the forward and the dQ pass work on half items (64 rows, two waves of a workgroup sharing each 32-row block).  As
-// for the dK/dV pass below: a step of a half item takes about 0.6 of a whole item's (each tile is copied for half the rows),
-// so halves pay when the heaviest item is what the pass waits for: when it is at least twice as long as the work per slot
-// (two workgroups per compute unit), six steps of prologue and stores per half item included.  Measured, forward and dQ pass,
-// whole -> halves (us): heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot
-// 187 -> 145, 213 -> 131; 93 steps, 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 3 steps, 168
-// items 12.2 -> 14.4, 13.3 -> 15.0; 251 steps, 156 per slot 336 -> 376, 450 -> 445; 8 x 2048, 32 heads 304 -> 425, 450 -> 534.
-bool split_rows(const hspmd_attn_plan* plan, hspmd_list_kind kind) {
-    const double slots = 512.0;
-    const double per_slot = ((double)plan->load[kind].total + 6.0 * 2.0 * (double)plan->count[kind]) / slots;
-    return (double)plan->load[kind].heaviest + 6.0 >= 2.0 * per_slot;
-}
-
-// Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass
-// takes as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs
-// 0.68 of the whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy
-// every Q / dO tile, and an item costs about eight steps beside its tiles.  Measured, whole and split (us): heaviest item 32
-// steps, 8.5 per slot (2 sequences, 8 heads) 50 and 41; 60 steps, 16 per slot (8 KV heads of 4) 85 and 61; 238 steps,
-// 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and 321; 3 steps, 168 items 17 and 23 (the
-// halves no longer fit the chip at once); 8 x 2048, 32 heads 652 and 826.
-bool split_dkv(const hspmd_attn_plan* plan) {
-    const double heaviest = (double)plan->load[HSPMD_LIST_DKV].heaviest, total = (double)plan->load[HSPMD_LIST_DKV].total;
-    const double items = (double)plan->count[HSPMD_LIST_DKV];
-    const double units = 256.0;   // compute units; whole items of tile width 64 fit a unit twice
-    const double slots = hspmd::tile_width(plan->head_dim) == 64 ? 2 * units : units;
-    const double whole = std::max(heaviest + 8, (total + 8 * items) / slots);
-    const double split = std::max(0.68 * heaviest + 8, (1.3 * total + 8 * 2 * items) / units);
-    return split < 0.9 * whole;
-}
-
-// Whether the dK/dV pass draws its items in persistent workgroups (tile width 128, whole items, packed plans).  One workgroup
-// fits a compute unit there, so the time between two of them (about 5 us) is exposed: a large part of a short item.  Inside
-// the item loop, on the other hand, the compiler's schedule of the tile loop is 2-4 % slower.  Measured, one workgroup per
-// item and persistent (us), by mean steps per item: 4 (57 sequences of 32 .. 506 tokens, 16 heads, head_dim 96 / 128) 142 and
-// 124 / 168 and 156; 5 (32 x 512, 32 heads) 365 and 338; 9 (16 x 1024) 463 and 438; 13 558 and 552; 17 (8 x 2048) 676 and
-// 665, but the whole layer 1396 and 1402 under sustained load, where idle time comes back as clock; 33 (8 x 4096, 16 heads)
-// 1080 and 1098; 58 2850 and 2945; and with two items per unit 317 and 343.
-bool short_items(const hspmd_attn_plan* plan) {
-    const int64_t total = plan->load[HSPMD_LIST_DKV].total, items = plan->count[HSPMD_LIST_DKV];
-    return total <= 10 * items && items >= 4 * 256;
+hspmd::Dispatch plan_dispatch(const hspmd_attn_plan* plan, hspmd_list_kind kind) {
+    return hspmd::pass_dispatch(kind, plan->load[kind], plan->count[kind], plan->head_dim, plan->is_block);
 }
 
 // Builds the three packed lists of a pack on the host (forward and dQ share one copy) and installs them.
@@ -575,7 +537,7 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
     p.scale_log2 = scale * 1.4426950408889634f;
     p.num_items = (int32_t)plan->count[HSPMD_LIST_FWD];
     p.queue = plan->queue[HSPMD_LIST_FWD];
-    p.split = split_rows(plan, HSPMD_LIST_FWD) ? 1 : 0;
+    p.split = plan_dispatch(plan, HSPMD_LIST_FWD) == hspmd::Dispatch::kHalves ? 1 : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, plan->head_dim, plan->count[HSPMD_LIST_FWD], false, s); });
     if (e != hipSuccess) return fail_hip(e, "forward launch");
@@ -632,14 +594,15 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     // D = rowsum(dO * O) is computed by the dQ pass itself (every (row, head) belongs to exactly one of its items)
     p.items = plan->items[HSPMD_LIST_DQ];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
-    p.split = split_rows(plan, HSPMD_LIST_DQ) ? 1 : 0;
+    p.split = plan_dispatch(plan, HSPMD_LIST_DQ) == hspmd::Dispatch::kHalves ? 1 : 0;
     auto dq_pass = [&] { return hspmd::launch_bwd_dq(p, plan->head_dim, plan->count[HSPMD_LIST_DQ], false, s); };
     hipError_t e = timed ? timed_launch(2, s, dq_pass) : dq_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dQ launch");
     p.items = plan->items[HSPMD_LIST_DKV];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DKV];
-    p.split = split_dkv(plan) ? 1 : 0;
-    p.persist = short_items(plan) ? 1 : 0;
+    const hspmd::Dispatch dkv = plan_dispatch(plan, HSPMD_LIST_DKV);
+    p.split = dkv == hspmd::Dispatch::kHalves ? 1 : 0;
+    p.persist = dkv == hspmd::Dispatch::kPersistent ? 1 : 0;
     p.queue = plan->queue[HSPMD_LIST_DKV];
     auto dkv_pass = [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], false, s); };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();
@@ -796,7 +759,6 @@ hspmd_status hspmd_attn_estimate_ms(const int32_t* cu_seqlens, int32_t num_seqs,
     if (!why.empty()) return fail(HSPMD_ERR_INVALID_ARG, why);
     if (!supported_head_dim(head_dim)) return fail(HSPMD_ERR_UNSUPPORTED, "head_dim must be a multiple of 8 between 8 and 128");
     try {
-        head_dim = hspmd::tile_width(head_dim);   // a narrower head runs on the next tile width up
         *fwd_ms = hspmd::estimate_pass_us(HSPMD_LIST_FWD, cu_seqlens, num_seqs, local_q_heads, local_kv_heads, head_dim) * 1e-3;
         *bwd_ms = (hspmd::estimate_pass_us(HSPMD_LIST_DQ, cu_seqlens, num_seqs, local_q_heads, local_kv_heads, head_dim) +
                    hspmd::estimate_pass_us(HSPMD_LIST_DKV, cu_seqlens, num_seqs, local_q_heads, local_kv_heads, head_dim)) * 1e-3;
@@ -891,7 +853,7 @@ hspmd_status hspmd_attn_block_fwd(const hspmd_attn_plan* plan, const void* q, co
     p.scale_log2 = scale * 1.4426950408889634f;
     p.num_items = (int32_t)plan->count[HSPMD_LIST_FWD];
     p.queue = plan->queue[HSPMD_LIST_FWD];
-    p.split = split_rows(plan, HSPMD_LIST_FWD) ? 1 : 0;
+    p.split = plan_dispatch(plan, HSPMD_LIST_FWD) == hspmd::Dispatch::kHalves ? 1 : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, plan->head_dim, plan->count[HSPMD_LIST_FWD], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block forward launch");
@@ -975,12 +937,12 @@ static hspmd_status block_bwd(const hspmd_attn_plan* plan, const void* q, const 
     }
     p.block_items = plan->block_items[HSPMD_LIST_DQ];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
-    p.split = split_rows(plan, HSPMD_LIST_DQ) ? 1 : 0;
+    p.split = plan_dispatch(plan, HSPMD_LIST_DQ) == hspmd::Dispatch::kHalves ? 1 : 0;
     e = timed_launch(2, s, [&] { return hspmd::launch_bwd_dq(p, plan->head_dim, plan->count[HSPMD_LIST_DQ], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dQ launch");
     p.block_items = plan->block_items[HSPMD_LIST_DKV];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DKV];
-    p.split = split_dkv(plan) ? 1 : 0;
+    p.split = plan_dispatch(plan, HSPMD_LIST_DKV) == hspmd::Dispatch::kHalves ? 1 : 0;
     e = timed_launch(3, s, [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dK/dV launch");
     if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");

@@ -23,7 +23,7 @@ struct FwdParams {
     float scale_log2;              // softmax_scale * log2(e)
     int32_t num_items;             // slots of the work list (padding included)
     int32_t* queue;                // this pass's draw counters (ItemQueue), zero between launches
-    int32_t split;                 // the unit of work is half an item (decided from the plan's loads, see split_rows)
+    int32_t split;                 // the unit of work is half an item (decided from the plan's loads, see pass_dispatch)
 };
 
 struct BwdParams {
@@ -53,8 +53,8 @@ struct BwdParams {
     float scale_log2;              // softmax_scale * log2(e)
     int32_t num_items;             // slots of the current pass's work list (padding included)
     int32_t* queue;                // the current pass's draw counters (ItemQueue), zero between launches
-    int32_t split;                 // dK/dV pass: two workgroups per item (decided from the plan's loads, see split_rows, split_dkv)
-    int32_t persist;               // dK/dV pass of a packed plan with whole items: persistent workgroups (see short_items)
+    int32_t split;                 // the pass works on half items (decided from the plan's loads, see pass_dispatch)
+    int32_t persist;               // dK/dV pass of a packed plan with whole items: persistent workgroups (see pass_dispatch)
 };
 
 // The kernels exist for tile widths 64 and 128 (LDS rows, MFMA contraction); a head_dim below the tile width runs

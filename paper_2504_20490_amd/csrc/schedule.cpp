@@ -20,6 +20,7 @@
 #include "schedule.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 
 namespace hspmd {
@@ -238,35 +239,100 @@ PassLoad pass_load(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, in
     return load;
 }
 
+// ------------------------------------------------------------------------------ dispatch of a pass
+// The rules below take every slot of the list for an item.  Padding slots (at most a queue's last few, more only on packs of few
+// chains) thus count as work, which leaves packs at the edge of a rule with whole items.
+namespace {
+
+// Whether the forward and the dQ pass work on half items (64 rows, two waves of a workgroup sharing each 32-row block).  As
+// for the dK/dV pass below: a step of a half item takes about 0.6 of a whole item's (each tile is copied for half the rows),
+// so halves pay when the heaviest item is what the pass waits for: when it is at least twice as long as the work per slot
+// (two workgroups per compute unit), six steps of prologue and stores per half item included.  Measured, forward and dQ pass,
+// whole -> halves (us): heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot
+// 187 -> 145, 213 -> 131; 93 steps, 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 3 steps, 168
+// items 12.2 -> 14.4, 13.3 -> 15.0; 251 steps, 156 per slot 336 -> 376, 450 -> 445; 8 x 2048, 32 heads 304 -> 425, 450 -> 534.
+bool split_rows(const PassLoad& load, int64_t slots) {
+    const double workgroups = 512.0;
+    const double per_slot = ((double)load.total + 6.0 * 2.0 * (double)slots) / workgroups;
+    return (double)load.heaviest + 6.0 >= 2.0 * per_slot;
+}
+
+// Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass
+// takes as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs
+// 0.68 of the whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy
+// every Q / dO tile, and an item costs about eight steps beside its tiles.  Measured, whole and split (us): heaviest item 32
+// steps, 8.5 per slot (2 sequences, 8 heads) 50 and 41; 60 steps, 16 per slot (8 KV heads of 4) 85 and 61; 238 steps,
+// 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and 321; 3 steps, 168 items 17 and 23 (the
+// halves no longer fit the chip at once); 8 x 2048, 32 heads 652 and 826.
+bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
+    const double heaviest = (double)load.heaviest, total = (double)load.total, items = (double)slots;
+    const double units = 256.0;   // compute units; whole items of tile width 64 fit a unit twice
+    const double workgroups = head_dim <= 64 ? 2 * units : units;
+    const double whole = std::max(heaviest + 8, (total + 8 * items) / workgroups);
+    const double split = std::max(0.68 * heaviest + 8, (1.3 * total + 8 * 2 * items) / units);
+    return split < 0.9 * whole;
+}
+
+// Whether the dK/dV pass draws its items in persistent workgroups (tile width 128, whole items, packed plans).  One workgroup
+// fits a compute unit there, so the time between two of them (about 5 us) is exposed: a large part of a short item.  Inside
+// the item loop, on the other hand, the compiler's schedule of the tile loop is 2-4 % slower.  Measured, one workgroup per
+// item and persistent (us), by mean steps per item: 4 (57 sequences of 32 .. 506 tokens, 16 heads, head_dim 96 / 128) 142 and
+// 124 / 168 and 156; 5 (32 x 512, 32 heads) 365 and 338; 9 (16 x 1024) 463 and 438; 13 558 and 552; 17 (8 x 2048) 676 and
+// 665, but the whole layer 1396 and 1402 under sustained load, where idle time comes back as clock; 33 (8 x 4096, 16 heads)
+// 1080 and 1098; 58 2850 and 2945; and with two items per unit 317 and 343.
+bool short_items(const PassLoad& load, int64_t slots) { return load.total <= 10 * slots && slots >= 4 * 256; }
+
+}  // namespace
+
+Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim, bool block) {
+    if (kind != HSPMD_LIST_DKV) return split_rows(load, slots) ? Dispatch::kHalves : Dispatch::kWhole;
+    if (split_dkv(load, slots, head_dim)) return Dispatch::kHalves;
+    return !block && head_dim > 64 && short_items(load, slots) ? Dispatch::kPersistent : Dispatch::kWhole;
+}
+
 // ------------------------------------------------------------------------------ cost model
 // The paper's planner dispatches mixed-length sequences with a cost model evaluated on the CPU (Appendix
-// "Scenario-specific Planning", mixed-length case); this is the per-operator predictor for the attention
-// kernels of this library.  Fitted by relative least squares to 40 packs per head_dim: mean absolute error
-// 6-8 %, at most 15-32 % (on packs that take about a hundred microseconds).
-PassCost pass_cost_coefficients(hspmd_list_kind kind, int32_t head_dim) {
-    static const PassCost k128[3] = {{13.1, 1.655, 10.37}, {7.6, 2.168, 18.64}, {24.8, 1.620, 11.66}};
-    static const PassCost k64[3] = {{13.1, 1.045, 6.22}, {7.6, 1.239, 9.02}, {18.5, 1.062, 6.41}};
-    return (head_dim == 64 ? k64 : k128)[(int)kind];
-}
+// "Scenario-specific Planning", mixed-length case); this is the per-operator predictor for the attention kernels of this library.
+// A pass takes a launch time and, of two times, a little more than the longer (the fourth root of the sum of their fourth
+// powers: where they are close, part of the chip idles at the end): the weight of the heaviest XCD queue -- steps x step time
+// + a fixed time per item -- shared by the workgroups that an XCD holds, and the heaviest item on a chip that is otherwise
+// idle.  Half items take the stated shares of a whole one's times.  Fitted by relative least squares to 124 packs at each of
+// five widths: mean |error| 6-7 % per pass, 95 % of the packs within 18 %, the others (passes of a few steps per item or
+// with a single item per workgroup) within 40 %.
+namespace {
+
+struct PassCost { double step_us, item_us, alone_us; };               // alone_us: a step with one workgroup per unit or fewer
+struct PassFixed { double launch_us, half_step, half_alone, half_item; };   // half_*: shares of a whole item's times
+constexpr PassFixed kPassFixed[3] = {{5.6, 0.69, 0.84, 0.44}, {0.0, 0.65, 0.59, 0.67}, {0.0, 0.46, 0.67, 0.88}};
+// head_dim up to 64, 80, 96, 112, 128: each has kernels of its own
+constexpr PassCost kPassCost[3][5] = {
+    {{1.078, 5.83, 0.587}, {1.383, 6.79, 0.725}, {1.461, 7.22, 0.720}, {1.695, 8.01, 0.745}, {1.729, 8.10, 0.754}},
+    {{1.922, 11.32, 0.617}, {1.700, 12.42, 0.808}, {1.863, 13.04, 0.858}, {2.201, 14.03, 0.914}, {2.338, 14.83, 0.926}},
+    {{1.741, 9.76, 0.892}, {1.328, 10.99, 0.981}, {1.377, 11.20, 1.131}, {1.642, 12.79, 1.109}, {1.662, 12.90, 1.217}}
+};
+
+}  // namespace
 
 double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim) {
     const std::vector<hspmd_work_item> list = build_work_list(kind, cu, num_seqs, hq, hkv, kNumXcd);
     if (list.empty()) return 0.0;
-    const PassCost c = pass_cost_coefficients(kind, head_dim);
-    const int32_t group = hq / hkv;
-    // workgroups resident per XCD: 32 compute units, two workgroups each in the forward and dQ passes, one in dK/dV
-    const double slots = kind == HSPMD_LIST_DKV ? 32.0 : 64.0;
+    const PassLoad load = pass_load(kind, cu, num_seqs, hq, hkv);
+    const bool narrow = head_dim <= 64;
+    const PassCost c = kPassCost[(int)kind][narrow ? 0 : std::max(1, (head_dim + 15) / 16 - 4)];
+    const PassFixed f = kPassFixed[(int)kind];
+    const bool halves = pass_dispatch(kind, load, (int64_t)list.size(), head_dim, false) == Dispatch::kHalves;
+    const double step = c.step_us * (halves ? 2 * f.half_step : 1.0), item = c.item_us * (halves ? 2 * f.half_item : 1.0);
+    // workgroups resident per XCD: 32 compute units, two workgroups each in the forward and dQ passes, one in dK/dV; at tile
+    // width 64 three in the dQ pass and two in dK/dV with whole items
+    const double per_unit = kind == HSPMD_LIST_DKV ? (narrow && !halves ? 2 : 1) : (narrow && kind == HSPMD_LIST_DQ ? 3 : 2);
     double queue_weight[kNumXcd] = {0};
-    double heaviest = 0.0;
     for (size_t p = 0; p < list.size(); ++p) {
         if (list[p].tile < 0) continue;
-        const double w = (double)item_cost(kind, list[p].seq_len, list[p].tile, group) * c.step_us + c.item_us;
-        queue_weight[p % kNumXcd] += w;
-        heaviest = std::max(heaviest, w);
+        queue_weight[p % kNumXcd] += (double)item_cost(kind, list[p].seq_len, list[p].tile, hq / hkv) * step + item;
     }
-    double worst = 0.0;
-    for (double w : queue_weight) worst = std::max(worst, w);
-    return c.launch_us + std::max(worst / slots, heaviest);
+    const double shared = *std::max_element(queue_weight, queue_weight + kNumXcd) / (32.0 * per_unit);
+    const double alone = (double)load.heaviest * c.alone_us * (halves ? f.half_alone : 1.0) + c.item_us * (halves ? f.half_item : 1.0);
+    return f.launch_us + std::sqrt(std::sqrt(shared * shared * shared * shared + alone * alone * alone * alone));
 }
 
 // ------------------------------------------------------------------------------ block variant

@@ -1,18 +1,20 @@
 """Refit the coefficients of hspmd_attn_estimate_ms on the GPU at hand.
 
-Runs forward + backward of a set of synthetic packs (uniform and log-normal length mixes, several head
-counts) through the library with per-kernel event timing, computes for every pass the two features the
-model uses -- inner steps and items of the heaviest XCD queue per resident workgroup -- from the host
-scheduler, and fits (launch_us, step_us, item_us) per pass by relative least squares.  Prints the table
-that goes into pass_cost_coefficients() (csrc/schedule.cpp).
+Runs forward + backward of a set of synthetic packs (uniform and log-normal length mixes, one to forty heads, with and without
+groups) at every width that has kernels of its own, with per-kernel event timing, takes the features that the model uses --
+inner steps and items of the eight XCD queues, the heaviest item, whole or half items -- from the host scheduler, and fits
+all widths of a pass together by relative least squares.  Prints the tables that go into csrc/schedule.cpp.
 
-    python -m paper_2504_20490_amd.fit_cost_model [--head-dim 128]
+    python -m paper_2504_20490_amd.fit_cost_model [--head-dim 64 96 ...]
 """
 from __future__ import annotations
 
 import argparse
 
 import numpy as np
+
+WIDTHS = {64: 0, 80: 1, 96: 2, 104: 3, 128: 4}      # a head_dim of every width class, in the order of the tables
+PASSES = ["fwd_kernel", "bwd_dq_kernel", "bwd_dkv_kernel"]   # in the order of the list kinds
 
 
 def _packs(rng):
@@ -23,6 +25,19 @@ def _packs(rng):
         n = int(rng.integers(2, 30))
         lens = [int(x) for x in np.clip(np.exp(rng.normal(7.0, 1.2, n)), 16, 20000)]
         yield lens, int(rng.choice([8, 16, 24, 32])), 8
+
+
+def _small_packs(rng):
+    """Packs of which one item takes a large part of a pass: few sequences, few heads, large groups."""
+    for hq, hkv in [(1, 1), (2, 2), (5, 5), (8, 2), (32, 8), (40, 40)]:
+        for lens in ([16384], [24000], [2048], [512] * 3, [300] * 12, [1024] * 6, [1500, 400, 153], [4000, 300, 200, 90],
+                     [6000, 1000, 500] * 2):
+            yield list(lens), hq, hkv
+    for _ in range(30):
+        n = int(rng.integers(1, 20))
+        lens = [int(x) for x in np.clip(np.exp(rng.normal(rng.uniform(4.5, 7.5), 1.0, n)), 16, 16384)]
+        hkv = int(rng.choice([1, 2, 3, 4, 8]))
+        yield lens, hkv * int(rng.choice([1, 1, 2, 4])), hkv
 
 
 def _measure(A, torch, lengths, hq, hkv, d):
@@ -55,35 +70,76 @@ def _measure(A, torch, lengths, hq, hkv, d):
     return {name: ms / n * 1e3 for name, (ms, n) in A.profile_read().items()}   # microseconds
 
 
-def _features(A, kind, slots, lengths, hq, hkv):
-    cu = np.concatenate([[0], np.cumsum(lengths)])
-    items = A.schedule(kind, cu, hq, hkv)
-    length, tile = items[:, 1].astype(np.int64), items[:, 2].astype(np.int64)
-    real = tile >= 0
-    rows_q, rows_k = A.tile_rows(A.LIST_FWD), A.tile_rows(A.LIST_DKV)
-    if kind == A.LIST_DKV:
-        steps = np.where(real, -(-(length - tile * rows_k) // 64) * (hq // hkv), 0)
-    else:
-        steps = np.where(real, -(-np.minimum(length, (tile + 1) * rows_q) // 64), 0)
-    return max(steps[x::8].sum() for x in range(8)) / slots, max(real[x::8].sum() for x in range(8)) / slots
+class _Features:
+    """What the model knows of one pass over one pack (all eight queues)."""
+
+    def __init__(self, A, kind, lengths, hq, hkv, head_dim):
+        cu = np.concatenate([[0], np.cumsum(lengths)])
+        items = A.schedule(kind, cu, hq, hkv)
+        length, tile = items[:, 1].astype(np.int64), items[:, 2].astype(np.int64)
+        real = tile >= 0
+        rows = A.tile_rows(kind)
+        if kind == A.LIST_DKV:
+            steps = np.where(real, -(-(length - tile * rows) // 64) * (hq // hkv), 0)
+        else:
+            steps = np.where(real, -(-np.minimum(length, (tile + 1) * rows) // 64), 0)
+        # the scheduler's own rules (pass_dispatch in csrc/schedule.cpp)
+        heaviest, total, n, narrow = float(steps.max()), float(steps.sum()), len(items), head_dim <= 64
+        if kind == A.LIST_DKV:
+            whole = max(heaviest + 8, (total + 8 * n) / (512 if narrow else 256))
+            self.halves = max(0.68 * heaviest + 8, (1.3 * total + 16 * n) / 256) < 0.9 * whole
+            per_unit = 2 if narrow and not self.halves else 1
+        else:
+            self.halves = heaviest + 6 >= 2 * (total + 12 * n) / 512
+            per_unit = 3 if narrow and kind == A.LIST_DQ else 2
+        self.slots = 32.0 * per_unit
+        self.queue_steps = np.array([steps[x::8].sum() for x in range(8)], dtype=float)
+        self.queue_items = np.array([real[x::8].sum() for x in range(8)], dtype=float)
+        self.heaviest = heaviest
+
+
+def _fit(A, rows, kind):
+    """rows: (lengths, q heads, kv heads, head_dim, {kernel: microseconds}).  Returns (launch_us, halves[3], table[width][3],
+    relative errors)."""
+    from scipy.optimize import least_squares
+    f = [_Features(A, kind, lens, hq, hkv, d) for lens, hq, hkv, d, _ in rows]
+    y = np.array([t[PASSES[kind]] for *_, t in rows])
+    width = np.array([WIDTHS[d] for *_, d, _ in rows])
+    S, N = np.stack([x.queue_steps for x in f]), np.stack([x.queue_items for x in f])
+    H, slots, halves = (np.array([getattr(x, name) for x in f]) for name in ("heaviest", "slots", "halves"))
+
+    def model(p):
+        p = np.abs(p)
+        half_step, half_alone, half_item = (np.where(halves, x, 1.0) for x in p[1:4])
+        step, item, alone = p[4:].reshape(-1, 3)[width].T
+        two = np.where(halves, 2.0, 1.0)
+        load = ((S * (two * half_step * step)[:, None] + N * (two * half_item * item)[:, None]).max(axis=1)) / slots
+        single = H * half_alone * alone + half_item * item
+        return p[0] + (load ** 4 + single ** 4) ** 0.25
+
+    start = np.concatenate([[8.0, 0.6, 0.65, 0.7], np.tile([1.6, 8.0, 1.2], len(WIDTHS))])
+    found = least_squares(lambda p: model(p) / y - 1.0, start, loss="soft_l1", f_scale=0.1, max_nfev=4000)
+    p = np.abs(found.x)
+    return p[0], p[1:4], p[4:].reshape(-1, 3), np.abs(model(found.x) / y - 1.0)
 
 
 def main() -> int:
     ap = argparse.ArgumentParser()
-    ap.add_argument("--head-dim", type=int, default=128, choices=[64, 128])
+    ap.add_argument("--head-dim", type=int, nargs="*", default=list(WIDTHS), choices=list(WIDTHS))
     args = ap.parse_args()
     import torch
     import paper_2504_20490_amd as A
     A.load_library()
-    passes = [(A.LIST_FWD, "fwd_kernel", 64.0), (A.LIST_DQ, "bwd_dq_kernel", 64.0), (A.LIST_DKV, "bwd_dkv_kernel", 32.0)]
-    rows = [(lens, hq, hkv, _measure(A, torch, lens, hq, hkv, args.head_dim)) for lens, hq, hkv in _packs(np.random.default_rng(7))]
-    print(f"// head_dim {args.head_dim}: {{launch_us, step_us, item_us}} for forward, dQ pass, dK/dV pass ({len(rows)} packs)")
-    for kind, name, slots in passes:
-        X = np.array([[1.0, *_features(A, kind, slots, lens, hq, hkv)] for lens, hq, hkv, _ in rows])
-        y = np.array([ms[name] for *_, ms in rows])
-        coef, *_ = np.linalg.lstsq(X / y[:, None], np.ones_like(y), rcond=None)
-        err = np.abs(X @ coef / y - 1.0)
-        print(f"{{{max(coef[0], 0.0):.1f}, {coef[1]:.3f}, {coef[2]:.2f}}},   // {name}: mean |error| {err.mean():.3f}, max {err.max():.3f}")
+    packs = list(_packs(np.random.default_rng(7))) + list(_small_packs(np.random.default_rng(11)))
+    rows = []
+    for d in args.head_dim:
+        rows += [(lens, hq, hkv, d, _measure(A, torch, lens, hq, hkv, d)) for lens, hq, hkv in packs]
+        print(f"// head_dim {d}: {len(packs)} packs", flush=True)
+    for kind, name in enumerate(PASSES):
+        launch, halves, table, err = _fit(A, rows, kind)
+        print(f"// {name}: mean |error| {err.mean():.3f}, 95 % below {np.quantile(err, 0.95):.2f}, max {err.max():.2f}")
+        print(f"{{{launch:.1f}, {{{', '.join(f'{x:.2f}' for x in halves)}}}}},")
+        print("{" + ", ".join(f"{{{s:.3f}, {i:.2f}, {a:.3f}}}" for s, i, a in table) + "},")
     return 0
 
 

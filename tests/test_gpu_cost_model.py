@@ -51,6 +51,23 @@ def test_prediction_matches_measurement(name, tolerance):
     assert abs(pb / bwd - 1.0) <= tolerance, (pb, bwd)
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,d,tolerance", [
+    ([2048] * 8, 32, 32, 64, 0.15),        # two and three workgroups per compute unit
+    ([2048] * 8, 32, 32, 96, 0.15),        # the narrower kernels of tile width 128
+    ([2048] * 8, 32, 32, 80, 0.15),
+    ([300] * 54, 16, 16, 64, 0.30),        # many short items
+    ([1800, 253], 8, 8, 128, 0.30),        # half items in all passes: the longest item decides
+    ([24000], 1, 1, 128, 0.30)])
+def test_prediction_at_other_widths_and_with_half_items(lengths, hq, hkv, d, tolerance):
+    """Bounds: about twice the fit's error on such packs (packs of milliseconds 7 %, of a hundred microseconds 15 %), for boxes
+    differ by some percent."""
+    import paper_2504_20490_amd as A
+    fwd, bwd, cu = _measured_ms(lengths, hq, hkv, d)
+    pf, pb = A.estimate_ms(cu, hq, hkv, d)
+    assert abs(pf / fwd - 1.0) <= tolerance, (pf, fwd)
+    assert abs(pb / bwd - 1.0) <= tolerance, (pb, bwd)
+
+
 def test_prediction_ranks_packs_like_the_measurement():
     """What a planner needs first: of two candidate packs the one predicted cheaper is the one measured cheaper."""
     import paper_2504_20490_amd as A
