@@ -21,6 +21,8 @@
 
 #include <algorithm>
 #include <cmath>
+#include <limits>
+#include <new>
 #include <numeric>
 
 namespace hspmd {
@@ -92,7 +94,8 @@ std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_q
                                Cost cost_of, Make make, Item pad) {
     int64_t total_cost = 0;
     for (int32_t s = 0; s < num_seqs; ++s) {
-        const int32_t n = chain_len(s);
+        const int64_t n = chain_len(s);
+        if (n > std::numeric_limits<int32_t>::max()) throw std::bad_alloc();   // no list of that size can be held
         for (int32_t i = 0; i < n; ++i) total_cost += cost_of(s, i);
     }
     total_cost *= kv_heads;
@@ -109,7 +112,7 @@ std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_q
     std::vector<SegmentClass> classes;
     int64_t segments = 0;
     for (int32_t s = 0; s < num_seqs; ++s) {
-        const int32_t n = chain_len(s);
+        const int32_t n = (int32_t)chain_len(s);
         if (n <= 0) continue;
         const size_t first_class = classes.size();
         SegmentClass seg{0, 0, 0, 0, s, 0, 0};
@@ -210,7 +213,7 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
     return place_chains<hspmd_work_item>(
         num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV || group == 1,
         [&](int32_t s) {
-            const int32_t n_tiles = (int32_t)ceil_div(cu[s + 1] - cu[s], tile_rows);
+            const int64_t n_tiles = ceil_div(cu[s + 1] - cu[s], tile_rows);
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
         },
         [&](int32_t s, int32_t i) {
@@ -386,7 +389,7 @@ std::vector<hspmd_block_item> build_block_list(hspmd_list_kind kind, const int32
     return place_chains<hspmd_block_item>(
         num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV || group == 1,
         [&](int32_t s) {
-            const int32_t n_tiles = (int32_t)ceil_div(rows_of(s), tile_rows);   // rows of the outputs the list owns
+            const int64_t n_tiles = ceil_div(rows_of(s), tile_rows);   // rows of the outputs the list owns
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
         },
         [&](int32_t s, int32_t i) { return block_item_cost(kind, make(s, 0, i), group); }, make,

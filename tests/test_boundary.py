@@ -185,6 +185,17 @@ def test_work_list_empty_and_zero_length():
     assert real.tolist() == [[0, 5, 0, 0]]
 
 
+@pytest.mark.parametrize("group", [1024, 1025])
+def test_a_list_that_cannot_be_held_is_refused(group):
+    """2^23 tiles x 1024 query heads of one KV head: more items than a list can hold, not an empty or a shorter list."""
+    with pytest.raises(A.HspmdError):
+        A.schedule(A.LIST_FWD, [0, 1 << 30], group, 1)
+    with pytest.raises(A.HspmdError):
+        A.block_schedule(A.LIST_DQ, [0, 1 << 30], [0, 1 << 30], [0], [0], group, 1)
+    with pytest.raises(A.HspmdError):
+        A.estimate_ms([0, 1 << 30], group, 1, 128)
+
+
 def test_schedule_rejects_bad_arguments():
     for bad, frag in ((dict(cu=[0, 4], hq=3, hkv=2), "multiple"), (dict(cu=[1, 4], hq=2, hkv=2), "cu_seqlens[0]"),
                       (dict(cu=[0, 4, 3], hq=2, hkv=2), "non-decreasing"), (dict(cu=[0, 4], hq=0, hkv=1), "positive")):
