@@ -9,6 +9,7 @@ pytestmark = pytest.mark.gpu
 def test_last_tiles_with_one_wave_of_rows_are_bit_identical_from_run_to_run(d):
     """Sequences of 257 .. 288 tokens end in a tile of five key tiles in which three of four waves own no row: those waves
     skip the first product and reach the copy of the third K tile long before the first wave has read the tile it lands on.
+    Their first tile, of two key tiles, is the case in which no wave may copy a third at all (test_fwd_tile_order.py).
     Which items suffer is chance, so the pack holds hundreds of them and runs many times; every run must give the same bits."""
     import torch
     import paper_2504_20490_amd as A

@@ -75,12 +75,13 @@ def test_ragged_lengths_span_tiles_and_tails(hq, hkv, d):
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(4, 4, 104), (4, 2, 104), (2, 2, 40), (3, 1, 120), (2, 2, 8), (2, 2, 112), (2, 1, 96),
-                                      (2, 2, 88)])
+                                      (2, 2, 88), (2, 2, 72), (3, 1, 80)])
 def test_head_dims_between_the_tile_widths(hq, hkv, d):
     """head_dim 104 is the paper's 32B model (hidden 6656 over 64 heads); any multiple of 8 runs on the next tile
     width up.  Outputs are written NaN-filled beforehand, so a column that the kernels leave out would show.
-    Up to 112 the kernels of width 128 contract over seven 16-column steps instead of eight (104, 112 and 96, 88: the
-    seventh step is then partly or wholly padding); 120 takes all eight."""
+    The kernels of width 128 exist with five 16-column steps of head_dim (up to 80), six (88, 96), seven (104, 112) and eight
+    (120), five and six of them with three 32-column output blocks instead of four; 40 and 8 run on width 64.  This pack
+    runs half items; the whole items of every width are compared in test_gpu_whole_items.py."""
     _full_check(RAGGED, hq, hkv, d, seed=30 + d)
 
 
