@@ -88,55 +88,53 @@ void walk_segments(const std::vector<SegmentClass>& classes, int32_t copies, Key
 }
 
 // chain_len(s): items of one kv head's chain of sequence s, most expensive first; cost_of(s, i): of its i-th item;
-// make(s, g, i): that item for kv head g.  one_head: a chain holds one item per tile, not one per query head of a group.
+// make(s, g, i): that item for kv head g.  finer_slots: workgroups that a queue holds at once, for lists whose chains may be cut
+// finer (chains with several query heads keep the coarse cut, so that a group's heads of one tile stay together), else 0.
 template <typename Item, typename ChainLen, typename Cost, typename Make>
-std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_queues, bool one_head, ChainLen chain_len,
+std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_queues, int32_t finer_slots, ChainLen chain_len,
                                Cost cost_of, Make make, Item pad) {
-    int64_t total_cost = 0;
+    int64_t total_cost = 0, chains = 0;
     for (int32_t s = 0; s < num_seqs; ++s) {
         const int64_t n = chain_len(s);
         if (n > std::numeric_limits<int32_t>::max()) throw std::bad_alloc();   // no list of that size can be held
         for (int32_t i = 0; i < n; ++i) total_cost += cost_of(s, i);
+        if (n > 0) chains += kv_heads;
     }
     total_cost *= kv_heads;
 
-    // cut chains into segments no heavier than 1/(4 * queues) of the total; fewer than two chains per queue are cut finer:
-    // their few segments left the heaviest queue a tenth above the mean (5 heads: one document of 16001 tokens, forward 355 ->
-    // 345, dK/dV 612 -> 586 us; one of 24976 tokens 445 -> 416, dQ 592 -> 550, dK/dV 802 -> 749 us).  With more chains the
-    // coarse cut balances as well and keeps more of a chain's K and V in one L2.  (Chains with several query heads keep the coarse
-    // cut, so that a group's heads of one tile stay together.)
-    int64_t chains = 0;
-    for (int32_t s = 0; s < num_seqs; ++s) chains += chain_len(s) > 0 ? kv_heads : 0;
-    const int64_t parts = one_head && chains < 2 * (int64_t)num_queues ? 16 : 4;
-    const int64_t cap = std::max<int64_t>(1, total_cost / (num_queues * parts));
     std::vector<SegmentClass> classes;
     int64_t segments = 0;
-    for (int32_t s = 0; s < num_seqs; ++s) {
-        const int32_t n = (int32_t)chain_len(s);
-        if (n <= 0) continue;
-        const size_t first_class = classes.size();
-        SegmentClass seg{0, 0, 0, 0, s, 0, 0};
-        for (int32_t i = 0; i < n; ++i) {
-            // an item that only writes zeros (block variant) still occupies a workgroup slot: weight 1, so that
-            // such items spread over the queues instead of piling up in one
-            const int64_t c = std::max<int64_t>(1, cost_of(s, i));
-            if (seg.count > 0 && seg.cost + c > cap) {
-                classes.push_back(seg);
-                seg = SegmentClass{0, 0, 0, 0, s, i, 0};
+    // cuts the chains into segments no heavier than 1/(parts * queues) of the total
+    auto cut = [&](int64_t parts) {
+        const int64_t cap = std::max<int64_t>(1, total_cost / (num_queues * parts));
+        classes.clear();
+        segments = 0;
+        for (int32_t s = 0; s < num_seqs; ++s) {
+            const int32_t n = (int32_t)chain_len(s);
+            if (n <= 0) continue;
+            const size_t first_class = classes.size();
+            SegmentClass seg{0, 0, 0, 0, s, 0, 0};
+            for (int32_t i = 0; i < n; ++i) {
+                // an item that only writes zeros (block variant) still occupies a workgroup slot: weight 1, so that
+                // such items spread over the queues instead of piling up in one
+                const int64_t c = std::max<int64_t>(1, cost_of(s, i));
+                if (seg.count > 0 && seg.cost + c > cap) {
+                    classes.push_back(seg);
+                    seg = SegmentClass{0, 0, 0, 0, s, i, 0};
+                }
+                if (seg.count == 0) seg.first_cost = c;
+                ++seg.count;
+                seg.cost += c;
             }
-            if (seg.count == 0) seg.first_cost = c;
-            ++seg.count;
-            seg.cost += c;
+            classes.push_back(seg);
+            const int64_t per_head = (int64_t)(classes.size() - first_class);
+            for (int64_t k = 0; k < per_head; ++k) {
+                classes[first_class + k].order0 = segments + k;
+                classes[first_class + k].stride = per_head;
+            }
+            segments += per_head * kv_heads;
         }
-        classes.push_back(seg);
-        const int64_t per_head = (int64_t)(classes.size() - first_class);
-        for (int64_t k = 0; k < per_head; ++k) {
-            classes[first_class + k].order0 = segments + k;
-            classes[first_class + k].stride = per_head;
-        }
-        segments += per_head * kv_heads;
-    }
-    if (classes.empty()) return {};
+    };
 
     // longest-processing-time assignment: each segment, heaviest first, goes to the least loaded queue (the lowest index
     // among equals).  The loads are a binary heap whose root is replaced, never popped and pushed.
@@ -146,23 +144,56 @@ std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_q
         bool before(const Load& o) const { return load != o.load ? load < o.load : queue < o.queue; }
     };
     std::vector<Load> heap((size_t)num_queues);
-    for (int32_t x = 0; x < num_queues; ++x) heap[x] = Load{0, x};   // sorted, hence a heap
-    std::vector<int32_t> queue_of((size_t)segments);
-    std::vector<int64_t> length((size_t)num_queues, 0);
-    walk_segments(classes, kv_heads, [](const SegmentClass& c) { return c.cost; }, [&](const SegmentClass& c, int32_t g) {
-        Load root = heap[0];
-        queue_of[(size_t)(c.order0 + g * c.stride)] = root.queue;
-        length[(size_t)root.queue] += c.count;
-        root.load += c.cost;
-        size_t at = 0;
-        for (size_t child = 1; child < heap.size(); child = 2 * at + 1) {
-            if (child + 1 < heap.size() && heap[child + 1].before(heap[child])) ++child;
-            if (!heap[child].before(root)) break;
-            heap[at] = heap[child];
-            at = child;
+    std::vector<int32_t> queue_of;
+    std::vector<int64_t> length((size_t)num_queues);
+    auto assign = [&] {
+        for (int32_t x = 0; x < num_queues; ++x) heap[x] = Load{0, x};   // sorted, hence a heap
+        queue_of.resize((size_t)segments);
+        std::fill(length.begin(), length.end(), (int64_t)0);
+        walk_segments(classes, kv_heads, [](const SegmentClass& c) { return c.cost; }, [&](const SegmentClass& c, int32_t g) {
+            Load root = heap[0];
+            queue_of[(size_t)(c.order0 + g * c.stride)] = root.queue;
+            length[(size_t)root.queue] += c.count;
+            root.load += c.cost;
+            size_t at = 0;
+            for (size_t child = 1; child < heap.size(); child = 2 * at + 1) {
+                if (child + 1 < heap.size() && heap[child + 1].before(heap[child])) ++child;
+                if (!heap[child].before(root)) break;
+                heap[at] = heap[child];
+                at = child;
+            }
+            heap[at] = root;
+        });
+    };
+
+    cut(4);
+    if (classes.empty()) return {};
+    assign();
+    // Fewer than two chains per queue leave few segments, and the heaviest queue up to a tenth above the mean.  They are cut four
+    // times finer where that is what the pass waits for: not when the queues are balanced (a chain's K and V then stay in one
+    // L2), when the heaviest item outlasts the work per slot, or when items cost alike and come in rounds anyway.  Measured, coarse
+    // and fine (us; forward, dQ, dK/dV): one document of 16001 tokens, 5 heads 339 / 326, 454 / 442, 590 / 555; 12 heads 716 /
+    // 682, 987 / 926, 1349 / 1287; dK/dV of 20000 tokens, 2 KV heads of 4, width 64 1169 / 1064.  Coarse by these rules: 8 heads,
+    // balanced, 476 / 483; a block of 8192 rows and keys, 8 KV heads of 4, balanced, dK/dV 900 / 944; 12 heads of 2000 tokens,
+    // forward, heaviest item five times the work per slot, 30 / 33.  (That last rule costs where only dQ gains: one head
+    // of 24151 tokens, forward 254 / 256, dQ 259 / 250.)
+    if (finer_slots > 0 && chains < 2 * (int64_t)num_queues) {
+        int64_t heaviest_queue = 0, heaviest_item = 0, total = 0, items = 0;
+        for (const Load& l : heap) {
+            heaviest_queue = std::max(heaviest_queue, l.load);
+            total += l.load;
         }
-        heap[at] = root;
-    });
+        for (const SegmentClass& c : classes) {
+            heaviest_item = std::max(heaviest_item, c.first_cost);
+            items += (int64_t)c.count * kv_heads;
+        }
+        const double queue = (double)total / num_queues;
+        if ((double)heaviest_queue > 1.03 * queue && (double)heaviest_item < 3.0 * queue / finer_slots &&
+            (double)heaviest_item > 1.1 * (double)total / (double)items) {
+            cut(16);
+            assign();
+        }
+    }
 
     // inside a queue: segments by their most expensive item, then creation order; slot p belongs to queue
     // p % num_queues, short queues are padded at their end
@@ -211,7 +242,7 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
         return kind == HSPMD_LIST_DKV ? i : (int32_t)ceil_div(len, tile_rows) - 1 - i / group;
     };
     return place_chains<hspmd_work_item>(
-        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV || group == 1,
+        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV ? 32 : group == 1 ? 64 : 0,
         [&](int32_t s) {
             const int64_t n_tiles = ceil_div(cu[s + 1] - cu[s], tile_rows);
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
@@ -387,7 +418,7 @@ std::vector<hspmd_block_item> build_block_list(hspmd_list_kind kind, const int32
     };
     // most expensive first inside a chain (with a shift the cost is still monotone in the tile index)
     return place_chains<hspmd_block_item>(
-        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV || group == 1,
+        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV ? 32 : group == 1 ? 64 : 0,
         [&](int32_t s) {
             const int64_t n_tiles = ceil_div(rows_of(s), tile_rows);   // rows of the outputs the list owns
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;

@@ -185,6 +185,22 @@ def test_work_list_empty_and_zero_length():
     assert real.tolist() == [[0, 5, 0, 0]]
 
 
+@pytest.mark.parametrize("kind", [A.LIST_FWD, A.LIST_DKV])
+@pytest.mark.parametrize("heads,whole_chains", [(8, True), (12, False)])
+def test_few_chains_are_cut_fine_only_where_the_queues_need_it(kind, heads, whole_chains):
+    """One document: eight heads fill eight queues, each keeps one head's items (its K and V in one L2); twelve do not, and the
+    heaviest queue must not stand far above the mean."""
+    length = 16001
+    items = A.schedule(kind, [0, length], heads, heads, 8)
+    tile, head = items[:, 2].astype(np.int64), items[:, 3]
+    steps = np.where(tile < 0, 0, -(-(length - tile * 128) // 64) if kind == A.LIST_DKV else -(-np.minimum(length, (tile + 1) * 128) // 64))
+    loads = np.array([steps[x::8].sum() for x in range(8)])
+    assert loads.max() <= 1.03 * loads.mean()
+    if whole_chains:
+        for x in range(8):
+            assert len(set(head[x::8][tile[x::8] >= 0])) == 1
+
+
 @pytest.mark.parametrize("group", [1024, 1025])
 def test_a_list_that_cannot_be_held_is_refused(group):
     """2^23 tiles x 1024 query heads of one KV head: more items than a list can hold, not an empty or a shorter list."""
