@@ -87,6 +87,77 @@ void walk_segments(const std::vector<SegmentClass>& classes, int32_t copies, Key
     }
 }
 
+// Cuts the chains into segments no heavier than `cap`.  chain_len, cost_of: see place_chains.  (Inlined by force: called from two
+// places it is not, and neither are then the costs and items of the list: a refill's lists take up to twice as long.)
+template <typename ChainLen, typename Cost>
+__attribute__((always_inline)) inline std::vector<SegmentClass> cut_chains(int32_t num_seqs, int32_t kv_heads, int64_t cap, ChainLen chain_len, Cost cost_of) {
+    std::vector<SegmentClass> classes;
+    int64_t segments = 0;
+    for (int32_t s = 0; s < num_seqs; ++s) {
+        const int32_t n = (int32_t)chain_len(s);
+        if (n <= 0) continue;
+        const size_t first_class = classes.size();
+        SegmentClass seg{0, 0, 0, 0, s, 0, 0};
+        for (int32_t i = 0; i < n; ++i) {
+            // an item that only writes zeros (block variant) still occupies a workgroup slot: weight 1, so that
+            // such items spread over the queues instead of piling up in one
+            const int64_t c = std::max<int64_t>(1, cost_of(s, i));
+            if (seg.count > 0 && seg.cost + c > cap) {
+                classes.push_back(seg);
+                seg = SegmentClass{0, 0, 0, 0, s, i, 0};
+            }
+            if (seg.count == 0) seg.first_cost = c;
+            ++seg.count;
+            seg.cost += c;
+        }
+        classes.push_back(seg);
+        const int64_t per_head = (int64_t)(classes.size() - first_class);
+        for (int64_t k = 0; k < per_head; ++k) {
+            classes[first_class + k].order0 = segments + k;
+            classes[first_class + k].stride = per_head;
+        }
+        segments += per_head * kv_heads;
+    }
+    return classes;
+}
+
+struct Assignment {
+    std::vector<int32_t> queue_of;   // per segment, by creation index
+    std::vector<int64_t> length;     // items per queue
+    int64_t heaviest = 0;            // cost of the heaviest queue
+};
+
+// Longest-processing-time assignment: each segment, heaviest first, goes to the least loaded queue (the lowest index among
+// equals).  The loads are a binary heap whose root is replaced, never popped and pushed.
+Assignment assign_segments(const std::vector<SegmentClass>& classes, int32_t kv_heads, int32_t num_queues) {
+    struct Load {
+        int64_t load;
+        int32_t queue;
+        bool before(const Load& o) const { return load != o.load ? load < o.load : queue < o.queue; }
+    };
+    std::vector<Load> heap((size_t)num_queues);
+    for (int32_t x = 0; x < num_queues; ++x) heap[x] = Load{0, x};   // sorted, hence a heap
+    std::vector<int32_t> queue_of((size_t)classes.size() * (size_t)kv_heads);
+    std::vector<int64_t> length((size_t)num_queues, 0);
+    walk_segments(classes, kv_heads, [](const SegmentClass& c) { return c.cost; }, [&](const SegmentClass& c, int32_t g) {
+        Load root = heap[0];
+        queue_of[(size_t)(c.order0 + g * c.stride)] = root.queue;
+        length[(size_t)root.queue] += c.count;
+        root.load += c.cost;
+        size_t at = 0;
+        for (size_t child = 1; child < heap.size(); child = 2 * at + 1) {
+            if (child + 1 < heap.size() && heap[child + 1].before(heap[child])) ++child;
+            if (!heap[child].before(root)) break;
+            heap[at] = heap[child];
+            at = child;
+        }
+        heap[at] = root;
+    });
+    int64_t heaviest = 0;
+    for (const Load& l : heap) heaviest = std::max(heaviest, l.load);
+    return Assignment{std::move(queue_of), std::move(length), heaviest};
+}
+
 // chain_len(s): items of one kv head's chain of sequence s, most expensive first; cost_of(s, i): of its i-th item;
 // make(s, g, i): that item for kv head g.  finer_slots: workgroups that a queue holds at once, for lists whose chains may be cut
 // finer (chains with several query heads keep the coarse cut, so that a group's heads of one tile stay together), else 0.
@@ -102,73 +173,11 @@ std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_q
     }
     total_cost *= kv_heads;
 
-    std::vector<SegmentClass> classes;
-    int64_t segments = 0;
-    // cuts the chains into segments no heavier than 1/(parts * queues) of the total
-    auto cut = [&](int64_t parts) {
-        const int64_t cap = std::max<int64_t>(1, total_cost / (num_queues * parts));
-        classes.clear();
-        segments = 0;
-        for (int32_t s = 0; s < num_seqs; ++s) {
-            const int32_t n = (int32_t)chain_len(s);
-            if (n <= 0) continue;
-            const size_t first_class = classes.size();
-            SegmentClass seg{0, 0, 0, 0, s, 0, 0};
-            for (int32_t i = 0; i < n; ++i) {
-                // an item that only writes zeros (block variant) still occupies a workgroup slot: weight 1, so that
-                // such items spread over the queues instead of piling up in one
-                const int64_t c = std::max<int64_t>(1, cost_of(s, i));
-                if (seg.count > 0 && seg.cost + c > cap) {
-                    classes.push_back(seg);
-                    seg = SegmentClass{0, 0, 0, 0, s, i, 0};
-                }
-                if (seg.count == 0) seg.first_cost = c;
-                ++seg.count;
-                seg.cost += c;
-            }
-            classes.push_back(seg);
-            const int64_t per_head = (int64_t)(classes.size() - first_class);
-            for (int64_t k = 0; k < per_head; ++k) {
-                classes[first_class + k].order0 = segments + k;
-                classes[first_class + k].stride = per_head;
-            }
-            segments += per_head * kv_heads;
-        }
-    };
-
-    // longest-processing-time assignment: each segment, heaviest first, goes to the least loaded queue (the lowest index
-    // among equals).  The loads are a binary heap whose root is replaced, never popped and pushed.
-    struct Load {
-        int64_t load;
-        int32_t queue;
-        bool before(const Load& o) const { return load != o.load ? load < o.load : queue < o.queue; }
-    };
-    std::vector<Load> heap((size_t)num_queues);
-    std::vector<int32_t> queue_of;
-    std::vector<int64_t> length((size_t)num_queues);
-    auto assign = [&] {
-        for (int32_t x = 0; x < num_queues; ++x) heap[x] = Load{0, x};   // sorted, hence a heap
-        queue_of.resize((size_t)segments);
-        std::fill(length.begin(), length.end(), (int64_t)0);
-        walk_segments(classes, kv_heads, [](const SegmentClass& c) { return c.cost; }, [&](const SegmentClass& c, int32_t g) {
-            Load root = heap[0];
-            queue_of[(size_t)(c.order0 + g * c.stride)] = root.queue;
-            length[(size_t)root.queue] += c.count;
-            root.load += c.cost;
-            size_t at = 0;
-            for (size_t child = 1; child < heap.size(); child = 2 * at + 1) {
-                if (child + 1 < heap.size() && heap[child + 1].before(heap[child])) ++child;
-                if (!heap[child].before(root)) break;
-                heap[at] = heap[child];
-                at = child;
-            }
-            heap[at] = root;
-        });
-    };
-
-    cut(4);
+    // segments no heavier than 1/(4 * queues) of the total
+    const int64_t cap = std::max<int64_t>(1, total_cost / ((int64_t)num_queues * 4));
+    std::vector<SegmentClass> classes = cut_chains(num_seqs, kv_heads, cap, chain_len, cost_of);
     if (classes.empty()) return {};
-    assign();
+    Assignment placed = assign_segments(classes, kv_heads, num_queues);
     // Fewer than two chains per queue leave few segments, and the heaviest queue up to a tenth above the mean.  They are cut four
     // times finer where that is what the pass waits for: not when the queues are balanced (a chain's K and V then stay in one
     // L2), when the heaviest item outlasts the work per slot, or when items cost alike and come in rounds anyway.  Measured, coarse
@@ -178,26 +187,25 @@ std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_q
     // forward, heaviest item five times the work per slot, 30 / 33.  (That last rule costs where only dQ gains: one head
     // of 24151 tokens, forward 254 / 256, dQ 259 / 250.)
     if (finer_slots > 0 && chains < 2 * (int64_t)num_queues) {
-        int64_t heaviest_queue = 0, heaviest_item = 0, total = 0, items = 0;
-        for (const Load& l : heap) {
-            heaviest_queue = std::max(heaviest_queue, l.load);
-            total += l.load;
-        }
+        int64_t heaviest_item = 0, total = 0, items = 0;
         for (const SegmentClass& c : classes) {
             heaviest_item = std::max(heaviest_item, c.first_cost);
+            total += c.cost * kv_heads;
             items += (int64_t)c.count * kv_heads;
         }
         const double queue = (double)total / num_queues;
-        if ((double)heaviest_queue > 1.03 * queue && (double)heaviest_item < 3.0 * queue / finer_slots &&
+        if ((double)placed.heaviest > 1.03 * queue && (double)heaviest_item < 3.0 * queue / finer_slots &&
             (double)heaviest_item > 1.1 * (double)total / (double)items) {
-            cut(16);
-            assign();
+            const int64_t fine = std::max<int64_t>(1, total_cost / ((int64_t)num_queues * 16));
+            classes = cut_chains(num_seqs, kv_heads, fine, chain_len, cost_of);
+            placed = assign_segments(classes, kv_heads, num_queues);
         }
     }
 
     // inside a queue: segments by their most expensive item, then creation order; slot p belongs to queue
     // p % num_queues, short queues are padded at their end
-    const int64_t longest = *std::max_element(length.begin(), length.end());
+    const std::vector<int32_t>& queue_of = placed.queue_of;
+    const int64_t longest = *std::max_element(placed.length.begin(), placed.length.end());
     std::vector<Item> out((size_t)(longest * num_queues), pad);
     std::vector<int64_t> cursor((size_t)num_queues);
     std::iota(cursor.begin(), cursor.end(), (int64_t)0);
