@@ -286,32 +286,40 @@ PassLoad pass_load(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, in
 // chains) thus count as work, which leaves packs at the edge of a rule with whole items.
 namespace {
 
-// Whether the forward and the dQ pass work on half items (64 rows, two waves of a workgroup sharing each 32-row block).  As
-// for the dK/dV pass below: a step of a half item takes about 0.6 of a whole item's (each tile is copied for half the rows),
-// so halves pay when the heaviest item is what the pass waits for: when it is at least twice as long as the work per slot
-// (two workgroups per compute unit), six steps of prologue and stores per half item included.  Measured, forward and dQ pass,
-// whole -> halves (us): heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot
-// 187 -> 145, 213 -> 131; 93 steps, 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 3 steps, 168
-// items 12.2 -> 14.4, 13.3 -> 15.0; 251 steps, 156 per slot 336 -> 376, 450 -> 445; 8 x 2048, 32 heads 304 -> 425, 450 -> 534.
-bool split_rows(const PassLoad& load, int64_t slots) {
-    const double workgroups = 512.0;
+// Whether the forward and the dQ pass work on half items (64 rows, two waves of a workgroup sharing each 32-row block).  A
+// step of a half item takes 0.6 to 0.85 of a whole item's (each tile is copied for half the rows), so halves pay when the
+// heaviest item is what the pass waits for: when it is at least twice as long as the work per slot (two workgroups per compute
+// unit), six steps of prologue and stores per half item included; and when it is long enough for what the halves cost, which
+// is more once there are more of them than compute units (above 128 items).  Measured, forward and dQ pass, whole -> halves (us):
+// heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot 187 -> 145, 213 -> 131; 93 steps,
+// 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 251 steps, 156 per slot 336 -> 376, 450 -> 445; 8 x
+// 2048, 32 heads 304 -> 425, 450 -> 534; and 2 steps, 128 items 11.6 -> 13.2, 8 steps, 192 items 17.2 -> 19.7, 20.2 -> 21.3; at tile
+// width 64 the latter 9.9 -> 12.2 and 13.4 -> 17.0.  Of 201 packs at three widths, measured in either form, none that
+// this rule halves takes more than 1.02 of its time whole; the halved forwards take 0.89 on average, the dQ passes 0.81.
+bool split_rows(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim) {
+    const double workgroups = 512.0, heaviest = (double)load.heaviest, crowd = std::max(0.0, (double)slots - 128.0);
+    const double least = kind == HSPMD_LIST_FWD ? (head_dim <= 64 ? 8 : 6) + 0.1 * crowd : crowd > 0 ? 8 + 0.05 * crowd : 2;
     const double per_slot = ((double)load.total + 6.0 * 2.0 * (double)slots) / workgroups;
-    return (double)load.heaviest + 6.0 >= 2.0 * per_slot;
+    return heaviest + 6.0 >= 2.0 * per_slot && heaviest >= least;
 }
 
 // Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass
 // takes as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs
 // 0.68 of the whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy
-// every Q / dO tile, and an item costs about eight steps beside its tiles.  Measured, whole and split (us): heaviest item 32
-// steps, 8.5 per slot (2 sequences, 8 heads) 50 and 41; 60 steps, 16 per slot (8 KV heads of 4) 85 and 61; 238 steps,
-// 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and 321; 3 steps, 168 items 17 and 23 (the
-// halves no longer fit the chip at once); 8 x 2048, 32 heads 652 and 826.
+// every Q / dO tile, and an item costs about eight steps beside its tiles.  At tile width 64, where two whole items share a unit but
+// halves do not, a full chip takes 1.6 for the halves; and with more halves than units a quarter of a half item is lost at the end.
+// Measured, whole and split (us): heaviest item 32 steps, 8.5 per slot (2 sequences, 8 heads) 50 and 41; 60 steps, 16 per slot
+// (8 KV heads of 4) 85 and 61; 238 steps, 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and 321;
+// 3 steps, 168 items 17 and 23; 8 x 2048, 32 heads 652 and 826; 10 x 512, 4 heads (160 items) 22.9 and 30.1; width 64, one document
+// of 16384 tokens, 2 heads 216 and 229.  Of the same packs none that this rule halves takes more than 1.01 of its time whole,
+// 0.85 on average.
 bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
     const double heaviest = (double)load.heaviest, total = (double)load.total, items = (double)slots;
     const double units = 256.0;   // compute units; whole items of tile width 64 fit a unit twice
-    const double workgroups = head_dim <= 64 ? 2 * units : units;
+    const double workgroups = head_dim <= 64 ? 2 * units : units, full = head_dim <= 64 ? 1.6 : 1.3;
     const double whole = std::max(heaviest + 8, (total + 8 * items) / workgroups);
-    const double split = std::max(0.68 * heaviest + 8, (1.3 * total + 8 * 2 * items) / units);
+    const double tail = 2 * items > units ? 0.25 * (0.5 * full * total / items + 8) : 0.0;
+    const double split = std::max(0.68 * heaviest + 8, (full * total + 8 * 2 * items) / units + tail);
     return split < 0.9 * whole;
 }
 
@@ -327,7 +335,7 @@ bool short_items(const PassLoad& load, int64_t slots) { return load.total <= 10 
 }  // namespace
 
 Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim, bool block) {
-    if (kind != HSPMD_LIST_DKV) return split_rows(load, slots) ? Dispatch::kHalves : Dispatch::kWhole;
+    if (kind != HSPMD_LIST_DKV) return split_rows(kind, load, slots, head_dim) ? Dispatch::kHalves : Dispatch::kWhole;
     if (split_dkv(load, slots, head_dim)) return Dispatch::kHalves;
     return !block && head_dim > 64 && short_items(load, slots) ? Dispatch::kPersistent : Dispatch::kWhole;
 }

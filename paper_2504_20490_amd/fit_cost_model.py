@@ -86,11 +86,18 @@ class _Features:
         # the scheduler's own rules (pass_dispatch in csrc/schedule.cpp)
         heaviest, total, n, narrow = float(steps.max()), float(steps.sum()), len(items), head_dim <= 64
         if kind == A.LIST_DKV:
+            full = 1.6 if narrow else 1.3
             whole = max(heaviest + 8, (total + 8 * n) / (512 if narrow else 256))
-            self.halves = max(0.68 * heaviest + 8, (1.3 * total + 16 * n) / 256) < 0.9 * whole
+            tail = 0.25 * (0.5 * full * total / n + 8) if 2 * n > 256 else 0.0
+            self.halves = max(0.68 * heaviest + 8, (full * total + 16 * n) / 256 + tail) < 0.9 * whole
             per_unit = 2 if narrow and not self.halves else 1
         else:
-            self.halves = heaviest + 6 >= 2 * (total + 12 * n) / 512
+            crowd = max(0, n - 128)
+            if kind == A.LIST_FWD:
+                least = (8 if narrow else 6) + 0.1 * crowd
+            else:
+                least = 8 + 0.05 * crowd if crowd else 2
+            self.halves = heaviest + 6 >= 2 * (total + 12 * n) / 512 and heaviest >= least
             per_unit = 3 if narrow and kind == A.LIST_DQ else 2
         self.slots = 32.0 * per_unit
         self.queue_steps = np.array([steps[x::8].sum() for x in range(8)], dtype=float)

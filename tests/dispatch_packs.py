@@ -12,7 +12,7 @@ PACKED = [(RAGGED, 8, 8, d, WHOLE, WHOLE) for d in (64, 40, 72, 80, 88, 96, 104,
 # groups: with few chains of long dK/dV items that pass takes halves, with more it does not
 PACKED += [(RAGGED, 8, 2, d, WHOLE, HALVES) for d in (64, 80, 128)] + [(RAGGED, 24, 12, d, WHOLE, WHOLE) for d in (64, 96, 128)]
 # more than a thousand dK/dV items of ten tiles and less: persistent workgroups, long enough for the loop that spreads its copies
-PERSISTENT_PACKS = [([1024, 700, 577, 449, 64, 1000, 640, 300] * 2, 16, 16, d, WHOLE, PERSISTENT) for d in (72, 96, 104, 128)]
+PERSISTENT_PACKS = [([640, 577, 449, 300, 600, 512, 64, 400] * 3, 12, 12, d, WHOLE, PERSISTENT) for d in (72, 96, 104, 128)]
 
 # (q lengths, k lengths, q positions, k positions): diagonals inside the block with either sign, blocks in the past and in the
 # future, empty chunks, ragged tails

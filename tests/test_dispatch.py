@@ -60,8 +60,26 @@ def test_block_packs(scheduler, hq, hkv, d, rows, dkv):
 
 def test_packs_of_the_other_form(scheduler):
     """The edges on which half items are compared with the oracle, and the many short items of the persistent pass."""
-    from test_gpu_split_items import EDGES
-    assert _packed(scheduler, EDGES, 2, 2, 128) == (packs.HALVES,) * 3
-    assert _packed(scheduler, [1100], 2, 1, 104) == (packs.HALVES,) * 3
-    assert _packed(scheduler, [1 + (i * 37) % 131 for i in range(150)], 8, 8, 72)[2] == packs.PERSISTENT
+    from test_gpu_split_items import EDGES, MANY_SHORT
+    for lengths in (EDGES, [449], [700, 64], [1100], [449, 70, 129]):
+        for hq, hkv, d in ((2, 2, 128), (3, 1, 128), (2, 1, 104), (2, 2, 96), (4, 2, 64), (2, 1, 64), (2, 2, 40)):
+            assert _packed(scheduler, lengths, hq, hkv, d) == (packs.HALVES,) * 3, (lengths, hq, hkv, d)
+    for hq, hkv, d in ((8, 8, 128), (16, 8, 104), (8, 8, 72)):
+        assert _packed(scheduler, MANY_SHORT, hq, hkv, d)[2] == packs.PERSISTENT
     assert _packed(scheduler, [2048] * 8, 32, 32, 128) == (packs.WHOLE,) * 3
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d", [([512] * 3, 16, 16, 128), ([512] * 3, 16, 16, 64), ([256] * 5, 16, 16, 96),
+                                              ([100] * 9, 16, 16, 64), ([64] * 2, 4, 4, 128)])
+def test_short_items_on_many_units_stay_whole(scheduler, lengths, hq, hkv, d):
+    """Halves of them are more than the chip has units, or too short for what halves cost."""
+    assert _packed(scheduler, lengths, hq, hkv, d)[:2] == (packs.WHOLE, packs.WHOLE)
+
+
+@pytest.mark.parametrize("lengths,heads,d,form", [
+    ([512] * 10, 4, 128, packs.WHOLE),            # 160 items: halves would come in two rounds
+    ([16384], 2, 64, packs.WHOLE),                # two whole items fit a unit, halves do not
+    ([400] * 33, 16, 128, packs.PERSISTENT), ([512] * 78, 16, 128, packs.PERSISTENT),
+    ([16384], 1, 128, packs.HALVES)])
+def test_form_of_the_dkv_pass(scheduler, lengths, heads, d, form):
+    assert _packed(scheduler, lengths, heads, heads, d)[2] == form
