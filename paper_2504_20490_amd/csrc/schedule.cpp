@@ -323,21 +323,27 @@ bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
     return split < 0.9 * whole;
 }
 
-// Whether the dK/dV pass draws its items in persistent workgroups (tile width 128, whole items, packed plans).  One workgroup
-// fits a compute unit there, so the time between two of them (about 5 us) is exposed: a large part of a short item.  Inside
-// the item loop, on the other hand, the compiler's schedule of the tile loop is 2-4 % slower.  Measured, one workgroup per
-// item and persistent (us), by mean steps per item: 4 (57 sequences of 32 .. 506 tokens, 16 heads, head_dim 96 / 128) 142 and
-// 124 / 168 and 156; 5 (32 x 512, 32 heads) 365 and 338; 9 (16 x 1024) 463 and 438; 13 558 and 552; 17 (8 x 2048) 676 and
-// 665, but the whole layer 1396 and 1402 under sustained load, where idle time comes back as clock; 33 (8 x 4096, 16 heads)
-// 1080 and 1098; 58 2850 and 2945; and with two items per unit 317 and 343.
-bool short_items(const PassLoad& load, int64_t slots) { return load.total <= 10 * slots && slots >= 4 * 256; }
+// Whether the dK/dV pass draws its items in persistent workgroups (tile width 128, whole items, packed plans): at least 1024
+// slots, between 3.2 and 6 steps per slot on average, 9 at head_dim up to 112, and no item that alone takes most of the pass.  One workgroup fits a compute unit there, so
+// the time between two of them is exposed, most of all, by the measurements, where chains of two, four or eight items bring heavy
+// and light items up in step with the order in which an XCD hands its workgroups out.  Against that, the next item's loads
+// wait for the last one's stores inside a workgroup, which short items feel, and the compiler's schedule of the tile loop is 2-4 %
+// slower in an item loop, which long ones feel.  Measured, one workgroup per item and persistent (us, head_dim 128): 33 x 400
+// tokens, 16 heads (4 steps) 179 and 148; 78 x 512, 16 heads (5) 442 and 390; 67 x 300, 8 heads (3) 98 and 105; 43 x 64, 24 heads
+// (1) 47 and 52; 18 sequences of up to 2734, 16 heads (9.9) 164 and 174; 5 x 1300, 24 heads (11) 140 and 153; 438 sequences, one of 3026, one head (5, the longest 48) 72 and 79;
+// head_dim 104, 7 x 1024, 40 heads (9) 247 and 233.  Over 114 packs at three widths persistent workgroups take 0.77 to 1.02 of the time, 0.93 on average.
+bool short_items(const PassLoad& load, int64_t slots, int32_t head_dim) {
+    const double per_unit = (double)(load.total + 8 * slots) / 256.0;
+    return slots >= 4 * 256 && 5 * load.total > 16 * slots && load.total <= (head_dim > 112 ? 6 : 9) * slots &&
+           (double)load.heaviest + 8 <= 0.8 * per_unit;
+}
 
 }  // namespace
 
 Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim, bool block) {
     if (kind != HSPMD_LIST_DKV) return split_rows(kind, load, slots, head_dim) ? Dispatch::kHalves : Dispatch::kWhole;
     if (split_dkv(load, slots, head_dim)) return Dispatch::kHalves;
-    return !block && head_dim > 64 && short_items(load, slots) ? Dispatch::kPersistent : Dispatch::kWhole;
+    return !block && head_dim > 64 && short_items(load, slots, head_dim) ? Dispatch::kPersistent : Dispatch::kWhole;
 }
 
 // ------------------------------------------------------------------------------ cost model

@@ -79,7 +79,8 @@ def test_short_items_on_many_units_stay_whole(scheduler, lengths, hq, hkv, d):
 @pytest.mark.parametrize("lengths,heads,d,form", [
     ([512] * 10, 4, 128, packs.WHOLE),            # 160 items: halves would come in two rounds
     ([16384], 2, 64, packs.WHOLE),                # two whole items fit a unit, halves do not
+    ([64] * 43, 24, 128, packs.WHOLE), ([300] * 67, 8, 128, packs.WHOLE), ([1300] * 5, 24, 128, packs.WHOLE),
     ([400] * 33, 16, 128, packs.PERSISTENT), ([512] * 78, 16, 128, packs.PERSISTENT),
-    ([16384], 1, 128, packs.HALVES)])
+    ([1024] * 7, 40, 128, packs.WHOLE), ([1024] * 7, 40, 104, packs.PERSISTENT), ([16384], 1, 128, packs.HALVES)])
 def test_form_of_the_dkv_pass(scheduler, lengths, heads, d, form):
     assert _packed(scheduler, lengths, heads, heads, d)[2] == form
