@@ -353,18 +353,18 @@ Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots
 // powers: where they are close, part of the chip idles at the end): the weight of the heaviest XCD queue -- steps x step time
 // + a fixed time per item -- shared by the workgroups that an XCD holds, and the heaviest item on a chip that is otherwise
 // idle.  Half items take the stated shares of a whole one's times.  Fitted by relative least squares to 124 packs at each of
-// five widths: mean |error| 6-7 % per pass, 95 % of the packs within 18 %, the others (passes of a few steps per item or
+// five widths: mean |error| 5-7 % per pass, 95 % of the packs within 21 %, the others (passes of a few steps per item or
 // with a single item per workgroup) within 40 %.
 namespace {
 
 struct PassCost { double step_us, item_us, alone_us; };               // alone_us: a step with one workgroup per unit or fewer
 struct PassFixed { double launch_us, half_step, half_alone, half_item; };   // half_*: shares of a whole item's times
-constexpr PassFixed kPassFixed[3] = {{5.6, 0.69, 0.84, 0.44}, {0.0, 0.65, 0.59, 0.67}, {0.0, 0.46, 0.67, 0.88}};
+constexpr PassFixed kPassFixed[3] = {{1.6, 0.64, 0.75, 0.83}, {0.0, 0.62, 0.61, 0.67}, {0.0, 0.52, 0.70, 0.84}};
 // head_dim up to 64, 80, 96, 112, 128: each has kernels of its own
 constexpr PassCost kPassCost[3][5] = {
-    {{1.078, 5.83, 0.587}, {1.383, 6.79, 0.725}, {1.461, 7.22, 0.720}, {1.695, 8.01, 0.745}, {1.729, 8.10, 0.754}},
-    {{1.922, 11.32, 0.617}, {1.700, 12.42, 0.808}, {1.863, 13.04, 0.858}, {2.201, 14.03, 0.914}, {2.338, 14.83, 0.926}},
-    {{1.741, 9.76, 0.892}, {1.328, 10.99, 0.981}, {1.377, 11.20, 1.131}, {1.642, 12.79, 1.109}, {1.662, 12.90, 1.217}}
+    {{1.092, 6.86, 0.692}, {1.359, 7.88, 0.845}, {1.447, 8.07, 0.835}, {1.686, 9.25, 0.849}, {1.712, 9.12, 0.858}},
+    {{1.919, 11.16, 0.593}, {1.701, 12.25, 0.786}, {1.859, 12.98, 0.827}, {2.206, 13.94, 0.876}, {2.331, 14.86, 0.896}},
+    {{1.724, 10.78, 0.835}, {1.357, 11.48, 0.938}, {1.405, 11.83, 1.075}, {1.659, 13.52, 1.059}, {1.666, 13.82, 1.163}}
 };
 
 }  // namespace
