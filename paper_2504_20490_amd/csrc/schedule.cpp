@@ -290,15 +290,16 @@ namespace {
 // step of a half item takes 0.6 to 0.85 of a whole item's (each tile is copied for half the rows), so halves pay when the
 // heaviest item is what the pass waits for: when it is at least twice as long as the work per slot (two workgroups per compute
 // unit), six steps of prologue and stores per half item included; and when it is long enough for what the halves cost, which
-// is more once there are more of them than compute units (above 128 items).  Measured, forward and dQ pass, whole -> halves (us):
+// grows with their number (above 128 items there are more of them than compute units).  Measured, forward and dQ pass, whole -> halves (us):
 // heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot 187 -> 145, 213 -> 131; 93 steps,
 // 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 251 steps, 156 per slot 336 -> 376, 450 -> 445; 8 x
 // 2048, 32 heads 304 -> 425, 450 -> 534; and 2 steps, 128 items 11.6 -> 13.2, 8 steps, 192 items 17.2 -> 19.7, 20.2 -> 21.3; at tile
 // width 64 the latter 9.9 -> 12.2 and 13.4 -> 17.0.  Of 201 packs at three widths, measured in either form, none that
 // this rule halves takes more than 1.02 of its time whole; the halved forwards take 0.89 on average, the dQ passes 0.81.
 bool split_rows(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim) {
-    const double workgroups = 512.0, heaviest = (double)load.heaviest, crowd = std::max(0.0, (double)slots - 128.0);
-    const double least = kind == HSPMD_LIST_FWD ? (head_dim <= 64 ? 8 : 6) + 0.1 * crowd : crowd > 0 ? 8 + 0.05 * crowd : 2;
+    const double workgroups = 512.0, heaviest = (double)load.heaviest, items = (double)slots;
+    const double least = kind == HSPMD_LIST_FWD ? std::max(5.0, (head_dim <= 64 ? 6 : 5) + 0.08 * (items - 96))
+                                                : items > 128 ? 8 + 0.05 * (items - 128) : 2;
     const double per_slot = ((double)load.total + 6.0 * 2.0 * (double)slots) / workgroups;
     return heaviest + 6.0 >= 2.0 * per_slot && heaviest >= least;
 }

@@ -92,11 +92,10 @@ class _Features:
             self.halves = max(0.68 * heaviest + 8, (full * total + 16 * n) / 256 + tail) < 0.9 * whole
             per_unit = 2 if narrow and not self.halves else 1
         else:
-            crowd = max(0, n - 128)
             if kind == A.LIST_FWD:
-                least = (8 if narrow else 6) + 0.1 * crowd
+                least = max(5, (6 if narrow else 5) + 0.08 * (n - 96))
             else:
-                least = 8 + 0.05 * crowd if crowd else 2
+                least = 8 + 0.05 * (n - 128) if n > 128 else 2
             self.halves = heaviest + 6 >= 2 * (total + 12 * n) / 512 and heaviest >= least
             per_unit = 3 if narrow and kind == A.LIST_DQ else 2
         self.slots = 32.0 * per_unit

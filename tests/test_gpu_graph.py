@@ -6,6 +6,7 @@ eager work and synchronisations between the replays."""
 import numpy as np
 import pytest
 
+from dispatch_packs import PERSISTENT_PACKS
 from gpu_util import make_case, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -16,11 +17,13 @@ def _bits(t):
     return t.contiguous().view(torch.int32 if t.element_size() == 4 else torch.int16).cpu().numpy()
 
 
+@pytest.mark.parametrize("lengths,hq,hkv", [([700, 45, 260, 1, 129], 4, 2), PERSISTENT_PACKS[-1][:3]])
 @pytest.mark.parametrize("rope", [False, True])
-def test_graph_replays_match_eager_calls(rope):
+def test_graph_replays_match_eager_calls(rope, lengths, hq, hkv):
+    """The second pack's dK/dV pass draws its items from counters, as every forward does: a replay must find them at zero."""
     import torch
     import paper_2504_20490_amd as A
-    lengths, hq, hkv, d = [700, 45, 260, 1, 129], 4, 2, 128
+    d = 128
     T = sum(lengths)
     cu, _, _ = A.build_cu_seqlens(lengths)
     plan = A.Plan(cu, hq, hkv, d)                        # plans are made outside the capture: creating one allocates
