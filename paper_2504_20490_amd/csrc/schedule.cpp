@@ -290,12 +290,13 @@ namespace {
 // step of a half item takes 0.6 to 0.85 of a whole item's (each tile is copied for half the rows), so halves pay when the
 // heaviest item is what the pass waits for: when it is at least twice as long as the work per slot (two workgroups per compute
 // unit), six steps of prologue and stores per half item included; and when it is long enough for what the halves cost, which
-// grows with their number (above 128 items there are more of them than compute units).  Measured, forward and dQ pass, whole -> halves (us):
-// heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot 187 -> 145, 213 -> 131; 93 steps,
-// 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 251 steps, 156 per slot 336 -> 376, 450 -> 445; 8 x
-// 2048, 32 heads 304 -> 425, 450 -> 534; and 2 steps, 128 items 11.6 -> 13.2, 8 steps, 192 items 17.2 -> 19.7, 20.2 -> 21.3; at tile
-// width 64 the latter 9.9 -> 12.2 and 13.4 -> 17.0.  Of 201 packs at three widths, measured in either form, none that
-// this rule halves takes more than 1.02 of its time whole; the halved forwards take 0.89 on average, the dQ passes 0.81.
+// grows with their number (above 128 items there are more of them than compute units).  Measured, forward and dQ pass, whole
+// -> halves (us): heaviest item 32 steps, 4 per slot (136 items) 36.7 -> 27.8, 43.5 -> 29.3; 220 steps, 26 per slot 187 ->
+// 145, 213 -> 131; 93 steps, 30 per slot 94 -> 83, 121 -> 104; but 42 steps, 28 per slot 75 -> 83, 98 -> 105; 251 steps, 156
+// per slot 336 -> 376, 450 -> 445; 8 x 2048, 32 heads 304 -> 425, 450 -> 534; and 2 steps, 128 items 11.6 -> 13.2, 8 steps,
+// 192 items 17.2 -> 19.7, 20.2 -> 21.3; at tile width 64 the latter 9.9 -> 12.2 and 13.4 -> 17.0.  Of 201 packs at three
+// widths, measured in either form, none that this rule halves takes more than 1.02 of its time whole; the halved forwards take
+// 0.89 on average, the dQ passes 0.81.
 bool split_rows(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim) {
     const double workgroups = 512.0, heaviest = (double)load.heaviest, items = (double)slots;
     const double least = kind == HSPMD_LIST_FWD ? std::max(5.0, (head_dim <= 64 ? 6 : 5) + 0.08 * (items - 96))
@@ -304,16 +305,16 @@ bool split_rows(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32
     return heaviest + 6.0 >= 2.0 * per_slot && heaviest >= least;
 }
 
-// Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass
-// takes as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs
-// 0.68 of the whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy
-// every Q / dO tile, and an item costs about eight steps beside its tiles.  At tile width 64, where two whole items share a unit but
-// halves do not, a full chip takes 1.6 for the halves; and with more halves than units a quarter of a half item is lost at the end.
+// Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass takes
+// as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs 0.68 of the
+// whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy every Q / dO
+// tile, and an item costs about eight steps beside its tiles.  At tile width 64, where two whole items share a unit but halves
+// do not, a full chip takes 1.6 for the halves; and with more halves than units a quarter of a half item is lost at the end.
 // Measured, whole and split (us): heaviest item 32 steps, 8.5 per slot (2 sequences, 8 heads) 50 and 41; 60 steps, 16 per slot
-// (8 KV heads of 4) 85 and 61; 238 steps, 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and 321;
-// 3 steps, 168 items 17 and 23; 8 x 2048, 32 heads 652 and 826; 10 x 512, 4 heads (160 items) 22.9 and 30.1; width 64, one document
-// of 16384 tokens, 2 heads 216 and 229.  Of the same packs none that this rule halves takes more than 1.01 of its time whole,
-// 0.85 on average.
+// (8 KV heads of 4) 85 and 61; 238 steps, 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and
+// 321; 3 steps, 168 items 17 and 23; 8 x 2048, 32 heads 652 and 826; 10 x 512, 4 heads (160 items) 22.9 and 30.1; width 64,
+// one document of 16384 tokens, 2 heads 216 and 229.  Of the same packs none that this rule halves takes more than 1.01 of its
+// time whole, 0.85 on average.
 bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
     const double heaviest = (double)load.heaviest, total = (double)load.total, items = (double)slots;
     const double units = 256.0;   // compute units; whole items of tile width 64 fit a unit twice
@@ -325,14 +326,16 @@ bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
 }
 
 // Whether the dK/dV pass draws its items in persistent workgroups (tile width 128, whole items, packed plans): at least 1024
-// slots, between 3.2 and 6 steps per slot on average, 9 at head_dim up to 112, and no item that alone takes most of the pass.  One workgroup fits a compute unit there, so
-// the time between two of them is exposed, most of all, by the measurements, where chains of two, four or eight items bring heavy
-// and light items up in step with the order in which an XCD hands its workgroups out.  Against that, the next item's loads
-// wait for the last one's stores inside a workgroup, which short items feel, and the compiler's schedule of the tile loop is 2-4 %
-// slower in an item loop, which long ones feel.  Measured, one workgroup per item and persistent (us, head_dim 128): 33 x 400
-// tokens, 16 heads (4 steps) 179 and 148; 78 x 512, 16 heads (5) 442 and 390; 67 x 300, 8 heads (3) 98 and 105; 43 x 64, 24 heads
-// (1) 47 and 52; 18 sequences of up to 2734, 16 heads (9.9) 164 and 174; 5 x 1300, 24 heads (11) 140 and 153; 438 sequences, one of 3026, one head (5, the longest 48) 72 and 79;
-// head_dim 104, 7 x 1024, 40 heads (9) 247 and 233.  Over 114 packs at three widths persistent workgroups take 0.77 to 1.02 of the time, 0.93 on average.
+// slots, between 3.2 and 6 steps per slot on average, 9 at head_dim up to 112, and no item that alone takes most of the pass.
+// One workgroup fits a compute unit there, so the time between two of them is exposed, most of all, by the measurements, where
+// chains of two, four or eight items bring heavy and light items up in step with the order in which an XCD hands its
+// workgroups out.  Against that, the next item's loads wait for the last one's stores inside a workgroup, which short items
+// feel, and the compiler's schedule of the tile loop is 2-4 % slower in an item loop, which long ones feel.  Measured, one
+// workgroup per item and persistent (us, head_dim 128): 33 x 400 tokens, 16 heads (4 steps) 179 and 148; 78 x 512, 16 heads
+// (5) 442 and 390; 67 x 300, 8 heads (3) 98 and 105; 43 x 64, 24 heads (1) 47 and 52; 18 sequences of up to 2734, 16 heads
+// (9.9) 164 and 174; 5 x 1300, 24 heads (11) 140 and 153; 438 sequences, one of 3026, one head (5, the longest 48) 72 and 79;
+// head_dim 104, 7 x 1024, 40 heads (9) 247 and 233.  Over 114 packs at three widths persistent workgroups take 0.77 to 1.02 of
+// the time, 0.93 on average.
 bool short_items(const PassLoad& load, int64_t slots, int32_t head_dim) {
     const double per_unit = (double)(load.total + 8 * slots) / 256.0;
     return slots >= 4 * 256 && 5 * load.total > 16 * slots && load.total <= (head_dim > 112 ? 6 : 9) * slots &&
