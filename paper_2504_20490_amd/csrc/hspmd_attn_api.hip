@@ -19,22 +19,17 @@
 
 namespace hspmd {
 
-// compute units of the current device (queried once per device)
+// compute units of the current device (queried once per device; a launch path, so it neither allocates nor throws)
 int persistent_grid(int64_t num_items, int per_cu) {
-    static std::mutex mutex;
-    static std::map<int, int> compute_units;
+    constexpr int kDevices = 64;
+    static std::atomic<int> compute_units[kDevices];   // 0: not asked yet
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
-    int cus = 0;
-    {
-        std::lock_guard<std::mutex> lock(mutex);
-        auto it = compute_units.find(dev);
-        if (it == compute_units.end()) {
-            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 0;
-            compute_units[dev] = cus;
-        } else {
-            cus = it->second;
-        }
+    const bool kept = dev >= 0 && dev < kDevices;
+    int cus = kept ? compute_units[dev].load(std::memory_order_relaxed) : 0;
+    if (cus <= 0) {
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 0;
+        if (kept) compute_units[dev].store(cus, std::memory_order_relaxed);
     }
     // a multiple of the queue count, like the list length
     const int64_t resident = (int64_t)(cus * per_cu / kNumXcd) * kNumXcd;
