@@ -124,10 +124,15 @@ __device__ __forceinline__ bf16x8 lds_read_tr(const char* lds, int a0, int a1) {
 //   tile and the position is part of the addresses.
 // dkey = my_key - (first row of block i) - 4 * (lane / 32): element e of an accumulator fragment is a
 // masked (row < key) pair iff 8 * (e / 4) + e % 4 < dkey.
-// SPREAD: the iteration also issues its share of the copies of a later tile (`load`), one instruction at a
-// time at fixed places among its LDS reads (the copies are ordered against LDS accesses, the reads are tied
-// to the MFMAs by the scheduling hints): pieces 0-3 in the first iteration of a tile, 4-8 in the second; all of them
-// when a tile has one iteration (!WHOLE).
+// SPREAD: the iteration also issues its share of the copies of a later tile (`load`), one instruction at a time.
+//
+// Both phases are written MFMA step by MFMA step: a step issues its MFMA, two or three LDS reads, a share of the exp / multiply
+// work and at most one copy, and ends in a scheduling barrier.  With one wave per SIMD the order of the instruction stream is
+// what overlaps, and left to scheduling hints it depended on what surrounded the loop: inside a loop over items one phase's 16
+// LDS reads ended up behind its MFMAs.  Against the hints (us): half items of 2 sequences, 8 heads 40.6 -> 38.1; blocks of a
+// ring of four over 32768 tokens, 24 heads 361.7 -> 345.4 each; 8 x 4096, 16 heads, head_dim 104 1026 -> 1005; long packs, which
+// the power limit decides, unchanged.  Tile width 64 has two waves per SIMD, which cover each other, and less MFMA work per
+// score: there the compiler orders each phase by a hint (short sequences 68.8 us against 70.2 step by step).
 template <int D, int KD, int RB, bool MASK, bool SPREAD, bool WHOLE>
 __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D, KD>& ahead,
                                               const DkvAddr<D, KD>& cur, int dkey, float c, const DkvTileLoad<D>& load) {
@@ -135,88 +140,117 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
     constexpr int KK = G::KK, DB = G::DB, K1 = G::K1;
     constexpr int NRB = RB ^ 1;
     constexpr int CUR = WHOLE ? RB : 0, AHEAD = WHOLE ? NRB : 0;   // positions of blocks i and i+1 beyond the addresses
-    constexpr int P0 = RB == 0 ? 0 : 4;   // first piece of this iteration (WHOLE)
-
-    // element e of an accumulator fragment -> packed bf16 pair index; one half = 8 elements = one B operand
-    auto softmax_half = [&](int half, u32x4& pw, u32x4& dw) {
+    constexpr int NA = 2 * KK, NB = 2 * K1;                        // MFMA steps of the two phases
+    constexpr bool kSteps = D == 128;
+    // this iteration's share of the copies, spread evenly over its steps
+    constexpr int kAll = DkvTileLoad<D>::kPieces;
+    constexpr int kFirstPiece = WHOLE && RB == 1 ? kAll / 2 : 0;
+    constexpr int kPieces = !SPREAD ? 0 : !WHOLE ? kAll : RB == 0 ? kAll / 2 : kAll - kAll / 2;
+    auto copies = [&](int step) {
+        if constexpr (kPieces > 0) {
 #pragma unroll
-        for (int e = 8 * half; e < 8 * half + 8; e += 2) {
-            float p0 = fast_exp2(st.s[RB][e] * c);
-            float p1 = fast_exp2(st.s[RB][e + 1] * c);
-            if (MASK && (8 * (e >> 2) + (e & 3) < dkey)) p0 = 0.f;
-            if (MASK && (8 * ((e + 1) >> 2) + ((e + 1) & 3) < dkey)) p1 = 0.f;
-            pw[(e >> 1) & 3] = pack_bf16(p0, p1);
-            dw[(e >> 1) & 3] = pack_bf16(p0 * st.dp[RB][e], p1 * st.dp[RB][e + 1]);
+            for (int x = 0; x < kPieces; ++x)
+                if ((2 * x + 1) * (NA + NB) / (2 * kPieces) == step) load.piece_at(kFirstPiece + x);
         }
     };
 
-    // ================= phase A =================
-    // statistics of block i+1 straight into its accumulators: rows 8 j + 4 (lane / 32) .. + 3 in registers 4 j .. 4 j + 3
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(lds + ahead.st + AHEAD * 128 + i4 * 32);
-        const f32x4 b = *reinterpret_cast<const f32x4*>(lds + ahead.st + AHEAD * 128 + i4 * 32 + 256);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { st.s[NRB][4 * i4 + j] = a[j]; st.dp[NRB][4 * i4 + j] = b[j]; }
-    }
-#pragma unroll
-    for (int kk = 0; kk < K1; ++kk) {
-        st.qf[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes);
-        st.dof[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes + G::kTileBytes);
-        if constexpr (SPREAD && !WHOLE) {
-            if (kk % 2 == 0) load.piece_at(kk / 2);
-        } else if constexpr (SPREAD) {
-            if (kk == KK / 4 - 1) load.template piece<P0>();
-            if (kk == 3 * KK / 4 - 1) load.template piece<P0 + 1>();
+    // The exp / multiply work of half a block (8 elements, one B operand of P and one of dS): four pairs, four shares each.  An
+    // empty statement on a share's results keeps it in its step: nothing else needs them before the end of the phase.
+    u32x4 pw, dw;
+    float p0 = 0.f, p1 = 0.f, d0 = 0.f;
+    auto share = [&](int half, int x) {
+        const int e = 8 * half + x / 4 * 2, w = x / 4;
+        if (x % 4 == 0) {
+            p0 = st.s[RB][e] * c;
+            p1 = st.s[RB][e + 1] * c;
+            if constexpr (kSteps) asm volatile("" : "+v"(p0), "+v"(p1));
+        } else if (x % 4 == 1) {
+            p0 = fast_exp2(p0);
+            p1 = fast_exp2(p1);
+            if constexpr (kSteps) asm volatile("" : "+v"(p0), "+v"(p1));
+        } else if (x % 4 == 2) {
+            if (MASK && (8 * (e >> 2) + (e & 3) < dkey)) p0 = 0.f;
+            if (MASK && (8 * ((e + 1) >> 2) + ((e + 1) & 3) < dkey)) p1 = 0.f;
+            uint32_t pair = pack_bf16(p0, p1);
+            d0 = p0 * st.dp[RB][e];
+            if constexpr (kSteps) asm volatile("" : "+v"(pair), "+v"(d0));
+            pw[w] = pair;
+        } else {
+            uint32_t pair = pack_bf16(d0, p1 * st.dp[RB][e + 1]);
+            if constexpr (kSteps) asm volatile("" : "+v"(pair));
+            dw[w] = pair;
         }
-    }
-    // G2(i-1)
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-        const int tt = kk / DB, db = kk % DB;
-        st.dv[db] = mfma(st.dotf[kk], st.pprev[tt], st.dv[db]);
-        st.dk[db] = mfma(st.qtf[kk], st.dsprev[tt], st.dk[db]);
-    }
-    u32x4 pw0, dw0;
-    softmax_half(0, pw0, dw0);
-    // per MFMA: LDS reads (8 statistics + 2*KK fragments in all) and a share of the VALU work
-    InterleaveHint<2 * KK, 2, (MASK ? 4 : 3), 0, 0x402>::apply();
-    __builtin_amdgcn_sched_barrier(0);
+    };
+    auto end_step = [] {
+        if constexpr (kSteps) __builtin_amdgcn_sched_barrier(0);
+    };
 
-    // ================= phase B =================
-    union { u32x4 u; bf16x8 v; } cv;
-    cv.u = pw0; st.pprev[0] = cv.v;
-    cv.u = dw0; st.dsprev[0] = cv.v;
+    // ================= phase A: G2(i-1); reads of block i+1 =================
+    // the statistics go straight into the accumulators: rows 8 j + 4 (lane / 32) .. + 3 in registers 4 j .. 4 j + 3
+    auto read_ahead = [&](int r) {
+        if (r < 8) {
+            const int i4 = r / 2;
+            const f32x4 a = *reinterpret_cast<const f32x4*>(lds + ahead.st + AHEAD * 128 + i4 * 32 + (r & 1) * 256);
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            const int off = (CUR * 2 + tt) * 16 * D * 2;   // 16 tile rows per k-step
-            st.qtf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off, cur.tr[db][1] + off);
-            st.dotf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off + G::kTileBytes, cur.tr[db][1] + off + G::kTileBytes);
-            if constexpr (SPREAD && !WHOLE) {
-                static_assert((K1 + 1) / 2 + KK >= DkvTileLoad<D>::kPieces, "a place for every piece");
-                load.piece_at((K1 + 1) / 2 + tt * DB + db);
-            } else if constexpr (SPREAD) {
-                if (tt == 0 && db == DB - 1) load.template piece<P0 + 2>();
-                if (tt == 1 && db == DB / 2 - 1) load.template piece<P0 + 3>();
-                if (RB == 1 && tt == 1 && db == DB - 1) load.template piece<P0 + 4>();
+            for (int j = 0; j < 4; ++j) {
+                if (r & 1) st.dp[NRB][4 * i4 + j] = a[j];
+                else st.s[NRB][4 * i4 + j] = a[j];
             }
+        } else {
+            const int kk = (r - 8) / 2;
+            if (r & 1) st.dof[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes + G::kTileBytes);
+            else st.qf[kk] = lds_read128(lds, ahead.rm[kk] + AHEAD * G::kBlockBytes);
         }
-    // G1(i+1) on top of the statistics
-    // the two accumulation chains alternate: an MFMA that continues a chain does not follow its predecessor directly
+    };
+    constexpr int kReadsA = 8 + 2 * K1;
+    static_assert(kReadsA <= 2 * NA, "two reads a step");
 #pragma unroll
-    for (int kk = 0; kk < K1; ++kk) {
-        st.s[NRB] = mfma(st.qf[kk], st.kf[kk], st.s[NRB]);
-        st.dp[NRB] = mfma(st.dof[kk], st.vf[kk], st.dp[NRB]);
+    for (int n = 0; n < NA; ++n) {
+        const int kk = n / 2, tt = kk / DB, db = kk % DB;
+        if (n % 2 == 0) st.dv[db] = mfma(st.dotf[kk], st.pprev[tt], st.dv[db]);
+        else st.dk[db] = mfma(st.qtf[kk], st.dsprev[tt], st.dk[db]);
+#pragma unroll
+        for (int r = 2 * n; r < 2 * n + 2; ++r)
+            if (r < kReadsA) read_ahead(r);
+#pragma unroll
+        for (int x = n * 16 / NA; x < (n + 1) * 16 / NA; ++x) share(0, x);
+        copies(n);
+        end_step();
     }
-    u32x4 pw1, dw1;
-    softmax_half(1, pw1, dw1);
-    cv.u = pw1; st.pprev[1] = cv.v;
-    cv.u = dw1; st.dsprev[1] = cv.v;
-    // per MFMA: a share of the 4 * KK transpose reads (2 each, 3 when the phase has fewer MFMAs), VALU share
-    InterleaveHint<2 * K1, (K1 == KK ? 2 : 3), (MASK ? 4 : 3), 1, 0x402>::apply();
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!kSteps) {
+        // per MFMA: LDS reads and a share of the VALU work
+        InterleaveHint<NA, 2, (MASK ? 4 : 3), 0, 0x402>::apply();
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // ================= phase B: G1(i+1) on top of the statistics; transpose reads of block i =================
+    union { u32x4 u; bf16x8 v; } cv;
+    cv.u = pw; st.pprev[0] = cv.v;
+    cv.u = dw; st.dsprev[0] = cv.v;
+    auto read_back = [&](int r) {
+        const int kk = r / 2, tt = kk / DB, db = kk % DB;
+        const int off = (CUR * 2 + tt) * 16 * D * 2;   // 16 tile rows per k-step
+        if (r % 2 == 0) st.dotf[kk] = lds_read_tr<D>(lds, cur.tr[db][0] + off + G::kTileBytes, cur.tr[db][1] + off + G::kTileBytes);
+        else st.qtf[kk] = lds_read_tr<D>(lds, cur.tr[db][0] + off, cur.tr[db][1] + off);
+    };
+    // the two accumulation chains in turn: an MFMA that continues a chain does not follow its predecessor directly
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        if (n % 2 == 0) st.s[NRB] = mfma(st.qf[n / 2], st.kf[n / 2], st.s[NRB]);
+        else st.dp[NRB] = mfma(st.dof[n / 2], st.vf[n / 2], st.dp[NRB]);
+#pragma unroll
+        for (int r = n * 2 * KK / NB; r < (n + 1) * 2 * KK / NB; ++r) read_back(r);
+#pragma unroll
+        for (int x = n * 16 / NB; x < (n + 1) * 16 / NB; ++x) share(1, x);
+        copies(NA + n);
+        end_step();
+    }
+    if constexpr (!kSteps) {
+        InterleaveHint<NB, 2, (MASK ? 4 : 3), 1, 0x402>::apply();
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    cv.u = pw; st.pprev[1] = cv.v;
+    cv.u = dw; st.dsprev[1] = cv.v;
 }
 
 }  // namespace
@@ -438,7 +472,9 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     // `load` arrives pointing at the first rows of tile qt - 3 of the head and leaves pointing one tile lower.
     auto tile_step_spread = [&](int u, int qt, DkvTileLoad<D>& load, auto par) {
         constexpr int kPar = decltype(par)::value;
-        if (u > 0) {
+        // the copies that a trip begins with: under its first MFMA, not in front of its barrier
+        if constexpr (!SPLIT && D == 128) asm volatile("" : "+a"(st.s[0]), "+a"(st.dp[0]));
+        if (kPar == 1 || u > 0) {
             wait_tile_loads_except<kLoadsPerTile>();   // u + 2 < n_tiles here
             __syncthreads();
         }
@@ -487,7 +523,10 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
             load.stat = ((wave & 1) == 0 ? p.nlse : p.negd) + (int64_t)hq * p.total_tokens + row;
             load.wave = wave;
             load.lane = lane;
-            if constexpr (SPLIT) {
+            if constexpr (SPLIT || D == 128) {
+                // Two tiles a trip.  Whole items: S' and dP' of a tile's first block, which come out of the tile before, are copied from
+                // accumulation registers to vector registers in one go where a trip begins, and one by one under the MFMAs inside it
+                // (8 x 2048, 32 heads 692.7 -> 687.3 us, the pack of 32768 tokens 2584 -> 2561 us)
                 for (; j > n_general; j -= 2, u += 2) {
                     tile_step_spread(u, first_qt + j, load, Even{});
                     tile_step_spread(u + 1, first_qt + j - 1, load, Odd{});
