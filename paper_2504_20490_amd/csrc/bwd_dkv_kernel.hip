@@ -129,9 +129,9 @@ __device__ __forceinline__ bf16x8 lds_read_tr(const char* lds, int a0, int a1) {
 // Both phases are written MFMA step by MFMA step: a step issues its MFMA, two or three LDS reads, a share of the exp / multiply
 // work and at most one copy, and ends in a scheduling barrier.  With one wave per SIMD the order of the instruction stream is
 // what overlaps, and left to scheduling hints it depended on what surrounded the loop: inside a loop over items one phase's 16
-// LDS reads ended up behind its MFMAs.  Against the hints (us): half items of 2 sequences, 8 heads 40.6 -> 38.1; blocks of a
-// ring of four over 32768 tokens, 24 heads 361.7 -> 345.4 each; 8 x 4096, 16 heads, head_dim 104 1026 -> 1005; long packs, which
-// the power limit decides, unchanged.  Tile width 64 has two waves per SIMD, which cover each other, and less MFMA work per
+// LDS reads ended up behind its MFMAs.  Against the hints (us, sustained): half items of 2 sequences, 8 heads 36.9 -> 33.8; blocks
+// of a ring of four over 32768 tokens, 24 heads 350 -> 338 each; 8 x 4096, 16 heads, head_dim 104 1000 -> 974; long packs, which
+// the power limit decides, unchanged.  The exp work is spread evenly: in the first 12 of 16 steps it takes 5 % longer.  Tile width 64 has two waves per SIMD, which cover each other, and less MFMA work per
 // score: there the compiler orders each phase by a hint (short sequences 68.8 us against 70.2 step by step).
 template <int D, int KD, int RB, bool MASK, bool SPREAD, bool WHOLE>
 __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D, KD>& ahead,
@@ -441,7 +441,14 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     // one: the ~400 live registers then meet at a join once per head, not once per iteration.
     int stage = 0;   // stage of tile u
     DkvTileLoad<D> no_load{};
-    // `par` (SPLIT, where a tile is one iteration): the accumulator pair that holds the tile's S' / dP'
+    // S' and dP' of a tile's first block come out of the matrix core in the tile before.  Told nothing, the compiler copies all 32 of
+    // them to vector registers where a loop or a branch begins; held in accumulation registers up to here (an empty statement),
+    // they are copied one by one under the MFMAs of the steps that use them.
+    auto hold_in_acc = [&] {
+        if constexpr (!SPLIT && D == 128) asm volatile("" : "+a"(st.s[0]), "+a"(st.dp[0]));
+    };
+    // `par`: SPLIT, where a tile is one iteration: the accumulator pair that holds the tile's S' / dP'.  Otherwise, 0 for the item's
+    // first tile, 1 for the first and 2 for the second tile of a trip
     auto tile_step = [&](int u, int qt, auto masked, auto par) {
         constexpr bool kMask = decltype(masked)::value;
         constexpr int kPar = decltype(par)::value;
@@ -457,6 +464,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
         const int to_next = (stage1 - stage) * G::kStageBytes;
         const DkvAddr<D, KD> next = shifted(off, u + 1 < n_tiles ? to_next : 0);
         const int dkey0 = my_key - shift - qt * BQ - row_block * 32 - 4 * hh;
+        hold_in_acc();
         if constexpr (SPLIT) {
             dkv_iteration<D, KD, kPar, kMask, false, false>(st, lds, next, off, dkey0, c, no_load);
         } else {
@@ -472,9 +480,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     // `load` arrives pointing at the first rows of tile qt - 3 of the head and leaves pointing one tile lower.
     auto tile_step_spread = [&](int u, int qt, DkvTileLoad<D>& load, auto par) {
         constexpr int kPar = decltype(par)::value;
-        // the copies that a trip begins with: under its first MFMA, not in front of its barrier
-        if constexpr (!SPLIT && D == 128) asm volatile("" : "+a"(st.s[0]), "+a"(st.dp[0]));
-        if (kPar == 1 || u > 0) {
+        if constexpr (kPar < 2) hold_in_acc();
+        if (kPar >= 1 || u > 0) {
             wait_tile_loads_except<kLoadsPerTile>();   // u + 2 < n_tiles here
             __syncthreads();
         }
@@ -509,6 +516,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     // SPLIT: tiles are walked in pairs, one per accumulator pair; after a single tile the pairs change places
     using Even = std::integral_constant<int, 0>;
     using Odd = std::integral_constant<int, 1>;
+    using Second = std::integral_constant<int, 2>;
     auto swap_pairs = [&] { st.s[0] = st.s[1]; st.dp[0] = st.dp[1]; };
     for (int h = 0, u = 0; h < p.group; ++h) {
         int j = per_head - 1;
@@ -523,15 +531,29 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
             load.stat = ((wave & 1) == 0 ? p.nlse : p.negd) + (int64_t)hq * p.total_tokens + row;
             load.wave = wave;
             load.lane = lane;
-            if constexpr (SPLIT || D == 128) {
-                // Two tiles a trip.  Whole items: S' and dP' of a tile's first block, which come out of the tile before, are copied from
-                // accumulation registers to vector registers in one go where a trip begins, and one by one under the MFMAs inside it
-                // (8 x 2048, 32 heads 692.7 -> 687.3 us, the pack of 32768 tokens 2584 -> 2561 us)
+            if constexpr (!SPLIT && D == 128) {
+                // Two tiles a trip, in one basic block: a conditional barrier in it, or one tile a trip, gathers the copies of S' and
+                // dP' (see hold_in_acc) where the block begins, with no MFMA beside them.  8 x 2048, 32 heads 639 -> 610 us against
+                // 623, the pack of 32768 tokens 2563 -> 2564 against 2604; four tiles a trip 623 and 2595 (7 KB of code more to fetch).
+                if (u == 0) {
+                    tile_step_spread(u, first_qt + j, load, Even{});
+                    --j, ++u;
+                }
+                for (; j > n_general; j -= 2, u += 2) {
+                    tile_step_spread(u, first_qt + j, load, Odd{});
+                    tile_step_spread(u + 1, first_qt + j - 1, load, Second{});
+                }
+                if (j >= n_general) {
+                    tile_step_spread(u, first_qt + j, load, Odd{});
+                    --j, ++u;
+                }
+            } else if constexpr (SPLIT) {
                 for (; j > n_general; j -= 2, u += 2) {
                     tile_step_spread(u, first_qt + j, load, Even{});
                     tile_step_spread(u + 1, first_qt + j - 1, load, Odd{});
                 }
             }
+            if constexpr (SPLIT || D == 64)
             for (; j >= n_general; --j, ++u) {
                 tile_step_spread(u, first_qt + j, load, Even{});
                 if constexpr (SPLIT) swap_pairs();
@@ -630,9 +652,11 @@ hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool sp
         if constexpr (D == 128) {
             if (!block && p.persist) {
                 const int workgroups = persistent_grid(num_items, 1);
-                if (workgroups <= 0) return hipErrorInvalidDevice;
-                hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, true>), dim3((unsigned)workgroups), threads, 0, stream, p);
-                return hipGetLastError();
+                if (workgroups > 0) {
+                    hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, true>), dim3((unsigned)workgroups), threads, 0, stream, p);
+                    return hipGetLastError();
+                }
+                if (p.persist == 1) return hipErrorInvalidDevice;
             }
         }
         if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false>), grid, threads, 0, stream, p);

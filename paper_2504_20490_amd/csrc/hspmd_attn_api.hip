@@ -597,7 +597,8 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DKV];
     const hspmd::Dispatch dkv = plan_dispatch(plan, HSPMD_LIST_DKV);
     p.split = dkv == hspmd::Dispatch::kHalves ? 1 : 0;
-    p.persist = dkv == hspmd::Dispatch::kPersistent ? 1 : 0;
+    p.persist = dkv == hspmd::Dispatch::kPersistent ? 1
+                : hspmd::persistent_dkv(dkv, plan->load[HSPMD_LIST_DKV], plan->count[HSPMD_LIST_DKV], p.group, plan->head_dim) ? 2 : 0;
     p.queue = plan->queue[HSPMD_LIST_DKV];
     auto dkv_pass = [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], false, s); };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();

@@ -350,6 +350,22 @@ Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots
     return !block && head_dim > 64 && short_items(load, slots, head_dim) ? Dispatch::kPersistent : Dispatch::kWhole;
 }
 
+// Items of one query head are drawn by persistent workgroups up to 48 steps (64 at head_dim up to 112), now that the instructions of
+// the tile loop do not depend on the loop around it: at least 1024 slots (four per compute unit), more than 3.2 steps per slot, no
+// item that alone takes most of the pass.  Measured, one workgroup per item and persistent (us, sustained): 8 x 2048, 32 heads (17
+// steps) 637 and 615; 4400 items of 512 tokens (5) 396 and 331, of 1024 (9) 462 and 426, of 1500 (13) 561 and 537; 8 x 4096, 16
+// heads, head_dim 104 (33) 1032 and 1006; 9 x 6887, 8 heads, head_dim 96 (55) 1312 and 1276; 16384 tokens, 32 heads (37) 1172 and
+// 1161.  Longer items gain nothing (32768 tokens, 24 heads, 58 steps, 2619 and 2620), items of several heads lose (65536 tokens, 32
+// heads on 8, a whole step 34263 and 34880), and so do few (536 items 291 and 298, 672 of 4 steps 41.7 and 42.3) and short ones
+// (2160 of 3 steps 142 and 144, 3136 of one tile 95 and 108).  Worst of 40 packs that the rule sends here: 1561 items, head_dim
+// 104 (6 steps) 131 and 134.
+bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim) {
+    if (form != Dispatch::kWhole || head_dim <= 64) return form == Dispatch::kPersistent;
+    const double per_unit = (double)(load.total + 8 * slots) / 256.0;
+    return group == 1 && slots >= 4 * 256 && 5 * load.total > 16 * slots && load.total <= (head_dim > 112 ? 48 : 64) * slots &&
+           (double)load.heaviest + 8 <= 0.8 * per_unit;
+}
+
 // ------------------------------------------------------------------------------ cost model
 // The paper's planner dispatches mixed-length sequences with a cost model evaluated on the CPU (Appendix
 // "Scenario-specific Planning", mixed-length case); this is the per-operator predictor for the attention kernels of this library.

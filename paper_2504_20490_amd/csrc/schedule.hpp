@@ -38,6 +38,8 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
 // plans; the forward is always persistent).  `slots`: length of the list, padding included.
 enum class Dispatch { kWhole, kHalves, kPersistent };
 Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim, bool block);
+// Whether the dK/dV pass of a packed plan draws its items in persistent workgroups: also where pass_dispatch says whole items.
+bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim);
 
 // ---- cost model: predicted kernel times (microseconds) of the three passes for a pack
 double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim);
