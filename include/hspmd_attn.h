@@ -164,7 +164,8 @@ hspmd_status hspmd_attn_schedule_ordered(hspmd_list_kind kind, hspmd_order order
  * plan needs a GPU: the lists are uploaded through a copy stream that the library owns (one per
  * device, created on first use) and the call waits for that upload only, never for `stream` or any
  * other work of the caller, so the plan of the next micro-batch can be built while the kernels of the
- * current one run.  The lists are in place when the call returns (`stream` is accepted and unused).
+ * current one run.  The lists are in place when the call returns (`stream` is accepted and unused).  (Short lists stay on the
+ * host, see hspmd_attn_plan_update.)
  *   local_q_heads   query heads held by this GPU (any positive count: an uneven share is fine)
  *   local_kv_heads  KV heads held by this GPU; local_q_heads % local_kv_heads must be 0
  *   head_dim        a multiple of 8 in 8..128 (rows move in 16-byte chunks).  The kernels are built for
@@ -190,6 +191,8 @@ hspmd_status hspmd_attn_plan_create_ordered(const int32_t* cu_seqlens_host, int3
  *   long ago once the ring has gone round), never for the device as a whole.  A slot that is too small is replaced
  *   by a larger one (hipFree + hipMalloc, with a quarter of headroom); packs of similar size therefore stop
  *   allocating after the first few refills.
+ *   Lists of up to 240 slots (120 of a block plan) take none of this: the plan keeps them on the host, every launch carries its
+ *   list among its arguments (a graph keeps the one it was captured with), nothing is uploaded and no event is recorded.
  *   Not for concurrent use: no other thread may launch with the plan during the call.  A launch recorded into a HIP
  *   graph records no event (events cannot be waited for from inside a capture): a plan that a graph replays must not be
  *   refilled while the graph may run.  On error the plan keeps its previous pack.

@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/hspmd_attn.h"
+#include "kernels.hpp"
 #include <stdint.h>
 
 namespace hspmd {
@@ -448,13 +449,34 @@ struct ItemGeom {
     int q_start, q_len, k_start, k_len, offset, tile, head;
     int q_pos;   // position of the chunk's first row inside its sequence (0 when !BLOCK); the key chunk's is q_pos - offset
 };
-template <bool BLOCK>
-__device__ __forceinline__ ItemGeom load_item(const hspmd_work_item* items, const hspmd_block_item* block_items, int idx) {
+// `idx` is the same in all lanes.  INLINE: the list is read where it lies, in the argument segment behind Params: as an object that
+// is indexed at run time the compiler would copy it to scratch memory first.
+template <bool BLOCK, bool INLINE, typename Params>
+__device__ __forceinline__ ItemGeom load_item(const Params& p, int idx) {
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    typedef const i32x4 __attribute__((address_space(4)))* ArgumentWords;
+    static_assert(alignof(Params) <= alignof(InlineList), "the list is the next argument, on its own alignment");
+    constexpr int kListAt = (int)((sizeof(Params) + alignof(InlineList) - 1) / alignof(InlineList));   // in units of 16 bytes
     if constexpr (BLOCK) {
-        const hspmd_block_item it = block_items[idx];
+        hspmd_block_item it;
+        if constexpr (INLINE) {
+            const ArgumentWords words = (ArgumentWords)__builtin_amdgcn_kernarg_segment_ptr() + kListAt;
+            const i32x4 a = words[2 * idx], b = words[2 * idx + 1];
+            it = hspmd_block_item{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        } else {
+            it = p.block_items[idx];
+        }
         return ItemGeom{it.q_start, it.q_len, it.k_start, it.k_len, it.offset, it.tile, it.head, it.q_pos};
     } else {
-        const hspmd_work_item it = items[idx];
+        hspmd_work_item it;
+        if constexpr (INLINE) {
+            const i32x4 a = ((ArgumentWords)__builtin_amdgcn_kernarg_segment_ptr() + kListAt)[idx];
+            it = hspmd_work_item{a[0], a[1], a[2], a[3]};
+            // four values of their own from here on: spilled as one group of four, they leave a stack object behind
+            asm volatile("" : "+s"(it.token_start), "+s"(it.seq_len), "+s"(it.tile), "+s"(it.head));
+        } else {
+            it = p.items[idx];
+        }
         return ItemGeom{it.token_start, it.seq_len, it.token_start, it.seq_len, 0, it.tile, it.head, 0};
     }
 }
@@ -479,8 +501,10 @@ struct ItemQueue {
         queue = blockIdx.x % kQueues;
         first_round = gridDim.x / kQueues;     // the grid is a multiple of kQueues: slots 0 .. gridDim.x-1 are taken
     }
-    // one thread per workgroup: the list index of the workgroup's next item (past the end when the queue is empty)
+    // one thread per workgroup: the list index of the workgroup's next item (past the end when the queue is empty, or when every
+    // slot has a workgroup of its own and there are no counters)
     __device__ __forceinline__ int draw() const {
+        if (counters == nullptr) return 0x7fffffff;
         const int k = __hip_atomic_fetch_add(counters + queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return (first_round + k) * kQueues + queue;
     }
@@ -490,6 +514,7 @@ struct ItemQueue {
         // every draw has been performed before the reset, and each workgroup's last draw has returned its value (the
         // workgroup acted on it) before this addition is issued.  Release and acquire at this scope write back and
         // invalidate caches of the whole XCD, once per workgroup that leaves, while others still compute.
+        if (counters == nullptr) return;
         asm volatile("" ::: "memory");
         const int gone = __hip_atomic_fetch_add(counters + kQueues, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (gone == (int)gridDim.x - 1) {

@@ -131,8 +131,9 @@ __device__ __forceinline__ bf16x8 lds_read_tr(const char* lds, int a0, int a1) {
 // what overlaps, and left to scheduling hints it depended on what surrounded the loop: inside a loop over items one phase's 16
 // LDS reads ended up behind its MFMAs.  Against the hints (us, sustained): half items of 2 sequences, 8 heads 36.9 -> 33.8; blocks
 // of a ring of four over 32768 tokens, 24 heads 350 -> 338 each; 8 x 4096, 16 heads, head_dim 104 1000 -> 974; long packs, which
-// the power limit decides, unchanged.  The exp work is spread evenly: in the first 12 of 16 steps it takes 5 % longer.  Tile width 64 has two waves per SIMD, which cover each other, and less MFMA work per
-// score: there the compiler orders each phase by a hint (short sequences 68.8 us against 70.2 step by step).
+// the power limit decides, unchanged.  The exp work is spread evenly: in the first 12 of 16 steps it takes 5 % longer.  Whole items of tile width 64 have two waves per SIMD, which
+// cover each other, and less MFMA work per score: there the compiler orders each phase by a hint (short sequences 68.8 us against
+// 70.2 step by step).
 template <int D, int KD, int RB, bool MASK, bool SPREAD, bool WHOLE>
 __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D, KD>& ahead,
                                               const DkvAddr<D, KD>& cur, int dkey, float c, const DkvTileLoad<D>& load) {
@@ -141,7 +142,7 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
     constexpr int NRB = RB ^ 1;
     constexpr int CUR = WHOLE ? RB : 0, AHEAD = WHOLE ? NRB : 0;   // positions of blocks i and i+1 beyond the addresses
     constexpr int NA = 2 * KK, NB = 2 * K1;                        // MFMA steps of the two phases
-    constexpr bool kSteps = D == 128;
+    constexpr bool kSteps = D == 128 || !WHOLE;
     // this iteration's share of the copies, spread evenly over its steps
     constexpr int kAll = DkvTileLoad<D>::kPieces;
     constexpr int kFirstPiece = WHOLE && RB == 1 ? kAll / 2 : 0;
@@ -265,8 +266,10 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
 // accumulator pairs of a key meet in LDS at the end, in one fixed order.
 //
 // PERSIST: the workgroup draws items from its queue until none is left (as the forward does), for packs of many short items.
-template <int D, bool BLOCK, int KD, bool SPLIT, bool PERSIST = false>
-__global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv_kernel(BwdParams p) {
+//
+// List: nothing, or InlineList when the work list is the second argument.
+template <int D, bool BLOCK, int KD, bool SPLIT, bool PERSIST, typename... List>
+__global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv_kernel(BwdParams p, List...) {
     static_assert(!PERSIST || (!BLOCK && !SPLIT), "whole items of packed plans only");
     using G = DkvGeom<D, KD>;
     constexpr int BKV = SPLIT ? kDkvKTile / 2 : kDkvKTile, BQ = kDkvQTile;
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     PersistentLoop<PERSIST> loop;
     loop.init(p.queue);
     do {
-    const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, slot);
+    const ItemGeom item = load_item<BLOCK, sizeof...(List) != 0>(p, slot);
     if (item.tile < 0) break;
     const int tid = threadIdx.x, lane = loop.item_lane();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -640,16 +643,16 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
 
 namespace {
 
-template <int D, int KD>
-hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream) {
+template <int D, int KD, typename... List>
+hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, hipStream_t stream, const List&... list) {
     const dim3 threads(kThreads);
-    if (split) {
+    if (p.split != 0) {
         const dim3 grid((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2));
-        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, true>), grid, threads, 0, stream, p);
-        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true>), grid, threads, 0, stream, p);
+        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, true, false, List...>), grid, threads, 0, stream, p, list...);
+        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true, false, List...>), grid, threads, 0, stream, p, list...);
     } else {
         const dim3 grid((unsigned)num_items);
-        if constexpr (D == 128) {
+        if constexpr (D == 128 && sizeof...(List) == 0) {   // (an inline list is too short for persistent workgroups)
             if (!block && p.persist) {
                 const int workgroups = persistent_grid(num_items, 1);
                 if (workgroups > 0) {
@@ -659,22 +662,27 @@ hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, bool sp
                 if (p.persist == 1) return hipErrorInvalidDevice;
             }
         }
-        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
-        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
+        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false, false, List...>), grid, threads, 0, stream, p, list...);
+        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, false, List...>), grid, threads, 0, stream, p, list...);
     }
     return hipGetLastError();
 }
 
+template <typename... List>
+hipError_t launch_dkv_width(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream, const List&... list) {
+    if (tile_width(head_dim) == 64) return launch_dkv<64, 4>(p, num_items, block, stream, list...);
+    if (contraction_steps(head_dim) <= 5) return launch_dkv<128, 5>(p, num_items, block, stream, list...);
+    if (contraction_steps(head_dim) == 6) return launch_dkv<128, 6>(p, num_items, block, stream, list...);
+    if (contraction_steps(head_dim) == 7) return launch_dkv<128, 7>(p, num_items, block, stream, list...);
+    return launch_dkv<128, 8>(p, num_items, block, stream, list...);
+}
+
 }  // namespace
 
-hipError_t launch_bwd_dkv(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
+hipError_t launch_bwd_dkv(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
-    const bool split = p.split != 0;
-    if (tile_width(head_dim) == 64) return launch_dkv<64, 4>(p, num_items, block, split, stream);
-    if (contraction_steps(head_dim) <= 5) return launch_dkv<128, 5>(p, num_items, block, split, stream);
-    if (contraction_steps(head_dim) == 6) return launch_dkv<128, 6>(p, num_items, block, split, stream);
-    if (contraction_steps(head_dim) == 7) return launch_dkv<128, 7>(p, num_items, block, split, stream);
-    return launch_dkv<128, 8>(p, num_items, block, split, stream);
+    return list ? launch_dkv_width(p, head_dim, num_items, block, stream, *list)
+                : launch_dkv_width(p, head_dim, num_items, block, stream);
 }
 
 }  // namespace hspmd

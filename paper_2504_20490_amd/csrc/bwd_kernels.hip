@@ -57,8 +57,9 @@ __global__ __launch_bounds__(kThreads) void bwd_dsum_kernel(BwdParams p) {
 // sequences of 32 .. 512 tokens, 16 heads: 55 -> 48 us; 8 x 2048, 32 heads: 244 -> 230 us.
 // SPLIT: a workgroup takes half an item, 64 rows; two waves share each 32-row block, one takes the first 32-key block of
 // every tile, the other the second, and their sums meet in LDS at the end (as in the forward).
-template <int D, bool BLOCK, int KD, bool SPLIT>
-__global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(BwdParams p) {
+// List: nothing, or InlineList when the work list is the second argument.
+template <int D, bool BLOCK, int KD, bool SPLIT, typename... List>
+__global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(BwdParams p, List...) {
     static_assert(KD >= 1 && KD <= D / 16, "k-steps inside the tile width");
     constexpr int BQ = SPLIT ? kFwdQTile / 2 : kFwdQTile, BK = kFwdKTile;
     constexpr int KK = KD, DB = (KD + 1) / 2;   // DB: 32-column blocks of dQ that hold data
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
     // workgroups p and p + 8 of 16 take the halves of an item, the second, which sees more keys, before the first
     const int slot = SPLIT ? (int)(blockIdx.x / (2 * kQueues)) * kQueues + (int)(blockIdx.x % kQueues) : (int)blockIdx.x;
     if (SPLIT && slot >= p.num_items) return;
-    const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, slot);
+    const ItemGeom item = load_item<BLOCK, sizeof...(List) != 0>(p, slot);
     if (item.tile < 0) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -404,25 +405,31 @@ hipError_t launch_bwd_dsum(const BwdParams& p, int head_dim, hipStream_t stream)
 
 namespace {
 
-template <int D, int KD>
-void launch_dq(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream) {
+template <int D, int KD, typename... List>
+void launch_dq(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream, const List&... list) {
     const dim3 grid((unsigned)(split ? (num_items + kQueues - 1) / kQueues * kQueues * 2 : num_items)), threads(kThreads);
-    if (block && split) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, true>), grid, threads, 0, stream, p);
-    else if (block) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
-    else if (split) hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, true>), grid, threads, 0, stream, p);
-    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
+    if (block && split) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, true, List...>), grid, threads, 0, stream, p, list...);
+    else if (block) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, false, List...>), grid, threads, 0, stream, p, list...);
+    else if (split) hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, true, List...>), grid, threads, 0, stream, p, list...);
+    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, false, List...>), grid, threads, 0, stream, p, list...);
+}
+
+template <typename... List>
+void launch_dq_width(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream, const List&... list) {
+    const bool split = p.split != 0;
+    if (tile_width(head_dim) == 64) launch_dq<64, 4>(p, num_items, block, split, stream, list...);
+    else if (contraction_steps(head_dim) <= 5) launch_dq<128, 5>(p, num_items, block, split, stream, list...);
+    else if (contraction_steps(head_dim) == 6) launch_dq<128, 6>(p, num_items, block, split, stream, list...);
+    else if (contraction_steps(head_dim) == 7) launch_dq<128, 7>(p, num_items, block, split, stream, list...);
+    else launch_dq<128, 8>(p, num_items, block, split, stream, list...);
 }
 
 }  // namespace
 
-hipError_t launch_bwd_dq(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
+hipError_t launch_bwd_dq(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
-    const bool split = p.split != 0;
-    if (tile_width(head_dim) == 64) launch_dq<64, 4>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) <= 5) launch_dq<128, 5>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) == 6) launch_dq<128, 6>(p, num_items, block, split, stream);
-    else if (contraction_steps(head_dim) == 7) launch_dq<128, 7>(p, num_items, block, split, stream);
-    else launch_dq<128, 8>(p, num_items, block, split, stream);
+    if (list) launch_dq_width(p, head_dim, num_items, block, stream, *list);
+    else launch_dq_width(p, head_dim, num_items, block, stream);
     return hipGetLastError();
 }
 

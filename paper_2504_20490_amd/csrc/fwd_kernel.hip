@@ -264,8 +264,9 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const cha
 // SPLIT: the unit of work is half an item, 64 rows; two waves share each 32-row block, one takes the first 32-key block of
 // every tile, the other the second, each with a running maximum and sum of its own, and their results meet in LDS at the
 // end.  Same copies and LDS per tile, half the products: for packs whose longest item outlasts the rest of the pass.
-template <int D, bool BLOCK, int KD, bool SPLIT>
-__global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
+// List: nothing, or InlineList when the work list is the second argument.
+template <int D, bool BLOCK, int KD, bool SPLIT, typename... List>
+__global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) {
     using G = FwdGeom<D, KD>;
     constexpr int BQ = SPLIT ? kFwdQTile / 2 : kFwdQTile, BK = kFwdKTile;
     constexpr int NB = SPLIT ? 1 : 2;
@@ -525,7 +526,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
     for (int turn = 0;; turn ^= 1) {
         const int list_slot = SPLIT ? slot / (2 * kQueues) * kQueues + slot % kQueues : slot;
         if (SPLIT && list_slot >= p.num_items) break;
-        const ItemGeom item = load_item<BLOCK>(p.items, p.block_items, list_slot);
+        const ItemGeom item = load_item<BLOCK, sizeof...(List) != 0>(p, list_slot);
         if (item.tile < 0) break;          // padding at the end of the queue: nothing left
         run_item(item, 1 - slot / kQueues % 2);
         if (tid == 0) next_slot[turn] = drawn;
@@ -538,29 +539,39 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p) {
 
 namespace {
 
-template <int D, int KD>
-void launch(const FwdParams& p, unsigned workgroups, bool block, bool split, hipStream_t stream) {
+template <int D, int KD, typename... List>
+void launch(const FwdParams& p, unsigned workgroups, bool block, bool split, hipStream_t stream, const List&... list) {
     const dim3 grid(workgroups), threads(kThreads);
-    if (block && split) hipLaunchKernelGGL((fwd_kernel<D, true, KD, true>), grid, threads, 0, stream, p);
-    else if (block) hipLaunchKernelGGL((fwd_kernel<D, true, KD, false>), grid, threads, 0, stream, p);
-    else if (split) hipLaunchKernelGGL((fwd_kernel<D, false, KD, true>), grid, threads, 0, stream, p);
-    else hipLaunchKernelGGL((fwd_kernel<D, false, KD, false>), grid, threads, 0, stream, p);
+    if (block && split) hipLaunchKernelGGL((fwd_kernel<D, true, KD, true, List...>), grid, threads, 0, stream, p, list...);
+    else if (block) hipLaunchKernelGGL((fwd_kernel<D, true, KD, false, List...>), grid, threads, 0, stream, p, list...);
+    else if (split) hipLaunchKernelGGL((fwd_kernel<D, false, KD, true, List...>), grid, threads, 0, stream, p, list...);
+    else hipLaunchKernelGGL((fwd_kernel<D, false, KD, false, List...>), grid, threads, 0, stream, p, list...);
+}
+
+// the kernel whose contraction over head_dim has as many 16-column steps as hold data, and whose products of output
+// width head_dim have as many 32-column blocks (three up to 96)
+template <typename... List>
+void launch_width(const FwdParams& p, int head_dim, unsigned workgroups, bool block, bool split, hipStream_t stream, const List&... list) {
+    if (tile_width(head_dim) == 64) launch<64, 4>(p, workgroups, block, split, stream, list...);
+    else if (contraction_steps(head_dim) <= 5) launch<128, 5>(p, workgroups, block, split, stream, list...);
+    else if (contraction_steps(head_dim) == 6) launch<128, 6>(p, workgroups, block, split, stream, list...);
+    else if (contraction_steps(head_dim) == 7) launch<128, 7>(p, workgroups, block, split, stream, list...);
+    else launch<128, 8>(p, workgroups, block, split, stream, list...);
 }
 
 }  // namespace
 
-hipError_t launch_fwd(const FwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
+hipError_t launch_fwd(const FwdParams& params, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
-    const bool split = p.split != 0;
-    const int workgroups = persistent_grid(split ? 2 * ((num_items + kQueues - 1) / kQueues * kQueues) : num_items, 2);
+    const bool split = params.split != 0;
+    const int64_t slots = split ? 2 * ((num_items + kQueues - 1) / kQueues * kQueues) : num_items;
+    // a short list has a workgroup for every slot: nothing to draw, and no round trip to the counters at the end of the item
+    FwdParams p = params;
+    const int64_t workgroups = list != nullptr ? slots : persistent_grid(slots, 2);
     if (workgroups <= 0) return hipErrorInvalidDevice;
-    // the kernel whose contraction over head_dim has as many 16-column steps as hold data, and whose products of output
-    // width head_dim have as many 32-column blocks (three up to 96)
-    if (tile_width(head_dim) == 64) launch<64, 4>(p, (unsigned)workgroups, block, split, stream);
-    else if (contraction_steps(head_dim) <= 5) launch<128, 5>(p, (unsigned)workgroups, block, split, stream);
-    else if (contraction_steps(head_dim) == 6) launch<128, 6>(p, (unsigned)workgroups, block, split, stream);
-    else if (contraction_steps(head_dim) == 7) launch<128, 7>(p, (unsigned)workgroups, block, split, stream);
-    else launch<128, 8>(p, (unsigned)workgroups, block, split, stream);
+    if (workgroups == slots) p.queue = nullptr;
+    if (list) launch_width(p, head_dim, (unsigned)workgroups, block, split, stream, *list);
+    else launch_width(p, head_dim, (unsigned)workgroups, block, split, stream);
     return hipGetLastError();
 }
 

@@ -174,6 +174,9 @@ struct hspmd_attn_plan {
     int64_t total_kv_tokens = 0;
     hspmd_block_item* block_items[3] = {nullptr, nullptr, nullptr};
     int32_t* queue[3] = {nullptr, nullptr, nullptr};   // device: draw counters of the three passes (zero between launches)
+    // lists that fit a launch's arguments are kept here instead (forward and dQ share one); items, block_items, queue are then NULL
+    bool is_inline = false;
+    hspmd::InlineList inline_rows{}, inline_keys{};
     // device copies of the lists
     ListSlot slots[kPlanSlots];
     int current = 0;
@@ -186,6 +189,7 @@ namespace {
 // it).  Nothing is recorded while the stream is being captured into a graph: a plan that a graph replays must not be
 // refilled while the graph may run, and that is the caller's to ensure.
 hipError_t mark_use(const hspmd_attn_plan* plan, hipStream_t stream) {
+    if (plan->is_inline) return hipSuccess;   // the launch took the list with it
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (stream != nullptr) {
         const hipError_t e = hipStreamIsCapturing(stream, &capturing);
@@ -241,6 +245,31 @@ hspmd::Dispatch plan_dispatch(const hspmd_attn_plan* plan, hspmd_list_kind kind)
     return hspmd::pass_dispatch(kind, plan->load[kind], plan->count[kind], plan->head_dim, plan->is_block);
 }
 
+const hspmd::InlineList* inline_list(const hspmd_attn_plan* plan, hspmd_list_kind kind) {
+    return !plan->is_inline ? nullptr : kind == HSPMD_LIST_DKV ? &plan->inline_keys : &plan->inline_rows;
+}
+
+// a plan is for a device, also one whose lists need none
+hspmd_status need_device() {
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    return e == hipSuccess ? HSPMD_OK : fail_hip(e, "hipGetDevice(plan)");
+}
+
+// Keeps lists that fit in the plan itself; false: they go to the device.  `all`: the rows list, then the keys list.
+template <typename Item>
+bool keep_inline(hspmd_attn_plan* plan, const std::vector<Item>& all, int64_t rows, int64_t keys, Item* (&views)[3]) {
+    if ((size_t)std::max(rows, keys) * sizeof(Item) > (size_t)hspmd::kListBytes) return false;
+    if (rows > 0) std::memcpy(plan->inline_rows.words, all.data(), (size_t)rows * sizeof(Item));
+    if (keys > 0) std::memcpy(plan->inline_keys.words, all.data() + rows, (size_t)keys * sizeof(Item));
+    for (int kind = 0; kind < 3; ++kind) {
+        views[kind] = nullptr;
+        plan->queue[kind] = nullptr;
+    }
+    plan->is_inline = true;
+    return true;
+}
+
 // Builds the three packed lists of a pack on the host (forward and dQ share one copy) and installs them.
 hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t num_seqs, bool first) {
     std::vector<hspmd_work_item> all;
@@ -264,17 +293,22 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
     }
-    // behind the lists: the draw counters of the three passes, uploaded as zeros (one list item = 16 bytes = 4 counters)
-    const size_t counters_at = all.size();
-    try {
-        all.resize(all.size() + 3 * kCounterItems, hspmd_work_item{0, 0, 0, 0});
-    } catch (const std::bad_alloc&) {
-        return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
+    if (hspmd_status rc = first ? need_device() : HSPMD_OK) return rc;
+    const bool kept = keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->items);
+    if (!kept) {
+        // behind the lists: the draw counters of the three passes, uploaded as zeros (one list item = 16 bytes = 4 counters)
+        const size_t counters_at = all.size();
+        try {
+            all.resize(all.size() + 3 * kCounterItems, hspmd_work_item{0, 0, 0, 0});
+        } catch (const std::bad_alloc&) {
+            return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
+        }
+        if (hspmd_status rc = install_lists(plan, all.data(), all.size() * sizeof(hspmd_work_item), first)) return rc;
+        plan->is_inline = false;
+        for (int kind = 0; kind < 3; ++kind)
+            plan->queue[kind] = reinterpret_cast<int32_t*>(static_cast<hspmd_work_item*>(plan->slots[plan->current].block) +
+                                                           counters_at + kind * kCounterItems);
     }
-    if (hspmd_status rc = install_lists(plan, all.data(), all.size() * sizeof(hspmd_work_item), first)) return rc;
-    for (int kind = 0; kind < 3; ++kind)
-        plan->queue[kind] = reinterpret_cast<int32_t*>(static_cast<hspmd_work_item*>(plan->slots[plan->current].block) +
-                                                       counters_at + kind * kCounterItems);
     plan->num_seqs = num_seqs;
     plan->total_tokens = cu[num_seqs];
     for (int kind = 0; kind < 3; ++kind)
@@ -283,7 +317,7 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
     for (int32_t i = 0; i < num_seqs; ++i) plan->max_position = std::max(plan->max_position, cu[i + 1] - cu[i]);
     for (int kind = 0; kind < 3; ++kind) {
         plan->count[kind] = count[kind];
-        plan->items[kind] = count[kind] > 0 ? static_cast<hspmd_work_item*>(plan->slots[plan->current].block) + offset[kind]
+        if (!kept) plan->items[kind] = count[kind] > 0 ? static_cast<hspmd_work_item*>(plan->slots[plan->current].block) + offset[kind]
                                             : nullptr;
     }
     return HSPMD_OK;
@@ -311,16 +345,21 @@ hspmd_status fill_block_plan(hspmd_attn_plan* plan, const int32_t* cu_q, const i
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
     }
-    const size_t counters_at = all.size();
-    try {
-        all.resize(all.size() + 3 * kCounterBlockItems, hspmd_block_item{0, 0, 0, 0, 0, 0, 0, 0});
-    } catch (const std::bad_alloc&) {
-        return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
+    if (hspmd_status rc = first ? need_device() : HSPMD_OK) return rc;
+    const bool kept = keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->block_items);
+    if (!kept) {
+        const size_t counters_at = all.size();
+        try {
+            all.resize(all.size() + 3 * kCounterBlockItems, hspmd_block_item{0, 0, 0, 0, 0, 0, 0, 0});
+        } catch (const std::bad_alloc&) {
+            return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
+        }
+        if (hspmd_status rc = install_lists(plan, all.data(), all.size() * sizeof(hspmd_block_item), first)) return rc;
+        plan->is_inline = false;
+        for (int kind = 0; kind < 3; ++kind)
+            plan->queue[kind] = reinterpret_cast<int32_t*>(static_cast<hspmd_block_item*>(plan->slots[plan->current].block) +
+                                                           counters_at + kind * kCounterBlockItems);
     }
-    if (hspmd_status rc = install_lists(plan, all.data(), all.size() * sizeof(hspmd_block_item), first)) return rc;
-    for (int kind = 0; kind < 3; ++kind)
-        plan->queue[kind] = reinterpret_cast<int32_t*>(static_cast<hspmd_block_item*>(plan->slots[plan->current].block) +
-                                                       counters_at + kind * kCounterBlockItems);
     plan->num_seqs = num_seqs;
     plan->total_tokens = cu_q[num_seqs];
     for (int kind = 0; kind < 3; ++kind)
@@ -333,6 +372,7 @@ hspmd_status fill_block_plan(hspmd_attn_plan* plan, const int32_t* cu_q, const i
                                                                    k_pos[i] + (cu_k[i + 1] - cu_k[i])));
     for (int kind = 0; kind < 3; ++kind) {
         plan->count[kind] = count[kind];
+        if (kept) continue;
         plan->block_items[kind] =
             count[kind] > 0 ? static_cast<hspmd_block_item*>(plan->slots[plan->current].block) + offset[kind] : nullptr;
     }
@@ -534,7 +574,7 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
     p.queue = plan->queue[HSPMD_LIST_FWD];
     p.split = plan_dispatch(plan, HSPMD_LIST_FWD) == hspmd::Dispatch::kHalves ? 1 : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, plan->head_dim, plan->count[HSPMD_LIST_FWD], false, s); });
+    const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, inline_list(plan, HSPMD_LIST_FWD), plan->head_dim, plan->count[HSPMD_LIST_FWD], false, s); });
     if (e != hipSuccess) return fail_hip(e, "forward launch");
     if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
     return HSPMD_OK;
@@ -590,7 +630,7 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     p.items = plan->items[HSPMD_LIST_DQ];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
     p.split = plan_dispatch(plan, HSPMD_LIST_DQ) == hspmd::Dispatch::kHalves ? 1 : 0;
-    auto dq_pass = [&] { return hspmd::launch_bwd_dq(p, plan->head_dim, plan->count[HSPMD_LIST_DQ], false, s); };
+    auto dq_pass = [&] { return hspmd::launch_bwd_dq(p, inline_list(plan, HSPMD_LIST_DQ), plan->head_dim, plan->count[HSPMD_LIST_DQ], false, s); };
     hipError_t e = timed ? timed_launch(2, s, dq_pass) : dq_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dQ launch");
     p.items = plan->items[HSPMD_LIST_DKV];
@@ -600,7 +640,7 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     p.persist = dkv == hspmd::Dispatch::kPersistent ? 1
                 : hspmd::persistent_dkv(dkv, plan->load[HSPMD_LIST_DKV], plan->count[HSPMD_LIST_DKV], p.group, plan->head_dim) ? 2 : 0;
     p.queue = plan->queue[HSPMD_LIST_DKV];
-    auto dkv_pass = [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], false, s); };
+    auto dkv_pass = [&] { return hspmd::launch_bwd_dkv(p, inline_list(plan, HSPMD_LIST_DKV), plan->head_dim, plan->count[HSPMD_LIST_DKV], false, s); };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dK/dV launch");
     if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
@@ -723,15 +763,15 @@ hspmd_status hspmd_rope_qk(const hspmd_attn_plan* plan, const void* q, const voi
     if (plan->is_block) {
         // query chunks through the forward list, key chunks through the dK/dV list
         p.block_items = plan->block_items[HSPMD_LIST_FWD];
-        hipError_t e = timed_launch(4, s, [&] { return hspmd::launch_rope_block(p, plan->count[HSPMD_LIST_FWD], false, s); });
+        hipError_t e = timed_launch(4, s, [&] { return hspmd::launch_rope_block(p, inline_list(plan, HSPMD_LIST_FWD), plan->count[HSPMD_LIST_FWD], false, s); });
         if (e != hipSuccess) return fail_hip(e, "rope launch (query chunks)");
         p.block_items = plan->block_items[HSPMD_LIST_DKV];
-        e = timed_launch(4, s, [&] { return hspmd::launch_rope_block(p, plan->count[HSPMD_LIST_DKV], true, s); });
+        e = timed_launch(4, s, [&] { return hspmd::launch_rope_block(p, inline_list(plan, HSPMD_LIST_DKV), plan->count[HSPMD_LIST_DKV], true, s); });
         if (e != hipSuccess) return fail_hip(e, "rope launch (key chunks)");
         if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
         return HSPMD_OK;
     }
-    const hipError_t e = timed_launch(4, s, [&] { return hspmd::launch_rope_qk(p, plan->count[HSPMD_LIST_FWD], s); });
+    const hipError_t e = timed_launch(4, s, [&] { return hspmd::launch_rope_qk(p, inline_list(plan, HSPMD_LIST_FWD), plan->count[HSPMD_LIST_FWD], s); });
     if (e != hipSuccess) return fail_hip(e, "rope launch");
     if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
     return HSPMD_OK;
@@ -851,7 +891,7 @@ hspmd_status hspmd_attn_block_fwd(const hspmd_attn_plan* plan, const void* q, co
     p.queue = plan->queue[HSPMD_LIST_FWD];
     p.split = plan_dispatch(plan, HSPMD_LIST_FWD) == hspmd::Dispatch::kHalves ? 1 : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, plan->head_dim, plan->count[HSPMD_LIST_FWD], true, s); });
+    const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, inline_list(plan, HSPMD_LIST_FWD), plan->head_dim, plan->count[HSPMD_LIST_FWD], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block forward launch");
     if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
     return HSPMD_OK;
@@ -934,12 +974,12 @@ static hspmd_status block_bwd(const hspmd_attn_plan* plan, const void* q, const 
     p.block_items = plan->block_items[HSPMD_LIST_DQ];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
     p.split = plan_dispatch(plan, HSPMD_LIST_DQ) == hspmd::Dispatch::kHalves ? 1 : 0;
-    e = timed_launch(2, s, [&] { return hspmd::launch_bwd_dq(p, plan->head_dim, plan->count[HSPMD_LIST_DQ], true, s); });
+    e = timed_launch(2, s, [&] { return hspmd::launch_bwd_dq(p, inline_list(plan, HSPMD_LIST_DQ), plan->head_dim, plan->count[HSPMD_LIST_DQ], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dQ launch");
     p.block_items = plan->block_items[HSPMD_LIST_DKV];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DKV];
     p.split = plan_dispatch(plan, HSPMD_LIST_DKV) == hspmd::Dispatch::kHalves ? 1 : 0;
-    e = timed_launch(3, s, [&] { return hspmd::launch_bwd_dkv(p, plan->head_dim, plan->count[HSPMD_LIST_DKV], true, s); });
+    e = timed_launch(3, s, [&] { return hspmd::launch_bwd_dkv(p, inline_list(plan, HSPMD_LIST_DKV), plan->head_dim, plan->count[HSPMD_LIST_DKV], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dK/dV launch");
     if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
     return HSPMD_OK;

@@ -7,6 +7,15 @@
 
 namespace hspmd {
 
+// Work lists of small packs travel as the kernels' second argument: a refill then uploads nothing and a launch records no event
+// for it, and a workgroup reads its item together with the other arguments instead of behind a pointer among them.  A launch may
+// carry 4 KB; this leaves 240 slots (120 of the block variant) beside the other arguments.  Sequences of 17, 64 and 111 tokens, 2
+// heads, refill, forward and backward: 43.2 -> 23.8 us; two sequences of 2053 tokens on 8 heads, forward and backward 91.9 -> 86.6.
+constexpr int kListBytes = 3840;
+struct alignas(16) InlineList {
+    int32_t words[kListBytes / 4];
+};
+
 struct FwdParams {
     const uint16_t* q;
     const uint16_t* k;
@@ -22,7 +31,7 @@ struct FwdParams {
     int32_t head_dim;              // elements per head in memory (a multiple of 8, at most the kernel's tile width)
     float scale_log2;              // softmax_scale * log2(e)
     int32_t num_items;             // slots of the work list (padding included)
-    int32_t* queue;                // this pass's draw counters (ItemQueue), zero between launches
+    int32_t* queue;                // this pass's draw counters (ItemQueue), zero between launches; NULL: every slot has a workgroup
     int32_t split;                 // the unit of work is half an item (decided from the plan's loads, see pass_dispatch)
 };
 
@@ -70,11 +79,12 @@ inline int contraction_steps(int head_dim) { return (head_dim + 15) / 16; }
 // compute unit, and not more than the list has slots (the list length is a multiple of the queue count).
 int persistent_grid(int64_t num_items, int per_cu);
 
+// `list`: the work list when it is inline (items and block_items are then unused), else NULL
 // `block`: the items are hspmd_block_item (separate query / key chunks, shifted causal mask)
-hipError_t launch_fwd(const FwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream);
+hipError_t launch_fwd(const FwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream);
 hipError_t launch_bwd_dsum(const BwdParams& p, int head_dim, hipStream_t stream);
-hipError_t launch_bwd_dq(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream);
-hipError_t launch_bwd_dkv(const BwdParams& p, int head_dim, int64_t num_items, bool block, hipStream_t stream);
+hipError_t launch_bwd_dq(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream);
+hipError_t launch_bwd_dkv(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream);
 
 // merge of two partial results of the same rows over disjoint key sets (fp32 O [T, Hq, d], LSE [Hq, T]):
 // out = a (+) b; out may alias a.  out_bf16 (may be NULL) also receives the merged O rounded to bf16.
@@ -105,9 +115,9 @@ struct RopeParams {
     float sin_sign;                // +1: rotate, -1: rotate back
 };
 hipError_t launch_rope_table(float* table, int32_t positions, int32_t head_dim, double base, hipStream_t stream);
-hipError_t launch_rope_qk(const RopeParams& p, int64_t num_items, hipStream_t stream);
+hipError_t launch_rope_qk(const RopeParams& p, const InlineList* list, int64_t num_items, hipStream_t stream);
 // block plans: `keys` selects the key chunks (p.block_items = dK/dV list) or the query chunks (forward list)
-hipError_t launch_rope_block(const RopeParams& p, int64_t num_items, bool keys, hipStream_t stream);
+hipError_t launch_rope_block(const RopeParams& p, const InlineList* list, int64_t num_items, bool keys, hipStream_t stream);
 
 // matrix-core rate probe: `grid` workgroups of kProbeThreads threads, each wave issues 16 * rounds MFMAs and
 // every thread writes one float to out[grid * kProbeThreads]

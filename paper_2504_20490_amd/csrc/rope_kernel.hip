@@ -87,14 +87,14 @@ __device__ __forceinline__ void rotate_rows(const uint16_t* src, uint16_t* dst, 
 // Packed plans: one workgroup per item of the forward list.  The items (tile, head) of one tile exist once per q
 // head, so the workgroup of head h takes the h-th share of the tile's rows and rotates ALL heads of those rows,
 // of q and of k.
-template <int VEC>
-__global__ __launch_bounds__(kRopeThreads) void rope_qk_kernel(RopeParams p) {
-    const hspmd_work_item item = p.items[blockIdx.x];
+template <int VEC, typename... List>
+__global__ __launch_bounds__(kRopeThreads) void rope_qk_kernel(RopeParams p, List...) {
+    const ItemGeom item = load_item<false, sizeof...(List) != 0>(p, (int)blockIdx.x);
     if (item.tile < 0) return;   // padding slot
     const int row0 = item.tile * kFwdQTile;
-    const int rows = min(kFwdQTile, item.seq_len - row0);
+    const int rows = min(kFwdQTile, item.q_len - row0);
     const int r_begin = rows * item.head / p.q_heads, r_end = rows * (item.head + 1) / p.q_heads;
-    const int64_t token0 = (int64_t)item.token_start + row0;
+    const int64_t token0 = (int64_t)item.q_start + row0;
     rotate_rows<VEC>(p.q, p.q_out, p.q_stride, p.q_out_stride, token0, row0, r_begin, r_end, p.q_heads, p.head_dim, p.table,
                      p.sin_sign);
     rotate_rows<VEC>(p.k, p.k_out, p.kv_stride, p.kv_out_stride, token0, row0, r_begin, r_end, p.q_heads / p.group,
@@ -103,9 +103,9 @@ __global__ __launch_bounds__(kRopeThreads) void rope_qk_kernel(RopeParams p) {
 
 // Block plans: the query chunks are walked through the forward list (items (q tile, q head)), the key chunks through
 // the dK/dV list (items (k tile, kv head)); positions are those of the chunks inside their sequences.
-template <int VEC, bool KEYS>
-__global__ __launch_bounds__(kRopeThreads) void rope_block_kernel(RopeParams p) {
-    const hspmd_block_item item = p.block_items[blockIdx.x];
+template <int VEC, bool KEYS, typename... List>
+__global__ __launch_bounds__(kRopeThreads) void rope_block_kernel(RopeParams p, List...) {
+    const ItemGeom item = load_item<true, sizeof...(List) != 0>(p, (int)blockIdx.x);
     if (item.tile < 0) return;   // padding slot
     const int tile_rows = KEYS ? kDkvKTile : kFwdQTile;
     const int heads = KEYS ? p.q_heads / p.group : p.q_heads;
@@ -132,26 +132,38 @@ hipError_t launch_rope_table(float* table, int32_t positions, int32_t head_dim, 
     return hipGetLastError();
 }
 
-hipError_t launch_rope_qk(const RopeParams& p, int64_t num_items, hipStream_t stream) {
-    if (num_items == 0) return hipSuccess;
+namespace {
+
+template <typename... List>
+void launch_qk(const RopeParams& p, int64_t num_items, hipStream_t stream, const List&... list) {
     const dim3 grid((unsigned)num_items), threads(kRopeThreads);
     // 16-byte pieces when half a head is a whole number of them, 8-byte pieces otherwise (head_dim is a multiple of 8)
-    if ((p.head_dim / 2) % 8 == 0) hipLaunchKernelGGL(rope_qk_kernel<8>, grid, threads, 0, stream, p);
-    else hipLaunchKernelGGL(rope_qk_kernel<4>, grid, threads, 0, stream, p);
+    if ((p.head_dim / 2) % 8 == 0) hipLaunchKernelGGL((rope_qk_kernel<8, List...>), grid, threads, 0, stream, p, list...);
+    else hipLaunchKernelGGL((rope_qk_kernel<4, List...>), grid, threads, 0, stream, p, list...);
+}
+
+template <bool KEYS, typename... List>
+void launch_chunks(const RopeParams& p, int64_t num_items, hipStream_t stream, const List&... list) {
+    const dim3 grid((unsigned)num_items), threads(kRopeThreads);
+    if ((p.head_dim / 2) % 8 == 0) hipLaunchKernelGGL((rope_block_kernel<8, KEYS, List...>), grid, threads, 0, stream, p, list...);
+    else hipLaunchKernelGGL((rope_block_kernel<4, KEYS, List...>), grid, threads, 0, stream, p, list...);
+}
+
+}  // namespace
+
+hipError_t launch_rope_qk(const RopeParams& p, const InlineList* list, int64_t num_items, hipStream_t stream) {
+    if (num_items == 0) return hipSuccess;
+    if (list) launch_qk(p, num_items, stream, *list);
+    else launch_qk(p, num_items, stream);
     return hipGetLastError();
 }
 
-hipError_t launch_rope_block(const RopeParams& p, int64_t num_items, bool keys, hipStream_t stream) {
+hipError_t launch_rope_block(const RopeParams& p, const InlineList* list, int64_t num_items, bool keys, hipStream_t stream) {
     if (num_items == 0) return hipSuccess;
-    const dim3 grid((unsigned)num_items), threads(kRopeThreads);
-    const bool wide = (p.head_dim / 2) % 8 == 0;
-    if (keys) {
-        if (wide) hipLaunchKernelGGL((rope_block_kernel<8, true>), grid, threads, 0, stream, p);
-        else hipLaunchKernelGGL((rope_block_kernel<4, true>), grid, threads, 0, stream, p);
-    } else {
-        if (wide) hipLaunchKernelGGL((rope_block_kernel<8, false>), grid, threads, 0, stream, p);
-        else hipLaunchKernelGGL((rope_block_kernel<4, false>), grid, threads, 0, stream, p);
-    }
+    if (keys && list) launch_chunks<true>(p, num_items, stream, *list);
+    else if (keys) launch_chunks<true>(p, num_items, stream);
+    else if (list) launch_chunks<false>(p, num_items, stream, *list);
+    else launch_chunks<false>(p, num_items, stream);
     return hipGetLastError();
 }
 
