@@ -163,8 +163,11 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const cha
         constexpr int kAheadK = 4;
         constexpr int NM = NB * KK;              // MFMAs of the phase
         static_assert(NB == 1 || 2 * NP <= NM, "one copy instruction per MFMA step");
+        // the tile's key blocks in turn: consecutive MFMAs take the same query fragment, and none continues its predecessor's chain
+        // (against one block after the other: 6001 tokens, 32 heads on 8, 100.6 -> 99.8 us; short sequences, width 64, 177.2 ->
+        // 178.4 -> 176.9 us)
         auto k_frag = [&](int n) {
-            return *reinterpret_cast<const bf16x8*>(kbuf + st.rm[n % KK] + (n / KK) * 32 * D * 2);
+            return *reinterpret_cast<const bf16x8*>(kbuf + st.rm[n / NB] + (n % NB) * 32 * D * 2);
         };
         bf16x8 kq[kAheadK + 1];
 #pragma unroll
@@ -176,7 +179,7 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const cha
 #pragma unroll
         for (int n = 0; n < NM; ++n) {
             if (n + kAheadK < NM) kq[(n + kAheadK) % (kAheadK + 1)] = k_frag(n + kAheadK);
-            sn[n / KK] = mfma(kq[n % (kAheadK + 1)], st.qf[n % KK], sn[n / KK]);
+            sn[n % NB] = mfma(kq[n % (kAheadK + 1)], st.qf[n / NB], sn[n % NB]);
             // the first 8 of the 16 score pairs (key block 0, P fragments 0 and 1) spread over the NM MFMAs; the
             // other 8 go under the first P V MFMAs of phase B, which only need fragments 0 and 1
             if constexpr (NB == 1) {
