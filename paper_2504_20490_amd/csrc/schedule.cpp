@@ -40,7 +40,8 @@ std::string check_pack(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t 
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-int64_t item_cost(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t group) {
+// (inlined by force where a list's costs are summed, twice per item)
+static inline __attribute__((always_inline)) int64_t item_steps(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t group) {
     if (kind == HSPMD_LIST_DKV) {
         const int64_t first_row = (int64_t)tile * kDkvKTile;          // rows r >= first key of the tile
         if (first_row >= seq_len) return 0;
@@ -49,6 +50,10 @@ int64_t item_cost(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t g
     const int64_t last_key = std::min<int64_t>(seq_len, (int64_t)(tile + 1) * kFwdQTile);
     if ((int64_t)tile * kFwdQTile >= seq_len) return 0;
     return ceil_div(last_key, kFwdKTile);
+}
+
+int64_t item_cost(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t group) {
+    return item_steps(kind, seq_len, tile, group);
 }
 
 // The placement, shared by the packed and the block lists: chains are cut into segments, segments are assigned to queues
@@ -60,6 +65,9 @@ int64_t item_cost(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t g
 // slots.  A whole refill (two lists and their upload), against chains held as vectors of items: 57 sequences of 32 .. 506
 // tokens, 16 heads (2 x 2496 items) 231 -> 38 us; 14 sequences, 32 heads on 8 (16576 + 4144 items) 167 -> 67 us.
 namespace {
+
+// workgroups that an XCD holds at once: two per compute unit in the forward and dQ passes, one in the dK/dV pass (tile width 128)
+constexpr int32_t kResidentRows = 64, kResidentKeys = 32;
 
 // A run of items of one sequence's chain; the chains of all `copies` kv heads of the sequence hold it.
 struct SegmentClass {
@@ -158,12 +166,45 @@ Assignment assign_segments(const std::vector<SegmentClass>& classes, int32_t kv_
     return Assignment{std::move(queue_of), std::move(length), heaviest};
 }
 
+// The last items of a queue, once and a half as many as it has workgroups at once, go by cost and not chain by chain where the
+// chains are alike (the last starts with an item at least half as heavy as the first's): a chain's heavy items would start when
+// the queue runs dry.  Measured, chain by chain and by cost (us, sustained; forward, dQ, dK/dV): 5 x 2697, 8 heads, head_dim 80 77.4
+// / 69.5, 100.4 / 88.0, 138.2 / 124.2; 4 x 4096, 12 heads 222 / 200, 289 / 273; 3 x 1500, 32 heads 77.6 / 68.8, 106.8 / 94.9, 142.3 /
+// 139.2; 16 x 800, 8 heads 40.9 / 39.1, 58.7 / 53.2, 74.9 / 68.7; one of 5067, 24 heads, width 64 107 / 100, 126 / 118, 165 / 155.
+// Not where the last chains are cheap anyway (41 log-normal sequences, 16 heads 49.5 / 52.0); nor where items are short, in the
+// rows lists below 13 steps (12 x 700, 16 heads 42.4 / 45.0), in the dK/dV list below 10; nor where more than five rounds make the
+// end a small part, against which K and V (Q and dO) are fetched again: dK/dV of 6 x 2048, 16 heads, six rounds 228 / 233.
+template <typename Item, typename Cost>
+__attribute__((noinline)) void order_last_items(const std::vector<SegmentClass>& classes, int32_t kv_heads, const Assignment& placed,
+                                                int64_t resident, int64_t least_cost, Cost cost_of_item, std::vector<Item>& out) {
+    const size_t queues = placed.length.size();
+    std::vector<int64_t> heaviest(queues, 0), lightest(queues, std::numeric_limits<int64_t>::max());
+    for (const SegmentClass& c : classes)
+        for (int32_t g = 0; g < kv_heads; ++g) {
+            const size_t x = (size_t)placed.queue_of[(size_t)(c.order0 + g * c.stride)];
+            heaviest[x] = std::max(heaviest[x], c.first_cost);
+            lightest[x] = std::min(lightest[x], c.first_cost);
+        }
+    std::vector<std::pair<int64_t, Item>> last;
+    for (size_t x = 0; x < queues; ++x) {
+        const int64_t length = placed.length[x];
+        if (length <= resident || length > 5 * resident || heaviest[x] < least_cost || 2 * lightest[x] < heaviest[x]) continue;
+        const int64_t window = std::min(length, resident * 3 / 2);
+        Item* const first = out.data() + (size_t)(length - window) * queues + x;
+        last.clear();
+        for (int64_t i = 0; i < window; ++i) last.emplace_back(cost_of_item(first[(size_t)i * queues]), first[(size_t)i * queues]);
+        std::stable_sort(last.begin(), last.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+        for (int64_t i = 0; i < window; ++i) first[(size_t)i * queues] = last[(size_t)i].second;
+    }
+}
+
 // chain_len(s): items of one kv head's chain of sequence s, most expensive first; cost_of(s, i): of its i-th item;
-// make(s, g, i): that item for kv head g.  finer_slots: workgroups that a queue holds at once, for lists whose chains may be cut
-// finer (chains with several query heads keep the coarse cut, so that a group's heads of one tile stay together), else 0.
-template <typename Item, typename ChainLen, typename Cost, typename Make>
+// make(s, g, i): that item for kv head g; cost_of_item(item): its cost.  finer_slots: workgroups that a queue holds at once, for
+// lists whose chains may be cut finer and whose end may go by cost (chains with several query heads keep the coarse cut and their
+// order, so that a group's heads of one tile stay together), else 0.
+template <typename Item, typename ChainLen, typename Cost, typename Make, typename ItemCost>
 std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_queues, int32_t finer_slots, ChainLen chain_len,
-                               Cost cost_of, Make make, Item pad) {
+                               Cost cost_of, Make make, ItemCost cost_of_item, Item pad) {
     int64_t total_cost = 0, chains = 0;
     for (int32_t s = 0; s < num_seqs; ++s) {
         const int64_t n = chain_len(s);
@@ -213,6 +254,8 @@ std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_q
         int64_t& slot = cursor[(size_t)queue_of[(size_t)(c.order0 + g * c.stride)]];
         for (int32_t i = c.first; i < c.first + c.count; ++i, slot += num_queues) out[(size_t)slot] = make(c.seq, g, i);
     });
+    if (finer_slots > 0 && longest > finer_slots)
+        order_last_items(classes, kv_heads, placed, finer_slots, finer_slots == kResidentRows ? 13 : 10, cost_of_item, out);
     return out;
 }
 
@@ -246,24 +289,24 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
     const int tile_rows = (kind == HSPMD_LIST_DKV) ? kDkvKTile : kFwdQTile;
 
     // a chain: all items that share one (sequence, kv head), most expensive first
-    auto tile_of = [=](int32_t len, int32_t i) {
+    auto tile_of = [=](int32_t len, int32_t i) __attribute__((always_inline)) {
         return kind == HSPMD_LIST_DKV ? i : (int32_t)ceil_div(len, tile_rows) - 1 - i / group;
     };
     return place_chains<hspmd_work_item>(
-        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV ? 32 : group == 1 ? 64 : 0,
+        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV ? kResidentKeys : group == 1 ? kResidentRows : 0,
         [&](int32_t s) {
             const int64_t n_tiles = ceil_div(cu[s + 1] - cu[s], tile_rows);
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
         },
-        [&](int32_t s, int32_t i) {
+        [&](int32_t s, int32_t i) __attribute__((always_inline)) {
             const int32_t len = cu[s + 1] - cu[s];
-            return item_cost(kind, len, tile_of(len, i), group);
+            return item_steps(kind, len, tile_of(len, i), group);
         },
-        [&](int32_t s, int32_t g, int32_t i) {
+        [&](int32_t s, int32_t g, int32_t i) __attribute__((always_inline)) {
             const int32_t len = cu[s + 1] - cu[s];
             return hspmd_work_item{cu[s], len, tile_of(len, i), kind == HSPMD_LIST_DKV ? g : g * group + i % group};
         },
-        hspmd_work_item{0, 0, -1, 0});
+        [&](const hspmd_work_item& it) { return item_cost(kind, it.seq_len, it.tile, group); }, hspmd_work_item{0, 0, -1, 0});
 }
 
 PassLoad pass_load(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv) {
@@ -460,12 +503,13 @@ std::vector<hspmd_block_item> build_block_list(hspmd_list_kind kind, const int32
     };
     // most expensive first inside a chain (with a shift the cost is still monotone in the tile index)
     return place_chains<hspmd_block_item>(
-        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV ? 32 : group == 1 ? 64 : 0,
+        num_seqs, hkv, num_queues, kind == HSPMD_LIST_DKV ? kResidentKeys : group == 1 ? kResidentRows : 0,
         [&](int32_t s) {
             const int64_t n_tiles = ceil_div(rows_of(s), tile_rows);   // rows of the outputs the list owns
             return kind == HSPMD_LIST_DKV ? n_tiles : n_tiles * group;
         },
-        [&](int32_t s, int32_t i) { return block_item_cost(kind, make(s, 0, i), group); }, make,
+        [&](int32_t s, int32_t i) __attribute__((always_inline)) { return block_item_cost(kind, make(s, 0, i), group); }, make,
+        [&](const hspmd_block_item& it) { return block_item_cost(kind, it, group); },
         hspmd_block_item{0, 0, 0, 0, 0, -1, 0, 0});
 }
 
