@@ -373,8 +373,8 @@ bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
 // One workgroup fits a compute unit there, so the time between two of them is exposed, most of all, by the measurements, where
 // chains of two, four or eight items bring heavy and light items up in step with the order in which an XCD hands its
 // workgroups out.  Against that, the next item's loads wait for the last one's stores inside a workgroup, which short items
-// feel, and the compiler's schedule of the tile loop is 2-4 % slower in an item loop, which long ones feel.  Measured, one
-// workgroup per item and persistent (us, head_dim 128): 33 x 400 tokens, 16 heads (4 steps) 179 and 148; 78 x 512, 16 heads
+// feel.  (Longer items: persistent_dkv below.)  Measured, one workgroup per item and persistent (us, head_dim 128, with a tile
+// loop that still lost 2-4 % in an item loop): 33 x 400 tokens, 16 heads (4 steps) 179 and 148; 78 x 512, 16 heads
 // (5) 442 and 390; 67 x 300, 8 heads (3) 98 and 105; 43 x 64, 24 heads (1) 47 and 52; 18 sequences of up to 2734, 16 heads
 // (9.9) 164 and 174; 5 x 1300, 24 heads (11) 140 and 153; 438 sequences, one of 3026, one head (5, the longest 48) 72 and 79;
 // head_dim 104, 7 x 1024, 40 heads (9) 247 and 233.  Over 114 packs at three widths persistent workgroups take 0.77 to 1.02 of
