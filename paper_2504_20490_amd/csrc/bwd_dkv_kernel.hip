@@ -16,7 +16,7 @@
 //     phase B: MFMA G1(i+1)  |  second half of V(i)  |  LDS reads: Q^T/dO^T of block i (for G2(i) next time)
 // so every MFMA operand is requested half an iteration (16 MFMAs) before its use and the exp/multiply work
 // of one block is spread under the MFMAs of its neighbours.  S'/dP' are double buffered (block i is still
-// being consumed while G1(i+1) accumulates).  Scheduling-group hints fix the interleaving.
+// being consumed while G1(i+1) accumulates).  The order is written out step by step, see dkv_iteration.
 //
 // LDS: four stages of {Q tile, dO tile (64 rows each), -LSE/scale [64], -D [64]}.  While iterations
 // 2t and 2t+1 work on tile t and read ahead into tile t+1, tiles t+2 and t+3 are in flight

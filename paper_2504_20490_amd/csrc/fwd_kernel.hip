@@ -164,8 +164,8 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const cha
         constexpr int NM = NB * KK;              // MFMAs of the phase
         static_assert(NB == 1 || 2 * NP <= NM, "one copy instruction per MFMA step");
         // the tile's key blocks in turn: consecutive MFMAs take the same query fragment, and none continues its predecessor's chain
-        // (against one block after the other: 6001 tokens, 32 heads on 8, 100.6 -> 99.8 us; short sequences, width 64, 177.2 ->
-        // 178.4 -> 176.9 us)
+        // (against one block after the other, in interleaved runs: 6001 tokens, 32 heads on 8, and short sequences of width 64 0.6 %
+        // faster, long packs equal)
         auto k_frag = [&](int n) {
             return *reinterpret_cast<const bf16x8*>(kbuf + st.rm[n / NB] + (n % NB) * 32 * D * 2);
         };
