@@ -217,10 +217,11 @@ hspmd_status install_lists(hspmd_attn_plan* plan, const void* host, size_t bytes
         slot.recorded = false;
     }
     if (!slot.last_use) {
-        // The event says that the kernels before it have ended, which is all that a refill waits for.  A fence of system scope with it
-        // would write back what they left in the caches, twice a step: short sequences, 16 heads 175.6 -> 171.9 us, one forward of
-        // 6001 tokens 97.7 -> 96.1, 519 -> 494 where small launches follow one another.
-        e = hipEventCreateWithFlags(&slot.last_use, hipEventDisableTiming | hipEventDisableSystemFence);
+        // With the fence that comes with an event by default.  The copy that overwrites the slot relies on the event alone: the kernels
+        // must have read the list, and their writes to the draw counters must be in memory, or a counter written back late would land
+        // on the uploaded zeros.  hipEventDisableSystemFence is documented for events that only measure time and do not synchronise
+        // with the work before them (it took 2 % of a step of short sequences, 174 -> 171 us); a device-scope release costs the same.
+        e = hipEventCreateWithFlags(&slot.last_use, hipEventDisableTiming);
         if (e != hipSuccess) return fail_hip(e, "hipEventCreate(work list slot)");
     }
     if (bytes > slot.capacity) {

@@ -154,3 +154,38 @@ def test_block_plan_refill_equals_fresh_block_plan():
     for i, (o, lse) in enumerate(outs):
         assert np.array_equal(_bits(o), fresh[i][0]) and np.array_equal(_bits(lse), fresh[i][1]), f"block geometry {i}"
     plan.destroy()
+
+
+LONG = [[2100, 1300, 900], [800] * 6, [64, 4500], [3000, 1, 129, 1700, 700], [5100], [1111] * 4, [257] * 17]
+
+
+def test_refills_of_lists_on_the_device_equal_fresh_plans():
+    """Lists that live on the device, each different from the one before it in its slot of the ring: every refill while the launches
+    of the packs before may still run, three times round.  A list or draw counter that a refill left stale would show."""
+    import torch
+    import paper_2504_20490_amd as A
+    hq, hkv, d = 8, 4, 64
+    bufs = [_Buffers(L, hq, hkv, d, 1700 + i) for i, L in enumerate(LONG)]
+    fresh = []
+    for b in bufs:
+        plan = A.Plan(A.build_cu_seqlens(b.lengths)[0], hq, hkv, d)
+        assert plan.num_items(A.LIST_FWD) > 240          # more than a launch's arguments hold
+        b.launch(A, plan)
+        torch.cuda.synchronize()
+        fresh.append(b.results())
+        plan.destroy()
+    plan = A.Plan(A.build_cu_seqlens(LONG[-1])[0], hq, hkv, d)
+    for _ in range(3):                                   # seven packs, three slots
+        for b in bufs:
+            for t in (b.o, b.lse, b.dq, b.dk, b.dv):
+                t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for b in bufs:
+            plan.update(A.build_cu_seqlens(b.lengths)[0])
+            b.launch(A, plan)
+        torch.cuda.synchronize()
+        for b, want in zip(bufs, fresh):
+            got = b.results()
+            for n in got:
+                assert np.array_equal(got[n], want[n]), (b.lengths, n)
+    plan.destroy()
