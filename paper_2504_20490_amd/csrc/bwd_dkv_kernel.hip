@@ -133,7 +133,7 @@ __device__ __forceinline__ bf16x8 lds_read_tr(const char* lds, int a0, int a1) {
 // of a ring of four over 32768 tokens, 24 heads 350 -> 338 each; 8 x 4096, 16 heads, head_dim 104 1000 -> 974; long packs, which
 // the power limit decides, unchanged.  The exp work is spread evenly: in the first 12 of 16 steps it takes 5 % longer.  Whole items of tile width 64 have two waves per SIMD, which
 // cover each other, and less MFMA work per score: there the compiler orders each phase by a hint (short sequences 68.8 us against
-// 70.2 step by step).
+// 70.2 step by step), and so do some items of several query heads, see dkv_iteration_hinted.
 template <int D, int KD, int RB, bool MASK, bool SPREAD, bool WHOLE>
 __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D, KD>& ahead,
                                               const DkvAddr<D, KD>& cur, int dkey, float c, const DkvTileLoad<D>& load) {
@@ -254,6 +254,96 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
     cv.u = dw; st.dsprev[1] = cv.v;
 }
 
+// The same iteration of a whole item, its order left to the compiler by hints: per MFMA two LDS reads and a share of the other work,
+// copies at fixed places among the LDS reads (the copies are ordered against LDS accesses, the reads are tied to the MFMAs by the
+// hints): pieces 0-3 in the first iteration of a tile, 4-8 in the second.
+//
+// For packed items of several query heads with all eight contraction steps, one tile per trip (see GROUPS below).  They gain nothing
+// from the order above and lose a little.  Interleaved in one process (us, hints / steps in trips of two): 65536 tokens, 32 heads on 8
+// 16188 / 16306, on other boxes 15948 / 16033, 16057 / 16156 and 17455 / 17813; 5 sequences of 700 .. 2500, 32 on 8 237.0 / 238.5;
+// 64 x 512, 32 on 16 520.4 / 521.7; 4 x 4096, 32 on 16 1003 / 1005; 2 x 8192 and 16384 tokens, 32 on 8 equal.  On the box of 17455,
+// steps with one tile a trip take 18070, trips of hints inside the function above 17862.  The others keep the steps: narrower heads
+// (2 x 8192, 32 on 8, head_dim 104 1775 / 1747, 96 1534 / 1517, 80 1479 / 1459; 64 x 512, 32 on 16, 104 535 / 527), blocks (6 x 2178,
+// 24 on 8 370 / 354; 2 x 8192, 32 on 8 1938 / 1819), persistent workgroups (head_dim 104 288 / 282).
+template <int D, int KD, int RB, bool MASK, bool SPREAD>
+__device__ __forceinline__ void dkv_iteration_hinted(DkvState<D, KD>& st, const char* lds, const DkvAddr<D, KD>& ahead,
+                                                     const DkvAddr<D, KD>& cur, int dkey, float c, const DkvTileLoad<D>& load) {
+    using G = DkvGeom<D, KD>;
+    constexpr int KK = G::KK, DB = G::DB, K1 = G::K1;
+    constexpr int NRB = RB ^ 1;
+    constexpr int P0 = RB == 0 ? 0 : 4;   // first piece of this iteration
+
+    // element e of an accumulator fragment -> packed bf16 pair index; one half = 8 elements = one B operand
+    auto softmax_half = [&](int half, u32x4& pw, u32x4& dw) {
+#pragma unroll
+        for (int e = 8 * half; e < 8 * half + 8; e += 2) {
+            float p0 = fast_exp2(st.s[RB][e] * c);
+            float p1 = fast_exp2(st.s[RB][e + 1] * c);
+            if (MASK && (8 * (e >> 2) + (e & 3) < dkey)) p0 = 0.f;
+            if (MASK && (8 * ((e + 1) >> 2) + ((e + 1) & 3) < dkey)) p1 = 0.f;
+            pw[(e >> 1) & 3] = pack_bf16(p0, p1);
+            dw[(e >> 1) & 3] = pack_bf16(p0 * st.dp[RB][e], p1 * st.dp[RB][e + 1]);
+        }
+    };
+
+    // ================= phase A =================
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(lds + ahead.st + NRB * 128 + i4 * 32);
+        const f32x4 b = *reinterpret_cast<const f32x4*>(lds + ahead.st + NRB * 128 + i4 * 32 + 256);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { st.s[NRB][4 * i4 + j] = a[j]; st.dp[NRB][4 * i4 + j] = b[j]; }
+    }
+#pragma unroll
+    for (int kk = 0; kk < K1; ++kk) {
+        st.qf[kk] = lds_read128(lds, ahead.rm[kk] + NRB * G::kBlockBytes);
+        st.dof[kk] = lds_read128(lds, ahead.rm[kk] + NRB * G::kBlockBytes + G::kTileBytes);
+        if constexpr (SPREAD) {
+            if (kk == KK / 4 - 1) load.template piece<P0>();
+            if (kk == 3 * KK / 4 - 1) load.template piece<P0 + 1>();
+        }
+    }
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+        const int tt = kk / DB, db = kk % DB;
+        st.dv[db] = mfma(st.dotf[kk], st.pprev[tt], st.dv[db]);
+        st.dk[db] = mfma(st.qtf[kk], st.dsprev[tt], st.dk[db]);
+    }
+    u32x4 pw0, dw0;
+    softmax_half(0, pw0, dw0);
+    InterleaveHint<2 * KK, 2, (MASK ? 4 : 3), 0, 0x402>::apply();
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ================= phase B =================
+    union { u32x4 u; bf16x8 v; } cv;
+    cv.u = pw0; st.pprev[0] = cv.v;
+    cv.u = dw0; st.dsprev[0] = cv.v;
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const int off = (RB * 2 + tt) * 16 * D * 2;   // 16 tile rows per k-step
+            st.qtf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off, cur.tr[db][1] + off);
+            st.dotf[tt * DB + db] = lds_read_tr<D>(lds, cur.tr[db][0] + off + G::kTileBytes, cur.tr[db][1] + off + G::kTileBytes);
+            if constexpr (SPREAD) {
+                if (tt == 0 && db == DB - 1) load.template piece<P0 + 2>();
+                if (tt == 1 && db == DB / 2 - 1) load.template piece<P0 + 3>();
+                if (RB == 1 && tt == 1 && db == DB - 1) load.template piece<P0 + 4>();
+            }
+        }
+#pragma unroll
+    for (int kk = 0; kk < K1; ++kk) {
+        st.s[NRB] = mfma(st.qf[kk], st.kf[kk], st.s[NRB]);
+        st.dp[NRB] = mfma(st.dof[kk], st.vf[kk], st.dp[NRB]);
+    }
+    u32x4 pw1, dw1;
+    softmax_half(1, pw1, dw1);
+    cv.u = pw1; st.pprev[1] = cv.v;
+    cv.u = dw1; st.dsprev[1] = cv.v;
+    InterleaveHint<2 * K1, (K1 == KK ? 2 : 3), (MASK ? 4 : 3), 1, 0x402>::apply();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 }  // namespace
 
 // Tile width 64: the accumulators are half as large, so two workgroups fit a compute unit (248 registers per wave, 2 x 68 KB
@@ -265,12 +355,18 @@ __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* l
 // 0.68 of the time: for packs whose longest item outlasts the rest of the pass.  The two
 // accumulator pairs of a key meet in LDS at the end, in one fixed order.
 //
-// PERSIST: the workgroup draws items from its queue until none is left (as the forward does), for packs of many short items.
+// PERSIST: the workgroup draws items from its queue until none is left (as the forward does), for packs of many items (short_items and
+// persistent_dkv in schedule.cpp).
+//
+// GROUPS: whole packed items of several query heads at head_dim above 112, one workgroup each; every head is walked one tile at a time,
+// in the compiler's order (dkv_iteration_hinted).
 //
 // List: nothing, or InlineList when the work list is the second argument.
-template <int D, bool BLOCK, int KD, bool SPLIT, bool PERSIST, typename... List>
+template <int D, bool BLOCK, int KD, bool SPLIT, bool PERSIST, bool GROUPS, typename... List>
 __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv_kernel(BwdParams p, List...) {
     static_assert(!PERSIST || (!BLOCK && !SPLIT), "whole items of packed plans only");
+    static_assert(!GROUPS || (KD == 8 && !BLOCK && !SPLIT && !PERSIST), "whole items of packed plans, head_dim above 112");
+    constexpr bool kTrips = !SPLIT && !GROUPS && D == 128;   // whole items, two tiles a trip
     using G = DkvGeom<D, KD>;
     constexpr int BKV = SPLIT ? kDkvKTile / 2 : kDkvKTile, BQ = kDkvQTile;
     constexpr int KK = G::KK, DB = G::DB, K1 = G::K1;
@@ -448,7 +544,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     // them to vector registers where a loop or a branch begins; held in accumulation registers up to here (an empty statement),
     // they are copied one by one under the MFMAs of the steps that use them.
     auto hold_in_acc = [&] {
-        if constexpr (!SPLIT && D == 128) asm volatile("" : "+a"(st.s[0]), "+a"(st.dp[0]));
+        if constexpr (kTrips) asm volatile("" : "+a"(st.s[0]), "+a"(st.dp[0]));
     };
     // `par`: SPLIT, where a tile is one iteration: the accumulator pair that holds the tile's S' / dP'.  Otherwise, 0 for the item's
     // first tile, 1 for the first and 2 for the second tile of a trip
@@ -470,6 +566,9 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
         hold_in_acc();
         if constexpr (SPLIT) {
             dkv_iteration<D, KD, kPar, kMask, false, false>(st, lds, next, off, dkey0, c, no_load);
+        } else if constexpr (GROUPS) {
+            dkv_iteration_hinted<D, KD, 0, kMask, false>(st, lds, off, off, dkey0, c, no_load);
+            dkv_iteration_hinted<D, KD, 1, kMask, false>(st, lds, next, off, dkey0 - 32, c, no_load);
         } else {
             dkv_iteration<D, KD, 0, kMask, false, true>(st, lds, off, off, dkey0, c, no_load);
             dkv_iteration<D, KD, 1, kMask, false, true>(st, lds, next, off, dkey0 - 32, c, no_load);
@@ -497,6 +596,9 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
         const int dkey0 = my_key - shift - qt * BQ - row_block * 32 - 4 * hh;
         if constexpr (SPLIT) {
             dkv_iteration<D, KD, kPar, false, true, false>(st, lds, next, off, dkey0, c, load);
+        } else if constexpr (GROUPS) {
+            dkv_iteration_hinted<D, KD, 0, false, true>(st, lds, off, off, dkey0, c, load);
+            dkv_iteration_hinted<D, KD, 1, false, true>(st, lds, next, off, dkey0 - 32, c, load);
         } else {
             dkv_iteration<D, KD, 0, false, true, true>(st, lds, off, off, dkey0, c, load);
             dkv_iteration<D, KD, 1, false, true, true>(st, lds, next, off, dkey0 - 32, c, load);
@@ -534,7 +636,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
             load.stat = ((wave & 1) == 0 ? p.nlse : p.negd) + (int64_t)hq * p.total_tokens + row;
             load.wave = wave;
             load.lane = lane;
-            if constexpr (!SPLIT && D == 128) {
+            if constexpr (kTrips) {
                 // Two tiles a trip, in one basic block: a conditional barrier in it, or one tile a trip, gathers the copies of S' and
                 // dP' (see hold_in_acc) where the block begins, with no MFMA beside them.  8 x 2048, 32 heads 639 -> 610 us against
                 // 623, the pack of 32768 tokens 2563 -> 2564 against 2604; four tiles a trip 623 and 2595 (7 KB of code more to fetch).
@@ -556,7 +658,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
                     tile_step_spread(u + 1, first_qt + j - 1, load, Odd{});
                 }
             }
-            if constexpr (SPLIT || D == 64)
+            if constexpr (!kTrips)
             for (; j >= n_general; --j, ++u) {
                 tile_step_spread(u, first_qt + j, load, Even{});
                 if constexpr (SPLIT) swap_pairs();
@@ -648,22 +750,28 @@ hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, hipStre
     const dim3 threads(kThreads);
     if (p.split != 0) {
         const dim3 grid((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2));
-        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, true, false, List...>), grid, threads, 0, stream, p, list...);
-        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true, false, List...>), grid, threads, 0, stream, p, list...);
+        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, true, false, false, List...>), grid, threads, 0, stream, p, list...);
+        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true, false, false, List...>), grid, threads, 0, stream, p, list...);
     } else {
         const dim3 grid((unsigned)num_items);
         if constexpr (D == 128 && sizeof...(List) == 0) {   // (an inline list is too short for persistent workgroups)
             if (!block && p.persist) {
                 const int workgroups = persistent_grid(num_items, 1);
                 if (workgroups > 0) {
-                    hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, true>), dim3((unsigned)workgroups), threads, 0, stream, p);
+                    hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, true, false>), dim3((unsigned)workgroups), threads, 0, stream, p);
                     return hipGetLastError();
                 }
                 if (p.persist == 1) return hipErrorInvalidDevice;
             }
         }
-        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false, false, List...>), grid, threads, 0, stream, p, list...);
-        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, false, List...>), grid, threads, 0, stream, p, list...);
+        if constexpr (KD == 8 && sizeof...(List) == 0) {   // (with the list in the arguments the two walks take the same time)
+            if (!block && p.group > 1) {
+                hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, false, true>), grid, threads, 0, stream, p);
+                return hipGetLastError();
+            }
+        }
+        if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, false, false, false, List...>), grid, threads, 0, stream, p, list...);
+        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, false, false, List...>), grid, threads, 0, stream, p, list...);
     }
     return hipGetLastError();
 }

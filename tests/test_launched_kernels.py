@@ -1,0 +1,38 @@
+"""Which kernels a pack launches, asked of the library itself (no GPU: see launch_recorder)."""
+import pytest
+
+import dispatch_packs as packs
+import launch_recorder as rec
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    return rec.build_stand_in(tmp_path_factory.mktemp("recorder"))
+
+
+def launched(stand_in, cases):
+    """Per case (lengths or block geometry, q heads, kv heads, head_dim): the kernels of its forward and backward."""
+    program = """
+for pack, hq, hkv, d in args[0]:
+    plan = BlockPlan(*pack, hq, hkv, d) if isinstance(pack[0], list) else Plan(pack, hq, hkv, d)
+    calls(); plan.forward(); plan.backward()
+    out([name for what, name, _ in calls() if what == "launch"])
+"""
+    return [[rec.kernel(name) for name in names] for names in rec.record(stand_in, program, cases)]
+
+
+def _steps(d):
+    return 4 if d <= 64 else max(5, -(-d // 16))
+
+
+# (fifth argument of the dK/dV kernel: persistent workgroups; sixth: the walk for items of several query heads)
+@pytest.mark.parametrize("pack,hq,hkv,d,block,persistent,groups", [
+    (packs.RAGGED, 24, 12, 128, False, False, True), (packs.RAGGED, 24, 12, 96, False, False, False),
+    ([4096] * 4, 32, 16, 112, False, False, False), ([16384], 32, 8, 120, False, False, True),
+    (packs.GEOMETRY, 24, 12, 128, True, False, False), (packs.GEOMETRY, 12, 12, 128, True, False, False),
+    (packs.RAGGED, 24, 12, 64, False, False, False), (packs.RAGGED, 8, 8, 128, False, False, False),
+    ([1 + (i * 37) % 131 for i in range(40)] + [449] * 24, 16, 8, 104, False, True, False), ([2048] * 8, 32, 32, 128, False, True, False)])
+def test_walk_of_the_dkv_pass(stand_in, pack, hq, hkv, d, block, persistent, groups):
+    (names,) = launched(stand_in, [(pack, hq, hkv, d)])
+    width = 64 if d <= 64 else 128
+    assert names[-1] == ("bwd_dkv_kernel", (width, block, _steps(d), False, persistent, groups, False))
