@@ -199,7 +199,7 @@ hspmd_status hspmd_attn_plan_create_ordered(const int32_t* cu_seqlens_host, int3
  * Errors: INVALID_ARG for a NULL plan, the wrong kind of plan, bad cu_seqlens; HIP for a failed runtime call.
  */
 hspmd_status hspmd_attn_plan_update(hspmd_attn_plan* plan, const int32_t* cu_seqlens_host, int32_t num_seqs);
-/* hipFree of the lists' device storage: waits for the device to go idle.  NULL is accepted. */
+/* Frees the lists' device storage, if they have any, and waits for the device to go idle either way.  NULL is accepted. */
 hspmd_status hspmd_attn_plan_destroy(hspmd_attn_plan* plan);
 int64_t hspmd_attn_plan_total_tokens(const hspmd_attn_plan* plan); /* -1 on NULL */
 int64_t hspmd_attn_plan_num_items(const hspmd_attn_plan* plan, hspmd_list_kind kind); /* slots incl. padding */

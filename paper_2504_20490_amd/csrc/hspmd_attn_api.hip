@@ -177,6 +177,7 @@ struct hspmd_attn_plan {
     // lists that fit a launch's arguments are kept here instead (forward and dQ share one); items, block_items, queue are then NULL
     bool is_inline = false;
     hspmd::InlineList inline_rows{}, inline_keys{};
+    int device = -1;   // current when the plan was made
     // device copies of the lists
     ListSlot slots[kPlanSlots];
     int current = 0;
@@ -254,10 +255,22 @@ const hspmd::InlineList* inline_list(const hspmd_attn_plan* plan, hspmd_list_kin
 }
 
 // a plan is for a device, also one whose lists need none
-hspmd_status need_device() {
-    int dev = 0;
-    const hipError_t e = hipGetDevice(&dev);
+hspmd_status need_device(hspmd_attn_plan* plan) {
+    const hipError_t e = hipGetDevice(&plan->device);
     return e == hipSuccess ? HSPMD_OK : fail_hip(e, "hipGetDevice(plan)");
+}
+
+// what hipFree does for a plan whose lists are on the device: returns when everything launched there has ended
+hipError_t wait_for_device(int device) {
+    int current = device;
+    hipError_t e = hipGetDevice(&current);
+    if (e == hipSuccess && current != device) e = hipSetDevice(device);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (current != device) {
+        const hipError_t back = hipSetDevice(current);
+        if (e == hipSuccess) e = back;
+    }
+    return e;
 }
 
 // Keeps lists that fit in the plan itself; false: they go to the device.  `all`: the rows list, then the keys list.
@@ -297,7 +310,7 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
     }
-    if (hspmd_status rc = first ? need_device() : HSPMD_OK) return rc;
+    if (hspmd_status rc = first ? need_device(plan) : HSPMD_OK) return rc;
     const bool kept = keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->items);
     if (!kept) {
         // behind the lists: the draw counters of the three passes, uploaded as zeros (one list item = 16 bytes = 4 counters)
@@ -349,7 +362,7 @@ hspmd_status fill_block_plan(hspmd_attn_plan* plan, const int32_t* cu_q, const i
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
     }
-    if (hspmd_status rc = first ? need_device() : HSPMD_OK) return rc;
+    if (hspmd_status rc = first ? need_device(plan) : HSPMD_OK) return rc;
     const bool kept = keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->block_items);
     if (!kept) {
         const size_t counters_at = all.size();
@@ -500,15 +513,21 @@ hspmd_status hspmd_attn_block_plan_update(hspmd_attn_plan* plan, const int32_t* 
 hspmd_status hspmd_attn_plan_destroy(hspmd_attn_plan* plan) {
     if (!plan) return HSPMD_OK;
     hspmd_status rc = HSPMD_OK;
+    bool waited = false;
     for (ListSlot& slot : plan->slots) {
         if (slot.block) {
             const hipError_t e = hipFree(slot.block);   // waits for the device: launches that read the slot have ended
+            waited = true;
             if (e != hipSuccess) rc = fail_hip(e, "hipFree(work lists)");
         }
         if (slot.last_use) {
             const hipError_t e = hipEventDestroy(slot.last_use);
             if (e != hipSuccess) rc = fail_hip(e, "hipEventDestroy(work list slot)");
         }
+    }
+    if (!waited && plan->device >= 0) {   // (below 0: its creation failed before anything could use it)
+        const hipError_t e = wait_for_device(plan->device);
+        if (e != hipSuccess) rc = fail_hip(e, "hipDeviceSynchronize(plan)");
     }
     delete plan;
     return rc;

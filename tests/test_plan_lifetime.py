@@ -30,3 +30,17 @@ out(calls())
     order = "".join({"copy": "c", "wait": "w", "launch": "l", "mark": "m"}.get(what, "") for what, _, _ in calls)
     assert order.count("c") == 7 and order.count("w") == 4, order
     assert order.replace("l", "").replace("m", "") == "ccc" + "wc" * 4, order
+
+
+@pytest.mark.parametrize("lengths", [[17, 64, 111], [900] * 8, [0]])
+def test_destroying_a_plan_waits_for_the_device(stand_in, lengths):
+    """As the header says, also where the lists never were on the device: a caller may free the tensors of its launches next."""
+    program = """
+plan = Plan(args[0], 8, 8, 128)
+plan.forward()
+calls()
+plan.destroy()
+out([what for what, _, _ in calls()])
+"""
+    calls = rec.record(stand_in, program, lengths)[0]
+    assert "free" in calls or "sync" in calls, calls
