@@ -394,18 +394,18 @@ Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots
 }
 
 // Items of one query head are drawn by persistent workgroups up to 48 steps (64 at head_dim up to 112), now that the instructions of
-// the tile loop do not depend on the loop around it: at least 1024 slots (four per compute unit), more than 3.2 steps per slot, no
-// item that alone takes most of the pass.  Measured, one workgroup per item and persistent (us, sustained): 8 x 2048, 32 heads (17
-// steps) 637 and 615; 4400 items of 512 tokens (5) 396 and 331, of 1024 (9) 462 and 426, of 1500 (13) 561 and 537; 8 x 4096, 16
-// heads, head_dim 104 (33) 1032 and 1006; 9 x 6887, 8 heads, head_dim 96 (55) 1312 and 1276; 16384 tokens, 32 heads (37) 1172 and
-// 1161.  Longer items gain nothing (32768 tokens, 24 heads, 58 steps, 2619 and 2620), items of several heads lose (65536 tokens, 32
-// heads on 8, a whole step 34263 and 34880), and so do few (536 items 291 and 298, 672 of 4 steps 41.7 and 42.3) and short ones
-// (2160 of 3 steps 142 and 144, 3136 of one tile 95 and 108).  Worst of 40 packs that the rule sends here: 1561 items, head_dim
-// 104 (6 steps) 131 and 134.
+// the tile loop do not depend on the loop around it: at least 1536 slots (six per compute unit), more than 3.2 steps per slot, no
+// item that alone takes most of the pass.  Measured, one workgroup per item and persistent (us, the same tile loop in both): 8 x 2048,
+// 32 heads (17 steps) 671 and 641; 7 x 1024, 40 heads (9) 252 and 236; 10 x 1448, 16 heads (12) 250 and 237; 24 of 900 and 1025, 12 heads
+// (8) 247 and 239; 8 x 4096, 16 heads, head_dim 104 (33) 1071 and 1053.  Longer items gain nothing (32768 tokens, 24 heads, 58 steps,
+// 2619 and 2620), items of several heads lose (65536 tokens, 32 heads on 8, a whole step 34263 and 34880), and so do short ones (2160
+// of 3 steps 142 and 144, 3136 of one tile 95 and 108).  Of 42 packs of 1120 to 2500 items of one head, five to fifty steps, three
+// widths: above 1536 items 0.95 to 1.02 of the time, 0.99 on average; below, where there are five rounds of items and fewer, 0.99 to 1.02,
+// 1.006 on average (5 x 1300, 24 heads 146 and 148; 8 x 1300, 16 heads, head_dim 104 151 and 156; 7 x 2440, 8 heads 185 and 189).
 bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim) {
     if (form != Dispatch::kWhole || head_dim <= 64) return form == Dispatch::kPersistent;
     const double per_unit = (double)(load.total + 8 * slots) / 256.0;
-    return group == 1 && slots >= 4 * 256 && 5 * load.total > 16 * slots && load.total <= (head_dim > 112 ? 48 : 64) * slots &&
+    return group == 1 && slots >= 6 * 256 && 5 * load.total > 16 * slots && load.total <= (head_dim > 112 ? 48 : 64) * slots &&
            (double)load.heaviest + 8 <= 0.8 * per_unit;
 }
 

@@ -12,8 +12,8 @@ import pytest
 from gpu_util import make_case, to_dev
 from paper_2504_20490_amd import build as lib_build
 
-PACKS = [([1300] * 5, 20, 20, 128), ([1300, 64, 1, 777, 2000, 129] * 2, 20, 20, 104), ([900, 1025] * 6, 12, 12, 128),
-         ([1300, 650] * 4, 18, 18, 80)]
+PACKS = [([1300] * 7, 20, 20, 128), ([1300, 64, 1, 777, 2000, 129] * 3, 14, 14, 104), ([900, 1025] * 8, 12, 12, 128),
+         ([1300, 650] * 4, 24, 24, 80)]
 
 
 @pytest.mark.gpu
@@ -25,7 +25,7 @@ def test_same_bits_as_one_workgroup_per_item(lengths, hq, hkv, d):
     q, k, v, do = (to_dev(x) for x in make_case(lengths, hq, hkv, d, seed=60 + d))
     cu, _, _ = A.build_cu_seqlens(lengths)
     plan = A.Plan(cu, hq, hkv, d)
-    assert plan.num_items(A.LIST_DKV) >= 1024
+    assert plan.num_items(A.LIST_DKV) >= 1536
     o, lse = torch.empty(T, hq, d, dtype=torch.bfloat16, device="cuda"), torch.empty(hq, T, dtype=torch.float32, device="cuda")
     full = lambda h: torch.full((T, h, d), float("nan"), dtype=torch.float32, device="cuda")
     ws = torch.empty(plan.bwd_workspace_bytes(), dtype=torch.uint8, device="cuda")
@@ -59,9 +59,9 @@ def rule(tmp_path_factory):
 
 
 @pytest.mark.parametrize("slots,total,heaviest,d,persistent", [
-    (1024, 1024 * 17, 32, 128, True), (1016, 1016 * 17, 32, 128, False), (1024, 3277, 4, 104, True), (1024, 3276, 4, 104, False),
-    (1024, 1024 * 17, 89, 128, False), (4096, 4096 * 64, 170, 65, True), (4096, 4096 * 49, 170, 113, False),
-    (4096, 4096 * 17, 32, 64, False)])
+    (1536, 1536 * 17, 32, 128, True), (1528, 1528 * 17, 32, 128, False), (1536, 4916, 4, 104, True), (1536, 4915, 4, 104, False),
+    (1536, 1536 * 17, 112, 128, True), (1536, 1536 * 17, 113, 128, False), (4096, 4096 * 64, 170, 65, True),
+    (4096, 4096 * 49, 170, 113, False), (4096, 4096 * 17, 32, 64, False)])
 def test_rule(rule, slots, total, heaviest, d, persistent):
     assert rule(0, total, heaviest, slots, 1, d) == persistent
     assert rule(0, total, heaviest, slots, 2, d) == 0       # items of several heads

@@ -36,3 +36,13 @@ def test_walk_of_the_dkv_pass(stand_in, pack, hq, hkv, d, block, persistent, gro
     (names,) = launched(stand_in, [(pack, hq, hkv, d)])
     width = 64 if d <= 64 else 128
     assert names[-1] == ("bwd_dkv_kernel", (width, block, _steps(d), False, persistent, groups, False))
+
+
+def test_packs_of_the_persistent_pass(stand_in):
+    from test_gpu_persistent_dkv import PACKS
+    for (lengths, hq, hkv, d), names in zip(PACKS, launched(stand_in, PACKS)):
+        assert names[-1] == ("bwd_dkv_kernel", (128, False, _steps(d), False, True, False, False)), (lengths, d)
+    # fewer than six items per compute unit: one workgroup each
+    few = [([1300] * 5, 24, 24, 128), ([1300] * 8, 16, 16, 104), ([2440] * 7, 8, 8, 128)]
+    for pack, names in zip(few, launched(stand_in, few)):
+        assert names[-1] == ("bwd_dkv_kernel", (128, False, _steps(pack[3]), False, False, False, False)), pack
