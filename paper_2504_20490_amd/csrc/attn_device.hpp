@@ -457,6 +457,7 @@ __device__ __forceinline__ ItemGeom load_item(const Params& p, int idx) {
     typedef const i32x4 __attribute__((address_space(4)))* ArgumentWords;
     static_assert(alignof(Params) <= alignof(InlineList), "the list is the next argument, on its own alignment");
     constexpr int kListAt = (int)((sizeof(Params) + alignof(InlineList) - 1) / alignof(InlineList));   // in units of 16 bytes
+    static_assert(!INLINE || kListAt * sizeof(i32x4) + sizeof(InlineList) <= kArgumentBytes, "what a launch may carry");
     if constexpr (BLOCK) {
         hspmd_block_item it;
         if constexpr (INLINE) {
