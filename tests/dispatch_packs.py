@@ -1,7 +1,8 @@
 """Packs that the scheduler's rules send to whole items or to persistent workgroups, with the form of each pass.
 
 Small packs run half items in most passes, so the kernels that large packs run are only met by packs that are chosen for it.
-`test_dispatch.py` holds every pack here to its form on the CPU; `test_gpu_whole_items.py` compares its outputs with the oracle."""
+`test_dispatch.py` holds every pack here to its form on the CPU; `test_gpu_whole_items.py` and `test_gpu_list_kinds.py` compare its
+outputs with the oracle; `test_launched_kernels.py` asks the library which kernels all of them launch together."""
 WHOLE, HALVES, PERSISTENT = 0, 1, 2
 
 # lengths on both sides of the tile edges, up to ten key tiles: every loop of the kernels' tile walk runs
@@ -25,3 +26,22 @@ BLOCKS = [(12, 12, 128, WHOLE, WHOLE), (8, 4, 128, WHOLE, HALVES), (24, 12, 128,
           (32, 16, 64, WHOLE, WHOLE), (12, 12, 104, WHOLE, WHOLE),
           (24, 12, 96, WHOLE, WHOLE),
           (12, 12, 80, WHOLE, WHOLE)]
+
+# ---- the two kinds of list: in the kernels' arguments (up to 240 slots, 120 of a block plan) or in device memory ----
+# lengths on both sides of the tile edges; with one or two heads half items, their lists in the arguments
+EDGES = [1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 257, 449]
+# one long sequence and many short ones: half items whose lists are too long for the arguments, and more of them than the forward
+# has workgroups (544 halves on 512), so that it draws some
+HALF_LONG = [2500] + EDGES + [1 + (i * 53) % 128 for i in range(25)]
+HALF_LONG_PACKS = [(HALF_LONG, 4, 4, d) for d in (40, 64, 80, 96, 104, 128)] + [(HALF_LONG, 6, 2, d) for d in (64, 128)]
+HALF_GEOMETRY = tuple(first + rest for first, rest in zip(([900, 1], [2400, 700], [1700, 300], [0, 0]), GEOMETRY))
+HALF_LONG_BLOCKS = [(HALF_GEOMETRY, 6, 2, d) for d in (64, 80, 96, 104, 128)]
+# short lists: whole items (one tile each) and half items at the widths that have kernels of their own
+ONE_TILE = [1 + (i * 53) % 128 for i in range(29)]
+SHORT_PACKS = [(ONE_TILE, 8, 8, d) for d in (64, 80, 96, 104, 128)] + [(EDGES, 2, 2, d) for d in (64, 80, 96, 104, 128)]
+ONE_TILE_GEOMETRY = ([min(130 - 7 * i, 128) for i in range(14)], [min(5 + 9 * i, 128) for i in range(14)], [40 + i for i in range(14)],
+                     [3 * i for i in range(14)])
+# (one step per item: with two the dQ pass of so few items would take halves)
+ONE_STEP_GEOMETRY = (ONE_TILE_GEOMETRY[0], [min(n, 64) for n in ONE_TILE_GEOMETRY[1]], *ONE_TILE_GEOMETRY[2:])
+SHORT_BLOCKS = [(g, hq, hkv, d) for d in (64, 80, 96, 104, 128)
+                for g, hq, hkv in ((ONE_TILE_GEOMETRY, 8, 8), (ONE_STEP_GEOMETRY, 8, 4), (HALF_GEOMETRY, 2, 1))]

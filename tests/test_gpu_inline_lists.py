@@ -34,22 +34,29 @@ def test_refills_between_the_two_kinds_of_list():
     """Large, small, large, ...: each refill while the launches of the one before may still run."""
     import torch
     import paper_2504_20490_amd as A
-    packs = [[700, 1500, 300], [17, 64, 111], [900, 900, 33], [5], [1, 1300, 800], [128] * 20, [2000, 129]]
+    packs = [[5000, 3000, 1500], [17, 64, 111], [900, 7300, 33], [5], [4100, 1300, 800, 2500], [128] * 20, [2000, 129], [8000]]
+    in_arguments = [False, True, False, True, False, True, True, False]
     bufs = [_Buffers(L, 4, 2, 128, 800 + i) for i, L in enumerate(packs)]
+    longest = lambda plan: max(plan.num_items(kind) for kind in (A.LIST_FWD, A.LIST_DKV))
     fresh = []
-    for b in bufs:
+    for b, short in zip(bufs, in_arguments):
         plan = A.Plan(A.build_cu_seqlens(b.lengths)[0], 4, 2, 128)
+        assert (longest(plan) <= 240) == short, (b.lengths, longest(plan))
         b.launch(A, plan)
         torch.cuda.synchronize()
         fresh.append(b.results())
-        for t in (b.o, b.lse, b.dq, b.dk, b.dv):
-            t.fill_(float("nan"))
-    plan = A.Plan(A.build_cu_seqlens(packs[-2])[0], 4, 2, 128)
-    for b in bufs:
-        plan.update(A.build_cu_seqlens(b.lengths)[0])
-        b.launch(A, plan)
-    torch.cuda.synchronize()
-    for b, want in zip(bufs, fresh):
-        got = b.results()
-        for n in got:
-            assert np.array_equal(got[n], want[n]), (b.lengths, n)
+    for start in (1, 0):                                 # a plan that begins with a short list, and one that begins with a long one
+        for b in bufs:
+            for t in (b.o, b.lse, b.dq, b.dk, b.dv):
+                t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        plan = A.Plan(A.build_cu_seqlens(packs[start])[0], 4, 2, 128)
+        for _ in range(2):
+            for b in bufs:
+                plan.update(A.build_cu_seqlens(b.lengths)[0])
+                b.launch(A, plan)
+        torch.cuda.synchronize()
+        for b, want in zip(bufs, fresh):
+            got = b.results()
+            for n in got:
+                assert np.array_equal(got[n], want[n]), (start, b.lengths, n)

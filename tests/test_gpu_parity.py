@@ -15,7 +15,7 @@ RAGGED = [1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200, 257, 0, 300]
 
 
 def _full_check(lengths, hq, hkv, d, seed, value_scale=1.0, grad_dtype=None, scale=0.0, magnitude_slack=False,
-                slack_roundings=1):
+                slack_roundings=1, ds_peak=False):
     gpu_util.CONTEXT["case"] = f"small pack {len(lengths)} seqs Hq{hq} Hkv{hkv} d{d} seed{seed}"
     q, k, v, do = make_case(lengths, hq, hkv, d, seed, value_scale)
     run = GpuRun(lengths, q, k, v, do, grad_dtype=grad_dtype, scale=scale).run()
@@ -31,8 +31,11 @@ def _full_check(lengths, hq, hkv, d, seed, value_scale=1.0, grad_dtype=None, sca
     assert_close("O", run.host("o"), ro, max_abs=bound(ro))
     lse_peak = float(np.max(np.abs(rlse))) if rlse.size else 0.0
     assert np.max(np.abs(run.host("lse") - rlse)) <= LSE_ABS * (lse_peak / 8.0 if magnitude_slack and lse_peak >= 8.0 else 1.0)
-    assert_close("dQ", run.host("dq"), rdq, max_abs=bound(rdq))
-    assert_close("dK", run.host("dk"), rdk, max_abs=bound(rdk))
+    # ds_peak: the pack's short sequences bring |dS| to 8 and more where no gradient element is (see test_many_tiny_sequences)
+    peak = _max_abs_ds(lengths, f64(q), f64(k), f64(v), f64(do), s) if ds_peak else 0.0
+    through_ds = (lambda ref: gpu_util.magnitude_bound(ref, slack_roundings, peak)) if magnitude_slack else bound
+    assert_close("dQ", run.host("dq"), rdq, max_abs=through_ds(rdq))
+    assert_close("dK", run.host("dk"), rdk, max_abs=through_ds(rdk))
     assert_close("dV", run.host("dv"), rdv, max_abs=bound(rdv))
     gpu_util.CONTEXT["slack"] = None
     return run

@@ -86,15 +86,19 @@ def test_refilled_plan_equals_fresh_plan_and_oracle():
     plan.destroy()
 
 
-def test_steady_state_refills_do_not_allocate():
+@pytest.mark.parametrize("heads,in_arguments", [(4, True), (24, False)])
+def test_steady_state_refills_do_not_allocate(heads, in_arguments):
     import torch
     import paper_2504_20490_amd as A
-    hq, hkv, d = 4, 4, 64
+    hq, hkv, d = heads, heads, 64
     lengths_a, lengths_b = [700, 45, 260, 1, 129], [600, 100, 300, 135]     # similar sizes: b fits the headroom of a
     ba, bb = _Buffers(lengths_a, hq, hkv, d, 801), _Buffers(lengths_b, hq, hkv, d, 802)
     cu_a, _, _ = A.build_cu_seqlens(lengths_a)
     cu_b, _, _ = A.build_cu_seqlens(lengths_b)
     plan = A.Plan(cu_a, hq, hkv, d)
+    for cu in (cu_b, cu_a):
+        plan.update(cu)
+        assert (plan.num_items(A.LIST_FWD) <= 240) == in_arguments
     for i in range(8):                      # every slot of the ring has been sized by now
         plan.update(cu_b if i % 2 == 0 else cu_a)
         (bb if i % 2 == 0 else ba).launch(A, plan)
@@ -119,10 +123,11 @@ def test_steady_state_refills_do_not_allocate():
     plan.destroy()
 
 
-def test_block_plan_refill_equals_fresh_block_plan():
+@pytest.mark.parametrize("hq,hkv,in_arguments", [(4, 2, True), (64, 32, False)])
+def test_block_plan_refill_equals_fresh_block_plan(hq, hkv, in_arguments):
     import torch
     import paper_2504_20490_amd as A
-    hq, hkv, d = 4, 2, 128
+    d = 128
     geoms = [([200, 64], [300, 10], [300, 0], [0, 0]), ([128, 1], [128, 500], [0, 499], [0, 0]),
              ([77, 300], [77, 300], [0, 0], [0, 0])]
 
@@ -139,6 +144,7 @@ def test_block_plan_refill_equals_fresh_block_plan():
     fresh = []
     for i, (ql, kl, qp, kp) in enumerate(geoms):
         plan = A.BlockPlan(cuof(ql), cuof(kl), qp, kp, hq, hkv, d)
+        assert (max(plan.num_items(A.LIST_FWD), plan.num_items(A.LIST_DKV)) <= 120) == in_arguments
         o, lse = run(plan, ql, kl, 900 + 2 * i)
         torch.cuda.synchronize()
         fresh.append((_bits(o), _bits(lse)))
@@ -146,12 +152,13 @@ def test_block_plan_refill_equals_fresh_block_plan():
     ql, kl, qp, kp = geoms[0]
     plan = A.BlockPlan(cuof(ql), cuof(kl), qp, kp, hq, hkv, d)
     outs = [run(plan, ql, kl, 900)]
-    for i, (ql, kl, qp, kp) in enumerate(geoms[1:], start=1):
+    for i in [1, 2, 1, 0, 2, 1, 0]:          # more refills than slots, another list in a slot each time
+        ql, kl, qp, kp = geoms[i]
         plan.update(cuof(ql), cuof(kl), qp, kp)
         assert plan.total_tokens == sum(ql) and plan.total_kv_tokens == sum(kl)
         outs.append(run(plan, ql, kl, 900 + 2 * i))
     torch.cuda.synchronize()
-    for i, (o, lse) in enumerate(outs):
+    for i, (o, lse) in zip([0, 1, 2, 1, 0, 2, 1, 0], outs):
         assert np.array_equal(_bits(o), fresh[i][0]) and np.array_equal(_bits(lse), fresh[i][1]), f"block geometry {i}"
     plan.destroy()
 

@@ -2,17 +2,18 @@
 
 Packs whose longest item outlasts the rest of a pass: the items are then shared out to two workgroups.  Parity with the
 oracle where that split has its edges: a half without any key, a half of one key, one tile or an odd number of them per
-head, groups of query heads (whose tiles follow one another in one item), head_dim below the tile width."""
+head, groups of query heads (whose tiles follow one another in one item), head_dim below the tile width.  The
+lists of these packs travel in the kernels' arguments; `test_gpu_list_kinds.py` has the same edges with lists on the device."""
 import numpy as np
 import pytest
 
 import oracle
+from dispatch_packs import EDGES   # (the longest decides that halves are taken)
 from gpu_util import GpuRun, LSE_ABS, assert_close, default_scale, f64, make_case, magnitude_bound
 from test_gpu_parity import _full_check
 
 pytestmark = pytest.mark.gpu
 
-EDGES = [1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 257, 449]   # (the longest decides that halves are taken)
 MANY_SHORT = [1 + (i * 37) % 131 for i in range(40)] + [449] * 24
 
 

@@ -46,3 +46,36 @@ def test_packs_of_the_persistent_pass(stand_in):
     few = [([1300] * 5, 24, 24, 128), ([1300] * 8, 16, 16, 104), ([2440] * 7, 8, 8, 128)]
     for pack, names in zip(few, launched(stand_in, few)):
         assert names[-1] == ("bwd_dkv_kernel", (128, False, _steps(pack[3]), False, False, False, False)), pack
+
+
+HALVES = {"fwd_kernel": 3, "bwd_dq_kernel": 3, "bwd_dkv_kernel": 3}      # the template argument that says half items
+
+
+def test_half_items_of_either_kind_of_list(stand_in):
+    long_lists, short_lists = packs.HALF_LONG_PACKS + packs.HALF_LONG_BLOCKS, [c for c in packs.SHORT_PACKS if c[0] is packs.EDGES]
+    short_lists += [c for c in packs.SHORT_BLOCKS if c[0] is packs.HALF_GEOMETRY]
+    for cases, in_arguments in ((long_lists, False), (short_lists, True)):
+        for case, names in zip(cases, launched(stand_in, cases)):
+            names = [k for k in names if k[0] in HALVES]
+            assert len(names) == 3
+            for name, args in names:
+                assert args[3] and args[-1] == in_arguments, (case, name, args)
+
+
+def test_every_attention_kernel_is_compared_with_the_oracle(stand_in):
+    """The packs of the GPU tests named in dispatch_packs reach every instance of the attention kernels that the library holds."""
+    from test_gpu_split_items import MANY_SHORT
+    cases = [c[:4] for c in packs.PACKED + packs.PERSISTENT_PACKS] + [(packs.GEOMETRY, *c[:3]) for c in packs.BLOCKS]
+    cases += packs.HALF_LONG_PACKS + packs.HALF_LONG_BLOCKS + packs.SHORT_PACKS + packs.SHORT_BLOCKS + [(MANY_SHORT, 16, 8, 104)]
+    seen = {k for names in launched(stand_in, cases) for k in names}
+    program = """
+name, names = ctypes.c_char_p(), []
+for i in range(fake.fake_kernels(0, ctypes.byref(name))):
+    fake.fake_kernels(i, ctypes.byref(name))
+    names.append(name.value.decode())
+out(names)
+"""
+    held = {rec.kernel(n) for n in rec.record(stand_in, program)[0]}
+    attention = {k for k in held if k[0] in HALVES}
+    assert len(attention) > 100
+    assert not attention - seen, sorted(attention - seen)
