@@ -325,8 +325,8 @@ hspmd_status hspmd_attn_block_bwd_rope(const hspmd_attn_plan* plan, const void* 
  * queue divided by the workgroups resident per XCD and the time of its heaviest item alone; passes that
  * work on half items take a share of these; backward = dQ pass + dK/dV pass.  The coefficients are fitted
  * per width class of head_dim (up to 64, 80, 96, 112, 128) to measured kernel times
- * (paper_2504_20490_amd/fit_cost_model.py refits them): forward and backward have a mean error of 4-7 %,
- * 95 % of the packs are within 20 and 14 %, all of them within 30 %.  Host-side plan creation is not included.
+ * (paper_2504_20490_amd/fit_cost_model.py refits them): forward and backward have a mean error of 7 and 5 %,
+ * 95 % of the packs are within 20 and 13 %, all of them within 36 and 25 %.  Host-side plan creation is not included.
  */
 hspmd_status hspmd_attn_estimate_ms(const int32_t* cu_seqlens, int32_t num_seqs, int32_t local_q_heads,
                                     int32_t local_kv_heads, int32_t head_dim, double* fwd_ms, double* bwd_ms);

@@ -131,9 +131,10 @@ __device__ __forceinline__ bf16x8 lds_read_tr(const char* lds, int a0, int a1) {
 // what overlaps, and left to scheduling hints it depended on what surrounded the loop: inside a loop over items one phase's 16
 // LDS reads ended up behind its MFMAs.  Against the hints (us, sustained): half items of 2 sequences, 8 heads 36.9 -> 33.8; blocks
 // of a ring of four over 32768 tokens, 24 heads 350 -> 338 each; 8 x 4096, 16 heads, head_dim 104 1000 -> 974; long packs, which
-// the power limit decides, unchanged.  The exp work is spread evenly: in the first 12 of 16 steps it takes 5 % longer.  Whole items of tile width 64 have two waves per SIMD, which
-// cover each other, and less MFMA work per score: there the compiler orders each phase by a hint (short sequences 68.8 us against
-// 70.2 step by step), and so do some items of several query heads, see dkv_iteration_hinted.
+// the power limit decides, unchanged.  The exp work is spread evenly: in the first 12 of 16 steps it takes 5 % longer.  Whole items of
+// tile width 64 have two waves per SIMD, which cover each other, and less MFMA work per score: there the compiler orders each phase by
+// a hint (short sequences 68.8 us against 70.2 step by step), and so it does for some items of several query heads, see
+// dkv_iteration_hinted.
 template <int D, int KD, int RB, bool MASK, bool SPREAD, bool WHOLE>
 __device__ __forceinline__ void dkv_iteration(DkvState<D, KD>& st, const char* lds, const DkvAddr<D, KD>& ahead,
                                               const DkvAddr<D, KD>& cur, int dkey, float c, const DkvTileLoad<D>& load) {

@@ -65,8 +65,9 @@ struct BwdParams {
     int32_t num_items;             // slots of the current pass's work list (padding included)
     int32_t* queue;                // the current pass's draw counters (ItemQueue), zero between launches
     int32_t split;                 // the pass works on half items (decided from the plan's loads, see pass_dispatch)
-    int32_t persist;               // dK/dV pass of a packed plan with whole items: 1 persistent workgroups (see pass_dispatch),
-                                   // 2 the same where the device's size is known (see persistent_dkv), 0 one per item
+    int32_t persist;               // dK/dV pass of a packed plan with whole items: 1 persistent workgroups (see pass_dispatch), an
+                                   // error where the device's size is unknown; 2 the same (see persistent_dkv), but there one
+                                   // workgroup per item: those packs need no size; 0 one per item
 };
 
 // The kernels exist for tile widths 64 and 128 (LDS rows, MFMA contraction); a head_dim below the tile width runs

@@ -66,7 +66,9 @@ int64_t item_cost(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t g
 // tokens, 16 heads (2 x 2496 items) 231 -> 38 us; 14 sequences, 32 heads on 8 (16576 + 4144 items) 167 -> 67 us.
 namespace {
 
-// workgroups that an XCD holds at once: two per compute unit in the forward and dQ passes, one in the dK/dV pass (tile width 128)
+// Workgroups that an XCD holds at once: two per compute unit in the forward and dQ passes, one in the dK/dV pass.  At tile width 64 a
+// unit holds three of the dQ and two of the dK/dV pass; a list does not know its width, and the lines drawn with these numbers hold
+// there too (order_last_items on ten packs of width 64: forward 0.85 to 1.01 of the time, dQ 0.87 to 1.00, dK/dV 0.82 to 1.01).
 constexpr int32_t kResidentRows = 64, kResidentKeys = 32;
 
 // A run of items of one sequence's chain; the chains of all `copies` kv heads of the sequence hold it.
@@ -200,8 +202,8 @@ __attribute__((noinline)) void order_last_items(const std::vector<SegmentClass>&
 
 // chain_len(s): items of one kv head's chain of sequence s, most expensive first; cost_of(s, i): of its i-th item;
 // make(s, g, i): that item for kv head g; cost_of_item(item): its cost.  finer_slots: workgroups that a queue holds at once, for
-// lists whose chains may be cut finer and whose end may go by cost (chains with several query heads keep the coarse cut and their
-// order, so that a group's heads of one tile stay together), else 0.
+// lists whose chains may be cut finer and whose end may go by cost, else 0 (rows lists of grouped heads: a finer cut would part the
+// heads of one tile, and an end by cost has not been measured there).
 template <typename Item, typename ChainLen, typename Cost, typename Make, typename ItemCost>
 std::vector<Item> place_chains(int32_t num_seqs, int32_t kv_heads, int32_t num_queues, int32_t finer_slots, ChainLen chain_len,
                                Cost cost_of, Make make, ItemCost cost_of_item, Item pad) {
@@ -357,7 +359,8 @@ bool split_rows(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32
 // (8 KV heads of 4) 85 and 61; 238 steps, 118 per slot (one head, width 128) 306 and 259; but 196 steps, 136 per slot 290 and
 // 321; 3 steps, 168 items 17 and 23; 8 x 2048, 32 heads 652 and 826; 10 x 512, 4 heads (160 items) 22.9 and 30.1; width 64,
 // one document of 16384 tokens, 2 heads 216 and 229.  Of the same packs none that this rule halves takes more than 1.01 of its
-// time whole, 0.85 on average.
+// time whole, 0.85 on average.  (Since then the halves' tile loop has become 8 % faster, 36.9 -> 33.8 us on 2 sequences, 8 heads, and the
+// whole items' by 0 to 5 %; the line is the one drawn before that and errs towards whole items.)
 bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
     const double heaviest = (double)load.heaviest, total = (double)load.total, items = (double)slots;
     const double units = 256.0;   // compute units; whole items of tile width 64 fit a unit twice
@@ -373,12 +376,12 @@ bool split_dkv(const PassLoad& load, int64_t slots, int32_t head_dim) {
 // One workgroup fits a compute unit there, so the time between two of them is exposed, most of all, by the measurements, where
 // chains of two, four or eight items bring heavy and light items up in step with the order in which an XCD hands its
 // workgroups out.  Against that, the next item's loads wait for the last one's stores inside a workgroup, which short items
-// feel.  (Longer items: persistent_dkv below.)  Measured, one workgroup per item and persistent (us, head_dim 128, with a tile
-// loop that still lost 2-4 % in an item loop): 33 x 400 tokens, 16 heads (4 steps) 179 and 148; 78 x 512, 16 heads
-// (5) 442 and 390; 67 x 300, 8 heads (3) 98 and 105; 43 x 64, 24 heads (1) 47 and 52; 18 sequences of up to 2734, 16 heads
-// (9.9) 164 and 174; 5 x 1300, 24 heads (11) 140 and 153; 438 sequences, one of 3026, one head (5, the longest 48) 72 and 79;
-// head_dim 104, 7 x 1024, 40 heads (9) 247 and 233.  Over 114 packs at three widths persistent workgroups take 0.77 to 1.02 of
-// the time, 0.93 on average.
+// feel.  Measured, one workgroup per item and persistent (us, head_dim 128, the same tile loop in both): 33 x 400 tokens, 16 heads
+// (4 steps) 179 and 140; 78 x 512, 16 heads (5) 434 and 362; 67 x 300, 8 heads (3) 99 and 100; 43 x 64, 24 heads (1) 47 and 47; 438
+// sequences, one of 3026, one head (5, the longest 48) 70.5 and 69.8; head_dim 104, 7 x 1024, 40 heads (9) 238 and 221, head_dim 96, 40 x
+// 512, 16 heads 200 and 177; items of two heads: 66 x 400, 16 heads on 8 255 and 190; head_dim 104, 39 x 512, 32 on 16 327 and 274.
+// The upper bounds were drawn with a tile loop that lost 2-4 % inside an item loop.  Items of one head go on to persistent_dkv; for
+// items of several heads they are on the safe side (head_dim 104, 16 x 1000, 32 heads on 16, 17 steps, 356 and 333, is not taken).
 bool short_items(const PassLoad& load, int64_t slots, int32_t head_dim) {
     const double per_unit = (double)(load.total + 8 * slots) / 256.0;
     return slots >= 4 * 256 && 5 * load.total > 16 * slots && load.total <= (head_dim > 112 ? 6 : 9) * slots &&
@@ -416,8 +419,9 @@ bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t 
 // powers: where they are close, part of the chip idles at the end): the weight of the heaviest XCD queue -- steps x step time
 // + a fixed time per item -- shared by the workgroups that an XCD holds, and the heaviest item on a chip that is otherwise
 // idle.  Half items take the stated shares of a whole one's times.  Fitted by relative least squares to 124 packs at each of
-// five widths: mean |error| 5-7 % per pass, 95 % of the packs within 21 %, the others (passes of a few steps per item or
-// with a single item per workgroup) within 40 %.
+// five widths, before the dK/dV loop was written step by step and short lists went into the arguments; with these kernels the mean
+// |error| on such packs is 6-8 % per pass, 95 % of them are within 20 %, the others (passes of a few steps per item or with a single
+// item per workgroup) within 43 %.  A new fit would take off half a percent of the mean.
 namespace {
 
 struct PassCost { double step_us, item_us, alone_us; };               // alone_us: a step with one workgroup per unit or fewer
