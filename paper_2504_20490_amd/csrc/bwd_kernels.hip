@@ -57,29 +57,35 @@ __global__ __launch_bounds__(kThreads) void bwd_dsum_kernel(BwdParams p) {
 // sequences of 32 .. 512 tokens, 16 heads: 55 -> 48 us; 8 x 2048, 32 heads: 244 -> 230 us.
 // SPLIT: a workgroup takes half an item, 64 rows; two waves share each 32-row block, one takes the first 32-key block of
 // every tile, the other the second, and their sums meet in LDS at the end (as in the forward).
-// List: nothing, or InlineList when the work list is the second argument.
-template <int D, bool BLOCK, int KD, bool SPLIT, typename... List>
-__global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(BwdParams p, List...) {
+// More: InlineList when the work list is the second argument; TwoTeams when two teams of four waves take an item's key tiles in
+// turn (the workgroup then has eight waves), see fwd_kernel.
+template <int D, bool BLOCK, int KD, bool SPLIT, typename... More>
+__global__ __launch_bounds__(kThreads * teams_of<More...>, (D == 64 && teams_of<More...> == 1 ? 3 : 2)) void bwd_dq_kernel(BwdParams p, More...) {
+    constexpr int TEAMS = teams_of<More...>;
     static_assert(KD >= 1 && KD <= D / 16, "k-steps inside the tile width");
     constexpr int BQ = SPLIT ? kFwdQTile / 2 : kFwdQTile, BK = kFwdKTile;
     constexpr int KK = KD, DB = (KD + 1) / 2;   // DB: 32-column blocks of dQ that hold data
     constexpr int kTileBytes = BK * D * 2;
-    __shared__ __attribute__((aligned(1024))) char lds[2 * 2 * kTileBytes];   // {K, V} x 2 stages
+    constexpr int kTeamBytes = 2 * 2 * kTileBytes;   // {K, V} x 2 stages
+    constexpr int kRowBlocks = BQ / 32, kShares = TEAMS * (SPLIT ? 2 : 1);   // waves that share a row block
+    __shared__ __attribute__((aligned(1024))) char lds[TEAMS * kTeamBytes];
 
     // packed variant: this pass also produces the row statistics (see below); the constants that go with them
     if (!BLOCK && blockIdx.x == 0 && threadIdx.x < 16) p.ninf_pad[threadIdx.x] = -INFINITY;
     // workgroups p and p + 8 of 16 take the halves of an item, the second, which sees more keys, before the first
     const int slot = SPLIT ? (int)(blockIdx.x / (2 * kQueues)) * kQueues + (int)(blockIdx.x % kQueues) : (int)blockIdx.x;
     if (SPLIT && slot >= p.num_items) return;
-    const ItemGeom item = load_item<BLOCK, sizeof...(List) != 0>(p, slot);
+    const ItemGeom item = load_item<BLOCK, has_inline_list<More...>>(p, slot);
     if (item.tile < 0) return;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = TEAMS > 1 ? wave_id & 3 : wave_id, team = TEAMS > 1 ? wave_id >> 2 : 0;
     const int Lq = item.q_len, L = item.k_len, off = item.offset;   // L: keys of the chunk (= rows when !BLOCK)
     const int h = item.head, hk = h / p.group;
     const int q_row0 = item.tile * kFwdQTile + (SPLIT ? (1 - (int)(blockIdx.x / kQueues % 2)) * BQ : 0);
     if (SPLIT && q_row0 >= Lq) return;   // the last item of a sequence may have no second half
     const int row_block = SPLIT ? wave & 1 : wave, key_block = SPLIT ? wave >> 1 : 0;   // this wave's 32 rows; its keys of a tile
+    const int share = team * (SPLIT ? 2 : 1) + key_block;
     const int wave_row0 = q_row0 + row_block * 32;
     const int my_row = wave_row0 + (lane & 31);
     const int hh = lane >> 5;
@@ -96,10 +102,15 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
 
     // key j is visible to row r iff j <= r + off: the tile's last row sees keys 0 .. kv_end-1
     const int kv_end = max(0, min(L, min(Lq, q_row0 + BQ) + off));
-    const int n_tiles = (kv_end + BK - 1) / BK;
-    if (BLOCK && n_tiles == 0) {
+    const int item_tiles = (kv_end + BK - 1) / BK, n_passes = (item_tiles + TEAMS - 1) / TEAMS;
+    // the team's tiles: tile kt of team `team` is tile TEAMS * kt + team of the item
+    auto share_of = [=](int n) { return (n - team + TEAMS - 1) / TEAMS; };   // the team's part of the item's first n tiles
+    auto tile_of = [=](int kt) { return TEAMS > 1 ? kt * TEAMS + team : kt; };
+    auto first_key = [=](int kt) { return tile_of(kt) * BK; };
+    const int n_tiles = share_of(item_tiles);
+    if (BLOCK && n_passes == 0) {
         // nothing visible: this block's share of dQ is zero
-        if (valid && key_block == 0 && !p.dq_accumulate) {
+        if (valid && share == 0 && !p.dq_accumulate) {
             float* row = static_cast<float*>(p.dq) + ((int64_t)(item.q_start + my_row) * p.q_heads + h) * hd;
 #pragma unroll
             for (int c4 = 0; c4 < D / 8; ++c4)
@@ -111,9 +122,11 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
 
     TileCopy<D, BK> kvcopy;   // K and V share stride and geometry
     kvcopy.init(p.kv_stride, wave, lane, hd);
-    const uint32_t lds0 = lds_address(lds);   // copy destinations are LDS byte addresses
-    kvcopy.issue(lds0, kbase, p.kv_stride, 0, L, wave, lane);
-    kvcopy.issue(lds0 + kTileBytes, vbase, p.kv_stride, 0, L, wave, lane);
+    const uint32_t lds0 = lds_address(lds) + team * kTeamBytes;   // copy destinations are LDS byte addresses
+    if (TEAMS == 1 || n_tiles > 0) {
+        kvcopy.issue(lds0, kbase, p.kv_stride, first_key(0), L, wave, lane);
+        kvcopy.issue(lds0 + kTileBytes, vbase, p.kv_stride, first_key(0), L, wave, lane);
+    }
 
     // Q and dO rows of this lane.  The packed variant owns every (row, head) exactly once in this pass, so it
     // also computes the row statistic D = <dO, O> here (no separate pass over O and dO) and leaves -D and
@@ -173,7 +186,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
         negd = -(d_part + partner32(d_part));            // the two half rows of lanes l and l + 32
         const float nlse = valid ? -stat_a / p.scale : -INFINITY;   // rows past the end get P = 0
         nlse2 = nlse * c;                                                // -LSE log2(e)
-        if (valid && hh == 0 && key_block == 0) {
+        if (valid && hh == 0 && share == 0) {
             p.negd[stat] = negd;
             p.nlse[stat] = nlse;
         }
@@ -202,8 +215,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
             tr[db][1] = tile_offset<D>(row + 8, col);
         }
     }
-    if constexpr (SPLIT) {
-        const int skip = key_block * 32 * D * 2;
+    if constexpr (kShares > 1) {
+        const int skip = team * kTeamBytes + key_block * 32 * D * 2;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) rm[kk] += skip;
 #pragma unroll
@@ -282,13 +295,13 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
         const char* vtile = ktile + kTileBytes;
         if (kt + 1 < n_tiles) {
             const uint32_t next = lds0 + ((kt + 1) & 1) * (2 * kTileBytes);
-            kvcopy.issue(next, kbase, p.kv_stride, (kt + 1) * BK, L, wave, lane);
-            kvcopy.issue(next + kTileBytes, vbase, p.kv_stride, (kt + 1) * BK, L, wave, lane);
+            kvcopy.issue(next, kbase, p.kv_stride, first_key(kt + 1), L, wave, lane);
+            kvcopy.issue(next + kTileBytes, vbase, p.kv_stride, first_key(kt + 1), L, wave, lane);
         }
         auto none = [](int, int) {};
 #pragma unroll
         for (int jb = 0; jb < (SPLIT ? 1 : 2); ++jb) {
-            const int kb = kt * BK + (SPLIT ? key_block : jb) * 32;
+            const int kb = first_key(kt) + (SPLIT ? key_block : jb) * 32;
             if (!kMask || kb <= wave_limit) block(ktile, vtile, jb, kb, masked, std::false_type{}, none);
         }
     };
@@ -303,26 +316,27 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
         const char* ktile = lds + par * (2 * kTileBytes);
         const char* vtile = ktile + kTileBytes;
         const uint32_t next = lds0 + (1 - par) * (2 * kTileBytes);
-        const uint16_t* k_row = kbase + (int64_t)(kt + 1) * BK * p.kv_stride;
-        const uint16_t* v_row = vbase + (int64_t)(kt + 1) * BK * p.kv_stride;
+        const uint16_t* k_row = kbase + (int64_t)tile_of(kt + 1) * BK * p.kv_stride;
+        const uint16_t* v_row = vbase + (int64_t)tile_of(kt + 1) * BK * p.kv_stride;
         auto piece = [&](int jb, int i) {
             constexpr int kPerTile = TileCopy<D, BK>::kPerWave;
             if (SPLIT ? i < kPerTile : jb == 0) kvcopy.issue_full_one_at(i, next, k_row, wave);
             else kvcopy.issue_full_one_at(SPLIT ? i - kPerTile : i, next + kTileBytes, v_row, wave);
         };
         if constexpr (SPLIT) {
-            block(ktile, vtile, 0, kt * BK + key_block * 32, std::false_type{}, std::true_type{}, piece);
+            block(ktile, vtile, 0, first_key(kt) + key_block * 32, std::false_type{}, std::true_type{}, piece);
         } else {
-            block(ktile, vtile, 0, kt * BK, std::false_type{}, std::true_type{}, piece);
-            block(ktile, vtile, 1, kt * BK + 32, std::false_type{}, std::true_type{}, piece);
+            block(ktile, vtile, 0, first_key(kt), std::false_type{}, std::true_type{}, piece);
+            block(ktile, vtile, 1, first_key(kt) + 32, std::false_type{}, std::true_type{}, piece);
         }
     };
     // separate loops instead of tests per tile: tiles wholly below the diagonal (with and without a whole
     // successor), then the (at most two) tiles on the diagonal
     // tiles whose every key exists and is visible to every row of this q tile (with the shift, keys past the end
     // of the chunk need the mask: the last, partial tile is never an interior one)
-    const int n_interior = BLOCK ? max(0, min(min(n_tiles, (q_row0 + off + 1) / BK), L / BK)) : min(n_tiles, q_row0 / BK);
-    const int n_spread = max(0, min(min(n_interior, n_tiles - 1), L / BK - 1));
+    const int item_interior = BLOCK ? max(0, min(min(item_tiles, (q_row0 + off + 1) / BK), L / BK)) : min(item_tiles, q_row0 / BK);
+    const int n_interior = TEAMS > 1 ? share_of(item_interior) : item_interior;
+    const int n_spread = max(0, min(min(n_interior, n_tiles - 1), share_of(L / BK) - 1));
     int kt = 0;
     // the long loop of a long sequence runs in pairs (even tile, odd tile) with constant stage offsets
     for (; kt + 1 < n_spread; kt += 2) {
@@ -332,35 +346,39 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
     for (; kt < n_spread; ++kt) step_spread(kt, kt & 1);
     for (; kt < n_interior; ++kt) step(kt, std::false_type{});
     for (; kt < n_tiles; ++kt) step(kt, std::true_type{});
+    if (TEAMS > 1 && kt < n_passes) __syncthreads();   // the other team's last tile
 
-    if constexpr (SPLIT) {
+    if constexpr (kShares > 1) {
         __syncthreads();   // every wave has left the tile loop
-        char* const area = lds + 2 * kTileBytes + row_block * (32 * D * 4);
-        if (key_block == 1) {
+        constexpr int kArea = 32 * D * 4;
+        auto area = [&](int x) { return lds + (x * kRowBlocks + row_block) * kArea; };   // of share x; share 0's is where dQ is staged
+        if (share > 0) {
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4)
-                    *reinterpret_cast<f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16) =
+                    *reinterpret_cast<f32x4*>(area(share) + ((db * 4 + i4) * 64 + lane) * 16) =
                         f32x4{acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]};
         }
         __syncthreads();
-        if (key_block == 0) {
+        if (share == 0) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+            for (int x = 1; x < kShares; ++x)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const f32x4 y = *reinterpret_cast<const f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16);
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[db][4 * i4 + j] += y[j];
-                }
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const f32x4 y = *reinterpret_cast<const f32x4*>(area(x) + ((db * 4 + i4) * 64 + lane) * 16);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc[db][4 * i4 + j] += y[j];
+                    }
         }
     }
     if (p.rope_table != nullptr) {
         // dQ with respect to the queries before their rotary embedding; row positions inside the sequence
         __syncthreads();
         char* wave_lds = lds + row_block * (32 * D * 4);
-        if (SPLIT && key_block == 1) return;
+        if (kShares > 1 && share > 0) return;
         const int64_t first_elem = ((int64_t)(item.q_start + wave_row0) * p.q_heads + h) * hd;
         const float* table_row0 = p.rope_table + (int64_t)(item.q_pos + wave_row0) * hd;
         if (BLOCK && p.dq_accumulate)
@@ -373,7 +391,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
         // whole rows per store instruction, staged through LDS (free once every wave has left the tile loop)
         __syncthreads();
         char* wave_lds = lds + row_block * (32 * D * 4);
-        if (SPLIT && key_block == 1) return;
+        if (kShares > 1 && share > 0) return;
         float* first_row = static_cast<float*>(p.dq) + ((int64_t)(item.q_start + wave_row0) * p.q_heads + h) * hd;
         const int rows = min(32, Lq - wave_row0);
         if (BLOCK && p.dq_accumulate)
@@ -382,7 +400,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void bwd_dq_kernel(Bwd
             store_tile_f32<D, false>(wave_lds, acc, p.scale, first_row, (int64_t)p.q_heads * hd, rows, hd, lane);
     } else {
         __syncthreads();
-        if (SPLIT && key_block == 1) return;
+        if (kShares > 1 && share > 0) return;
         store_tile_bf16<D>(lds + row_block * (32 * D * 2), acc, p.scale,
                            static_cast<uint16_t*>(p.dq) + ((int64_t)(item.q_start + wave_row0) * p.q_heads + h) * hd,
                            (int64_t)p.q_heads * hd, min(32, Lq - wave_row0), hd, lane);
@@ -407,7 +425,20 @@ namespace {
 
 template <int D, int KD, typename... List>
 void launch_dq(const BwdParams& p, int64_t num_items, bool block, bool split, hipStream_t stream, const List&... list) {
-    const dim3 grid((unsigned)(split ? (num_items + kQueues - 1) / kQueues * kQueues * 2 : num_items)), threads(kThreads);
+    const dim3 grid((unsigned)(split ? (num_items + kQueues - 1) / kQueues * kQueues * 2 : num_items)), threads(kThreads), both_teams(2 * kThreads);
+    const TwoTeams two{};
+    if constexpr (sizeof...(List) == 0) {   // (whole items: only lists too long for the arguments)
+        if (p.teams == 2 && !split) {
+            hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, false, TwoTeams>), grid, both_teams, 0, stream, p, two);
+            return;
+        }
+    }
+    if constexpr (sizeof...(List) != 0) {   // (half items: only lists in the arguments)
+        if (p.teams == 2 && split) {
+            hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, true, List..., TwoTeams>), grid, both_teams, 0, stream, p, list..., two);
+            return;
+        }
+    }
     if (block && split) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, true, List...>), grid, threads, 0, stream, p, list...);
     else if (block) hipLaunchKernelGGL((bwd_dq_kernel<D, true, KD, false, List...>), grid, threads, 0, stream, p, list...);
     else if (split) hipLaunchKernelGGL((bwd_dq_kernel<D, false, KD, true, List...>), grid, threads, 0, stream, p, list...);

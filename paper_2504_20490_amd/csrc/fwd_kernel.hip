@@ -93,12 +93,12 @@ __device__ __forceinline__ float pair_max(float x) {
 // SPREAD: the iteration also issues this wave's share of the copies of K(kt+2) and V(kt+1), both whole
 // tiles, one instruction per MFMA step of phase A.  Issued back to back after the barrier, the copies of
 // all waves queue up in front of the CU's one address unit.
-// BLOCK and NB = 1: a lane's row may have no visible key so far, or, with half of the keys, none with a finite score (its
+// SOME (block variant, half items, teams): a lane's row may have no visible key so far, or, with a share of the keys, none with a finite score (its
 // running max is still -inf): the maximum that the exponentials are taken against is then replaced by 0, which keeps every
 // weight and the rescale factor at 0.
 // NB = 1: the wave's only 32-key block of the tile is part of the addresses; its eight score pairs all go under the
 // MFMAs of phase A, the copies too (two per step where the phase has fewer steps than copies).
-template <int D, int KD, int NB, bool MASK, bool LAST, bool SPREAD, bool BLOCK>
+template <int D, int KD, int NB, bool MASK, bool LAST, bool SPREAD, bool SOME>
 __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const char* kbuf, const char* vbuf, float c,
                                               int dkey /* my_row - key0 - 4 * (lane / 32) */,
                                               const FwdTileLoad<D>& load) {
@@ -127,7 +127,7 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const cha
     // becomes rare after the first tiles.  (-inf - -inf = NaN compares false: a row without a visible key keeps -inf.)
     constexpr float kMaxSlack = 8.f;
     const float m_new = (tmax - st.m) * c > kMaxSlack ? tmax : st.m;
-    const float m_ref = ((BLOCK || NB == 1) && m_new == -INFINITY) ? 0.f : m_new;
+    const float m_ref = (SOME && m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = fast_exp2((st.m - m_ref) * c);
     const float mc = m_ref * c;
     if (__any(m_new > st.m)) {      // wave-uniform: skip the accumulator rescale when no lane's max moved
@@ -267,27 +267,37 @@ __device__ __forceinline__ void fwd_iteration(FwdState<D, KD, NB>& st, const cha
 // SPLIT: the unit of work is half an item, 64 rows; two waves share each 32-row block, one takes the first 32-key block of
 // every tile, the other the second, each with a running maximum and sum of its own, and their results meet in LDS at the
 // end.  Same copies and LDS per tile, half the products: for packs whose longest item outlasts the rest of the pass.
-// List: nothing, or InlineList when the work list is the second argument.
-template <int D, bool BLOCK, int KD, bool SPLIT, typename... List>
-__global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) {
+// More: InlineList when the work list is the second argument; TwoTeams when two teams of four waves take an item's key tiles in
+// turn (the workgroup then has eight waves).
+// Two teams: what bounds a pass whose longest item outlasts the rest is the number of iterations of that item, each of which takes a
+// step's latency (barrier, first operand reads, softmax chain) whatever else is idle.  With the tiles dealt out in turn there are
+// half as many; a SIMD then holds a wave of either team, as it does with two workgroups per unit.  The teams hold a maximum and a sum of
+// their own and meet in LDS, as the halves of a tile do.  One head of 8192 tokens 88.9 -> 68.9 us (half items), 5 heads of 16001 321 ->
+// 310 (whole), width 64, 8 heads of 8192 99 -> 86.  The choice is in teams_of_rows.
+template <int D, bool BLOCK, int KD, bool SPLIT, typename... More>
+__global__ __launch_bounds__(kThreads * teams_of<More...>, 2) void fwd_kernel(FwdParams p, More...) {
+    constexpr int TEAMS = teams_of<More...>;
     using G = FwdGeom<D, KD>;
     constexpr int BQ = SPLIT ? kFwdQTile / 2 : kFwdQTile, BK = kFwdKTile;
     constexpr int NB = SPLIT ? 1 : 2;
     constexpr int KK = G::KK, DB = G::DB;
     constexpr int kTileBytes = G::kTileBytes;
-    // K tiles kt+1 / kt+2 and V tiles kt / kt+1: two buffers each
-    __shared__ __attribute__((aligned(1024))) char lds[4 * kTileBytes];
+    constexpr int kTeamBytes = 4 * kTileBytes;   // K tiles kt+1 / kt+2 and V tiles kt / kt+1: two buffers each
+    constexpr int kRowBlocks = BQ / 32, kShares = TEAMS * (SPLIT ? 2 : 1);   // waves that share a row block
+    __shared__ __attribute__((aligned(1024))) char lds[TEAMS * kTeamBytes];
     // the slot handed round after an item, double-buffered: between two hand-overs there is one barrier, and with a single
     // word the leader could overwrite it before a late wave has read it (items that only write zeros pass no other barrier)
     __shared__ int next_slot[2];
-    __shared__ float2 row_stats[SPLIT ? 2 * 64 : 1];   // (maximum, sum) that the second wave of a row block hands to the first
+    __shared__ float2 row_stats[kShares > 1 ? (kShares - 1) * kRowBlocks * 64 : 1];   // (maximum, sum) that the other waves of a row block hand to the first
     char* const kbuf0 = lds;
     char* const vbuf0 = lds + 2 * kTileBytes;
-    const uint32_t kdst0 = lds_address(lds), vdst0 = kdst0 + 2 * kTileBytes;   // the same buffers as copy destinations
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = TEAMS > 1 ? wave_id & 3 : wave_id, team = TEAMS > 1 ? wave_id >> 2 : 0;
+    const uint32_t kdst0 = lds_address(lds) + team * kTeamBytes, vdst0 = kdst0 + 2 * kTileBytes;   // the team's buffers as copy destinations
     const int row_block = SPLIT ? wave & 1 : wave, key_block = SPLIT ? wave >> 1 : 0;   // this wave's 32 rows; its keys of a tile
+    const int share = team * (SPLIT ? 2 : 1) + key_block;
     const int hh = lane >> 5;
     const int hd = p.head_dim;   // elements per head in memory, <= D (columns hd .. D-1 exist only in LDS and registers)
     const float c = p.scale_log2;
@@ -308,8 +318,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
             tr[db][1] = tile_offset<D>(row + 8, col);
         }
     }
-    if constexpr (SPLIT) {
-        const int skip = key_block * 32 * D * 2;
+    if constexpr (kShares > 1) {
+        const int skip = team * kTeamBytes + key_block * 32 * D * 2;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) rm[kk] += skip;
 #pragma unroll
@@ -351,11 +361,11 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
 
         // last key this lane's row may see (key j is visible to row r iff j <= r + off), as an index into the chunk
         const int my_limit = BLOCK ? min(my_row + off, L - 1) : my_row;
-        const FwdTiles tiles = fwd_tiles(SPLIT, Lq, L, off, q_row0, row_block, key_block);
+        const FwdTiles tiles = fwd_tiles(SPLIT, Lq, L, off, q_row0, row_block, key_block, TEAMS, team);
         const int n_tiles = tiles.n_tiles, n_tiles_w = tiles.n_tiles_w;
-        if (BLOCK && n_tiles == 0) {
+        if (BLOCK && tiles.n_passes == 0) {
             // no key of the chunk is visible to any row of the tile: O = 0, LSE = -inf
-            if (my_row < Lq && key_block == 0) {
+            if (my_row < Lq && share == 0) {
                 float* orow = p.o_f32 + ((int64_t)(item.q_start + my_row) * p.q_heads + h) * hd;
     #pragma unroll
                 for (int c4 = 0; c4 < D / 8; ++c4)
@@ -367,10 +377,14 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
             return;
         }
 
+        auto tile_of = [=](int kt) { return TEAMS > 1 ? kt * TEAMS + team : kt; };   // the item's number of the team's tile kt
+        auto first_key = [=](int kt) { return tile_of(kt) * BK; };
         // K(0), V(0), K(1)
-        kvcopy.issue(kdst0, kbase, p.kv_stride, 0, L, wave, lane);
-        kvcopy.issue(vdst0, vbase, p.kv_stride, 0, L, wave, lane);
-        if (n_tiles > 1) kvcopy.issue(kdst0 + kTileBytes, kbase, p.kv_stride, BK, L, wave, lane);
+        if (TEAMS == 1 || n_tiles > 0) {
+            kvcopy.issue(kdst0, kbase, p.kv_stride, first_key(0), L, wave, lane);
+            kvcopy.issue(vdst0, vbase, p.kv_stride, first_key(0), L, wave, lane);
+        }
+        if (n_tiles > 1) kvcopy.issue(kdst0 + kTileBytes, kbase, p.kv_stride, first_key(1), L, wave, lane);
 
     #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
@@ -413,11 +427,11 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
                 wait_tile_loads();
                 __syncthreads();   // K(kt+1) and V(kt) have landed; every wave is done with iteration kt-1
             }
-            if (kt + 2 < n_tiles) kvcopy.issue(kdst0 + (kt & 1) * kTileBytes, kbase, p.kv_stride, (kt + 2) * BK, L, wave, lane);
-            if (kt + 1 < n_tiles) kvcopy.issue(vdst0 + ((kt + 1) & 1) * kTileBytes, vbase, p.kv_stride, (kt + 1) * BK, L, wave, lane);
-            fwd_iteration<D, KD, NB, decltype(masked)::value, decltype(last)::value, false, BLOCK>(
+            if (kt + 2 < n_tiles) kvcopy.issue(kdst0 + (kt & 1) * kTileBytes, kbase, p.kv_stride, first_key(kt + 2), L, wave, lane);
+            if (kt + 1 < n_tiles) kvcopy.issue(vdst0 + ((kt + 1) & 1) * kTileBytes, vbase, p.kv_stride, first_key(kt + 1), L, wave, lane);
+            fwd_iteration<D, KD, NB, decltype(masked)::value, decltype(last)::value, false, BLOCK || (kShares > 1)>(
                 st, kbuf0 + ((kt + 1) & 1) * kTileBytes, vbuf0 + (kt & 1) * kTileBytes, c,
-                my_limit - kt * BK - key_block * 32 - 4 * hh, no_load);
+                my_limit - first_key(kt) - key_block * 32 - 4 * hh, no_load);
         };
         // the same for an unmasked tile whose successors kt+1 and kt+2 are whole tiles: their copies need no case
         // distinction and are issued from inside the iteration
@@ -431,13 +445,13 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
             }
             FwdTileLoad<D> load;
             load.copy = &kvcopy;
-            load.k_row = kbase + (int64_t)(kt + 2) * BK * p.kv_stride;
-            load.v_row = vbase + (int64_t)(kt + 1) * BK * p.kv_stride;
+            load.k_row = kbase + (int64_t)tile_of(kt + 2) * BK * p.kv_stride;
+            load.v_row = vbase + (int64_t)tile_of(kt + 1) * BK * p.kv_stride;
             load.k_dst = kdst0 + par * kTileBytes;
             load.v_dst = vdst0 + (1 - par) * kTileBytes;
             load.wave = wave;
-            fwd_iteration<D, KD, NB, false, false, true, BLOCK>(st, kbuf0 + (1 - par) * kTileBytes, vbuf0 + par * kTileBytes, c,
-                                                        my_limit - kt * BK - 4 * hh, load);
+            fwd_iteration<D, KD, NB, false, false, true, BLOCK || (kShares > 1)>(st, kbuf0 + (1 - par) * kTileBytes, vbuf0 + par * kTileBytes, c,
+                                                        my_limit - first_key(kt) - 4 * hh, load);
         };
         // a tile past this wave's own diagonal: the barrier and the wave's share of the copies, nothing else
         auto idle = [&](int kt) {
@@ -445,8 +459,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
                 wait_tile_loads();
                 __syncthreads();
             }
-            if (kt + 2 < n_tiles) kvcopy.issue(kdst0 + (kt & 1) * kTileBytes, kbase, p.kv_stride, (kt + 2) * BK, L, wave, lane);
-            if (kt + 1 < n_tiles) kvcopy.issue(vdst0 + ((kt + 1) & 1) * kTileBytes, vbase, p.kv_stride, (kt + 1) * BK, L, wave, lane);
+            if (kt + 2 < n_tiles) kvcopy.issue(kdst0 + (kt & 1) * kTileBytes, kbase, p.kv_stride, first_key(kt + 2), L, wave, lane);
+            if (kt + 1 < n_tiles) kvcopy.issue(vdst0 + ((kt + 1) & 1) * kTileBytes, vbase, p.kv_stride, first_key(kt + 1), L, wave, lane);
         };
         // separate loops instead of branches inside one: unmasked tiles (with and without whole successors), masked
         // tiles, and the wave's final tile (which has no successor to compute scores for); the large register state
@@ -466,7 +480,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
             step(kt, std::true_type{}, std::true_type{});   // the wave's final tile touches its diagonal (always, when !BLOCK)
             ++kt;
         }
-        for (; kt < n_tiles; ++kt) idle(kt);
+        for (; kt < tiles.n_passes; ++kt) idle(kt);
 
         // the next slot is requested when the tiles are done (not earlier: a slot reserved at the start of a long item
         // would wait for that item while other workgroups run out of work) and looked at after the stores
@@ -475,32 +489,42 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
         // O leaves through LDS (free once every wave has left the tile loop) so that every store instruction writes
         // whole rows; a row that saw no key (BLOCK only) has l = 0 and m = -inf: O = 0, LSE = -inf
         __syncthreads();
-        if constexpr (SPLIT) {
-            char* const area = vbuf0 + row_block * (32 * D * 4);
-            if (key_block == 1) {
+        if constexpr (kShares > 1) {
+            constexpr int kArea = 32 * D * 4;
+            auto area = [&](int x) { return lds + (x * kRowBlocks + row_block) * kArea; };   // of share x; share 0's is where O is staged
+            auto stats = [&](int x) -> float2& { return row_stats[((x - 1) * kRowBlocks + row_block) * 64 + lane]; };
+            if (share > 0) {
     #pragma unroll
                 for (int db = 0; db < DB; ++db)
     #pragma unroll
                     for (int i4 = 0; i4 < 4; ++i4)
-                        *reinterpret_cast<f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16) =
+                        *reinterpret_cast<f32x4*>(area(share) + ((db * 4 + i4) * 64 + lane) * 16) =
                             f32x4{st.acc[db][4 * i4], st.acc[db][4 * i4 + 1], st.acc[db][4 * i4 + 2], st.acc[db][4 * i4 + 3]};
-                row_stats[row_block * 64 + lane] = make_float2(st.m, l_row);
+                stats(share) = make_float2(st.m, l_row);
             }
             __syncthreads();
-            if (key_block == 1) return;
+            if (share > 0) return;
             // (a wave that met no key has m = -inf, l = 0, O = 0: its factor is exp2(-inf) = 0)
-            const float2 other = row_stats[row_block * 64 + lane];
-            const float m = fmaxf(st.m, other.x), m_ref = m == -INFINITY ? 0.f : m;
-            const float fa = fast_exp2((st.m - m_ref) * c), fb = fast_exp2((other.x - m_ref) * c);
+            float m = st.m;
     #pragma unroll
-            for (int db = 0; db < DB; ++db)
+            for (int x = 1; x < kShares; ++x) m = fmaxf(m, stats(x).x);
+            const float m_ref = m == -INFINITY ? 0.f : m;
+            float fa = fast_exp2((st.m - m_ref) * c);
     #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const f32x4 y = *reinterpret_cast<const f32x4*>(area + ((db * 4 + i4) * 64 + lane) * 16);
+            for (int x = 1; x < kShares; ++x) {
+                const float2 other = stats(x);
+                const float fb = fast_exp2((other.x - m_ref) * c);
     #pragma unroll
-                    for (int j = 0; j < 4; ++j) st.acc[db][4 * i4 + j] = st.acc[db][4 * i4 + j] * fa + y[j] * fb;
-                }
-            l_row = l_row * fa + other.y * fb;
+                for (int db = 0; db < DB; ++db)
+    #pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const f32x4 y = *reinterpret_cast<const f32x4*>(area(x) + ((db * 4 + i4) * 64 + lane) * 16);
+    #pragma unroll
+                        for (int j = 0; j < 4; ++j) st.acc[db][4 * i4 + j] = st.acc[db][4 * i4 + j] * fa + y[j] * fb;
+                    }
+                l_row = l_row * fa + other.y * fb;
+                fa = 1.f;
+            }
             st.m = m;
         }
         const float inv = (!BLOCK || l_row > 0.f) ? 1.f / l_row : 0.f;
@@ -529,7 +553,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdParams p, List...) 
     for (int turn = 0;; turn ^= 1) {
         const int list_slot = SPLIT ? slot / (2 * kQueues) * kQueues + slot % kQueues : slot;
         if (SPLIT && list_slot >= p.num_items) break;
-        const ItemGeom item = load_item<BLOCK, sizeof...(List) != 0>(p, list_slot);
+        const ItemGeom item = load_item<BLOCK, has_inline_list<More...>>(p, list_slot);
         if (item.tile < 0) break;          // padding at the end of the queue: nothing left
         run_item(item, 1 - slot / kQueues % 2);
         if (tid == 0) next_slot[turn] = drawn;
@@ -544,7 +568,20 @@ namespace {
 
 template <int D, int KD, typename... List>
 void launch(const FwdParams& p, unsigned workgroups, bool block, bool split, hipStream_t stream, const List&... list) {
-    const dim3 grid(workgroups), threads(kThreads);
+    const dim3 grid(workgroups), threads(kThreads), both_teams(2 * kThreads);
+    const TwoTeams two{};
+    if constexpr (D == 64 || sizeof...(List) == 0) {   // (whole items at tile width 128: only lists too long for the arguments)
+        if (p.teams == 2 && !split) {
+            hipLaunchKernelGGL((fwd_kernel<D, false, KD, false, List..., TwoTeams>), grid, both_teams, 0, stream, p, list..., two);
+            return;
+        }
+    }
+    if constexpr (sizeof...(List) != 0) {               // (half items: only lists in the arguments)
+        if (p.teams == 2 && split) {
+            hipLaunchKernelGGL((fwd_kernel<D, false, KD, true, List..., TwoTeams>), grid, both_teams, 0, stream, p, list..., two);
+            return;
+        }
+    }
     if (block && split) hipLaunchKernelGGL((fwd_kernel<D, true, KD, true, List...>), grid, threads, 0, stream, p, list...);
     else if (block) hipLaunchKernelGGL((fwd_kernel<D, true, KD, false, List...>), grid, threads, 0, stream, p, list...);
     else if (split) hipLaunchKernelGGL((fwd_kernel<D, false, KD, true, List...>), grid, threads, 0, stream, p, list...);
@@ -570,7 +607,7 @@ hipError_t launch_fwd(const FwdParams& params, const InlineList* list, int head_
     const int64_t slots = split ? 2 * ((num_items + kQueues - 1) / kQueues * kQueues) : num_items;
     // a short list has a workgroup for every slot: nothing to draw, and no round trip to the counters at the end of the item
     FwdParams p = params;
-    const int64_t workgroups = list != nullptr ? slots : persistent_grid(slots, 2);
+    const int64_t workgroups = list != nullptr ? slots : persistent_grid(slots, p.teams == 2 ? 1 : 2);
     if (workgroups <= 0) return hipErrorInvalidDevice;
     if (workgroups == slots) p.queue = nullptr;
     if (list) launch_width(p, head_dim, (unsigned)workgroups, block, split, stream, *list);

@@ -250,6 +250,13 @@ hspmd::Dispatch plan_dispatch(const hspmd_attn_plan* plan, hspmd_list_kind kind)
     return hspmd::pass_dispatch(kind, plan->load[kind], plan->count[kind], plan->head_dim, plan->is_block);
 }
 
+template <typename Params>
+void set_rows_form(const hspmd_attn_plan* plan, hspmd_list_kind kind, Params& p) {
+    const hspmd::RowsForm form = hspmd::rows_form(kind, plan->load[kind], plan->count[kind], p.group, plan->head_dim, plan->is_inline);
+    p.split = form.halves ? 1 : 0;
+    p.teams = form.teams;
+}
+
 const hspmd::InlineList* inline_list(const hspmd_attn_plan* plan, hspmd_list_kind kind) {
     return !plan->is_inline ? nullptr : kind == HSPMD_LIST_DKV ? &plan->inline_keys : &plan->inline_rows;
 }
@@ -595,7 +602,7 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
     p.scale_log2 = scale * 1.4426950408889634f;
     p.num_items = (int32_t)plan->count[HSPMD_LIST_FWD];
     p.queue = plan->queue[HSPMD_LIST_FWD];
-    p.split = plan_dispatch(plan, HSPMD_LIST_FWD) == hspmd::Dispatch::kHalves ? 1 : 0;
+    set_rows_form(plan, HSPMD_LIST_FWD, p);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, inline_list(plan, HSPMD_LIST_FWD), plan->head_dim, plan->count[HSPMD_LIST_FWD], false, s); });
     if (e != hipSuccess) return fail_hip(e, "forward launch");
@@ -652,7 +659,7 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     // D = rowsum(dO * O) is computed by the dQ pass itself (every (row, head) belongs to exactly one of its items)
     p.items = plan->items[HSPMD_LIST_DQ];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
-    p.split = plan_dispatch(plan, HSPMD_LIST_DQ) == hspmd::Dispatch::kHalves ? 1 : 0;
+    set_rows_form(plan, HSPMD_LIST_DQ, p);
     auto dq_pass = [&] { return hspmd::launch_bwd_dq(p, inline_list(plan, HSPMD_LIST_DQ), plan->head_dim, plan->count[HSPMD_LIST_DQ], false, s); };
     hipError_t e = timed ? timed_launch(2, s, dq_pass) : dq_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dQ launch");
@@ -913,6 +920,7 @@ hspmd_status hspmd_attn_block_fwd(const hspmd_attn_plan* plan, const void* q, co
     p.num_items = (int32_t)plan->count[HSPMD_LIST_FWD];
     p.queue = plan->queue[HSPMD_LIST_FWD];
     p.split = plan_dispatch(plan, HSPMD_LIST_FWD) == hspmd::Dispatch::kHalves ? 1 : 0;
+    p.teams = 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = timed_launch(0, s, [&] { return hspmd::launch_fwd(p, inline_list(plan, HSPMD_LIST_FWD), plan->head_dim, plan->count[HSPMD_LIST_FWD], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block forward launch");
@@ -997,6 +1005,7 @@ static hspmd_status block_bwd(const hspmd_attn_plan* plan, const void* q, const 
     p.block_items = plan->block_items[HSPMD_LIST_DQ];
     p.num_items = (int32_t)plan->count[HSPMD_LIST_DQ];
     p.split = plan_dispatch(plan, HSPMD_LIST_DQ) == hspmd::Dispatch::kHalves ? 1 : 0;
+    p.teams = 1;
     e = timed_launch(2, s, [&] { return hspmd::launch_bwd_dq(p, inline_list(plan, HSPMD_LIST_DQ), plan->head_dim, plan->count[HSPMD_LIST_DQ], true, s); });
     if (e != hipSuccess) return fail_hip(e, "block backward dQ launch");
     p.block_items = plan->block_items[HSPMD_LIST_DKV];

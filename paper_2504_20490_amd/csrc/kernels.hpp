@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/hspmd_attn.h"
 
 namespace hspmd {
@@ -17,6 +19,13 @@ constexpr int kListBytes = 3840;
 struct alignas(16) InlineList {
     int32_t words[kListBytes / 4];
 };
+
+// Says that two teams of four waves share an item (an argument without content, after the list if that is one).
+struct TwoTeams {};
+template <typename... More>
+constexpr int teams_of = (std::is_same_v<More, TwoTeams> || ... || false) ? 2 : 1;
+template <typename... More>
+constexpr bool has_inline_list = (std::is_same_v<More, InlineList> || ... || false);
 
 struct FwdParams {
     const uint16_t* q;
@@ -35,6 +44,7 @@ struct FwdParams {
     int32_t num_items;             // slots of the work list (padding included)
     int32_t* queue;                // this pass's draw counters (ItemQueue), zero between launches; NULL: every slot has a workgroup
     int32_t split;                 // the unit of work is half an item (decided from the plan's loads, see pass_dispatch)
+    int32_t teams;                 // 2: two teams of four waves take an item's key tiles in turn (see rows_form); 1: one team
 };
 
 struct BwdParams {
@@ -65,6 +75,7 @@ struct BwdParams {
     int32_t num_items;             // slots of the current pass's work list (padding included)
     int32_t* queue;                // the current pass's draw counters (ItemQueue), zero between launches
     int32_t split;                 // the pass works on half items (decided from the plan's loads, see pass_dispatch)
+    int32_t teams;                 // dQ pass: 2: two teams of four waves take an item's key tiles in turn (see rows_form); 1: one team
     int32_t persist;               // dK/dV pass of a packed plan with whole items: 1 persistent workgroups (see pass_dispatch), an
                                    // error where the device's size is unknown; 2 the same (see persistent_dkv), but there one
                                    // workgroup per item: those packs need no size; 0 one per item

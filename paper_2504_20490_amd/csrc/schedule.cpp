@@ -350,6 +350,39 @@ bool split_rows(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32
     return heaviest + 6.0 >= 2.0 * per_slot && heaviest >= least;
 }
 
+// Where an item of the forward or the dQ pass goes to two teams of four waves, one workgroup of eight per compute unit: half as many
+// iterations per item, at the price of what the teams' sums cost at the end of an item and of the second workgroup that would have
+// covered its loads and stores.  Half items: where each has a unit to itself, more or less, and is long (at most 240 slots: lists in the
+// arguments, the only ones that these kernels take).  Whole items: where the
+// heaviest is longer than the work per slot, and not so much that halves are better.  Measured, without and with (us; F forward,
+// Q dQ pass; steps of the heaviest item, slots; ratio = (heaviest + 6) / work per slot as in split_rows):
+//   half items, one team / two: one head of 8192 tokens (128, 64) F 88.9 / 68.9, Q 82 / 73; 4 heads of 4096 (64, 128) F 52 / 44, Q 49 / 46;
+//   width 64, 8 heads of 2048 F 21.4 / 18.4, Q 18.7 / 18.4; lost where shorter or more (2 x 1024, 8 heads F 18.3 / 19.7, Q 20.4 / 22.6; 184 slots,
+//   40 steps F 35.7 / 40.6; 200 slots, 100 steps Q 67.7 / 72).
+//   whole items, one team / two: 5 heads of 16001 (251, 625, ratio 1.50) F 321 / 310, Q 438 / 414; 16 heads of 4096 (64, 512, 1.55) F 81.5 /
+//   79; width 64, 8 heads of 8192 F 99 / 86, Q 116 / 99, 2 of 16384 F 155 / 130; against halves width 80, 477 slots of 318, 1.98 F 296 / 256, Q 338 /
+//   307; lost at lower ratios (12 heads of 8192, 1.2 F 199 / 208, Q 267 / 280), for dQ at higher ones, where halves win (134 steps, 270
+//   slots, 3.9 Q 114 / 136), and with heads in groups, which already share tiles in the L1 (24 on 6, 74 steps, 1.7 F 99 / 110).
+// Over 1160 packs of five widths the packs that this takes run in 0.84 (F, width 64), 0.89 (F) and 0.93 (Q) of the time on average; the worst are
+// F 1.02 and Q 1.04.
+int teams_of_rows(hspmd_list_kind kind, bool halves, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim, bool in_arguments,
+                  bool* whole) {
+    const double heaviest = (double)load.heaviest, items = (double)slots;
+    const double ratio = (heaviest + 6.0) / (((double)load.total + 6.0 * 2.0 * items) / 512.0);
+    const bool fwd = kind == HSPMD_LIST_FWD, narrow = head_dim <= 64;
+    *whole = !halves;
+    const double least = (fwd ? narrow ? 17 : 30 : narrow ? 32 : 48) + (fwd ? 0.25 : 1.2) * std::max(0.0, items - 128);
+    if (halves && in_arguments && ratio >= 4.2 && heaviest >= least) return 2;
+    const double from = fwd ? (narrow ? 1.35 + 0.3 * 64 / heaviest : 1.3 + 0.5 * 64 / heaviest) + (group == 1 ? 0.0 : narrow ? 0.1 : 0.35)
+                            : (narrow ? 1.35 : 1.4) + 0.2 * 64 / heaviest;
+    const double to = fwd ? narrow ? 9.0 : 3.4 : narrow ? 2.3 : 2.0;
+    if ((fwd || group == 1) && items >= (fwd && narrow ? 150 : 250) && heaviest >= (fwd ? narrow ? 44 : 64 : 100) && ratio >= from && ratio <= to) {
+        *whole = true;
+        return 2;
+    }
+    return 1;
+}
+
 // Whether the dK/dV pass gives every item to two workgroups (each with half of its keys and half of its time).  The pass takes
 // as long as its heaviest item or as the work that one workgroup slot gets, whichever is longer; a half item costs 0.68 of the
 // whole one alone on its compute unit and 0.65 (2 x 0.65 = 1.3 in all) on a full chip, because both halves copy every Q / dO
@@ -396,6 +429,13 @@ Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots
     return !block && head_dim > 64 && short_items(load, slots, head_dim) ? Dispatch::kPersistent : Dispatch::kWhole;
 }
 
+RowsForm rows_form(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim, bool in_arguments) {
+    const bool halves = split_rows(kind, load, slots, head_dim);
+    bool whole = !halves;
+    const int teams = teams_of_rows(kind, halves, load, slots, group, head_dim, in_arguments, &whole);
+    return RowsForm{!whole, teams};
+}
+
 // Items of one query head are drawn by persistent workgroups up to 48 steps (64 at head_dim up to 112), now that the instructions of
 // the tile loop do not depend on the loop around it: at least 1536 slots (six per compute unit), more than 3.2 steps per slot, no
 // item that alone takes most of the pass.  Measured, one workgroup per item and persistent (us, the same tile loop in both): 8 x 2048,
@@ -426,6 +466,10 @@ namespace {
 
 struct PassCost { double step_us, item_us, alone_us; };               // alone_us: a step with one workgroup per unit or fewer
 struct PassFixed { double launch_us, half_step, half_alone, half_item; };   // half_*: shares of a whole item's times
+struct Shares { double step, alone, item; };
+// the same shares where two teams of waves take an item: whole items, half items (fitted to 205 and 143 forwards, 48 and 71 dQ passes;
+// mean |error| 3 to 5 %)
+constexpr Shares kTeamShares[2][2] = {{{1.19, 0.65, 1.30}, {0.80, 0.51, 0.98}}, {{1.18, 0.69, 1.01}, {0.68, 0.49, 0.85}}};
 constexpr PassFixed kPassFixed[3] = {{1.6, 0.64, 0.75, 0.83}, {0.0, 0.62, 0.61, 0.67}, {0.0, 0.52, 0.70, 0.84}};
 // head_dim up to 64, 80, 96, 112, 128: each has kernels of its own
 constexpr PassCost kPassCost[3][5] = {
@@ -443,8 +487,12 @@ double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seq
     const bool narrow = head_dim <= 64;
     const PassCost c = kPassCost[(int)kind][narrow ? 0 : std::max(1, (head_dim + 15) / 16 - 4)];
     const PassFixed f = kPassFixed[(int)kind];
-    const bool halves = pass_dispatch(kind, load, (int64_t)list.size(), head_dim, false) == Dispatch::kHalves;
-    const double step = c.step_us * (halves ? 2 * f.half_step : 1.0), item = c.item_us * (halves ? 2 * f.half_item : 1.0);
+    RowsForm form{pass_dispatch(kind, load, (int64_t)list.size(), head_dim, false) == Dispatch::kHalves, 1};
+    if (kind != HSPMD_LIST_DKV) form = rows_form(kind, load, (int64_t)list.size(), hq / hkv, head_dim, list.size() <= 240);
+    const bool halves = form.halves;
+    const Shares share = form.teams == 2 ? kTeamShares[(int)kind][halves] : halves ? Shares{f.half_step, f.half_alone, f.half_item}
+                                                                                   : Shares{1.0, 1.0, 1.0};
+    const double step = c.step_us * share.step * (halves ? 2 : 1), item = c.item_us * share.item * (halves ? 2 : 1);
     // workgroups resident per XCD: 32 compute units, two workgroups each in the forward and dQ passes, one in dK/dV; at tile
     // width 64 three in the dQ pass and two in dK/dV with whole items
     const double per_unit = kind == HSPMD_LIST_DKV ? (narrow && !halves ? 2 : 1) : (narrow && kind == HSPMD_LIST_DQ ? 3 : 2);
@@ -454,7 +502,7 @@ double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seq
         queue_weight[p % kNumXcd] += (double)item_cost(kind, list[p].seq_len, list[p].tile, hq / hkv) * step + item;
     }
     const double shared = *std::max_element(queue_weight, queue_weight + kNumXcd) / (32.0 * per_unit);
-    const double alone = (double)load.heaviest * c.alone_us * (halves ? f.half_alone : 1.0) + c.item_us * (halves ? f.half_item : 1.0);
+    const double alone = (double)load.heaviest * c.alone_us * share.alone + c.item_us * share.item;
     return f.launch_us + std::sqrt(std::sqrt(shared * shared * shared * shared + alone * alone * alone * alone));
 }
 

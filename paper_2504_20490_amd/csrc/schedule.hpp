@@ -38,6 +38,14 @@ std::vector<hspmd_work_item> build_work_list(hspmd_list_kind kind, const int32_t
 // plans; the forward is always persistent).  `slots`: length of the list, padding included.
 enum class Dispatch { kWhole, kHalves, kPersistent };
 Dispatch pass_dispatch(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t head_dim, bool block);
+// How the forward or the dQ pass of a packed plan deals out its items: `halves` as pass_dispatch says, except where `teams` is 2 (two
+// teams of four waves share an item's key tiles), which may also take whole items where pass_dispatch says halves.
+struct RowsForm {
+    bool halves;
+    int teams;
+};
+// in_arguments: the list travels in the launch's arguments.
+RowsForm rows_form(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim, bool in_arguments);
 // Whether the dK/dV pass of a packed plan draws its items in persistent workgroups: also where pass_dispatch says whole items.
 bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim);
 
