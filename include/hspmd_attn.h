@@ -193,6 +193,10 @@ hspmd_status hspmd_attn_plan_create_ordered(const int32_t* cu_seqlens_host, int3
  *   allocating after the first few refills.
  *   Lists of up to 240 slots (120 of a block plan) take none of this: the plan keeps them on the host, every launch carries its
  *   list among its arguments (a graph keeps the one it was captured with), nothing is uploaded and no event is recorded.
+ *   Packed plans of grouped heads may deal the dK/dV pass's items out by query heads where a pack's longest item would outlast
+ *   the rest; the shares' list goes to a slot as described, also beside lists in the arguments (under capture those are used and
+ *   nothing is dealt out), and the plan owns the memory of the shares' sums, at most 128 MB, which a refill enlarges when a pack
+ *   needs more than any before it (hipFree + hipMalloc).
  *   Not for concurrent use: no other thread may launch with the plan during the call.  A launch recorded into a HIP
  *   graph records no event (events cannot be waited for from inside a capture): a plan that a graph replays must not be
  *   refilled while the graph may run.  On error the plan keeps its previous pack.

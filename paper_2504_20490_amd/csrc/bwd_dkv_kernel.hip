@@ -362,11 +362,14 @@ __device__ __forceinline__ void dkv_iteration_hinted(DkvState<D, KD>& st, const 
 // GROUPS: whole packed items of several query heads at head_dim above 112, one workgroup each; every head is walked one tile at a time,
 // in the compiler's order (dkv_iteration_hinted).
 //
-// List: nothing, or InlineList when the work list is the second argument.
+// List: nothing, InlineList when the work list is the second argument, or HeadPieces where items are dealt out by query heads: a share
+// leaves fp32 sums in its area (build_piece_list in schedule.cpp).
 template <int D, bool BLOCK, int KD, bool SPLIT, bool PERSIST, bool GROUPS, typename... List>
 __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv_kernel(BwdParams p, List...) {
     static_assert(!PERSIST || (!BLOCK && !SPLIT), "whole items of packed plans only");
     static_assert(!GROUPS || (KD == 8 && !BLOCK && !SPLIT && !PERSIST), "whole items of packed plans, head_dim above 112");
+    constexpr bool kPieces = has_pieces<List...>;
+    static_assert(!kPieces || (!BLOCK && !PERSIST && !GROUPS && sizeof...(List) == 1), "packed plans, a workgroup per share");
     constexpr bool kTrips = !SPLIT && !GROUPS && D == 128;   // whole items, two tiles a trip
     using G = DkvGeom<D, KD>;
     constexpr int BKV = SPLIT ? kDkvKTile / 2 : kDkvKTile, BQ = kDkvQTile;
@@ -379,11 +382,24 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     PersistentLoop<PERSIST> loop;
     loop.init(p.queue);
     do {
-    const ItemGeom item = load_item<BLOCK, sizeof...(List) != 0>(p, slot);
+    ItemGeom item;
+    int first_head = 0, n_heads = p.group;   // query heads of the group that this workgroup walks
+    if constexpr (kPieces) {
+        const HeadPiece it = p.pieces[slot];
+        // (each a value of its own: spilled as one group, they leave a stack object behind)
+        auto field = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+        const int start = field(it.token_start), length = field(it.seq_len);
+        item = ItemGeom{start, length, start, length, 0, field(it.tile), field(it.head), 0};
+        first_head = field(it.first_head);
+        n_heads = field(it.heads);
+    } else {
+        item = load_item<BLOCK, has_inline_list<List...>>(p, slot);
+    }
     if (item.tile < 0) break;
     const int tid = threadIdx.x, lane = loop.item_lane();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = item.q_len, Lk = item.k_len, shift = item.offset, g = item.head;   // L: rows of the chunk
+    const int first_q_head = g * p.group + first_head;
     const int key0 = item.tile * kDkvKTile + (SPLIT ? (int)(blockIdx.x / kQueues % 2) * BKV : 0);
     if (SPLIT && key0 >= Lk) return;             // the last item of a sequence may have no second half
     const int row_block = SPLIT ? wave >> 1 : 0;   // the 32-row block of every tile that is this wave's
@@ -392,7 +408,9 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     const int hh = lane >> 5;
     const bool valid = my_key < Lk;
 
-    const int hd = p.head_dim;   // elements per head in memory, <= D (columns hd .. D-1 exist only in LDS and registers)
+    int hd = p.head_dim;   // elements per head in memory, <= D (columns hd .. D-1 exist only in LDS and registers)
+    // (a value of its own: spilled as one group with its neighbours among the parameters, it leaves a stack object behind)
+    if constexpr (kPieces) asm volatile("" : "+s"(hd));
     const uint16_t* kbase = p.k + (int64_t)item.k_start * p.kv_stride + (int64_t)g * hd;
     const uint16_t* vbase = p.v + (int64_t)item.k_start * p.kv_stride + (int64_t)g * hd;
 
@@ -402,7 +420,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     const int first_qt = max(0, key0 - shift) / BQ;
     const int n_qt = (L + BQ - 1) / BQ;
     const int per_head = max(0, n_qt - first_qt);
-    const int n_tiles = per_head * p.group;
+    const int n_tiles = per_head * n_heads;
     if (BLOCK && per_head == 0) {
         // no row of the chunk sees these keys
         if (valid && row_block == 0) {
@@ -424,7 +442,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     docopy.init((int64_t)p.q_heads * hd, wave, lane, hd);
     auto load_tile = [&](int u, int stage_index) {
         const uint32_t stage = lds0 + stage_index * G::kStageBytes;
-        const int hq = g * p.group + u / per_head;
+        const int hq = first_q_head + u / per_head;
         const int row0 = (n_qt - 1 - u % per_head) * BQ;   // q tiles are walked from the end of the sequence down
         const uint16_t* qb = p.q + (int64_t)item.q_start * p.q_stride + (int64_t)hq * hd;
         const uint16_t* dob = p.d_o + ((int64_t)item.q_start * p.q_heads + hq) * hd;
@@ -624,10 +642,10 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     using Odd = std::integral_constant<int, 1>;
     using Second = std::integral_constant<int, 2>;
     auto swap_pairs = [&] { st.s[0] = st.s[1]; st.dp[0] = st.dp[1]; };
-    for (int h = 0, u = 0; h < p.group; ++h) {
+    for (int h = 0, u = 0; h < n_heads; ++h) {
         int j = per_head - 1;
         if (j >= n_general) {
-            const int hq = g * p.group + h;
+            const int hq = first_q_head + h;
             const int64_t row = item.q_start + (int64_t)(first_qt + j - 3) * BQ;   // first row of the tile loaded first
             DkvTileLoad<D> load;
             load.qcopy = &qcopy;
@@ -685,7 +703,14 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     }
 
     // whole rows per store instruction, staged through LDS (free once every wave has left the tile loop)
-    const bool rope = p.rope_table != nullptr;
+    int area = -1;   // where the sums of a share go
+    if constexpr (kPieces) {
+        int again = slot;   // (read here and not kept through the tile loop)
+        asm volatile("" : "+s"(again));
+        area = p.pieces[again].area;
+    }
+    const bool sums = kPieces && area >= 0;
+    const bool rope = !sums && p.rope_table != nullptr;
     __syncthreads();
     constexpr int kWaveArea = 32 * D * 4;
     static_assert(!SPLIT || 8 * kWaveArea <= G::kStages * G::kStageBytes, "exchange and staging areas");
@@ -721,22 +746,24 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
         wave_lds += 4 * kWaveArea;   // the partner may still read this wave's exchange area
     }
     const bool stores_dk = !SPLIT || row_block == 0, stores_dv = !SPLIT || row_block == 1;
-    const int64_t row0_elem = ((int64_t)(item.k_start + wave_key0) * p.kv_heads + g) * hd;
-    const int64_t row_stride = (int64_t)p.kv_heads * hd;
+    const int64_t row0_elem = sums ? (int64_t)(wave_key0 - item.tile * kDkvKTile) * D : ((int64_t)(item.k_start + wave_key0) * p.kv_heads + g) * hd;
+    const int64_t row_stride = sums ? D : (int64_t)p.kv_heads * hd;
+    float* const dk_f32 = sums ? p.piece_sums + (int64_t)area * (2 * kDkvKTile * D) : static_cast<float*>(p.dk);
+    float* const dv_f32 = sums ? p.piece_sums + (int64_t)area * (2 * kDkvKTile * D) + kDkvKTile * D : static_cast<float*>(p.dv);
     const int rows = min(32, Lk - wave_key0);
     if (!stores_dk) {
     } else if (rope) {
         // dK with respect to the keys before their rotary embedding; key positions inside the sequence
         store_tile_rope_transposed<D>(wave_lds, st.dk, p.scale, p.dk, row0_elem, p.grad_f32 != 0, row_stride, rows, hd,
                                       p.rope_table + (int64_t)(item.q_pos - item.offset + wave_key0) * hd, lane);
-    } else if (p.grad_f32 != 0) {
-        store_tile_f32<D, false>(wave_lds, st.dk, p.scale, static_cast<float*>(p.dk) + row0_elem, row_stride, rows, hd, lane);
+    } else if (sums || p.grad_f32 != 0) {
+        store_tile_f32<D, false>(wave_lds, st.dk, sums ? 1.f : p.scale, dk_f32 + row0_elem, row_stride, rows, hd, lane);
     } else {
         store_tile_bf16<D>(wave_lds, st.dk, p.scale, static_cast<uint16_t*>(p.dk) + row0_elem, row_stride, rows, hd, lane);
     }
     if (!stores_dv) {
-    } else if (p.grad_f32 != 0) {
-        store_tile_f32<D, false>(wave_lds, st.dv, 1.f, static_cast<float*>(p.dv) + row0_elem, row_stride, rows, hd, lane);
+    } else if (sums || p.grad_f32 != 0) {
+        store_tile_f32<D, false>(wave_lds, st.dv, 1.f, dv_f32 + row0_elem, row_stride, rows, hd, lane);
     } else {
         store_tile_bf16<D>(wave_lds, st.dv, 1.f, static_cast<uint16_t*>(p.dv) + row0_elem, row_stride, rows, hd, lane);
     }
@@ -744,11 +771,53 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     loop.leave();
 }
 
+// Sum of an item's areas, in the order of the heads.  A workgroup takes 16 keys; a thread four columns of the lower half of a row and the
+// four that the rotary embedding pairs them with, of dK and dV.  Bound by the areas' way out of L2 and memory.
+__global__ __launch_bounds__(kThreads) void bwd_piece_sums_kernel(BwdParams p, const PieceSum* sums, int width) {
+    const PieceSum it = sums[blockIdx.x / (kDkvKTile / 16)];
+    const int hd = p.head_dim, half = hd / 2, pairs = hd / 8;
+    const int row = (int)(blockIdx.x % (kDkvKTile / 16)) * 16 + (int)threadIdx.x / 16, c = (int)threadIdx.x % 16;
+    if (row >= it.rows || c >= pairs) return;
+    const int64_t area = 2 * kDkvKTile * (int64_t)width;
+    const float* at = p.piece_sums + it.first_area * area + (int64_t)row * width + c * 4;
+    f32x4 k_lo{0.f, 0.f, 0.f, 0.f}, k_hi = k_lo, v_lo = k_lo, v_hi = k_lo;
+    for (int i = 0; i < it.areas; ++i, at += area) {
+        k_lo += *reinterpret_cast<const f32x4*>(at);
+        k_hi += *reinterpret_cast<const f32x4*>(at + half);
+        v_lo += *reinterpret_cast<const f32x4*>(at + kDkvKTile * width);
+        v_hi += *reinterpret_cast<const f32x4*>(at + kDkvKTile * width + half);
+    }
+    k_lo *= p.scale;
+    k_hi *= p.scale;
+    if (p.rope_table != nullptr) {
+        const float* t = p.rope_table + ((int64_t)(it.position0 + row) * half + c * 4) * 2;
+        const f32x4 t01 = *reinterpret_cast<const f32x4*>(t), t23 = *reinterpret_cast<const f32x4*>(t + 4);
+        const f32x4 cs{t01[0], t01[2], t23[0], t23[2]}, sn{t01[1], t01[3], t23[1], t23[3]};
+        const f32x4 lo = k_lo, hi = k_hi;
+        k_lo = lo * cs + hi * sn;
+        k_hi = hi * cs - lo * sn;
+    }
+    const int64_t elem = ((int64_t)(it.row0 + row) * p.kv_heads + it.head) * hd + c * 4;
+    const bool f32 = p.grad_f32 != 0;
+    store_grad4(p.dk, elem, f32, k_lo[0], k_lo[1], k_lo[2], k_lo[3]);
+    store_grad4(p.dk, elem + half, f32, k_hi[0], k_hi[1], k_hi[2], k_hi[3]);
+    store_grad4(p.dv, elem, f32, v_lo[0], v_lo[1], v_lo[2], v_lo[3]);
+    store_grad4(p.dv, elem + half, f32, v_hi[0], v_hi[1], v_hi[2], v_hi[3]);
+}
+
 namespace {
 
 template <int D, int KD, typename... List>
 hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, hipStream_t stream, const List&... list) {
     const dim3 threads(kThreads);
+    if constexpr (sizeof...(List) == 0) {
+        if (p.pieces != nullptr) {
+            const HeadPieces shares{};
+            if (p.split != 0) hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true, false, false, HeadPieces>), dim3((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2)), threads, 0, stream, p, shares);
+            else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, false, false, HeadPieces>), dim3((unsigned)num_items), threads, 0, stream, p, shares);
+            return hipGetLastError();
+        }
+    }
     if (p.split != 0) {
         const dim3 grid((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2));
         if (block) hipLaunchKernelGGL((bwd_dkv_kernel<D, true, KD, true, false, false, List...>), grid, threads, 0, stream, p, list...);
@@ -792,6 +861,12 @@ hipError_t launch_bwd_dkv(const BwdParams& p, const InlineList* list, int head_d
     if (num_items == 0) return hipSuccess;
     return list ? launch_dkv_width(p, head_dim, num_items, block, stream, *list)
                 : launch_dkv_width(p, head_dim, num_items, block, stream);
+}
+
+hipError_t launch_piece_sums(const BwdParams& p, const PieceSum* sums, int64_t count, hipStream_t stream) {
+    if (count == 0) return hipSuccess;
+    hipLaunchKernelGGL(bwd_piece_sums_kernel, dim3((unsigned)(count * (kDkvKTile / 16))), dim3(kThreads), 0, stream, p, sums, tile_width(p.head_dim));
+    return hipGetLastError();
 }
 
 }  // namespace hspmd

@@ -177,6 +177,14 @@ struct hspmd_attn_plan {
     // lists that fit a launch's arguments are kept here instead (forward and dQ share one); items, block_items, queue are then NULL
     bool is_inline = false;
     hspmd::InlineList inline_rows{}, inline_keys{};
+    // dK/dV items dealt out by query heads (packed plans of grouped heads): the list of the shares and of their sums, views into the
+    // current slot, and the sums' memory, which the plan's launches (ordered on the device) use in turn
+    int64_t piece_count = 0, sum_count = 0;   // 0: the pass walks the ordinary list
+    bool piece_halves = false;
+    const hspmd::HeadPiece* pieces = nullptr;
+    const hspmd::PieceSum* sums = nullptr;
+    float* piece_sums = nullptr;
+    size_t piece_bytes = 0;
     int device = -1;   // current when the plan was made
     // device copies of the lists
     ListSlot slots[kPlanSlots];
@@ -189,14 +197,21 @@ namespace {
 // Marks the plan's current slot as read by work just enqueued on `stream` (a later refill of that slot waits for
 // it).  Nothing is recorded while the stream is being captured into a graph: a plan that a graph replays must not be
 // refilled while the graph may run, and that is the caller's to ensure.
-hipError_t mark_use(const hspmd_attn_plan* plan, hipStream_t stream) {
-    if (plan->is_inline) return hipSuccess;   // the launch took the list with it
+hipError_t is_captured(hipStream_t stream, bool* captured) {
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (stream != nullptr) {
         const hipError_t e = hipStreamIsCapturing(stream, &capturing);
         if (e != hipSuccess) return e;
     }
-    if (capturing != hipStreamCaptureStatusNone) return hipSuccess;
+    *captured = capturing != hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+
+hipError_t mark_use(const hspmd_attn_plan* plan, hipStream_t stream, bool shares = false) {
+    if (plan->is_inline && !shares) return hipSuccess;   // the launch took the list with it
+    bool captured = false;
+    if (const hipError_t e = is_captured(stream, &captured)) return e;
+    if (captured) return hipSuccess;
     std::lock_guard<std::mutex> lock(plan->use_mutex);
     ListSlot& slot = const_cast<hspmd_attn_plan*>(plan)->slots[plan->current];
     if (!slot.last_use) return hipSuccess;
@@ -282,8 +297,12 @@ hipError_t wait_for_device(int device) {
 
 // Keeps lists that fit in the plan itself; false: they go to the device.  `all`: the rows list, then the keys list.
 template <typename Item>
+bool fits_inline(int64_t rows, int64_t keys) {
+    return (size_t)std::max(rows, keys) * sizeof(Item) <= (size_t)hspmd::kListBytes;
+}
+template <typename Item>
 bool keep_inline(hspmd_attn_plan* plan, const std::vector<Item>& all, int64_t rows, int64_t keys, Item* (&views)[3]) {
-    if ((size_t)std::max(rows, keys) * sizeof(Item) > (size_t)hspmd::kListBytes) return false;
+    if (!fits_inline<Item>(rows, keys)) return false;
     if (rows > 0) std::memcpy(plan->inline_rows.words, all.data(), (size_t)rows * sizeof(Item));
     if (keys > 0) std::memcpy(plan->inline_keys.words, all.data() + rows, (size_t)keys * sizeof(Item));
     for (int kind = 0; kind < 3; ++kind) {
@@ -294,12 +313,36 @@ bool keep_inline(hspmd_attn_plan* plan, const std::vector<Item>& all, int64_t ro
     return true;
 }
 
+// Room for the sums of dealt-out items; grows only (hipFree waits for launches that still use the former).
+hspmd_status reserve_piece_sums(hspmd_attn_plan* plan, int64_t areas) {
+    const size_t bytes = (size_t)areas * 2 * hspmd::kDkvKTile * (size_t)hspmd::tile_width(plan->head_dim) * sizeof(float);
+    if (bytes <= plan->piece_bytes) return HSPMD_OK;
+    plan->piece_count = plan->sum_count = 0;   // until there is room the pass walks the ordinary list
+    if (plan->piece_sums) {
+        const hipError_t e = hipFree(plan->piece_sums);
+        plan->piece_sums = nullptr;
+        plan->piece_bytes = 0;
+        if (e != hipSuccess) return fail_hip(e, "hipFree(sums of dealt-out items)");
+    }
+    void* block = nullptr;
+    const hipError_t e = hipMalloc(&block, bytes);
+    if (e != hipSuccess) return fail_hip(e, "hipMalloc(sums of dealt-out items)");
+    plan->piece_sums = static_cast<float*>(block);
+    plan->piece_bytes = bytes;
+    return HSPMD_OK;
+}
+
 // Builds the three packed lists of a pack on the host (forward and dQ share one copy) and installs them.
 hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t num_seqs, bool first) {
     std::vector<hspmd_work_item> all;
     size_t offset[3] = {0, 0, 0};
     int64_t count[3] = {0, 0, 0};
+    hspmd::PassLoad load[3];
+    hspmd::PieceList pieces;
+    bool dealt = false;
     try {
+        for (int kind = 0; kind < 3; ++kind)
+            load[kind] = hspmd::pass_load((hspmd_list_kind)kind, cu, num_seqs, plan->q_heads, plan->kv_heads);
         for (int kind = 0; kind < 3; ++kind) {
             if (kind == HSPMD_LIST_DQ) {
                 // same items, costs and order as the forward list: one copy serves both passes
@@ -314,29 +357,47 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
             if (all.empty()) all = std::move(list);
             else all.insert(all.end(), list.begin(), list.end());
         }
+        dealt = plan->order == HSPMD_ORDER_XCD_COST &&
+                hspmd::build_piece_list(cu, num_seqs, plan->q_heads, plan->kv_heads, hspmd::kNumXcd, load[HSPMD_LIST_DKV],
+                                        count[HSPMD_LIST_DKV], plan->head_dim, pieces);
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
     }
     if (hspmd_status rc = first ? need_device(plan) : HSPMD_OK) return rc;
-    const bool kept = keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->items);
-    if (!kept) {
+    if (hspmd_status rc = dealt ? reserve_piece_sums(plan, pieces.areas) : HSPMD_OK) return rc;
+    // shares of items go to the device also where the lists themselves travel in the arguments
+    const bool kept = fits_inline<hspmd_work_item>(count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV]);
+    if (!kept || dealt) {
         // behind the lists: the draw counters of the three passes, uploaded as zeros (one list item = 16 bytes = 4 counters)
-        const size_t counters_at = all.size();
+        constexpr size_t kPieceItems = sizeof(hspmd::HeadPiece) / sizeof(hspmd_work_item), kSumItems = sizeof(hspmd::PieceSum) / sizeof(hspmd_work_item);
+        const size_t counters_at = kept ? 0 : all.size(), pieces_at = kept ? 0 : counters_at + 3 * kCounterItems;
+        const size_t sums_at = pieces_at + pieces.items.size() * kPieceItems;
+        std::vector<hspmd_work_item> shares;
+        std::vector<hspmd_work_item>& upload = kept ? shares : all;
         try {
-            all.resize(all.size() + 3 * kCounterItems, hspmd_work_item{0, 0, 0, 0});
+            upload.resize(sums_at + pieces.sums.size() * kSumItems, hspmd_work_item{0, 0, 0, 0});
         } catch (const std::bad_alloc&) {
             return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
         }
-        if (hspmd_status rc = install_lists(plan, all.data(), all.size() * sizeof(hspmd_work_item), first)) return rc;
+        if (dealt) {
+            std::memcpy(upload.data() + pieces_at, pieces.items.data(), pieces.items.size() * sizeof(hspmd::HeadPiece));
+            std::memcpy(upload.data() + sums_at, pieces.sums.data(), pieces.sums.size() * sizeof(hspmd::PieceSum));
+        }
+        if (hspmd_status rc = install_lists(plan, upload.data(), upload.size() * sizeof(hspmd_work_item), first)) return rc;
+        hspmd_work_item* const lists = static_cast<hspmd_work_item*>(plan->slots[plan->current].block);
+        plan->pieces = dealt ? reinterpret_cast<const hspmd::HeadPiece*>(lists + pieces_at) : nullptr;
+        plan->sums = dealt ? reinterpret_cast<const hspmd::PieceSum*>(lists + sums_at) : nullptr;
         plan->is_inline = false;
-        for (int kind = 0; kind < 3; ++kind)
-            plan->queue[kind] = reinterpret_cast<int32_t*>(static_cast<hspmd_work_item*>(plan->slots[plan->current].block) +
-                                                           counters_at + kind * kCounterItems);
+        if (!kept)
+            for (int kind = 0; kind < 3; ++kind) plan->queue[kind] = reinterpret_cast<int32_t*>(lists + counters_at + kind * kCounterItems);
     }
+    if (kept) keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->items);
     plan->num_seqs = num_seqs;
     plan->total_tokens = cu[num_seqs];
-    for (int kind = 0; kind < 3; ++kind)
-        plan->load[kind] = hspmd::pass_load((hspmd_list_kind)kind, cu, num_seqs, plan->q_heads, plan->kv_heads);
+    plan->piece_count = dealt ? (int64_t)pieces.items.size() : 0;
+    plan->sum_count = dealt ? (int64_t)pieces.sums.size() : 0;
+    plan->piece_halves = pieces.halves;
+    for (int kind = 0; kind < 3; ++kind) plan->load[kind] = load[kind];
     plan->max_position = 0;
     for (int32_t i = 0; i < num_seqs; ++i) plan->max_position = std::max(plan->max_position, cu[i + 1] - cu[i]);
     for (int kind = 0; kind < 3; ++kind) {
@@ -536,6 +597,10 @@ hspmd_status hspmd_attn_plan_destroy(hspmd_attn_plan* plan) {
         const hipError_t e = wait_for_device(plan->device);
         if (e != hipSuccess) rc = fail_hip(e, "hipDeviceSynchronize(plan)");
     }
+    if (plan->piece_sums) {
+        const hipError_t e = hipFree(plan->piece_sums);
+        if (e != hipSuccess) rc = fail_hip(e, "hipFree(sums of dealt-out items)");
+    }
     delete plan;
     return rc;
 }
@@ -670,10 +735,25 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     p.persist = dkv == hspmd::Dispatch::kPersistent ? 1
                 : hspmd::persistent_dkv(dkv, plan->load[HSPMD_LIST_DKV], plan->count[HSPMD_LIST_DKV], p.group, plan->head_dim) ? 2 : 0;
     p.queue = plan->queue[HSPMD_LIST_DKV];
-    auto dkv_pass = [&] { return hspmd::launch_bwd_dkv(p, inline_list(plan, HSPMD_LIST_DKV), plan->head_dim, plan->count[HSPMD_LIST_DKV], false, s); };
+    // (a graph keeps the lists that it took in the arguments, so a plan that has them may be refilled: no shares there)
+    bool captured = false;
+    if (plan->piece_count > 0 && plan->is_inline)
+        if (const hipError_t c = is_captured(s, &captured)) return fail_hip(c, "hipStreamIsCapturing");
+    const bool dealt = plan->piece_count > 0 && !captured;
+    if (dealt) {
+        p.pieces = plan->pieces;
+        p.piece_sums = plan->piece_sums;
+        p.num_items = (int32_t)plan->piece_count;
+        p.split = plan->piece_halves ? 1 : 0;
+        p.persist = 0;
+    }
+    auto dkv_pass = [&] {
+        const hipError_t launched = hspmd::launch_bwd_dkv(p, dealt ? nullptr : inline_list(plan, HSPMD_LIST_DKV), plan->head_dim, p.num_items, false, s);
+        return launched == hipSuccess && dealt ? hspmd::launch_piece_sums(p, plan->sums, plan->sum_count, s) : launched;
+    };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dK/dV launch");
-    if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
+    if (const hipError_t m = mark_use(plan, s, dealt)) return fail_hip(m, "hipEventRecord(work list slot)");
     return HSPMD_OK;
 }
 

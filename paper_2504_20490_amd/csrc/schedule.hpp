@@ -49,6 +49,28 @@ RowsForm rows_form(hspmd_list_kind kind, const PassLoad& load, int64_t slots, in
 // Whether the dK/dV pass of a packed plan draws its items in persistent workgroups: also where pass_dispatch says whole items.
 bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim);
 
+// ---- dK/dV items of grouped heads, dealt out by query heads
+// A share of an item: query heads first_head .. first_head + heads - 1 of the KV group.  area: where its dK and dV go, as fp32 sums that
+// one more kernel adds up; below 0: it is the whole item and writes them itself.
+struct HeadPiece {
+    int32_t token_start, seq_len, tile, head;   // as hspmd_work_item; tile < 0: padding
+    int32_t first_head, heads, area, pad;
+};
+// An item that is dealt out: its keys (rows of dK and dV) and the consecutive areas whose sum they are.
+struct PieceSum {
+    int32_t row0, rows, head, position0;   // position of the first key inside its sequence
+    int32_t first_area, areas, pad[2];
+};
+struct PieceList {
+    std::vector<HeadPiece> items;    // launch order, as build_work_list's
+    std::vector<PieceSum> sums;
+    int64_t areas = 0;
+    bool halves = false;             // the unit of work is half a piece
+};
+// The dK/dV list of a pack by pieces, where that pays (`load`, `slots`: of the ordinary list); else false.
+bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t num_queues, const PassLoad& load,
+                      int64_t slots, int32_t head_dim, PieceList& out);
+
 // ---- cost model: predicted kernel times (microseconds) of the three passes for a pack
 double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim);
 
