@@ -193,10 +193,6 @@ hspmd_status hspmd_attn_plan_create_ordered(const int32_t* cu_seqlens_host, int3
  *   allocating after the first few refills.
  *   Lists of up to 240 slots (120 of a block plan) take none of this: the plan keeps them on the host, every launch carries its
  *   list among its arguments (a graph keeps the one it was captured with), nothing is uploaded and no event is recorded.
- *   Packed plans of grouped heads may deal the dK/dV pass's items out by query heads where a pack's longest item would outlast
- *   the rest; the shares' list goes to a slot as described, also beside lists in the arguments (under capture those are used and
- *   nothing is dealt out), and the plan owns the memory of the shares' sums, at most 128 MB, which a refill enlarges when a pack
- *   needs more than any before it (hipFree + hipMalloc).
  *   Not for concurrent use: no other thread may launch with the plan during the call.  A launch recorded into a HIP
  *   graph records no event (events cannot be waited for from inside a capture): a plan that a graph replays must not be
  *   refilled while the graph may run.  On error the plan keeps its previous pack.
@@ -236,7 +232,10 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
  *   lse     fp32 [local_q_heads, T] as written by the forward
  *   dq      [T, local_q_heads, head_dim]; dk, dv [T, local_kv_heads, head_dim]; contiguous,
  *           bf16 or fp32 according to grad_dtype; fully overwritten
- *   workspace  device, at least hspmd_attn_bwd_workspace_bytes(plan) bytes, 16-byte aligned
+ *   workspace  device, hspmd_attn_bwd_workspace_bytes(plan) bytes, 16-byte aligned.  The row statistics take
+ *              (2 * local_q_heads * T + 16) * 4 bytes of it; less than that is WORKSPACE_TOO_SMALL.  For packs whose longest dK/dV
+ *              items would outlast the pass it also holds partial sums of dK and dV (at most 128 MB), so that those items can be
+ *              dealt out; a workspace without room for them gives the same gradients, summed in another order, later.
  */
 hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, const void* k, const void* v,
                                    const void* o, const float* lse, const void* d_o,
@@ -251,7 +250,7 @@ hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, c
  * the dK/dV pass go into a fixed device array inside the library (HSPMD_STATIC_WORKSPACE_BYTES bytes on every GPU the
  * library runs on, held until the process ends).  The call allocates and frees nothing and creates no events
  * (per-kernel timing does not apply to it).
- *   Limit: hspmd_attn_bwd_workspace_bytes(plan) <= HSPMD_STATIC_WORKSPACE_BYTES, i.e.
+ *   Limit: (2 * local_q_heads * T + 16) * 4 <= HSPMD_STATIC_WORKSPACE_BYTES, i.e.
  *   local_q_heads * total_tokens <= 2^21 (the 65536-token, 32-head configuration just fits);
  *   larger packs get WORKSPACE_TOO_SMALL and nothing is launched.
  *   All calls on one GPU share the array: two calls that may overlap on one GPU (different streams, no event between

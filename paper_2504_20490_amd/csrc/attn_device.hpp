@@ -482,6 +482,27 @@ __device__ __forceinline__ ItemGeom load_item(const Params& p, int idx) {
     }
 }
 
+// The same for a list of shares (HeadPiece).
+template <bool INLINE, typename Params>
+__device__ __forceinline__ HeadPiece load_piece(const Params& p, int idx) {
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    typedef const i32x4 __attribute__((address_space(4)))* ArgumentWords;
+    constexpr int kListAt = (int)((sizeof(Params) + alignof(InlineList) - 1) / alignof(InlineList));
+    static_assert(!INLINE || kListAt * sizeof(i32x4) + sizeof(InlineList) + 16 <= kArgumentBytes, "what a launch may carry");
+    int a, b, c, d;
+    if constexpr (INLINE) {
+        const i32x4 w = ((ArgumentWords)__builtin_amdgcn_kernarg_segment_ptr() + kListAt)[idx];
+        a = w[0], b = w[1], c = w[2], d = w[3];
+    } else {
+        const HeadPiece it = p.pieces[idx];
+        a = it.token_start, b = it.seq_len, c = (int)it.where, d = (int)it.deal;
+    }
+    a = __builtin_amdgcn_readfirstlane(a), b = __builtin_amdgcn_readfirstlane(b);   // (read behind stores, they arrive in vector registers)
+    c = __builtin_amdgcn_readfirstlane(c), d = __builtin_amdgcn_readfirstlane(d);
+    asm volatile("" : "+s"(a), "+s"(b), "+s"(c), "+s"(d));   // four values of their own, as in load_item
+    return HeadPiece{a, b, (uint32_t)c, (uint32_t)d};
+}
+
 // Work distribution of the persistent kernels.  A launch starts as many workgroups as the device holds at once;
 // workgroup b begins with slot b of the launch-ordered list (slot p belongs to queue p % kQueues, and workgroups are
 // handed to the XCDs round-robin, so queue q is served by the workgroups of XCD q) and then draws further slots of

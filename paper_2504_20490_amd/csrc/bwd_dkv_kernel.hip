@@ -362,14 +362,14 @@ __device__ __forceinline__ void dkv_iteration_hinted(DkvState<D, KD>& st, const 
 // GROUPS: whole packed items of several query heads at head_dim above 112, one workgroup each; every head is walked one tile at a time,
 // in the compiler's order (dkv_iteration_hinted).
 //
-// List: nothing, InlineList when the work list is the second argument, or HeadPieces where items are dealt out by query heads: a share
+// List: nothing, InlineList when the work list is the second argument, or HeadPieces where items are dealt out by query heads and tiles: a share
 // leaves fp32 sums in its area (build_piece_list in schedule.cpp).
 template <int D, bool BLOCK, int KD, bool SPLIT, bool PERSIST, bool GROUPS, typename... List>
 __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv_kernel(BwdParams p, List...) {
     static_assert(!PERSIST || (!BLOCK && !SPLIT), "whole items of packed plans only");
     static_assert(!GROUPS || (KD == 8 && !BLOCK && !SPLIT && !PERSIST), "whole items of packed plans, head_dim above 112");
     constexpr bool kPieces = has_pieces<List...>;
-    static_assert(!kPieces || (!BLOCK && !PERSIST && !GROUPS && sizeof...(List) == 1), "packed plans, a workgroup per share");
+    static_assert(!kPieces || (!BLOCK && !PERSIST && !GROUPS), "packed plans, a workgroup per share");
     constexpr bool kTrips = !SPLIT && !GROUPS && D == 128;   // whole items, two tiles a trip
     using G = DkvGeom<D, KD>;
     constexpr int BKV = SPLIT ? kDkvKTile / 2 : kDkvKTile, BQ = kDkvQTile;
@@ -384,14 +384,15 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     do {
     ItemGeom item;
     int first_head = 0, n_heads = p.group;   // query heads of the group that this workgroup walks
+    int share_first = 0, share_end = 0;      // kPieces: the query tiles
     if constexpr (kPieces) {
-        const HeadPiece it = p.pieces[slot];
-        // (each a value of its own: spilled as one group, they leave a stack object behind)
-        auto field = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
-        const int start = field(it.token_start), length = field(it.seq_len);
-        item = ItemGeom{start, length, start, length, 0, field(it.tile), field(it.head), 0};
-        first_head = field(it.first_head);
-        n_heads = field(it.heads);
+        const HeadPiece it = load_piece<has_inline_list<List...>>(p, slot);
+        if (it.padding()) break;
+        item = ItemGeom{it.token_start, it.seq_len, it.token_start, it.seq_len, 0, it.tile(), it.head(), 0};
+        first_head = it.first_head();
+        n_heads = it.n_heads(p.group);
+        share_first = it.first_tile();
+        share_end = it.end_tile();
     } else {
         item = load_item<BLOCK, has_inline_list<List...>>(p, slot);
     }
@@ -417,8 +418,10 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     constexpr int kLoadsPerTile = 2 * (BQ * D * 2 / 1024) / 4 + 1;   // per wave: Q and dO chunks + one statistics copy
     // tiles: for each head of the group, q tiles first_qt .. n_qt-1 (rows at or below the diagonal: row r sees
     // key j iff j <= r + shift, so the tile's first key is seen by the rows from key0 - shift on)
-    const int first_qt = max(0, key0 - shift) / BQ;
-    const int n_qt = (L + BQ - 1) / BQ;
+    const int diagonal_qt = max(0, key0 - shift) / BQ;
+    // (a share has two tiles and more, so the second half of an item, which starts a tile further down, finds one in its first share too)
+    const int first_qt = kPieces ? max(diagonal_qt, share_first) : diagonal_qt;
+    const int n_qt = kPieces ? share_end : (L + BQ - 1) / BQ;
     const int per_head = max(0, n_qt - first_qt);
     const int n_tiles = per_head * n_heads;
     if (BLOCK && per_head == 0) {
@@ -635,7 +638,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     // q tiles that hold some (row, key) pair above the shifted diagonal for the keys of this workgroup:
     // qt BQ + shift < key0 + BKV - 1; the two nearest the diagonal when there is no shift
     const int n_masked = BLOCK ? (key0 + BKV - 2 - shift < 0 ? 0 : max(0, min(per_head, (key0 + BKV - 2 - shift) / BQ - first_qt + 1)))
-                               : min(BKV / BQ, per_head);
+                               : kPieces ? max(0, min(BKV / BQ - (first_qt - diagonal_qt), per_head)) : min(BKV / BQ, per_head);
     const int n_general = max(3, n_masked);   // tiles below this index (from the diagonal) take the general path
     // SPLIT: tiles are walked in pairs, one per accumulator pair; after a single tile the pairs change places
     using Even = std::integral_constant<int, 0>;
@@ -707,7 +710,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     if constexpr (kPieces) {
         int again = slot;   // (read here and not kept through the tile loop)
         asm volatile("" : "+s"(again));
-        area = p.pieces[again].area;
+        const HeadPiece it = load_piece<has_inline_list<List...>>(p, again);
+        if (it.shares(p.group) > 1) area = it.area();
     }
     const bool sums = kPieces && area >= 0;
     const bool rope = !sums && p.rope_table != nullptr;
@@ -771,17 +775,23 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     loop.leave();
 }
 
-// Sum of an item's areas, in the order of the heads.  A workgroup takes 16 keys; a thread four columns of the lower half of a row and the
-// four that the rotary embedding pairs them with, of dK and dV.  Bound by the areas' way out of L2 and memory.
-__global__ __launch_bounds__(kThreads) void bwd_piece_sums_kernel(BwdParams p, const PieceSum* sums, int width) {
-    const PieceSum it = sums[blockIdx.x / (kDkvKTile / 16)];
-    const int hd = p.head_dim, half = hd / 2, pairs = hd / 8;
+// Sum of an item's areas, in the order of the heads and tiles.  A workgroup takes 16 keys of the item whose first share its entry of the list
+// is; a thread four columns of the lower half of a row and the four that the rotary embedding pairs them with, of dK and dV.  Bound by
+// the areas' way out of L2 and memory.
+template <typename... List>
+__global__ __launch_bounds__(kThreads) void bwd_piece_sums_kernel(BwdParams p, List...) {
+    const HeadPiece it = load_piece<has_inline_list<List...>>(p, blockIdx.x / (kDkvKTile / 16));
+    if (it.padding() || it.index() != 0) return;
+    const int areas = it.shares(p.group);
+    if (areas == 1) return;
+    const int hd = p.head_dim, half = hd / 2, pairs = hd / 8, width = hd <= 64 ? 64 : 128;
     const int row = (int)(blockIdx.x % (kDkvKTile / 16)) * 16 + (int)threadIdx.x / 16, c = (int)threadIdx.x % 16;
-    if (row >= it.rows || c >= pairs) return;
+    const int position = it.tile() * kDkvKTile + row;
+    if (position >= it.seq_len || c >= pairs) return;
     const int64_t area = 2 * kDkvKTile * (int64_t)width;
-    const float* at = p.piece_sums + it.first_area * area + (int64_t)row * width + c * 4;
+    const float* at = p.piece_sums + it.area() * area + (int64_t)row * width + c * 4;
     f32x4 k_lo{0.f, 0.f, 0.f, 0.f}, k_hi = k_lo, v_lo = k_lo, v_hi = k_lo;
-    for (int i = 0; i < it.areas; ++i, at += area) {
+    for (int i = 0; i < areas; ++i, at += area) {
         k_lo += *reinterpret_cast<const f32x4*>(at);
         k_hi += *reinterpret_cast<const f32x4*>(at + half);
         v_lo += *reinterpret_cast<const f32x4*>(at + kDkvKTile * width);
@@ -790,14 +800,14 @@ __global__ __launch_bounds__(kThreads) void bwd_piece_sums_kernel(BwdParams p, c
     k_lo *= p.scale;
     k_hi *= p.scale;
     if (p.rope_table != nullptr) {
-        const float* t = p.rope_table + ((int64_t)(it.position0 + row) * half + c * 4) * 2;
+        const float* t = p.rope_table + ((int64_t)position * half + c * 4) * 2;
         const f32x4 t01 = *reinterpret_cast<const f32x4*>(t), t23 = *reinterpret_cast<const f32x4*>(t + 4);
         const f32x4 cs{t01[0], t01[2], t23[0], t23[2]}, sn{t01[1], t01[3], t23[1], t23[3]};
         const f32x4 lo = k_lo, hi = k_hi;
         k_lo = lo * cs + hi * sn;
         k_hi = hi * cs - lo * sn;
     }
-    const int64_t elem = ((int64_t)(it.row0 + row) * p.kv_heads + it.head) * hd + c * 4;
+    const int64_t elem = ((int64_t)(it.token_start + position) * p.kv_heads + it.head()) * hd + c * 4;
     const bool f32 = p.grad_f32 != 0;
     store_grad4(p.dk, elem, f32, k_lo[0], k_lo[1], k_lo[2], k_lo[3]);
     store_grad4(p.dk, elem + half, f32, k_hi[0], k_hi[1], k_hi[2], k_hi[3]);
@@ -810,13 +820,11 @@ namespace {
 template <int D, int KD, typename... List>
 hipError_t launch_dkv(const BwdParams& p, int64_t num_items, bool block, hipStream_t stream, const List&... list) {
     const dim3 threads(kThreads);
-    if constexpr (sizeof...(List) == 0) {
-        if (p.pieces != nullptr) {
-            const HeadPieces shares{};
-            if (p.split != 0) hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true, false, false, HeadPieces>), dim3((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2)), threads, 0, stream, p, shares);
-            else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, false, false, HeadPieces>), dim3((unsigned)num_items), threads, 0, stream, p, shares);
-            return hipGetLastError();
-        }
+    if (p.piece_sums != nullptr) {
+        const HeadPieces shares{};
+        if (p.split != 0) hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, true, false, false, List..., HeadPieces>), dim3((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2)), threads, 0, stream, p, list..., shares);
+        else hipLaunchKernelGGL((bwd_dkv_kernel<D, false, KD, false, false, false, List..., HeadPieces>), dim3((unsigned)num_items), threads, 0, stream, p, list..., shares);
+        return hipGetLastError();
     }
     if (p.split != 0) {
         const dim3 grid((unsigned)((num_items + kQueues - 1) / kQueues * kQueues * 2));
@@ -863,9 +871,11 @@ hipError_t launch_bwd_dkv(const BwdParams& p, const InlineList* list, int head_d
                 : launch_dkv_width(p, head_dim, num_items, block, stream);
 }
 
-hipError_t launch_piece_sums(const BwdParams& p, const PieceSum* sums, int64_t count, hipStream_t stream) {
+hipError_t launch_piece_sums(const BwdParams& p, const InlineList* list, int64_t count, hipStream_t stream) {
     if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(bwd_piece_sums_kernel, dim3((unsigned)(count * (kDkvKTile / 16))), dim3(kThreads), 0, stream, p, sums, tile_width(p.head_dim));
+    const dim3 grid((unsigned)(count * (kDkvKTile / 16))), threads(kThreads);
+    if (list) hipLaunchKernelGGL((bwd_piece_sums_kernel<InlineList>), grid, threads, 0, stream, p, *list);
+    else hipLaunchKernelGGL((bwd_piece_sums_kernel<>), grid, threads, 0, stream, p);
     return hipGetLastError();
 }
 

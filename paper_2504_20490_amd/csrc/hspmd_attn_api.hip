@@ -177,14 +177,12 @@ struct hspmd_attn_plan {
     // lists that fit a launch's arguments are kept here instead (forward and dQ share one); items, block_items, queue are then NULL
     bool is_inline = false;
     hspmd::InlineList inline_rows{}, inline_keys{};
-    // dK/dV items dealt out by query heads (packed plans of grouped heads): the list of the shares and of their sums, views into the
-    // current slot, and the sums' memory, which the plan's launches (ordered on the device) use in turn
-    int64_t piece_count = 0, sum_count = 0;   // 0: the pass walks the ordinary list
+    // dK/dV items that are dealt out (packed plans): the shares' list, a view into the current slot or, beside lists in the arguments, kept
+    // here; their sums take `areas` of the caller's workspace, and where it has no room the pass walks the ordinary list
+    int64_t piece_count = 0, areas = 0;   // 0: nothing is dealt out
     bool piece_halves = false;
     const hspmd::HeadPiece* pieces = nullptr;
-    const hspmd::PieceSum* sums = nullptr;
-    float* piece_sums = nullptr;
-    size_t piece_bytes = 0;
+    hspmd::InlineList inline_pieces{};
     int device = -1;   // current when the plan was made
     // device copies of the lists
     ListSlot slots[kPlanSlots];
@@ -197,21 +195,14 @@ namespace {
 // Marks the plan's current slot as read by work just enqueued on `stream` (a later refill of that slot waits for
 // it).  Nothing is recorded while the stream is being captured into a graph: a plan that a graph replays must not be
 // refilled while the graph may run, and that is the caller's to ensure.
-hipError_t is_captured(hipStream_t stream, bool* captured) {
+hipError_t mark_use(const hspmd_attn_plan* plan, hipStream_t stream) {
+    if (plan->is_inline) return hipSuccess;   // the launch took the list with it
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (stream != nullptr) {
         const hipError_t e = hipStreamIsCapturing(stream, &capturing);
         if (e != hipSuccess) return e;
     }
-    *captured = capturing != hipStreamCaptureStatusNone;
-    return hipSuccess;
-}
-
-hipError_t mark_use(const hspmd_attn_plan* plan, hipStream_t stream, bool shares = false) {
-    if (plan->is_inline && !shares) return hipSuccess;   // the launch took the list with it
-    bool captured = false;
-    if (const hipError_t e = is_captured(stream, &captured)) return e;
-    if (captured) return hipSuccess;
+    if (capturing != hipStreamCaptureStatusNone) return hipSuccess;
     std::lock_guard<std::mutex> lock(plan->use_mutex);
     ListSlot& slot = const_cast<hspmd_attn_plan*>(plan)->slots[plan->current];
     if (!slot.last_use) return hipSuccess;
@@ -313,24 +304,12 @@ bool keep_inline(hspmd_attn_plan* plan, const std::vector<Item>& all, int64_t ro
     return true;
 }
 
-// Room for the sums of dealt-out items; grows only (hipFree waits for launches that still use the former).
-hspmd_status reserve_piece_sums(hspmd_attn_plan* plan, int64_t areas) {
-    const size_t bytes = (size_t)areas * 2 * hspmd::kDkvKTile * (size_t)hspmd::tile_width(plan->head_dim) * sizeof(float);
-    if (bytes <= plan->piece_bytes) return HSPMD_OK;
-    plan->piece_count = plan->sum_count = 0;   // until there is room the pass walks the ordinary list
-    if (plan->piece_sums) {
-        const hipError_t e = hipFree(plan->piece_sums);
-        plan->piece_sums = nullptr;
-        plan->piece_bytes = 0;
-        if (e != hipSuccess) return fail_hip(e, "hipFree(sums of dealt-out items)");
-    }
-    void* block = nullptr;
-    const hipError_t e = hipMalloc(&block, bytes);
-    if (e != hipSuccess) return fail_hip(e, "hipMalloc(sums of dealt-out items)");
-    plan->piece_sums = static_cast<float*>(block);
-    plan->piece_bytes = bytes;
-    return HSPMD_OK;
+// What the backward needs of its workspace: -D [Hq,T], -LSE/scale [Hq,T], and 16 floats of -inf.
+size_t statistics_bytes(const hspmd_attn_plan* plan) {
+    return (2 * (size_t)plan->q_heads * (size_t)plan->total_tokens + 16) * sizeof(float);
 }
+// Behind them, where items are dealt out, their sums.
+size_t sums_offset(const hspmd_attn_plan* plan) { return (statistics_bytes(plan) + 255) / 256 * 256; }
 
 // Builds the three packed lists of a pack on the host (forward and dQ share one copy) and installs them.
 hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t num_seqs, bool first) {
@@ -339,7 +318,7 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
     int64_t count[3] = {0, 0, 0};
     hspmd::PassLoad load[3];
     hspmd::PieceList pieces;
-    bool dealt = false;
+    bool kept = false, dealt = false;
     try {
         for (int kind = 0; kind < 3; ++kind)
             load[kind] = hspmd::pass_load((hspmd_list_kind)kind, cu, num_seqs, plan->q_heads, plan->kv_heads);
@@ -357,45 +336,38 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
             if (all.empty()) all = std::move(list);
             else all.insert(all.end(), list.begin(), list.end());
         }
+        kept = fits_inline<hspmd_work_item>(count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV]);
         dealt = plan->order == HSPMD_ORDER_XCD_COST &&
                 hspmd::build_piece_list(cu, num_seqs, plan->q_heads, plan->kv_heads, hspmd::kNumXcd, load[HSPMD_LIST_DKV],
-                                        count[HSPMD_LIST_DKV], plan->head_dim, pieces);
+                                        count[HSPMD_LIST_DKV], plan->head_dim,
+                                        kept ? hspmd::kListBytes / (int64_t)sizeof(hspmd::HeadPiece) : std::numeric_limits<int32_t>::max(), pieces);
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
     }
     if (hspmd_status rc = first ? need_device(plan) : HSPMD_OK) return rc;
-    if (hspmd_status rc = dealt ? reserve_piece_sums(plan, pieces.areas) : HSPMD_OK) return rc;
-    // shares of items go to the device also where the lists themselves travel in the arguments
-    const bool kept = fits_inline<hspmd_work_item>(count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV]);
-    if (!kept || dealt) {
-        // behind the lists: the draw counters of the three passes, uploaded as zeros (one list item = 16 bytes = 4 counters)
-        constexpr size_t kPieceItems = sizeof(hspmd::HeadPiece) / sizeof(hspmd_work_item), kSumItems = sizeof(hspmd::PieceSum) / sizeof(hspmd_work_item);
-        const size_t counters_at = kept ? 0 : all.size(), pieces_at = kept ? 0 : counters_at + 3 * kCounterItems;
-        const size_t sums_at = pieces_at + pieces.items.size() * kPieceItems;
-        std::vector<hspmd_work_item> shares;
-        std::vector<hspmd_work_item>& upload = kept ? shares : all;
+    if (!kept) {
+        // behind the lists: the draw counters of the three passes, uploaded as zeros (one list item = 16 bytes = 4 counters), and the shares
+        const size_t counters_at = all.size(), pieces_at = counters_at + 3 * kCounterItems;
         try {
-            upload.resize(sums_at + pieces.sums.size() * kSumItems, hspmd_work_item{0, 0, 0, 0});
+            all.resize(pieces_at + (dealt ? pieces.items.size() : 0), hspmd_work_item{0, 0, 0, 0});
         } catch (const std::bad_alloc&) {
             return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
         }
-        if (dealt) {
-            std::memcpy(upload.data() + pieces_at, pieces.items.data(), pieces.items.size() * sizeof(hspmd::HeadPiece));
-            std::memcpy(upload.data() + sums_at, pieces.sums.data(), pieces.sums.size() * sizeof(hspmd::PieceSum));
-        }
-        if (hspmd_status rc = install_lists(plan, upload.data(), upload.size() * sizeof(hspmd_work_item), first)) return rc;
+        if (dealt) std::memcpy(all.data() + pieces_at, pieces.items.data(), pieces.items.size() * sizeof(hspmd::HeadPiece));
+        if (hspmd_status rc = install_lists(plan, all.data(), all.size() * sizeof(hspmd_work_item), first)) return rc;
+        plan->is_inline = false;
         hspmd_work_item* const lists = static_cast<hspmd_work_item*>(plan->slots[plan->current].block);
         plan->pieces = dealt ? reinterpret_cast<const hspmd::HeadPiece*>(lists + pieces_at) : nullptr;
-        plan->sums = dealt ? reinterpret_cast<const hspmd::PieceSum*>(lists + sums_at) : nullptr;
-        plan->is_inline = false;
-        if (!kept)
-            for (int kind = 0; kind < 3; ++kind) plan->queue[kind] = reinterpret_cast<int32_t*>(lists + counters_at + kind * kCounterItems);
+        for (int kind = 0; kind < 3; ++kind) plan->queue[kind] = reinterpret_cast<int32_t*>(lists + counters_at + kind * kCounterItems);
+    } else {
+        keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->items);
+        plan->pieces = nullptr;
+        if (dealt) std::memcpy(plan->inline_pieces.words, pieces.items.data(), pieces.items.size() * sizeof(hspmd::HeadPiece));
     }
-    if (kept) keep_inline(plan, all, count[HSPMD_LIST_FWD], count[HSPMD_LIST_DKV], plan->items);
     plan->num_seqs = num_seqs;
     plan->total_tokens = cu[num_seqs];
     plan->piece_count = dealt ? (int64_t)pieces.items.size() : 0;
-    plan->sum_count = dealt ? (int64_t)pieces.sums.size() : 0;
+    plan->areas = dealt ? pieces.areas : 0;
     plan->piece_halves = pieces.halves;
     for (int kind = 0; kind < 3; ++kind) plan->load[kind] = load[kind];
     plan->max_position = 0;
@@ -597,10 +569,6 @@ hspmd_status hspmd_attn_plan_destroy(hspmd_attn_plan* plan) {
         const hipError_t e = wait_for_device(plan->device);
         if (e != hipSuccess) rc = fail_hip(e, "hipDeviceSynchronize(plan)");
     }
-    if (plan->piece_sums) {
-        const hipError_t e = hipFree(plan->piece_sums);
-        if (e != hipSuccess) rc = fail_hip(e, "hipFree(sums of dealt-out items)");
-    }
     delete plan;
     return rc;
 }
@@ -614,8 +582,8 @@ int64_t hspmd_attn_plan_num_items(const hspmd_attn_plan* plan, hspmd_list_kind k
 
 size_t hspmd_attn_bwd_workspace_bytes(const hspmd_attn_plan* plan) {
     if (!plan) return 0;
-    // -D [Hq,T], -LSE/scale [Hq,T], and 16 floats of -inf
-    return (2 * (size_t)plan->q_heads * (size_t)plan->total_tokens + 16) * sizeof(float);
+    if (plan->areas == 0) return statistics_bytes(plan);
+    return sums_offset(plan) + (size_t)plan->areas * 2 * hspmd::kDkvKTile * (size_t)hspmd::tile_width(plan->head_dim) * sizeof(float);
 }
 
 static hspmd_status check_strides(const hspmd_attn_plan* plan, int64_t q_token_stride, int64_t kv_token_stride) {
@@ -692,7 +660,7 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
         !aligned16(dk) || !aligned16(dv) || !aligned16(workspace))
         return fail(HSPMD_ERR_INVALID_ARG, "tensors and workspace must be 16-byte aligned");
     if (hspmd_status rc = check_strides(plan, q_token_stride, kv_token_stride)) return rc;
-    if (workspace_bytes < hspmd_attn_bwd_workspace_bytes(plan))
+    if (workspace_bytes < statistics_bytes(plan))
         return fail(HSPMD_ERR_WORKSPACE_TOO_SMALL, "workspace smaller than hspmd_attn_bwd_workspace_bytes(plan)");
     float scale = 0.f;
     if (hspmd_status rc = resolve_scale(softmax_scale, plan->head_dim, &scale)) return rc;
@@ -735,25 +703,22 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     p.persist = dkv == hspmd::Dispatch::kPersistent ? 1
                 : hspmd::persistent_dkv(dkv, plan->load[HSPMD_LIST_DKV], plan->count[HSPMD_LIST_DKV], p.group, plan->head_dim) ? 2 : 0;
     p.queue = plan->queue[HSPMD_LIST_DKV];
-    // (a graph keeps the lists that it took in the arguments, so a plan that has them may be refilled: no shares there)
-    bool captured = false;
-    if (plan->piece_count > 0 && plan->is_inline)
-        if (const hipError_t c = is_captured(s, &captured)) return fail_hip(c, "hipStreamIsCapturing");
-    const bool dealt = plan->piece_count > 0 && !captured;
-    if (dealt) {
+    const hspmd::InlineList* keys = inline_list(plan, HSPMD_LIST_DKV);
+    if (plan->piece_count > 0 && workspace_bytes >= hspmd_attn_bwd_workspace_bytes(plan)) {
         p.pieces = plan->pieces;
-        p.piece_sums = plan->piece_sums;
+        p.piece_sums = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + sums_offset(plan));
         p.num_items = (int32_t)plan->piece_count;
         p.split = plan->piece_halves ? 1 : 0;
         p.persist = 0;
+        if (keys) keys = &plan->inline_pieces;
     }
     auto dkv_pass = [&] {
-        const hipError_t launched = hspmd::launch_bwd_dkv(p, dealt ? nullptr : inline_list(plan, HSPMD_LIST_DKV), plan->head_dim, p.num_items, false, s);
-        return launched == hipSuccess && dealt ? hspmd::launch_piece_sums(p, plan->sums, plan->sum_count, s) : launched;
+        const hipError_t launched = hspmd::launch_bwd_dkv(p, keys, plan->head_dim, p.num_items, false, s);
+        return launched == hipSuccess && p.piece_sums ? hspmd::launch_piece_sums(p, keys, p.num_items, s) : launched;
     };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dK/dV launch");
-    if (const hipError_t m = mark_use(plan, s, dealt)) return fail_hip(m, "hipEventRecord(work list slot)");
+    if (const hipError_t m = mark_use(plan, s)) return fail_hip(m, "hipEventRecord(work list slot)");
     return HSPMD_OK;
 }
 
@@ -799,7 +764,7 @@ hspmd_status hspmd_attn_varlen_bwd_static_ws(const hspmd_attn_plan* plan, const 
                                              int64_t kv_token_stride, float softmax_scale, void* dq, void* dk, void* dv,
                                              hspmd_grad_dtype grad_dtype, void* stream) {
     if (!plan) return fail(HSPMD_ERR_INVALID_ARG, "plan is NULL");
-    const size_t need = hspmd_attn_bwd_workspace_bytes(plan);
+    const size_t need = statistics_bytes(plan);
     if (need > (size_t)HSPMD_STATIC_WORKSPACE_BYTES)
         return fail(HSPMD_ERR_WORKSPACE_TOO_SMALL,
                     "local_q_heads * total_tokens exceeds what the library's fixed workspace holds "

@@ -81,8 +81,8 @@ struct BwdParams {
     int32_t* queue;                // the current pass's draw counters (ItemQueue), zero between launches
     int32_t split;                 // the pass works on half items (decided from the plan's loads, see pass_dispatch)
     int32_t teams;                 // dQ pass: 2: two teams of four waves take an item's key tiles in turn (see rows_form); 1: one team
-    const HeadPiece* pieces;       // dK/dV pass of a packed plan: shares of items instead of `items`, or NULL
-    float* piece_sums;             // their areas: [area][dK, dV][128 keys][tile width]
+    const HeadPiece* pieces;       // dK/dV pass of a packed plan whose items are dealt out: the shares' list, where it is not inline
+    float* piece_sums;             // their areas, [area][dK, dV][128 keys][tile width]; NULL: the pass walks `items`
     int32_t persist;               // dK/dV pass of a packed plan with whole items: 1 persistent workgroups (see pass_dispatch), an
                                    // error where the device's size is unknown; 2 the same (see persistent_dkv), but there one
                                    // workgroup per item: those packs need no size; 0 one per item
@@ -107,8 +107,9 @@ hipError_t launch_bwd_dsum(const BwdParams& p, int head_dim, hipStream_t stream)
 hipError_t launch_bwd_dq(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream);
 hipError_t launch_bwd_dkv(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream);
 
-// adds up the areas of the items that were dealt out: dK and dV, rotated back and rounded as the pass itself would
-hipError_t launch_piece_sums(const BwdParams& p, const PieceSum* sums, int64_t count, hipStream_t stream);
+// adds up the areas of the items that were dealt out: dK and dV, rotated back and rounded as the pass itself would.  `list`, count: as
+// the pass's own
+hipError_t launch_piece_sums(const BwdParams& p, const InlineList* list, int64_t count, hipStream_t stream);
 
 // merge of two partial results of the same rows over disjoint key sets (fp32 O [T, Hq, d], LSE [Hq, T]):
 // out = a (+) b; out may alias a.  out_bf16 (may be NULL) also receives the merged O rounded to bf16.

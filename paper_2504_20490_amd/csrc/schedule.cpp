@@ -453,16 +453,20 @@ bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t 
 }
 
 // ------------------------------------------------------------------------------ pieces of dK/dV items
-// An item of grouped heads walks the query tiles of every head of its group, so on packs of few KV heads the first key tiles of a long
-// sequence outlast everything else.  Items above a limit are dealt out by query heads (the walk's outer loop): every share leaves its
-// sums of dK and dV as fp32 in memory, and a kernel behind the pass adds them up in the order of the heads.  That costs a launch and
+// An item walks the query tiles of every head of its group, so on packs of few KV heads the first key tiles of a long sequence
+// outlast everything else.  Items above a limit are dealt out by query heads (the walk's outer loop) or, where heads are not
+// grouped, by query tiles: every share leaves its sums of dK and dV as fp32 in memory, and a kernel behind the pass adds them up in the order of
+// heads and tiles.  That costs a launch and
 // the way of the sums through memory, about seven steps and 0.025 per share, and the shares' own prologues and stores.
 // Measured, the dK/dV pass without and with, sums included (us): 8 query heads on 2 KV heads, 3000 and 500 tokens 146 / 68, 2048 tokens 100 /
 // 43, 512 tokens 36 / 21, 16384 tokens 1136 / 968; 8 on 1, 4096 tokens 352 / 98; 16 on 4, 8192 tokens 589 / 513; 28 on 7, 1947 tokens 107 / 92; width
-// 64, 8 on 2, 8192 tokens 270 / 155.  Of 62 packs of 256 to 32000 tokens, 1 to 8 KV heads and groups of 2 to 8, the 38 that this takes run in
-// 0.72 of the time on average, 0.98 at worst.  The line is at 0.9 of the steps because idle time comes back as clock: at 0.95 it also takes
-// 32 heads on 8, 9 sequences of 103 .. 3079 321 / 322, and 10 on 5, head_dim 104, 8 of up to 12995 877 / 893.  Limits finer than a quarter of the
-// mean only add sums; a limit of the mean leaves queues of 41 heavy shares on 32 units (8192 tokens, 16 on 4 617).
+// 64, 8 on 2, 8192 tokens 270 / 155; one head of 8192 tokens 100 / 52, 4 heads of 4096 62 / 57, width 64, 2 heads of 16384 209 / 154.  Of 62 packs of
+// 256 to 32000 tokens, 1 to 8 KV heads and groups of 2 to 8, the 38 that this takes run in 0.72 of the time on average, 0.98 at worst; of 61
+// packs of 1000 to 50000 tokens and 1 to 8 heads, most of one query head each, 28 in 0.81, 0.98 at worst.  The line is at 0.9 of the steps because
+// idle time comes back as clock: at 0.95 it also takes 32 heads on 8, 9 sequences of 103 .. 3079 321 / 322, and 10 on 5, head_dim 104, 8 of up to
+// 12995 877 / 893; and at 0.75 against half items of single heads that are more than the units can hold at once (5000, 3000 and 300 tokens, 3
+// heads 72 / 80; 16001 tokens, 2 heads 274 / 282).  Limits finer than a quarter of the mean only add sums; a limit of the mean leaves queues of 41
+// heavy shares on 32 units (8192 tokens, 16 on 4 617).
 namespace {
 
 // What the dK/dV pass takes, in steps, and whether on half items (split_dkv): its longest item, or its work and what the last items
@@ -478,40 +482,47 @@ double dkv_steps(double heaviest, double total, double items, int32_t head_dim, 
     return std::max(heaviest + 8, (total + 8 * items) / (head_dim <= 64 ? 2 * units : units) + 0.35 * heaviest);
 }
 
-// heads of a share where an item of `per_head` steps a head may hold `limit` steps
-inline int32_t heads_per_piece(int64_t per_head, int64_t limit, int32_t group) {
-    return (int32_t)std::min<int64_t>(group, std::max<int64_t>(1, limit / std::max<int64_t>(1, per_head)));
-}
+// How an item of `per_head` steps a head is dealt out where a share may hold `limit` steps.
+struct Deal {
+    int32_t heads, parts;   // heads of a share; shares of a head's tiles
+    Deal(int64_t per_head, int64_t limit, int32_t group)
+        : heads((int32_t)std::min<int64_t>(group, std::max<int64_t>(1, limit / std::max<int64_t>(1, per_head)))),
+          parts(group == 1 && per_head > limit ? (int32_t)ceil_div(per_head, limit) : 1) {}
+    int64_t shares(int32_t group) const { return ceil_div(group, heads) * parts; }
+    int64_t heaviest(int64_t per_head) const { return heads * ceil_div(per_head, parts); }
+};
 
 }  // namespace
 
 bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t num_queues, const PassLoad& load,
-                      int64_t slots, int32_t head_dim, PieceList& out) {
+                      int64_t slots, int32_t head_dim, int64_t most_items, PieceList& out) {
     const int32_t group = hq / hkv;
-    if (group < 2 || slots == 0) return false;
-    constexpr int64_t kMostAreas = 1024;   // 128 MB of sums at tile width 128
+    if (slots == 0 || hkv > HeadPiece::kMostKvHeads || group > HeadPiece::kMostGroup) return false;
     const double units = head_dim <= 64 ? 512.0 : 256.0, items = (double)slots;
     bool halves = false;
     const double now = dkv_steps((double)load.heaviest, (double)load.total, items, head_dim, &halves);
     const double mean = ((double)load.total + 8 * items) / units;
     int64_t best = 0;
+    if (group == 1 && halves && slots > 240) return false;
     double least = 0.9 * now;
     for (const double share : {1.0, 0.7, 0.5, 0.25}) {
-        const int64_t limit = std::max<int64_t>(4, (int64_t)(share * mean));
+        const int64_t limit = std::max<int64_t>(6, (int64_t)(share * mean));   // (a share of a head's tiles then has three and more)
         if (load.heaviest <= limit) continue;
-        int64_t heaviest = 0, more = 0, areas = 0;
+        int64_t heaviest = 0, more = 0, areas = 0, parts = 1;
         for (int32_t s = 0; s < num_seqs; ++s) {
             const int32_t len = cu[s + 1] - cu[s], n_tiles = (int32_t)ceil_div(len, kDkvKTile);
+            if (n_tiles > HeadPiece::kMostTiles) return false;
             for (int32_t t = 0; t < n_tiles; ++t) {
                 const int64_t per_head = item_steps(HSPMD_LIST_DKV, len, t, 1);
-                const int32_t heads = heads_per_piece(per_head, limit, group);
-                const int64_t pieces = ceil_div(group, heads);
-                heaviest = std::max(heaviest, per_head * heads);
+                const Deal deal(per_head, limit, group);
+                const int64_t pieces = deal.shares(group);
+                heaviest = std::max(heaviest, deal.heaviest(per_head));
+                parts = std::max<int64_t>(parts, deal.parts);
                 more += (pieces - 1) * hkv;
                 if (pieces > 1) areas += pieces * hkv;
             }
         }
-        if (areas > kMostAreas) continue;
+        if (areas > HeadPiece::kMostAreas || parts > HeadPiece::kMostParts || slots + more > most_items) continue;
         bool h = false;
         const double then = dkv_steps((double)heaviest, (double)load.total, items + (double)more, head_dim, &h) + 7 + 0.025 * (double)areas;
         if (then < least) {
@@ -524,24 +535,21 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
 
     struct Share {
         int64_t cost;
-        int32_t tile, first_head, heads, index, pieces, area0;   // area0: kv head 0's first area, below 0 where the item is whole
+        int32_t tile, area0, pieces;   // area0: kv head 0's first area
+        uint32_t deal;                 // as HeadPiece's
     };
     std::vector<std::vector<Share>> shares((size_t)num_seqs);
     out = PieceList();
     for (int32_t s = 0; s < num_seqs; ++s) {
         const int32_t len = cu[s + 1] - cu[s], n_tiles = (int32_t)ceil_div(len, kDkvKTile);
         for (int32_t t = 0; t < n_tiles; ++t) {
-            const int64_t per_head = item_steps(HSPMD_LIST_DKV, len, t, 1);
-            const int32_t heads = heads_per_piece(per_head, best, group), pieces = (int32_t)ceil_div(group, heads);
-            for (int32_t h = 0; h < group; h += heads) {
-                const int32_t n = std::min(heads, group - h);
-                shares[s].push_back(Share{per_head * n, t, h, n, h / heads, pieces, pieces > 1 ? (int32_t)out.areas : -1});
+            const Deal deal(item_steps(HSPMD_LIST_DKV, len, t, 1), best, group);
+            const int32_t pieces = (int32_t)deal.shares(group);
+            for (int32_t index = 0; index < pieces; ++index) {
+                const HeadPiece x{0, len, (uint32_t)t, (uint32_t)deal.heads | (uint32_t)deal.parts << 8 | (uint32_t)index << 15};
+                shares[s].push_back(Share{(int64_t)x.n_heads(group) * (x.end_tile() - x.first_tile()), t, (int32_t)out.areas, pieces, x.deal});
             }
-            if (pieces == 1) continue;
-            for (int32_t g = 0; g < hkv; ++g)
-                out.sums.push_back(PieceSum{cu[s] + t * kDkvKTile, std::min(kDkvKTile, len - t * kDkvKTile), g, t * kDkvKTile,
-                                            (int32_t)out.areas + g * pieces, pieces, {0, 0}});
-            out.areas += (int64_t)pieces * hkv;
+            if (pieces > 1) out.areas += (int64_t)pieces * hkv;
         }
         std::stable_sort(shares[s].begin(), shares[s].end(), [](const Share& a, const Share& b) { return a.cost > b.cost; });
     }
@@ -551,11 +559,11 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
         [&](int32_t s, int32_t i) { return shares[s][i].cost; },
         [&](int32_t s, int32_t g, int32_t i) {
             const Share& x = shares[s][i];
-            const int32_t area = x.area0 < 0 ? -1 : x.area0 + g * x.pieces + x.index;
-            return HeadPiece{cu[s], cu[s + 1] - cu[s], x.tile, g, x.first_head, x.heads, area, 0};
+            const int32_t area = x.pieces > 1 ? x.area0 + g * x.pieces + (int32_t)(x.deal >> 15) : 0;
+            return HeadPiece{cu[s], cu[s + 1] - cu[s], (uint32_t)x.tile | (uint32_t)g << 14 | (uint32_t)area << 21, x.deal};
         },
-        [&](const HeadPiece& it) { return item_cost(HSPMD_LIST_DKV, it.seq_len, it.tile, it.heads); },
-        HeadPiece{0, 0, -1, 0, 0, 0, -1, 0});
+        [&](const HeadPiece& it) { return (int64_t)it.n_heads(group) * (it.end_tile() - it.first_tile()); }, HeadPiece{0, 0, 0, 0});
+    if ((int64_t)out.items.size() > most_items) return false;   // (short queues are padded)
     return true;
 }
 

@@ -49,27 +49,39 @@ RowsForm rows_form(hspmd_list_kind kind, const PassLoad& load, int64_t slots, in
 // Whether the dK/dV pass of a packed plan draws its items in persistent workgroups: also where pass_dispatch says whole items.
 bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim);
 
-// ---- dK/dV items of grouped heads, dealt out by query heads
-// A share of an item: query heads first_head .. first_head + heads - 1 of the KV group.  area: where its dK and dV go, as fp32 sums that
-// one more kernel adds up; below 0: it is the whole item and writes them itself.
+// ---- dK/dV items, dealt out by query heads, or, where heads are not grouped, by query tiles
+// A share of an item, as long as an ordinary item.  Its dK and dV go to area `area()` as fp32 sums that one more kernel adds up, or,
+// where it is the only share, to their own place.
 struct HeadPiece {
-    int32_t token_start, seq_len, tile, head;   // as hspmd_work_item; tile < 0: padding
-    int32_t first_head, heads, area, pad;
+    int32_t token_start, seq_len;   // as hspmd_work_item
+    uint32_t where, deal;           // tile 14 bits, kv head 7, area 11; heads of a share 8, shares of a head's tiles 7, number of the share 10
+    static constexpr int64_t kMostTiles = 1 << 14, kMostKvHeads = 1 << 7, kMostAreas = 1 << 10, kMostGroup = 255, kMostParts = 127;
+    constexpr bool padding() const { return deal == 0; }
+    constexpr int tile() const { return (int)(where & 0x3fff); }
+    constexpr int head() const { return (int)(where >> 14 & 0x7f); }
+    constexpr int area() const { return (int)(where >> 21); }
+    constexpr int heads() const { return (int)(deal & 0xff); }
+    constexpr int parts() const { return (int)(deal >> 8 & 0x7f); }
+    constexpr int index() const { return (int)(deal >> 15); }
+    constexpr int shares(int group) const { return (group + heads() - 1) / heads() * parts(); }
+    // the share's query heads of the group, and the query tiles that it walks of each
+    constexpr int first_head() const { return index() / parts() * heads(); }
+    constexpr int n_heads(int group) const { return group - first_head() < heads() ? group - first_head() : heads(); }
+    constexpr int diagonal() const { return tile() * (kDkvKTile / kDkvQTile); }
+    constexpr int end() const { return (seq_len + kDkvQTile - 1) / kDkvQTile; }
+    constexpr int first_tile() const { return diagonal() + (end() - diagonal()) * (index() % parts()) / parts(); }
+    constexpr int end_tile() const { return diagonal() + (end() - diagonal()) * (index() % parts() + 1) / parts(); }
 };
-// An item that is dealt out: its keys (rows of dK and dV) and the consecutive areas whose sum they are.
-struct PieceSum {
-    int32_t row0, rows, head, position0;   // position of the first key inside its sequence
-    int32_t first_area, areas, pad[2];
-};
+static_assert(sizeof(HeadPiece) == sizeof(hspmd_work_item), "lists of either travel alike");
 struct PieceList {
     std::vector<HeadPiece> items;    // launch order, as build_work_list's
-    std::vector<PieceSum> sums;
     int64_t areas = 0;
     bool halves = false;             // the unit of work is half a piece
 };
-// The dK/dV list of a pack by pieces, where that pays (`load`, `slots`: of the ordinary list); else false.
+// The dK/dV list of a pack by pieces, where that pays (`load`, `slots`: of the ordinary list), with at most `most_items`
+// of them; else false.
 bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t num_queues, const PassLoad& load,
-                      int64_t slots, int32_t head_dim, PieceList& out);
+                      int64_t slots, int32_t head_dim, int64_t most_items, PieceList& out);
 
 // ---- cost model: predicted kernel times (microseconds) of the three passes for a pack
 double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim);

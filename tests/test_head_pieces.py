@@ -1,4 +1,4 @@
-"""dK/dV items of grouped heads that are dealt out by query heads: what the shares cover, on the CPU, and the outputs on the GPU."""
+"""dK/dV items that are dealt out by query heads and tiles: what the shares cover, on the CPU, and the outputs on the GPU."""
 import ctypes
 import os
 import subprocess
@@ -13,22 +13,31 @@ LONG = [2500, 449, 1, 64, 130, 127]
 PACKS = [(LONG, 6, 2, d, 1) for d in (40, 64, 80, 96, 104, 128)]
 PACKS += [([3200, 1500, 900, 65, 1], 28, 7, d, 0) for d in (80, 96, 104, 128)] + [([3200, 900, 65, 1], 32, 4, 64, 0)]
 PACKS += [([700, 300, 128], 6, 2, 128, 1), ([512], 8, 2, 128, 1), ([449], 5, 1, 72, 1)]
-# no longest item that outlasts the rest, or heads that are not grouped
-ORDINARY = [([2048] * 4, 32, 8, 128), ([3000, 500], 8, 8, 128), ([64] * 40, 8, 4, 128), ([256], 4, 1, 128), ([], 8, 2, 128)]
+# no longest item that outlasts the rest by what the sums cost
+# shares of one head's tiles, alone and beside shares of heads
+PACKS += [([4500, 300, 1], 1, 1, d, 0) for d in (64, 80, 104, 128)] + [([8000, 129], 2, 1, 96, 1), ([8200, 64], 2, 2, 64, 0)]
+# half shares
+PACKS += [([1967], 2, 2, d, 1) for d in (64, 40)] + [([1411], 1, 1, d, 1) for d in (80, 96, 104, 128)]
+ORDINARY = [([2048] * 4, 32, 8, 128), ([2048], 8, 8, 128), ([2048] * 8, 32, 32, 128), ([1024] * 2, 8, 8, 64), ([64] * 40, 8, 4, 128), ([256], 4, 1, 128), ([], 8, 2, 128)]
 
 SHIM = """
 #include "schedule.hpp"
-#include <cstring>
 using namespace hspmd;
 static PieceList list;
-extern "C" int build(const int* cu, int n, int hq, int hkv, int d) {
+static int group;
+extern "C" int build(const int* cu, int n, int hq, int hkv, int d, long long most) {
     const PassLoad load = pass_load(HSPMD_LIST_DKV, cu, n, hq, hkv);
-    return build_piece_list(cu, n, hq, hkv, kNumXcd, load, (int64_t)build_work_list(HSPMD_LIST_DKV, cu, n, hq, hkv, kNumXcd).size(), d, list);
+    group = hq / hkv;
+    return build_piece_list(cu, n, hq, hkv, kNumXcd, load, (int64_t)build_work_list(HSPMD_LIST_DKV, cu, n, hq, hkv, kNumXcd).size(), d, most, list);
 }
-extern "C" void sizes(long long* out) { out[0] = list.items.size(); out[1] = list.sums.size(); out[2] = list.areas; out[3] = list.halves; }
-extern "C" void copy(int* items, int* sums) {
-    memcpy(items, list.items.data(), list.items.size() * sizeof(HeadPiece));
-    memcpy(sums, list.sums.data(), list.sums.size() * sizeof(PieceSum));
+extern "C" void sizes(long long* out) { out[0] = list.items.size(); out[1] = list.areas; out[2] = list.halves; }
+extern "C" void copy(int* out) {
+    for (const HeadPiece& x : list.items) {
+        const bool pad = x.padding();
+        const int fields[] = {x.token_start, x.seq_len, pad ? -1 : x.tile(), x.head(), pad ? 0 : x.first_head(), pad ? 0 : x.n_heads(group),
+                              pad ? 0 : x.first_tile(), pad ? 0 : x.end_tile(), x.index(), pad ? 0 : x.shares(group), x.area()};
+        for (int f : fields) *out++ = f;
+    }
 }
 """
 
@@ -42,49 +51,54 @@ def pieces(tmp_path_factory):
                     os.path.join(lib_build.CSRC, "schedule.cpp")], check=True)
     lib = ctypes.CDLL(str(so))
 
-    def call(lengths, hq, hkv, d):
+    def call(lengths, hq, hkv, d, most=1 << 30):
         cu = (ctypes.c_int32 * (len(lengths) + 1))(*np.concatenate([[0], np.cumsum(lengths)]).astype(int).tolist())
-        if not lib.build(cu, len(lengths), hq, hkv, d):
+        if not lib.build(cu, len(lengths), hq, hkv, d, ctypes.c_longlong(most)):
             return None
-        size = (ctypes.c_longlong * 4)()
+        size = (ctypes.c_longlong * 3)()
         lib.sizes(size)
-        items, sums = np.zeros((size[0], 8), np.int32), np.zeros((size[1], 8), np.int32)
-        lib.copy(items.ctypes.data_as(ctypes.c_void_p), sums.ctypes.data_as(ctypes.c_void_p))
-        return items, sums, size[2], size[3]
+        items = np.zeros((size[0], 11), np.int32)
+        lib.copy(items.ctypes.data_as(ctypes.c_void_p))
+        return items, size[1], size[2]
     return call
 
 
 @pytest.mark.parametrize("lengths,hq,hkv,d,halves", PACKS)
 def test_shares_cover_every_head_of_every_item_once(pieces, lengths, hq, hkv, d, halves):
-    items, sums, areas, in_halves = pieces(lengths, hq, hkv, d)
+    items, areas, in_halves = pieces(lengths, hq, hkv, d)
     assert in_halves == halves and len(items) % 8 == 0
     starts = np.concatenate([[0], np.cumsum(lengths)])
     seen, parts = set(), {}
-    for start, length, tile, head, first, n, area, _ in items[items[:, 2] >= 0]:
+    for start, length, tile, head, first, n, first_tile, end_tile, index, shares, area in items[items[:, 2] >= 0]:
         assert length in lengths and start in starts and 128 * tile < length and 0 <= head < hkv
+        diagonal, end = 2 * tile, -(-length // 64)
+        assert (first_tile, end_tile) == (diagonal, end) or (n == hq // hkv == 1 and diagonal <= first_tile < end_tile - 1 < end)
         for h in range(first, first + n):
-            assert (start, tile, head, h) not in seen and 0 <= h < hq // hkv
-            seen.add((start, tile, head, h))
-        if area < 0:
-            assert (first, n) == (0, hq // hkv)
-        else:
-            parts.setdefault((start, tile, head), []).append((first, area))
-    assert len(seen) == sum(-(-n // 128) for n in lengths) * hq
-    assert sorted(a for p in parts.values() for _, a in p) == list(range(areas))
-    # the areas of an item follow each other in the order of its heads
-    want = {}
-    for (start, tile, head), p in parts.items():
+            assert 0 <= h < hq // hkv
+            rows = {(start, tile, head, h, t) for t in range(first_tile, end_tile)}
+            assert not rows & seen
+            seen |= rows
+        parts.setdefault((start, tile, head), []).append((first, first_tile, index, shares, area))
+    assert len(seen) == sum(-(-n // 64) - 2 * t for n in lengths for t in range(-(-n // 128))) * hq
+    # the areas of an item follow each other in the order of its heads and tiles, from its first share's on
+    used = []
+    for p in parts.values():
         p.sort()
-        assert [a for _, a in p] == list(range(p[0][1], p[0][1] + len(p)))
-        length = lengths[int(np.where(starts == start)[0][0])] if start else lengths[0]
-        want[(start + 128 * tile, head)] = (min(128, length - 128 * tile), 128 * tile, p[0][1], len(p))
-    got = {(r, h): (rows, pos, first, n) for r, rows, h, pos, first, n, _, _ in sums}
-    assert got == want and len(sums) == len(want) > 0
+        assert [x[2] for x in p] == list(range(p[0][3])) and all(x[3] == len(p) for x in p)
+        if len(p) > 1:
+            assert [x[4] for x in p] == list(range(p[0][4], p[0][4] + len(p)))
+            used += [x[4] for x in p]
+    assert sorted(used) == list(range(areas)) and areas > 0
 
 
 @pytest.mark.parametrize("lengths,hq,hkv,d", ORDINARY)
 def test_other_packs_keep_their_items(pieces, lengths, hq, hkv, d):
     assert pieces(lengths, hq, hkv, d) is None
+
+
+def test_no_more_shares_than_asked_for(pieces):
+    few = pieces([3000, 500], 8, 2, 128, 240)
+    assert few is not None and len(few[0]) <= 240 and pieces([3000, 500], 8, 2, 128, 60) is None
 
 
 @pytest.mark.gpu
@@ -97,14 +111,15 @@ def test_outputs(lengths, hq, hkv, d, halves):
 
 @pytest.mark.gpu
 def test_refills_of_one_plan():
-    """From a pack without shares to packs with few and with many of them and back: what a plan of its own gives, every time."""
+    """From a pack without shares to packs with few and with many of them and back: what a plan of its own gives, every time; and with a
+    workspace that has no room for the sums, what they sum to."""
     import torch
     import paper_2504_20490_amd as A
     from gpu_util import GpuRun, make_case
     hq, hkv, d = 8, 2, 128
     packs = [[100, 60], [512, 40], [4096, 300], [100, 60], [4096, 300], [2048] * 3]
     cu = [A.build_cu_seqlens(p)[0] for p in packs]
-    plan = A.Plan(cu[0], hq, hkv, d)
+    plan, dealt = A.Plan(cu[0], hq, hkv, d), 0
     for lengths, offsets in zip(packs, cu):
         q, k, v, do = make_case(lengths, hq, hkv, d, seed=31)
         run = GpuRun(lengths, q, k, v, do).run()
@@ -116,3 +131,16 @@ def test_refills_of_one_plan():
         run.backward()
         torch.cuda.synchronize()
         assert all(torch.equal(getattr(run, n), x) for n, x in zip(("dq", "dk", "dv"), want)), lengths
+        # the statistics alone
+        least = (2 * hq * sum(lengths) + 16) * 4
+        dealt += plan.bwd_workspace_bytes() > least
+        run.ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+        run.backward()
+        torch.cuda.synchronize()
+        for n, x in zip(("dq", "dk", "dv"), want):
+            # the order of fp32 sums over the group's rows, and P and dS of another 32-row block's partial products
+            assert (getattr(run, n) - x).norm() <= 1e-5 * x.norm(), (lengths, n)
+        with pytest.raises(A.HspmdError):
+            run.ws = torch.empty(least - 4, dtype=torch.uint8, device="cuda")
+            run.backward()
+    assert dealt >= 2
