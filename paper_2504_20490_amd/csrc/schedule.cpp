@@ -458,15 +458,15 @@ bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t 
 // grouped, by query tiles: every share leaves its sums of dK and dV as fp32 in memory, and a kernel behind the pass adds them up in the order of
 // heads and tiles.  That costs a launch and
 // the way of the sums through memory, about seven steps and 0.025 per share, and the shares' own prologues and stores.
-// Measured, the dK/dV pass without and with, sums included (us): 8 query heads on 2 KV heads, 3000 and 500 tokens 146 / 68, 2048 tokens 100 /
-// 43, 512 tokens 36 / 21, 16384 tokens 1136 / 968; 8 on 1, 4096 tokens 352 / 98; 16 on 4, 8192 tokens 589 / 513; 28 on 7, 1947 tokens 107 / 92; width
-// 64, 8 on 2, 8192 tokens 270 / 155; one head of 8192 tokens 100 / 52, 4 heads of 4096 62 / 57, width 64, 2 heads of 16384 209 / 154.  Of 62 packs of
-// 256 to 32000 tokens, 1 to 8 KV heads and groups of 2 to 8, the 38 that this takes run in 0.72 of the time on average, 0.98 at worst; of 61
-// packs of 1000 to 50000 tokens and 1 to 8 heads, most of one query head each, 28 in 0.81, 0.98 at worst.  The line is at 0.9 of the steps because
-// idle time comes back as clock: at 0.95 it also takes 32 heads on 8, 9 sequences of 103 .. 3079 321 / 322, and 10 on 5, head_dim 104, 8 of up to
-// 12995 877 / 893; and at 0.75 against half items of single heads that are more than the units can hold at once (5000, 3000 and 300 tokens, 3
-// heads 72 / 80; 16001 tokens, 2 heads 274 / 282).  Limits finer than a quarter of the mean only add sums; a limit of the mean leaves queues of 41
-// heavy shares on 32 units (8192 tokens, 16 on 4 617).
+// Measured, the dK/dV pass without and with, sums included (us): 8 query heads on 2 KV heads, 3000 and 500 tokens 146 / 70, 2048 tokens 100 /
+// 42, 512 tokens 36 / 21, 16384 tokens 1171 / 996; 8 on 1, 4096 tokens 354 / 102; 16 on 4, 8192 tokens 599 / 513; 28 on 7, 1947 tokens 104 / 95; width
+// 64, 8 on 2, 8192 tokens 273 / 159; by tiles: one head of 8192 tokens 100 / 56, width 64, 2 heads of 16384 208 / 157.  Of 62 packs of 256 to 32000
+// tokens, 1 to 8 KV heads and groups of 2 to 8, the 38 that this takes run in 0.74 of the time on average, 0.99 at worst; of 61 packs of 1000 to
+// 50000 tokens and 1 to 8 heads, most of one query head each, 18 in 0.75, 0.96 at worst.  The line is at 0.9 of the steps because idle time comes
+// back as clock: at 0.95 it also takes 32 heads on 8, 9 sequences of 103 .. 3079 321 / 322, and 10 on 5, head_dim 104, 8 of up to 12995 877 / 893.
+// Not against half items of single heads that are more than the units hold at once (5000, 3000 and 300 tokens, 3 heads 72 / 80; 16001 tokens, 2
+// heads 274 / 282).  Limits finer than a quarter of the mean only add sums; a limit of the mean leaves queues of 41 heavy shares on 32 units (8192
+// tokens, 16 on 4 617).
 namespace {
 
 // What the dK/dV pass takes, in steps, and whether on half items (split_dkv): its longest item, or its work and what the last items
@@ -505,7 +505,10 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
     int64_t best = 0;
     if (group == 1 && halves && slots > 240) return false;
     double least = 0.9 * now;
-    for (const double share : {1.0, 0.7, 0.5, 0.25}) {
+    if (std::max(mean, 8.0) + 7 >= least) return false;   // what is left with every share as short as can be
+    const bool short_list = most_items < slots + HeadPiece::kMostAreas;   // (coarser limits, so that some list fits)
+    for (const double share : {2.0, 1.4, 1.0, 0.7, 0.5, 0.25}) {
+        if (share > 1.0 && !short_list) continue;
         const int64_t limit = std::max<int64_t>(6, (int64_t)(share * mean));   // (a share of a head's tiles then has three and more)
         if (load.heaviest <= limit) continue;
         int64_t heaviest = 0, more = 0, areas = 0, parts = 1;
@@ -522,7 +525,7 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
                 if (pieces > 1) areas += pieces * hkv;
             }
         }
-        if (areas > HeadPiece::kMostAreas || parts > HeadPiece::kMostParts || slots + more > most_items) continue;
+        if (areas > HeadPiece::kMostAreas || parts > HeadPiece::kMostParts || slots + more + (short_list ? 16 : 0) > most_items) continue;   // (16: padding of short queues)
         bool h = false;
         const double then = dkv_steps((double)heaviest, (double)load.total, items + (double)more, head_dim, &h) + 7 + 0.025 * (double)areas;
         if (then < least) {
@@ -604,6 +607,14 @@ double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seq
     const PassFixed f = kPassFixed[(int)kind];
     RowsForm form{pass_dispatch(kind, load, (int64_t)list.size(), head_dim, false) == Dispatch::kHalves, 1};
     if (kind != HSPMD_LIST_DKV) form = rows_form(kind, load, (int64_t)list.size(), hq / hkv, head_dim, list.size() <= 240);
+    // items that are dealt out: their shares, and what adding up their sums takes
+    PieceList pieces;
+    const int64_t rows = kind == HSPMD_LIST_DKV ? (int64_t)build_work_list(HSPMD_LIST_FWD, cu, num_seqs, hq, hkv, kNumXcd).size() : 0;
+    const bool short_lists = std::max(rows, (int64_t)list.size()) <= 240;
+    const bool dealt = kind == HSPMD_LIST_DKV &&
+                       build_piece_list(cu, num_seqs, hq, hkv, kNumXcd, load, (int64_t)list.size(), head_dim,
+                                        short_lists ? 240 : std::numeric_limits<int32_t>::max(), pieces);
+    if (dealt) form.halves = pieces.halves;
     const bool halves = form.halves;
     const Shares share = form.teams == 2 ? kTeamShares[(int)kind][halves] : halves ? Shares{f.half_step, f.half_alone, f.half_item}
                                                                                    : Shares{1.0, 1.0, 1.0};
@@ -612,13 +623,17 @@ double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seq
     // width 64 three in the dQ pass and two in dK/dV with whole items
     const double per_unit = kind == HSPMD_LIST_DKV ? (narrow && !halves ? 2 : 1) : (narrow && kind == HSPMD_LIST_DQ ? 3 : 2);
     double queue_weight[kNumXcd] = {0};
-    for (size_t p = 0; p < list.size(); ++p) {
-        if (list[p].tile < 0) continue;
-        queue_weight[p % kNumXcd] += (double)item_cost(kind, list[p].seq_len, list[p].tile, hq / hkv) * step + item;
+    int64_t heaviest = dealt ? 0 : load.heaviest;
+    for (size_t p = 0; p < (dealt ? pieces.items.size() : list.size()); ++p) {
+        if (dealt ? pieces.items[p].padding() : list[p].tile < 0) continue;
+        const int64_t cost = dealt ? (int64_t)pieces.items[p].n_heads(hq / hkv) * (pieces.items[p].end_tile() - pieces.items[p].first_tile())
+                                   : item_cost(kind, list[p].seq_len, list[p].tile, hq / hkv);
+        heaviest = std::max(heaviest, cost);
+        queue_weight[p % kNumXcd] += (double)cost * step + item;
     }
     const double shared = *std::max_element(queue_weight, queue_weight + kNumXcd) / (32.0 * per_unit);
-    const double alone = (double)load.heaviest * c.alone_us * share.alone + c.item_us * share.item;
-    return f.launch_us + std::sqrt(std::sqrt(shared * shared * shared * shared + alone * alone * alone * alone));
+    const double alone = (double)heaviest * c.alone_us * share.alone + c.item_us * share.item;
+    return f.launch_us + (dealt ? 5.0 + 0.03 * (double)pieces.areas : 0.0) + std::sqrt(std::sqrt(shared * shared * shared * shared + alone * alone * alone * alone));
 }
 
 // ------------------------------------------------------------------------------ block variant
