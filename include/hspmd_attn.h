@@ -205,7 +205,8 @@ int64_t hspmd_attn_plan_total_tokens(const hspmd_attn_plan* plan); /* -1 on NULL
 int64_t hspmd_attn_plan_num_items(const hspmd_attn_plan* plan, hspmd_list_kind kind); /* slots incl. padding */
 
 /* Bytes of device workspace the backward needs (two fp32 [local_q_heads, T] arrays: the row statistics
- * D = rowsum(dO * O) and the logsumexp in the form the kernels consume them, plus a few constants). */
+ * D = rowsum(dO * O) and the logsumexp in the form the kernels consume them, plus a few constants; for some packs room for
+ * partial sums of dK and dV behind them, see hspmd_attn_varlen_bwd).  A plan refilled with another pack may want another size. */
 size_t hspmd_attn_bwd_workspace_bytes(const hspmd_attn_plan* plan);
 
 /*

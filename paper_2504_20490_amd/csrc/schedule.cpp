@@ -497,7 +497,7 @@ struct Deal {
 bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t num_queues, const PassLoad& load,
                       int64_t slots, int32_t head_dim, int64_t most_items, PieceList& out) {
     const int32_t group = hq / hkv;
-    if (slots == 0 || hkv > HeadPiece::kMostKvHeads || group > HeadPiece::kMostGroup) return false;
+    if (load.heaviest < 9 || hkv > HeadPiece::kMostKvHeads || group > HeadPiece::kMostGroup) return false;   // (too short for what the sums cost)
     const double units = head_dim <= 64 ? 512.0 : 256.0, items = (double)slots;
     bool halves = false;
     const double now = dkv_steps((double)load.heaviest, (double)load.total, items, head_dim, &halves);
