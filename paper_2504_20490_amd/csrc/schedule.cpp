@@ -517,6 +517,10 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
             if (n_tiles > HeadPiece::kMostTiles) return false;
             for (int32_t t = 0; t < n_tiles; ++t) {
                 const int64_t per_head = item_steps(HSPMD_LIST_DKV, len, t, 1);
+                if (per_head * group <= limit) {   // neither this nor any later item is dealt out
+                    heaviest = std::max(heaviest, per_head * group);
+                    break;
+                }
                 const Deal deal(per_head, limit, group);
                 const int64_t pieces = deal.shares(group);
                 heaviest = std::max(heaviest, deal.heaviest(per_head));
