@@ -235,7 +235,7 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
  *           bf16 or fp32 according to grad_dtype; fully overwritten
  *   workspace  device, hspmd_attn_bwd_workspace_bytes(plan) bytes, 16-byte aligned.  The row statistics take
  *              (2 * local_q_heads * T + 16) * 4 bytes of it; less than that is WORKSPACE_TOO_SMALL.  For packs whose longest dK/dV
- *              items would outlast the pass it also holds partial sums of dK and dV (at most 128 MB), so that those items can be
+ *              items would outlast the pass it also holds partial sums of dK and dV (at most 64 MB), so that those items can be
  *              dealt out; a workspace without room for them gives the same gradients, summed in another order, later.
  */
 hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, const void* k, const void* v,
@@ -248,7 +248,8 @@ hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, c
  * hspmd_attn_varlen_bwd for callers that cannot allocate device memory and have no workspace to pass: code that
  * runs under HIP graph capture, tight serving / training loops, harnesses that forbid hipMalloc.  Same arguments,
  * kernels and results as hspmd_attn_varlen_bwd, without `workspace`: the row statistics that the dQ pass leaves for
- * the dK/dV pass go into a fixed device array inside the library (HSPMD_STATIC_WORKSPACE_BYTES bytes on every GPU the
+ * the dK/dV pass, and the partial sums of dK and dV, go into a fixed device array inside the library
+ * (HSPMD_STATIC_WORKSPACE_BYTES bytes for the statistics and 64 MB for the sums, on every GPU the
  * library runs on, held until the process ends).  The call allocates and frees nothing and creates no events
  * (per-kernel timing does not apply to it).
  *   Limit: (2 * local_q_heads * T + 16) * 4 <= HSPMD_STATIC_WORKSPACE_BYTES, i.e.
@@ -256,7 +257,7 @@ hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, c
  *   larger packs get WORKSPACE_TOO_SMALL and nothing is launched.
  *   All calls on one GPU share the array: two calls that may overlap on one GPU (different streams, no event between
  *   them) race on it; calls on one stream are ordered and safe.  Nothing in it needs clearing between calls: every
- *   value the dK/dV pass reads is written by the dQ pass of the same call.
+ *   value that a kernel reads from it is written by an earlier kernel of the same call.
  *   The array's device address is looked up on the first call on each device; make that first call outside a graph
  *   capture.
  * Other errors as hspmd_attn_varlen_bwd.

@@ -583,7 +583,7 @@ int64_t hspmd_attn_plan_num_items(const hspmd_attn_plan* plan, hspmd_list_kind k
 size_t hspmd_attn_bwd_workspace_bytes(const hspmd_attn_plan* plan) {
     if (!plan) return 0;
     if (plan->areas == 0) return statistics_bytes(plan);
-    return sums_offset(plan) + (size_t)plan->areas * 2 * hspmd::kDkvKTile * (size_t)hspmd::tile_width(plan->head_dim) * sizeof(float);
+    return sums_offset(plan) + (size_t)(plan->areas * hspmd::sums_area_bytes(plan->head_dim));
 }
 
 static hspmd_status check_strides(const hspmd_attn_plan* plan, int64_t q_token_stride, int64_t kv_token_stride) {
@@ -732,10 +732,12 @@ hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, c
 }
 
 // ---- backward with the library's own workspace: for callers that cannot allocate -------------------------------
-// The row statistics that the dQ pass leaves for the dK/dV pass live in a fixed device array instead of a buffer
-// from the caller.  In host code the array's name is only a handle for hipGetSymbolAddress: the device address is
+// The row statistics that the dQ pass leaves for the dK/dV pass, and the sums of items that are dealt out, live in a fixed device
+// array instead of a buffer from the caller, with room for the sums of any pack, so that this entry point takes the same kernels as
+// the one with a workspace.  In host code the array's name is only a handle for hipGetSymbolAddress: the device address is
 // looked up once per device and kept; the kernels get that address like any other workspace pointer.
-static __device__ __attribute__((used)) __align__(256) unsigned char scratch[HSPMD_STATIC_WORKSPACE_BYTES];
+static __device__ __attribute__((used)) __align__(256) unsigned char scratch[HSPMD_STATIC_WORKSPACE_BYTES + hspmd::kMostSumsBytes];
+static_assert(HSPMD_STATIC_WORKSPACE_BYTES % 256 == 0, "sums_offset of the largest statistics");
 
 namespace {
 std::mutex g_scratch_mutex;
@@ -775,7 +777,7 @@ hspmd_status hspmd_attn_varlen_bwd_static_ws(const hspmd_attn_plan* plan, const 
     // Per-kernel timing creates events on first use; this entry point must not create anything, so it launches
     // untimed whatever the switch says.
     return varlen_bwd(plan, q, k, v, o, lse, d_o, q_token_stride, kv_token_stride, softmax_scale, dq, dk, dv, grad_dtype,
-                      nullptr, workspace, (size_t)HSPMD_STATIC_WORKSPACE_BYTES, stream, /*timed=*/false);
+                      nullptr, workspace, sizeof scratch, stream, /*timed=*/false);
 }
 
 // ---- rotary position embedding ---------------------------------------------------------------------------------

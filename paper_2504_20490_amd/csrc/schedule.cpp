@@ -529,7 +529,7 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
                 if (pieces > 1) areas += pieces * hkv;
             }
         }
-        if (areas > HeadPiece::kMostAreas || parts > HeadPiece::kMostParts || slots + more + (short_list ? 16 : 0) > most_items) continue;   // (16: padding of short queues)
+        if (areas * sums_area_bytes(head_dim) > kMostSumsBytes || parts > HeadPiece::kMostParts || slots + more + (short_list ? 16 : 0) > most_items) continue;   // (16: padding of short queues)
         bool h = false;
         const double then = dkv_steps((double)heaviest, (double)load.total, items + (double)more, head_dim, &h) + 7 + 0.025 * (double)areas;
         if (then < least) {

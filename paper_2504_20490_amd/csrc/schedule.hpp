@@ -73,6 +73,10 @@ struct HeadPiece {
     constexpr int end_tile() const { return diagonal() + (end() - diagonal()) * (index() % parts() + 1) / parts(); }
 };
 static_assert(sizeof(HeadPiece) == sizeof(hspmd_work_item), "lists of either travel alike");
+// The sums of a share: dK and dV of an item's keys, fp32, at the tile width that head_dim runs at; and the most that a pass may keep.
+constexpr int64_t sums_area_bytes(int32_t head_dim) { return 2 * kDkvKTile * (head_dim <= 64 ? 64 : 128) * 4; }
+constexpr int64_t kMostSumsBytes = 64 << 20;
+static_assert(kMostSumsBytes / sums_area_bytes(64) <= HeadPiece::kMostAreas, "an area's number fits its field");
 struct PieceList {
     std::vector<HeadPiece> items;    // launch order, as build_work_list's
     int64_t areas = 0;

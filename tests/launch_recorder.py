@@ -43,6 +43,7 @@ int hipEventCreateWithFlags(void** e, unsigned f) { *e = malloc(1); line("event"
 int hipEventRecord(void* e, void* s) { (void)e; (void)s; line("mark", "-", 0); return 0; }
 int hipEventSynchronize(void* e) { (void)e; line("wait", "-", 0); return 0; }
 int hipEventDestroy(void* e) { free(e); return 0; }
+int hipGetSymbolAddress(void** p, const void* s) { (void)s; *p = (void*)(1 << 20); return 0; }
 int hipGetLastError(void) { return 0; }
 const char* hipGetErrorString(int e) { return e ? "stand-in error" : "no error"; }
 typedef struct { unsigned x, y, z; } dim3_t;
@@ -87,6 +88,9 @@ class Plan:
         b, qs, ks = p(1 << 20), i64(self.hq * self.d), i64(self.hkv * self.d)
         n = ctypes.c_size_t(lib.hspmd_attn_bwd_workspace_bytes(self.h))
         assert lib.hspmd_attn_varlen_bwd(self.h, b, b, b, b, b, b, qs, ks, f32(0), b, b, b, 0, b, n, p(0)) == 0
+    def backward_static(self):
+        b, qs, ks = p(1 << 20), i64(self.hq * self.d), i64(self.hkv * self.d)
+        assert lib.hspmd_attn_varlen_bwd_static_ws(self.h, b, b, b, b, b, b, qs, ks, f32(0), b, b, b, 0, p(0)) == 0
     def destroy(self):
         assert lib.hspmd_attn_plan_destroy(self.h) == 0
 class BlockPlan(Plan):

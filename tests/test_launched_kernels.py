@@ -79,3 +79,19 @@ out(names)
     attention = {k for k in held if k[0] in HALVES}
     assert len(attention) > 100
     assert not attention - seen, sorted(attention - seen)
+
+
+def test_static_workspace_takes_the_same_kernels(stand_in):
+    """The entry point without a workspace launches what the one with a workspace launches, also where the sums of items that are dealt
+    out are more than the statistics leave of the array."""
+    from test_head_pieces import ORDINARY, PACKS
+    cases = [c[:4] for c in PACKS + ORDINARY if c[0]] + [([3000, 500], 8, 2, 128), ([700, 45, 260, 1, 129, 1500], 8, 2, 128),
+                                                         ([12000] + [128] * 150, 8, 1, 128), ([29082, 18500], 8, 2, 128)]
+    program = """
+for pack, hq, hkv, d in args[0]:
+    plan = Plan(pack, hq, hkv, d)
+    calls(); plan.backward(); both = calls(); plan.backward_static()
+    out([[c for c in x if c[0] == "launch"] for x in (both, calls())])
+"""
+    for case, (with_workspace, without) in zip(cases, rec.record(stand_in, program, cases)):
+        assert with_workspace == without, case

@@ -66,6 +66,20 @@ def test_static_workspace_backward_equals_the_workspace_backward():
     check("second round")
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,d", [([3000, 500], 8, 2, 128), ([4096, 300], 8, 1, 128), ([16384], 2, 2, 64)])
+def test_static_workspace_holds_the_sums_of_any_pack(lengths, hq, hkv, d):
+    """dK/dV items that are dealt out, with sums of 20 to 40 MB."""
+    import torch
+    import paper_2504_20490_amd as A
+    plan, (q, k, v, o, lse, do), ref, got, ws = _case(A, lengths, hq, hkv, d, 44, A.GRAD_F32)
+    assert ws.numel() > 16 << 20
+    A.attn_varlen_bwd(plan, q, k, v, o, lse, do, *ref, ws, grad_dtype=A.GRAD_F32)
+    A.attn_varlen_bwd_static_ws(plan, q, k, v, o, lse, do, *got, grad_dtype=A.GRAD_F32)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("dq", "dk", "dv"), ref, got):
+        assert not torch.isnan(b).any() and np.array_equal(_bits(a), _bits(b)), name
+
+
 def test_static_workspace_limit_and_validation():
     import torch
     import paper_2504_20490_amd as A
