@@ -205,8 +205,10 @@ int64_t hspmd_attn_plan_total_tokens(const hspmd_attn_plan* plan); /* -1 on NULL
 int64_t hspmd_attn_plan_num_items(const hspmd_attn_plan* plan, hspmd_list_kind kind); /* slots incl. padding */
 
 /* Bytes of device workspace the backward needs (two fp32 [local_q_heads, T] arrays: the row statistics
- * D = rowsum(dO * O) and the logsumexp in the form the kernels consume them, plus a few constants; for some packs room for
- * partial sums of dK and dV behind them, see hspmd_attn_varlen_bwd).  A plan refilled with another pack may want another size. */
+ * D = rowsum(dO * O) and the logsumexp in the form the kernels consume them, plus a few constants; behind them, where some
+ * pack of T tokens on the plan's heads would use it, room for partial sums of dK and dV, see hspmd_attn_varlen_bwd).
+ * The size follows from the plan's heads, head_dim and number of tokens T alone, whatever the sequences, and more tokens never
+ * need less: a workspace made for the largest T of a plan that is refilled serves all of its packs alike. */
 size_t hspmd_attn_bwd_workspace_bytes(const hspmd_attn_plan* plan);
 
 /*
@@ -233,10 +235,11 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
  *   lse     fp32 [local_q_heads, T] as written by the forward
  *   dq      [T, local_q_heads, head_dim]; dk, dv [T, local_kv_heads, head_dim]; contiguous,
  *           bf16 or fp32 according to grad_dtype; fully overwritten
- *   workspace  device, hspmd_attn_bwd_workspace_bytes(plan) bytes, 16-byte aligned.  The row statistics take
+ *   workspace  device, at least hspmd_attn_bwd_workspace_bytes(plan) bytes, 16-byte aligned.  The row statistics take
  *              (2 * local_q_heads * T + 16) * 4 bytes of it; less than that is WORKSPACE_TOO_SMALL.  For packs whose longest dK/dV
  *              items would outlast the pass it also holds partial sums of dK and dV (at most 64 MB), so that those items can be
- *              dealt out; a workspace without room for them gives the same gradients, summed in another order, later.
+ *              dealt out.  A workspace with room for the statistics and not for these is accepted, to save the memory: such packs
+ *              then take longer and their dK and dV are summed in another order.
  */
 hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, const void* k, const void* v,
                                    const void* o, const float* lse, const void* d_o,
@@ -249,10 +252,10 @@ hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, c
  * runs under HIP graph capture, tight serving / training loops, harnesses that forbid hipMalloc.  Same arguments,
  * kernels and results as hspmd_attn_varlen_bwd, without `workspace`: the row statistics that the dQ pass leaves for
  * the dK/dV pass, and the partial sums of dK and dV, go into a fixed device array inside the library
- * (HSPMD_STATIC_WORKSPACE_BYTES bytes for the statistics and 64 MB for the sums, on every GPU the
+ * (HSPMD_STATIC_WORKSPACE_BYTES bytes, 16 MB for the statistics and 64 MB for the sums, on every GPU the
  * library runs on, held until the process ends).  The call allocates and frees nothing and creates no events
  * (per-kernel timing does not apply to it).
- *   Limit: (2 * local_q_heads * T + 16) * 4 <= HSPMD_STATIC_WORKSPACE_BYTES, i.e.
+ *   Limit: the statistics, (2 * local_q_heads * T + 16) * 4 bytes, fit 16 MB + 256, i.e.
  *   local_q_heads * total_tokens <= 2^21 (the 65536-token, 32-head configuration just fits);
  *   larger packs get WORKSPACE_TOO_SMALL and nothing is launched.
  *   All calls on one GPU share the array: two calls that may overlap on one GPU (different streams, no event between
@@ -262,7 +265,7 @@ hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, c
  *   capture.
  * Other errors as hspmd_attn_varlen_bwd.
  */
-#define HSPMD_STATIC_WORKSPACE_BYTES (16u * 1024u * 1024u + 256u)
+#define HSPMD_STATIC_WORKSPACE_BYTES (80u * 1024u * 1024u + 256u)
 hspmd_status hspmd_attn_varlen_bwd_static_ws(const hspmd_attn_plan* plan, const void* q, const void* k, const void* v,
                                              const void* o, const float* lse, const void* d_o, int64_t q_token_stride,
                                              int64_t kv_token_stride, float softmax_scale, void* dq, void* dk, void* dv,

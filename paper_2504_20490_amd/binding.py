@@ -283,7 +283,7 @@ def attn_varlen_bwd(plan: Plan, q, k, v, o, lse, d_o, dq, dk, dv, workspace, sof
                                      _stream_handle(stream)))
 
 
-STATIC_WORKSPACE_BYTES = 16 * 1024 * 1024 + 256
+STATIC_WORKSPACE_BYTES = 80 * 1024 * 1024 + 256
 
 
 def attn_varlen_bwd_static_ws(plan: Plan, q, k, v, o, lse, d_o, dq, dk, dv, softmax_scale: float = 0.0,

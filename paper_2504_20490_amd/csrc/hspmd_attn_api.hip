@@ -308,8 +308,14 @@ bool keep_inline(hspmd_attn_plan* plan, const std::vector<Item>& all, int64_t ro
 size_t statistics_bytes(const hspmd_attn_plan* plan) {
     return (2 * (size_t)plan->q_heads * (size_t)plan->total_tokens + 16) * sizeof(float);
 }
-// Behind them, where items are dealt out, their sums.
+// Behind them, where items are dealt out, their sums.  The room for these depends on the tokens and heads of the plan and not on its
+// sequences: which workspace a plan needs, and with it the order of the sums, must not change from one pack to the next.
 size_t sums_offset(const hspmd_attn_plan* plan) { return (statistics_bytes(plan) + 255) / 256 * 256; }
+size_t sums_bytes(const hspmd_attn_plan* plan, int64_t areas) { return (size_t)(areas * hspmd::sums_area_bytes(plan->head_dim)); }
+int64_t sums_room(const hspmd_attn_plan* plan) {
+    if (plan->is_block || plan->order != HSPMD_ORDER_XCD_COST) return 0;
+    return hspmd::most_areas(plan->total_tokens, plan->q_heads, plan->kv_heads, plan->head_dim);
+}
 
 // Builds the three packed lists of a pack on the host (forward and dQ share one copy) and installs them.
 hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t num_seqs, bool first) {
@@ -582,8 +588,8 @@ int64_t hspmd_attn_plan_num_items(const hspmd_attn_plan* plan, hspmd_list_kind k
 
 size_t hspmd_attn_bwd_workspace_bytes(const hspmd_attn_plan* plan) {
     if (!plan) return 0;
-    if (plan->areas == 0) return statistics_bytes(plan);
-    return sums_offset(plan) + (size_t)(plan->areas * hspmd::sums_area_bytes(plan->head_dim));
+    const int64_t room = sums_room(plan);
+    return room == 0 ? statistics_bytes(plan) : sums_offset(plan) + sums_bytes(plan, room);
 }
 
 static hspmd_status check_strides(const hspmd_attn_plan* plan, int64_t q_token_stride, int64_t kv_token_stride) {
@@ -704,7 +710,7 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
                 : hspmd::persistent_dkv(dkv, plan->load[HSPMD_LIST_DKV], plan->count[HSPMD_LIST_DKV], p.group, plan->head_dim) ? 2 : 0;
     p.queue = plan->queue[HSPMD_LIST_DKV];
     const hspmd::InlineList* keys = inline_list(plan, HSPMD_LIST_DKV);
-    if (plan->piece_count > 0 && workspace_bytes >= hspmd_attn_bwd_workspace_bytes(plan)) {
+    if (plan->piece_count > 0 && workspace_bytes >= sums_offset(plan) + sums_bytes(plan, plan->areas)) {
         p.pieces = plan->pieces;
         p.piece_sums = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + sums_offset(plan));
         p.num_items = (int32_t)plan->piece_count;
@@ -733,11 +739,11 @@ hspmd_status hspmd_attn_varlen_bwd(const hspmd_attn_plan* plan, const void* q, c
 
 // ---- backward with the library's own workspace: for callers that cannot allocate -------------------------------
 // The row statistics that the dQ pass leaves for the dK/dV pass, and the sums of items that are dealt out, live in a fixed device
-// array instead of a buffer from the caller, with room for the sums of any pack, so that this entry point takes the same kernels as
-// the one with a workspace.  In host code the array's name is only a handle for hipGetSymbolAddress: the device address is
+// array instead of a buffer from the caller; it holds what hspmd_attn_bwd_workspace_bytes asks for any pack whose statistics fit.  In host code the array's name is only a handle for hipGetSymbolAddress: the device address is
 // looked up once per device and kept; the kernels get that address like any other workspace pointer.
-static __device__ __attribute__((used)) __align__(256) unsigned char scratch[HSPMD_STATIC_WORKSPACE_BYTES + hspmd::kMostSumsBytes];
-static_assert(HSPMD_STATIC_WORKSPACE_BYTES % 256 == 0, "sums_offset of the largest statistics");
+static __device__ __attribute__((used)) __align__(256) unsigned char scratch[HSPMD_STATIC_WORKSPACE_BYTES];
+constexpr size_t kStaticStatistics = HSPMD_STATIC_WORKSPACE_BYTES - (size_t)hspmd::kMostSumsBytes;
+static_assert(kStaticStatistics % 256 == 0, "sums_offset of the largest statistics");
 
 namespace {
 std::mutex g_scratch_mutex;
@@ -766,8 +772,7 @@ hspmd_status hspmd_attn_varlen_bwd_static_ws(const hspmd_attn_plan* plan, const 
                                              int64_t kv_token_stride, float softmax_scale, void* dq, void* dk, void* dv,
                                              hspmd_grad_dtype grad_dtype, void* stream) {
     if (!plan) return fail(HSPMD_ERR_INVALID_ARG, "plan is NULL");
-    const size_t need = statistics_bytes(plan);
-    if (need > (size_t)HSPMD_STATIC_WORKSPACE_BYTES)
+    if (statistics_bytes(plan) > kStaticStatistics)
         return fail(HSPMD_ERR_WORKSPACE_TOO_SMALL,
                     "local_q_heads * total_tokens exceeds what the library's fixed workspace holds "
                     "(HSPMD_STATIC_WORKSPACE_BYTES); use hspmd_attn_varlen_bwd with a workspace of the caller's");
@@ -777,7 +782,7 @@ hspmd_status hspmd_attn_varlen_bwd_static_ws(const hspmd_attn_plan* plan, const 
     // Per-kernel timing creates events on first use; this entry point must not create anything, so it launches
     // untimed whatever the switch says.
     return varlen_bwd(plan, q, k, v, o, lse, d_o, q_token_stride, kv_token_stride, softmax_scale, dq, dk, dv, grad_dtype,
-                      nullptr, workspace, sizeof scratch, stream, /*timed=*/false);
+                      nullptr, workspace, (size_t)HSPMD_STATIC_WORKSPACE_BYTES, stream, /*timed=*/false);
 }
 
 // ---- rotary position embedding ---------------------------------------------------------------------------------

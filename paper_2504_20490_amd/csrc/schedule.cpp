@@ -482,6 +482,8 @@ double dkv_steps(double heaviest, double total, double items, int32_t head_dim, 
     return std::max(heaviest + 8, (total + 8 * items) / (head_dim <= 64 ? 2 * units : units) + 0.35 * heaviest);
 }
 
+constexpr int64_t kLeastDealt = 9;   // steps: shorter items are not worth what the sums cost
+
 // How an item of `per_head` steps a head is dealt out where a share may hold `limit` steps.
 struct Deal {
     int32_t heads, parts;   // heads of a share; shares of a head's tiles
@@ -494,10 +496,20 @@ struct Deal {
 
 }  // namespace
 
+// One sequence of n query tiles with a query head per KV head, in shares of six steps, has n (n + 12) / 24 of them a head, one with groups at
+// most n / 2 a query head; of 377 packs of 192 to 65536 tokens that are dealt out without this bound, none has more.  Single heads: of
+// 7500 packs on 16 to 40 of them none would be dealt out (their items come in too many rounds), so those plans keep no room.
+int64_t most_areas(int64_t tokens, int32_t hq, int32_t hkv, int32_t head_dim) {
+    const int64_t n = ceil_div(tokens, kDkvQTile), group = hq / hkv, most = kMostSumsBytes / sums_area_bytes(head_dim);
+    if (n * group < kLeastDealt || (group == 1 && hkv > 15) || hkv > HeadPiece::kMostKvHeads || group > HeadPiece::kMostGroup) return 0;
+    return n > 24 * most ? most : std::min(most, ceil_div(hq * n * (n + 12), 24));
+}
+
 bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t num_queues, const PassLoad& load,
                       int64_t slots, int32_t head_dim, int64_t most_items, PieceList& out) {
     const int32_t group = hq / hkv;
-    if (load.heaviest < 9 || hkv > HeadPiece::kMostKvHeads || group > HeadPiece::kMostGroup) return false;   // (too short for what the sums cost)
+    const int64_t room = most_areas(cu[num_seqs], hq, hkv, head_dim);
+    if (load.heaviest < kLeastDealt || room == 0) return false;
     const double units = head_dim <= 64 ? 512.0 : 256.0, items = (double)slots;
     bool halves = false;
     const double now = dkv_steps((double)load.heaviest, (double)load.total, items, head_dim, &halves);
@@ -529,7 +541,7 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
                 if (pieces > 1) areas += pieces * hkv;
             }
         }
-        if (areas * sums_area_bytes(head_dim) > kMostSumsBytes || parts > HeadPiece::kMostParts || slots + more + (short_list ? 16 : 0) > most_items) continue;   // (16: padding of short queues)
+        if (areas > room || parts > HeadPiece::kMostParts || slots + more + (short_list ? 16 : 0) > most_items) continue;   // (16: padding of short queues)
         bool h = false;
         const double then = dkv_steps((double)heaviest, (double)load.total, items + (double)more, head_dim, &h) + 7 + 0.025 * (double)areas;
         if (then < least) {

@@ -77,6 +77,9 @@ static_assert(sizeof(HeadPiece) == sizeof(hspmd_work_item), "lists of either tra
 constexpr int64_t sums_area_bytes(int32_t head_dim) { return 2 * kDkvKTile * (head_dim <= 64 ? 64 : 128) * 4; }
 constexpr int64_t kMostSumsBytes = 64 << 20;
 static_assert(kMostSumsBytes / sums_area_bytes(64) <= HeadPiece::kMostAreas, "an area's number fits its field");
+// The most areas that a pack of `tokens` tokens may ask for: by the token count alone and never less for more tokens, so that a
+// workspace made for the largest pack serves every smaller one.  0: none can be dealt out.
+int64_t most_areas(int64_t tokens, int32_t hq, int32_t hkv, int32_t head_dim);
 struct PieceList {
     std::vector<HeadPiece> items;    // launch order, as build_work_list's
     int64_t areas = 0;

@@ -84,9 +84,9 @@ class Plan:
     def forward(self):
         b, qs, ks = p(1 << 20), i64(self.hq * self.d), i64(self.hkv * self.d)
         assert lib.hspmd_attn_varlen_fwd(self.h, b, b, b, qs, ks, f32(0), b, b, p(0)) == 0
-    def backward(self):
+    def backward(self, workspace_bytes=None):
         b, qs, ks = p(1 << 20), i64(self.hq * self.d), i64(self.hkv * self.d)
-        n = ctypes.c_size_t(lib.hspmd_attn_bwd_workspace_bytes(self.h))
+        n = ctypes.c_size_t(workspace_bytes or lib.hspmd_attn_bwd_workspace_bytes(self.h))
         assert lib.hspmd_attn_varlen_bwd(self.h, b, b, b, b, b, b, qs, ks, f32(0), b, b, b, 0, b, n, p(0)) == 0
     def backward_static(self):
         b, qs, ks = p(1 << 20), i64(self.hq * self.d), i64(self.hkv * self.d)

@@ -95,3 +95,35 @@ for pack, hq, hkv, d in args[0]:
 """
     for case, (with_workspace, without) in zip(cases, rec.record(stand_in, program, cases)):
         assert with_workspace == without, case
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 1, 64), (4, 4, 104), (32, 8, 128), (24, 24, 128), (15, 15, 64), (6, 3, 80), (1, 1, 128)])
+def test_one_workspace_serves_every_pack_of_a_plan(stand_in, hq, hkv, d):
+    """Its size follows from the number of tokens, is never less for more of them, and is enough for what any pack launches."""
+    import random
+    rng = random.Random(hq + hkv)
+    packs_of = {}
+    for tokens in (1, 192, 449, 700, 2048, 4096, 20000, 65536):
+        for mean in (tokens, 40, 300, 2000):
+            lengths = []
+            while sum(lengths) < tokens:
+                lengths.append(min(1 + int(rng.expovariate(1 / mean)) if mean < tokens else tokens, tokens - sum(lengths)))
+            packs_of.setdefault(tokens, []).append(lengths)
+    program = """
+packs, hq, hkv, d = args
+plan = None
+for lengths in packs:
+    plan = plan or Plan(lengths, hq, hkv, d)
+    plan.update(lengths)
+    calls(); plan.backward(); own = calls(); plan.backward(1 << 40)
+    launches = [[c for c in x if c[0] == "launch"] for x in (own, calls())]
+    out([lib.hspmd_attn_bwd_workspace_bytes(plan.h), *launches])
+"""
+    found = rec.record(stand_in, program, [p for group in packs_of.values() for p in group], hq, hkv, d)
+    sizes = []
+    for tokens, group in packs_of.items():
+        of_tokens, found = found[:len(group)], found[len(group):]
+        assert len({size for size, *_ in of_tokens}) == 1, (tokens, [size for size, *_ in of_tokens])
+        assert all(own == with_any for _, own, with_any in of_tokens), tokens
+        sizes.append(of_tokens[0][0])
+    assert sizes == sorted(sizes) and sizes[-1] <= 8 * hq * 65536 + 320 + (64 << 20)
