@@ -180,8 +180,9 @@ struct hspmd_attn_plan {
     // dK/dV items that are dealt out (packed plans): the shares' list, a view into the current slot or, beside lists in the arguments, kept
     // here; their sums take `areas` of the caller's workspace, and where it has no room the pass walks the ordinary list
     int64_t piece_count = 0, areas = 0;   // 0: nothing is dealt out
+    int64_t dealt_count = 0;              // items of which the shares' sums are added up
     bool piece_halves = false;
-    const hspmd::HeadPiece* pieces = nullptr;
+    const hspmd::HeadPiece* pieces = nullptr;   // the shares; behind them the first share of every item that has several
     hspmd::InlineList inline_pieces{};
     int device = -1;   // current when the plan was made
     // device copies of the lists
@@ -355,11 +356,14 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
         // behind the lists: the draw counters of the three passes, uploaded as zeros (one list item = 16 bytes = 4 counters), and the shares
         const size_t counters_at = all.size(), pieces_at = counters_at + 3 * kCounterItems;
         try {
-            all.resize(pieces_at + (dealt ? pieces.items.size() : 0), hspmd_work_item{0, 0, 0, 0});
+            all.resize(pieces_at + (dealt ? pieces.items.size() + pieces.dealt.size() : 0), hspmd_work_item{0, 0, 0, 0});
         } catch (const std::bad_alloc&) {
             return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
         }
-        if (dealt) std::memcpy(all.data() + pieces_at, pieces.items.data(), pieces.items.size() * sizeof(hspmd::HeadPiece));
+        if (dealt) {
+            std::memcpy(all.data() + pieces_at, pieces.items.data(), pieces.items.size() * sizeof(hspmd::HeadPiece));
+            std::memcpy(all.data() + pieces_at + pieces.items.size(), pieces.dealt.data(), pieces.dealt.size() * sizeof(hspmd::HeadPiece));
+        }
         if (hspmd_status rc = install_lists(plan, all.data(), all.size() * sizeof(hspmd_work_item), first)) return rc;
         plan->is_inline = false;
         hspmd_work_item* const lists = static_cast<hspmd_work_item*>(plan->slots[plan->current].block);
@@ -374,6 +378,7 @@ hspmd_status fill_packed_plan(hspmd_attn_plan* plan, const int32_t* cu, int32_t 
     plan->total_tokens = cu[num_seqs];
     plan->piece_count = dealt ? (int64_t)pieces.items.size() : 0;
     plan->areas = dealt ? pieces.areas : 0;
+    plan->dealt_count = dealt ? (int64_t)pieces.dealt.size() : 0;
     plan->piece_halves = pieces.halves;
     for (int kind = 0; kind < 3; ++kind) plan->load[kind] = load[kind];
     plan->max_position = 0;
@@ -720,7 +725,13 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
     }
     auto dkv_pass = [&] {
         const hipError_t launched = hspmd::launch_bwd_dkv(p, keys, plan->head_dim, p.num_items, false, s);
-        return launched == hipSuccess && p.piece_sums ? hspmd::launch_piece_sums(p, keys, p.num_items, s) : launched;
+        if (launched != hipSuccess || !p.piece_sums) return launched;
+        if (keys) return hspmd::launch_piece_sums(p, keys, plan->piece_count, s);
+        // A long list holds far more items than are dealt out, and eight workgroups for each of them cost more than the sums (us, the pass with
+        // them, by the whole list and by these; items whole): width 64, 5000 tokens and 3000 single ones, 32 heads on 4 621 / 579; 571.
+        hspmd::BwdParams sums = p;
+        sums.pieces = plan->pieces + plan->piece_count;
+        return hspmd::launch_piece_sums(sums, keys, plan->dealt_count, s);
     };
     e = timed ? timed_launch(3, s, dkv_pass) : dkv_pass();
     if (e != hipSuccess) return fail_hip(e, "backward dK/dV launch");

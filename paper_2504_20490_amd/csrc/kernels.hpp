@@ -107,8 +107,8 @@ hipError_t launch_bwd_dsum(const BwdParams& p, int head_dim, hipStream_t stream)
 hipError_t launch_bwd_dq(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream);
 hipError_t launch_bwd_dkv(const BwdParams& p, const InlineList* list, int head_dim, int64_t num_items, bool block, hipStream_t stream);
 
-// adds up the areas of the items that were dealt out: dK and dV, rotated back and rounded as the pass itself would.  `list`, count: as
-// the pass's own
+// adds up the areas of the items that were dealt out: dK and dV, rotated back and rounded as the pass itself would.  The first share
+// of each such item has to be among the `count` entries of `list` or p.pieces; others are passed over
 hipError_t launch_piece_sums(const BwdParams& p, const InlineList* list, int64_t count, hipStream_t stream);
 
 // merge of two partial results of the same rows over disjoint key sets (fp32 O [T, Hq, d], LSE [Hq, T]):

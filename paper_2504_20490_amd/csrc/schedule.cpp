@@ -583,6 +583,8 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
         },
         [&](const HeadPiece& it) { return (int64_t)it.n_heads(group) * (it.end_tile() - it.first_tile()); }, HeadPiece{0, 0, 0, 0});
     if ((int64_t)out.items.size() > most_items) return false;   // (short queues are padded)
+    for (const HeadPiece& it : out.items)
+        if (!it.padding() && it.index() == 0 && it.shares(group) > 1) out.dealt.push_back(it);
     return true;
 }
 

@@ -82,6 +82,7 @@ static_assert(kMostSumsBytes / sums_area_bytes(64) <= HeadPiece::kMostAreas, "an
 int64_t most_areas(int64_t tokens, int32_t hq, int32_t hkv, int32_t head_dim);
 struct PieceList {
     std::vector<HeadPiece> items;    // launch order, as build_work_list's
+    std::vector<HeadPiece> dealt;    // the first share of every item that has several
     int64_t areas = 0;
     bool halves = false;             // the unit of work is half a piece
 };

@@ -127,3 +127,16 @@ for lengths in packs:
         assert all(own == with_any for _, own, with_any in of_tokens), tokens
         sizes.append(of_tokens[0][0])
     assert sizes == sorted(sizes) and sizes[-1] <= 8 * hq * 65536 + 320 + (64 << 20)
+
+
+@pytest.mark.parametrize("long,short,count,hq,hkv,d", [(16000, 33, 2000, 4, 2, 128), (9000, 100, 578, 8, 1, 128), (5000, 1, 3000, 32, 4, 64)])
+def test_sums_are_looked_for_among_the_items_that_have_some(stand_in, long, short, count, hq, hkv, d):
+    """Few of a long list's items are dealt out: those of the long sequence."""
+    program = """
+pack, hq, hkv, d = args
+plan = Plan(pack, hq, hkv, d)
+calls(); plan.backward(); out([c for c in calls() if c[0] == "launch"])
+"""
+    (found,) = rec.record(stand_in, program, [long] + [short] * count, hq, hkv, d)
+    _, name, workgroups = found[-1]
+    assert rec.kernel(name)[0] == "bwd_piece_sums_kernel" and 0 < workgroups <= 8 * hkv * -(-long // 128)
