@@ -888,9 +888,11 @@ hspmd_status hspmd_attn_estimate_ms(const int32_t* cu_seqlens, int32_t num_seqs,
     if (!why.empty()) return fail(HSPMD_ERR_INVALID_ARG, why);
     if (!supported_head_dim(head_dim)) return fail(HSPMD_ERR_UNSUPPORTED, "head_dim must be a multiple of 8 between 8 and 128");
     try {
-        *fwd_ms = hspmd::estimate_pass_us(HSPMD_LIST_FWD, cu_seqlens, num_seqs, local_q_heads, local_kv_heads, head_dim) * 1e-3;
-        *bwd_ms = (hspmd::estimate_pass_us(HSPMD_LIST_DQ, cu_seqlens, num_seqs, local_q_heads, local_kv_heads, head_dim) +
-                   hspmd::estimate_pass_us(HSPMD_LIST_DKV, cu_seqlens, num_seqs, local_q_heads, local_kv_heads, head_dim)) * 1e-3;
+        hspmd::PassFeatures f[3];
+        hspmd::pack_features(cu_seqlens, num_seqs, local_q_heads, local_kv_heads, head_dim, f);
+        *fwd_ms = hspmd::estimate_pass_us(HSPMD_LIST_FWD, f[HSPMD_LIST_FWD], head_dim) * 1e-3;
+        *bwd_ms = (hspmd::estimate_pass_us(HSPMD_LIST_DQ, f[HSPMD_LIST_DQ], head_dim) +
+                   hspmd::estimate_pass_us(HSPMD_LIST_DKV, f[HSPMD_LIST_DKV], head_dim)) * 1e-3;
     } catch (const std::bad_alloc&) {
         return fail(HSPMD_ERR_INVALID_ARG, "out of host memory while building the work lists");
     }

@@ -616,42 +616,64 @@ constexpr PassCost kPassCost[3][5] = {
 
 }  // namespace
 
-double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim) {
-    const std::vector<hspmd_work_item> list = build_work_list(kind, cu, num_seqs, hq, hkv, kNumXcd);
-    if (list.empty()) return 0.0;
-    const PassLoad load = pass_load(kind, cu, num_seqs, hq, hkv);
+void pack_features(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim, PassFeatures (&out)[3]) {
+    const int32_t group = hq / hkv;
+    // one list serves the forward and the dQ pass, as in a plan
+    const std::vector<hspmd_work_item> rows = build_work_list(HSPMD_LIST_FWD, cu, num_seqs, hq, hkv, kNumXcd);
+    const std::vector<hspmd_work_item> keys = build_work_list(HSPMD_LIST_DKV, cu, num_seqs, hq, hkv, kNumXcd);
+    const bool in_arguments = std::max(rows.size(), keys.size()) <= 240;
+    auto walk = [](const auto& list, auto real, auto cost_of, PassFeatures& f) {
+        f.heaviest = 0.0;
+        for (size_t p = 0; p < list.size(); ++p) {
+            if (!real(list[p])) continue;
+            const double cost = (double)cost_of(list[p]);
+            f.heaviest = std::max(f.heaviest, cost);
+            f.queue_steps[p % kNumXcd] += cost;
+            f.queue_items[p % kNumXcd] += 1.0;
+        }
+    };
+    auto real = [](const hspmd_work_item& it) { return it.tile >= 0; };
+    PassFeatures& fwd = out[HSPMD_LIST_FWD] = PassFeatures();
+    PassFeatures& dkv = out[HSPMD_LIST_DKV] = PassFeatures();
+    walk(rows, real, [&](const hspmd_work_item& it) { return item_cost(HSPMD_LIST_FWD, it.seq_len, it.tile, group); }, fwd);
+    out[HSPMD_LIST_DQ] = fwd;
+    const PassLoad row_load = pass_load(HSPMD_LIST_FWD, cu, num_seqs, hq, hkv), key_load = pass_load(HSPMD_LIST_DKV, cu, num_seqs, hq, hkv);
+    for (const hspmd_list_kind kind : {HSPMD_LIST_FWD, HSPMD_LIST_DQ}) {
+        const RowsForm form = rows_form(kind, row_load, (int64_t)rows.size(), group, head_dim, in_arguments);
+        out[kind].halves = form.halves;
+        out[kind].teams = form.teams;
+    }
+    PieceList pieces;
+    if (!keys.empty() && build_piece_list(cu, num_seqs, hq, hkv, kNumXcd, key_load, (int64_t)keys.size(), head_dim,
+                                          in_arguments ? 240 : std::numeric_limits<int32_t>::max(), pieces)) {
+        dkv.halves = pieces.halves;
+        dkv.areas = pieces.areas;
+        walk(pieces.items, [](const HeadPiece& it) { return !it.padding(); },
+             [&](const HeadPiece& it) { return (int64_t)it.n_heads(group) * (it.end_tile() - it.first_tile()); }, dkv);
+    } else {
+        dkv.halves = pass_dispatch(HSPMD_LIST_DKV, key_load, (int64_t)keys.size(), head_dim, false) == Dispatch::kHalves;
+        walk(keys, real, [&](const hspmd_work_item& it) { return item_cost(HSPMD_LIST_DKV, it.seq_len, it.tile, group); }, dkv);
+    }
+}
+
+double estimate_pass_us(hspmd_list_kind kind, const PassFeatures& f, int32_t head_dim) {
+    if (f.heaviest == 0.0) return 0.0;   // an empty pack
     const bool narrow = head_dim <= 64;
     const PassCost c = kPassCost[(int)kind][narrow ? 0 : std::max(1, (head_dim + 15) / 16 - 4)];
-    const PassFixed f = kPassFixed[(int)kind];
-    RowsForm form{pass_dispatch(kind, load, (int64_t)list.size(), head_dim, false) == Dispatch::kHalves, 1};
-    if (kind != HSPMD_LIST_DKV) form = rows_form(kind, load, (int64_t)list.size(), hq / hkv, head_dim, list.size() <= 240);
-    // items that are dealt out: their shares, and what adding up their sums takes
-    PieceList pieces;
-    const int64_t rows = kind == HSPMD_LIST_DKV ? (int64_t)build_work_list(HSPMD_LIST_FWD, cu, num_seqs, hq, hkv, kNumXcd).size() : 0;
-    const bool short_lists = std::max(rows, (int64_t)list.size()) <= 240;
-    const bool dealt = kind == HSPMD_LIST_DKV &&
-                       build_piece_list(cu, num_seqs, hq, hkv, kNumXcd, load, (int64_t)list.size(), head_dim,
-                                        short_lists ? 240 : std::numeric_limits<int32_t>::max(), pieces);
-    if (dealt) form.halves = pieces.halves;
-    const bool halves = form.halves;
-    const Shares share = form.teams == 2 ? kTeamShares[(int)kind][halves] : halves ? Shares{f.half_step, f.half_alone, f.half_item}
+    const PassFixed fixed = kPassFixed[(int)kind];
+    const Shares share = f.teams == 2 ? kTeamShares[(int)kind][f.halves] : f.halves ? Shares{fixed.half_step, fixed.half_alone, fixed.half_item}
                                                                                    : Shares{1.0, 1.0, 1.0};
-    const double step = c.step_us * share.step * (halves ? 2 : 1), item = c.item_us * share.item * (halves ? 2 : 1);
+    const double step = c.step_us * share.step * (f.halves ? 2 : 1), item = c.item_us * share.item * (f.halves ? 2 : 1);
     // workgroups resident per XCD: 32 compute units, two workgroups each in the forward and dQ passes, one in dK/dV; at tile
     // width 64 three in the dQ pass and two in dK/dV with whole items
-    const double per_unit = kind == HSPMD_LIST_DKV ? (narrow && !halves ? 2 : 1) : (narrow && kind == HSPMD_LIST_DQ ? 3 : 2);
-    double queue_weight[kNumXcd] = {0};
-    int64_t heaviest = dealt ? 0 : load.heaviest;
-    for (size_t p = 0; p < (dealt ? pieces.items.size() : list.size()); ++p) {
-        if (dealt ? pieces.items[p].padding() : list[p].tile < 0) continue;
-        const int64_t cost = dealt ? (int64_t)pieces.items[p].n_heads(hq / hkv) * (pieces.items[p].end_tile() - pieces.items[p].first_tile())
-                                   : item_cost(kind, list[p].seq_len, list[p].tile, hq / hkv);
-        heaviest = std::max(heaviest, cost);
-        queue_weight[p % kNumXcd] += (double)cost * step + item;
-    }
-    const double shared = *std::max_element(queue_weight, queue_weight + kNumXcd) / (32.0 * per_unit);
-    const double alone = (double)heaviest * c.alone_us * share.alone + c.item_us * share.item;
-    return f.launch_us + (dealt ? 5.0 + 0.03 * (double)pieces.areas : 0.0) + std::sqrt(std::sqrt(shared * shared * shared * shared + alone * alone * alone * alone));
+    const double per_unit = kind == HSPMD_LIST_DKV ? (narrow && !f.halves ? 2 : 1) : (narrow && kind == HSPMD_LIST_DQ ? 3 : 2);
+    double shared = 0.0;
+    for (int x = 0; x < kNumXcd; ++x) shared = std::max(shared, f.queue_steps[x] * step + f.queue_items[x] * item);
+    shared /= 32.0 * per_unit;
+    const double alone = f.heaviest * c.alone_us * share.alone + c.item_us * share.item;
+    // (items that are dealt out: what adding up their sums takes)
+    return fixed.launch_us + (f.areas > 0 ? 5.0 + 0.03 * (double)f.areas : 0.0) +
+           std::sqrt(std::sqrt(shared * shared * shared * shared + alone * alone * alone * alone));
 }
 
 // ------------------------------------------------------------------------------ block variant

@@ -92,7 +92,15 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
                       int64_t slots, int32_t head_dim, int64_t most_items, PieceList& out);
 
 // ---- cost model: predicted kernel times (microseconds) of the three passes for a pack
-double estimate_pass_us(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim);
+// What the model knows of a pass: the form that it takes, and the inner steps and items (or shares of items) of each queue.
+struct PassFeatures {
+    bool halves = false;
+    int teams = 1;
+    int64_t areas = 0;   // of a dK/dV pass whose items are dealt out
+    double heaviest = 0.0, queue_steps[kNumXcd] = {0.0}, queue_items[kNumXcd] = {0.0};
+};
+void pack_features(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim, PassFeatures (&out)[3]);
+double estimate_pass_us(hspmd_list_kind kind, const PassFeatures& f, int32_t head_dim);
 
 // ---- block variant (one step of context-parallel attention): per sequence a query chunk and a key chunk
 // with positions inside the sequence; key j is visible to row r iff j <= r + (q_pos - k_pos).
