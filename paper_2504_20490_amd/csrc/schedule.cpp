@@ -316,6 +316,7 @@ PassLoad pass_load(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, in
     PassLoad load;
     for (int32_t s = 0; s < num_seqs; ++s) {
         const int32_t len = cu[s + 1] - cu[s], n_tiles = (int32_t)ceil_div(len, tile_rows);
+        load.items += n_tiles;
         for (int32_t t = 0; t < n_tiles; ++t) {
             const int64_t c = item_cost(kind, len, t, hq / hkv);
             load.total += c;
@@ -323,6 +324,7 @@ PassLoad pass_load(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, in
         }
     }
     load.total *= (kind == HSPMD_LIST_DKV) ? hkv : hq;
+    load.items *= (kind == HSPMD_LIST_DKV) ? hkv : hq;
     return load;
 }
 
@@ -355,28 +357,34 @@ bool split_rows(hspmd_list_kind kind, const PassLoad& load, int64_t slots, int32
 // covered its loads and stores.  Half items: where each has a unit to itself, more or less, and is long (at most 240 slots: lists in the
 // arguments, the only ones that these kernels take).  Whole items: where the
 // heaviest is longer than the work per slot, and not so much that halves are better.  Measured, without and with (us; F forward,
-// Q dQ pass; steps of the heaviest item, slots; ratio = (heaviest + 6) / work per slot as in split_rows):
-//   half items, one team / two: one head of 8192 tokens (128, 64) F 88.9 / 68.9, Q 82 / 73; 4 heads of 4096 (64, 128) F 52 / 44, Q 49 / 46;
-//   width 64, 8 heads of 2048 F 21.4 / 18.4, Q 18.7 / 18.4; lost where shorter or more (2 x 1024, 8 heads F 18.3 / 19.7, Q 20.4 / 22.6; 184 slots,
+// Q dQ pass; steps of the heaviest item, slots of the list with its padding; ratio = (heaviest + 6) / work per slot as in split_rows):
+//   half items, one team / two: one head of 8192 tokens (128, 144) F 88.9 / 68.9, Q 82 / 73; 4 heads of 4096 (64, 168) F 52 / 44;
+//   width 64, 8 heads of 2048 (32, 128) F 21.4 / 18.4, Q 18.7 / 18.4; lost where shorter or more (2 x 1024, 8 heads F 18.3 / 19.7, Q 20.4 / 22.6; 184 slots,
 //   40 steps F 35.7 / 40.6; 200 slots, 100 steps Q 67.7 / 72).
-//   whole items, one team / two: 5 heads of 16001 (251, 625, ratio 1.50) F 321 / 310, Q 438 / 414; 16 heads of 4096 (64, 512, 1.55) F 81.5 /
-//   79; width 64, 8 heads of 8192 F 99 / 86, Q 116 / 99, 2 of 16384 F 155 / 130; against halves width 80, 477 slots of 318, 1.98 F 296 / 256, Q 338 /
-//   307; lost at lower ratios (12 heads of 8192, 1.2 F 199 / 208, Q 267 / 280), for dQ at higher ones, where halves win (134 steps, 270
+//   whole items, one team / two: 5 heads of 16001 (251, 816, ratio 1.47) F 321 / 310, Q 438 / 414; width 64, 8 heads of 8192 (128, 512, 1.74)
+//   F 99 / 86, Q 116 / 99, 2 of 16384 (256, 336, 3.62) F 155 / 130; against halves width 80, 318 items of 477 slots, 1.98 F 296 / 256, Q 338 /
+//   307; lost at lower ratios (12 heads of 8192, 1.1 F 199 / 208, Q 267 / 280), for dQ at higher ones, where halves win (134 steps, 270
 //   slots, 3.9 Q 114 / 136), and with heads in groups, which already share tiles in the L1 (24 on 6, 74 steps, 1.7 F 99 / 110).
-// Over 1160 packs of five widths the packs that this takes run in 0.84 (F, width 64), 0.89 (F) and 0.93 (Q) of the time on average; the worst are
-// F 1.02 and Q 1.04.
+//   Lists without padding (one sequence on 8 heads, say) end together by themselves, with halves and with whole items: there the dQ pass asks
+//   for a little more (ratio 1.52 at 109 steps Q 169 / 181, 124 steps 190 / 199), and so does the forward at width 64 against halves below 80
+//   steps (45 steps F 27.4 / 30.1, 56 33.8 / 36.6, 76 45.2 / 46.9; with padding 45 steps 35.6 / 31.7).  At head_dim above 112 whole items
+//   against halves gain nothing below 80 steps (64 steps F 53.9 / 56.6, 77 69.1 / 71.0; 107 119 / 103).
+// Over 677 packs of five widths, one to 40 heads, the passes that this takes run in 0.86 (F, width 64), 0.89 (F) and 0.93 (Q) of the time on
+// average; 18 of 831 lose more than 1 %, the worst F 1.08 (24.4 / 26.4) and Q 1.02.
 int teams_of_rows(hspmd_list_kind kind, bool halves, const PassLoad& load, int64_t slots, int32_t group, int32_t head_dim, bool in_arguments,
                   bool* whole) {
     const double heaviest = (double)load.heaviest, items = (double)slots;
     const double ratio = (heaviest + 6.0) / (((double)load.total + 6.0 * 2.0 * items) / 512.0);
     const bool fwd = kind == HSPMD_LIST_FWD, narrow = head_dim <= 64;
+    const bool even = load.items == slots;   // no queue is shorter than the others
     *whole = !halves;
     const double least = (fwd ? narrow ? 17 : 30 : narrow ? 32 : 48) + (fwd ? 0.25 : 1.2) * std::max(0.0, items - 128);
     if (halves && in_arguments && ratio >= 4.2 && heaviest >= least) return 2;
     const double from = fwd ? (narrow ? 1.35 + 0.3 * 64 / heaviest : 1.3 + 0.5 * 64 / heaviest) + (group == 1 ? 0.0 : narrow ? 0.1 : 0.35)
-                            : (narrow ? 1.35 : 1.4) + 0.2 * 64 / heaviest;
-    const double to = fwd ? narrow ? 9.0 : 3.4 : narrow ? 2.3 : 2.0;
-    if ((fwd || group == 1) && items >= (fwd && narrow ? 150 : 250) && heaviest >= (fwd ? narrow ? 44 : 64 : 100) && ratio >= from && ratio <= to) {
+                            : (narrow ? 1.35 : even ? 1.45 : 1.4) + 0.2 * 64 / heaviest;
+    const double to = fwd ? narrow ? halves && even && heaviest < 80 ? 2.5 : 9.0 : 3.4 : narrow ? 2.3 : 2.0;
+    const double longer = fwd ? narrow ? 44 : halves && head_dim > 112 ? 80 : 64 : 100;
+    if ((fwd || group == 1) && items >= (fwd && narrow ? 150 : 250) && heaviest >= longer && ratio >= from && ratio <= to) {
         *whole = true;
         return 2;
     }
@@ -478,7 +486,7 @@ namespace {
 // What the dK/dV pass takes, in steps, and whether on half items (split_dkv): its longest item, or its work and what the last items
 // leave idle at the end.
 double dkv_steps(double heaviest, double total, double items, int32_t head_dim, bool* halves) {
-    const PassLoad load{(int64_t)total, (int64_t)heaviest};
+    const PassLoad load{(int64_t)total, (int64_t)heaviest, (int64_t)items};
     *halves = split_dkv(load, (int64_t)items, head_dim);
     const double units = 256.0;
     if (*halves) {
@@ -753,6 +761,7 @@ PassLoad block_pass_load(hspmd_list_kind kind, const int32_t* cu_q, const int32_
     for (int32_t s = 0; s < num_seqs; ++s) {
         hspmd_block_item it{cu_q[s], cu_q[s + 1] - cu_q[s], cu_k[s], cu_k[s + 1] - cu_k[s], q_pos[s] - k_pos[s], 0, 0, q_pos[s]};
         const int32_t n_tiles = (int32_t)ceil_div(kind == HSPMD_LIST_DKV ? it.k_len : it.q_len, tile_rows);
+        load.items += n_tiles;
         for (it.tile = 0; it.tile < n_tiles; ++it.tile) {
             const int64_t c = block_item_cost(kind, it, hq / hkv);
             load.total += c;
@@ -760,6 +769,7 @@ PassLoad block_pass_load(hspmd_list_kind kind, const int32_t* cu_q, const int32_
         }
     }
     load.total *= (kind == HSPMD_LIST_DKV) ? hkv : hq;
+    load.items *= (kind == HSPMD_LIST_DKV) ? hkv : hq;
     return load;
 }
 

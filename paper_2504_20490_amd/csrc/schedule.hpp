@@ -21,9 +21,10 @@ std::string check_pack(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t 
 // Cost (number of inner steps) of one item.
 int64_t item_cost(hspmd_list_kind kind, int32_t seq_len, int32_t tile, int32_t group);
 
-// What a pass has to do, in inner steps: all items together, and the heaviest one (the pass takes at least that long).
+// What a pass has to do, in inner steps: all items together, and the heaviest one (the pass takes at least that long); and the number
+// of items, which the list's length exceeds by its padding.
 struct PassLoad {
-    int64_t total = 0, heaviest = 0;
+    int64_t total = 0, heaviest = 0, items = 0;
 };
 PassLoad pass_load(hspmd_list_kind kind, const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t hkv);
 PassLoad block_pass_load(hspmd_list_kind kind, const int32_t* cu_q, const int32_t* cu_k, const int32_t* q_pos,

@@ -153,3 +153,19 @@ calls(); plan.backward(); out([c[1] for c in calls() if c[0] == "launch"])
 """
     (names,) = rec.record(stand_in, program, lengths, hq, hkv, d)
     assert rec.kernel(names[-1])[0] == "bwd_dkv_kernel" and "HeadPieces" not in names[-1]
+
+
+@pytest.mark.parametrize("lengths,heads,d,fwd,dq", [
+    # lists without padding: (forward, dQ) of two teams
+    ([2835], 8, 64, False, False), ([3582], 8, 64, False, False), ([3281, 344, 534], 8, 64, False, False), ([4800], 8, 64, False, False),
+    ([233, 918, 6919, 480, 837, 1553, 1293, 549], 8, 128, False, False), ([415, 2508, 656, 7878], 8, 104, False, False),
+    ([4096], 8, 128, False, False), ([5900], 8, 64, True, False), ([6850], 8, 128, True, False), ([16001], 5, 128, True, True)])
+def test_items_keep_one_team_where_two_would_take_longer(stand_in, lengths, heads, d, fwd, dq):
+    program = """
+pack, h, d = args
+plan = Plan(pack, h, h, d)
+calls(); plan.forward(); plan.backward(); out([c[1] for c in calls() if c[0] == "launch"])
+"""
+    (names,) = rec.record(stand_in, program, lengths, heads, d)
+    assert [rec.kernel(n)[0] for n in names[:2]] == ["fwd_kernel", "bwd_dq_kernel"]
+    assert ["TwoTeams" in n for n in names[:2]] == [fwd, dq]

@@ -124,7 +124,7 @@ LONG, LONG_GROUPS = [3200, 70, 1, 64], [3199, 65]
 PACKS = [(LONG, 2, 2, d, HALF, HALF) for d in (40, 64, 80, 96, 104, 128)] + [(LONG_GROUPS, 2, 1, d, HALF, HALF) for d in (64, 128)]
 PACKS += [([6465], 10, 10, d, WHOLE, WHOLE) for d in (64, 80, 96, 104, 128)]
 # whole items with the list in the arguments
-PACKS += [([3840], 8, 8, 64, WHOLE, (1, 1))]
+PACKS += [([3000], 7, 7, 64, WHOLE, (1, 1))]
 
 FORM_SHIM = """
 #include "schedule.hpp"
