@@ -128,7 +128,8 @@ def record(stand_in: str, program: str, *args):
 
 
 def kernel(mangled: str):
-    """(name, template arguments) of a kernel of this library; True at the end: its list is in the arguments."""
+    """(name, template arguments) of a kernel of this library: its numbers, then TwoTeams and HeadPieces by name where they are among
+    them, then whether its list is in the launch's arguments."""
     m = re.match(r"_ZN5hspmd(\d+)", mangled)
     if not m:
         return mangled, ()
@@ -137,4 +138,7 @@ def kernel(mangled: str):
     if not values:
         return mangled[m.end():at], ()
     found = tuple(int(x) if t == "i" else x == "1" for t, x in re.findall(r"L([ib])(\d+)E", values.group(1)))
-    return mangled[m.end():at], found + (("InlineList" in mangled[at:at + values.end() + 20],) if values.group(2) is not None else ())
+    if values.group(2) is None:
+        return mangled[m.end():at], found
+    pack = mangled[at:at + values.end() + 20]
+    return mangled[m.end():at], found + tuple(x for x in ("TwoTeams", "HeadPieces") if x in pack) + ("InlineList" in pack,)

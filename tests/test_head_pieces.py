@@ -13,22 +13,26 @@ LONG = [2500, 449, 1, 64, 130, 127]
 PACKS = [(LONG, 6, 2, d, 1) for d in (40, 64, 80, 96, 104, 128)]
 PACKS += [([3200, 1500, 900, 65, 1], 28, 7, d, 0) for d in (80, 96, 104, 128)] + [([3200, 900, 65, 1], 32, 4, 64, 0)]
 PACKS += [([700, 300, 128], 6, 2, 128, 1), ([512], 8, 2, 128, 1), ([449], 5, 1, 72, 1)]
-# no longest item that outlasts the rest by what the sums cost
-# shares of one head's tiles, alone and beside shares of heads
-PACKS += [([4500, 300, 1], 1, 1, d, 0) for d in (64, 80, 104, 128)] + [([8000, 129], 2, 1, 96, 1), ([8200, 64], 2, 2, 64, 0)]
-# half shares
+# shares of one head's tiles: whole, with the list in the arguments and on the device
+PACKS += [([2438, 32], 2, 2, 64, 0), ([2681], 3, 3, 96, 0), ([1769, 473], 3, 3, 128, 0), ([4466, 410], 5, 5, 64, 0), ([7617, 1702, 1436], 4, 4, 128, 0)]
+# half shares, the last of heads
 PACKS += [([1967], 2, 2, d, 1) for d in (64, 40)] + [([1411], 1, 1, d, 1) for d in (80, 96, 104, 128)]
-ORDINARY = [([2048] * 4, 32, 8, 128), ([2048], 8, 8, 128), ([2048] * 8, 32, 32, 128), ([1024] * 2, 8, 8, 64), ([64] * 40, 8, 4, 128), ([256], 4, 1, 128), ([], 8, 2, 128)]
+PACKS += [([4500, 300, 1], 1, 1, d, 1) for d in (80, 104, 128)] + [([8000, 129], 2, 1, 96, 1)]
+# no longest item that outlasts the rest by what the sums cost; lists in the arguments that shares which pay would not fit into
+ORDINARY = [([4500, 300, 1], 1, 1, 64), ([8200, 64], 2, 2, 64), ([2048] * 4, 32, 8, 128), ([2048], 8, 8, 128), ([2048] * 8, 32, 32, 128), ([1024] * 2, 8, 8, 64), ([64] * 40, 8, 4, 128), ([256], 4, 1, 128), ([], 8, 2, 128)]
 
 SHIM = """
+#include <algorithm>
 #include "schedule.hpp"
 using namespace hspmd;
 static PieceList list;
 static int group;
 extern "C" int build(const int* cu, int n, int hq, int hkv, int d, long long most) {
     const PassLoad load = pass_load(HSPMD_LIST_DKV, cu, n, hq, hkv);
+    const size_t rows = build_work_list(HSPMD_LIST_FWD, cu, n, hq, hkv, kNumXcd).size(), keys = build_work_list(HSPMD_LIST_DKV, cu, n, hq, hkv, kNumXcd).size();
+    if (most == 0) most = std::max(rows, keys) <= 240 ? 240 : 1 << 30;   // as a plan, whose lists are all in the arguments or none is
     group = hq / hkv;
-    return build_piece_list(cu, n, hq, hkv, kNumXcd, load, (int64_t)build_work_list(HSPMD_LIST_DKV, cu, n, hq, hkv, kNumXcd).size(), d, most, list);
+    return build_piece_list(cu, n, hq, hkv, kNumXcd, load, (int64_t)keys, d, most, list);
 }
 extern "C" void sizes(long long* out) { out[0] = list.items.size(); out[1] = list.areas; out[2] = list.halves; }
 extern "C" void copy(int* out) {
@@ -51,7 +55,7 @@ def pieces(tmp_path_factory):
                     os.path.join(lib_build.CSRC, "schedule.cpp")], check=True)
     lib = ctypes.CDLL(str(so))
 
-    def call(lengths, hq, hkv, d, most=1 << 30):
+    def call(lengths, hq, hkv, d, most=0):
         cu = (ctypes.c_int32 * (len(lengths) + 1))(*np.concatenate([[0], np.cumsum(lengths)]).astype(int).tolist())
         if not lib.build(cu, len(lengths), hq, hkv, d, ctypes.c_longlong(most)):
             return None
@@ -104,9 +108,27 @@ def test_no_more_shares_than_asked_for(pieces):
 @pytest.mark.gpu
 @pytest.mark.parametrize("lengths,hq,hkv,d,halves", PACKS)
 def test_outputs(lengths, hq, hkv, d, halves):
-    """Sampled rows and keys against the oracle; bf16 and rotated gradients against the fp32 ones."""
+    """Sampled rows and keys against the oracle; bf16 and rotated gradients against the fp32 ones; every key against the pass that walks
+    whole items, and no sum read that was not written."""
+    import torch
     import test_gpu_whole_items
+    from gpu_util import GpuRun, make_case
     test_gpu_whole_items.test_persistent_dkv_pass_on_long_items(lengths, hq, hkv, d, None, None)
+    q, k, v, do = make_case(lengths, hq, hkv, d, seed=41)
+    run = GpuRun(lengths, q, k, v, do)
+    run.ws = torch.full((run.plan.bwd_workspace_bytes() // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    run.run()
+    dealt = run.dk.clone(), run.dv.clone()
+    assert run.ws.numel() > 2 * hq * sum(lengths) + 16
+    run.ws = torch.full((2 * hq * sum(lengths) + 16,), float("nan"), dtype=torch.float32, device="cuda")
+    run.dk.fill_(float("nan")), run.dv.fill_(float("nan"))
+    run.backward()
+    torch.cuda.synchronize()
+    for got, whole in zip(dealt, (run.dk, run.dv)):
+        # fp32 sums in another order; a weight whose fp32 value then lies on the other side of a rounding edge differs by a bf16 step, 2^-8 of
+        # it at most; a key may have a single row, or rows that cancel (hence the mean).  (NaN compares false.)
+        difference, size = (got - whole).norm(dim=2), whole.norm(dim=2)
+        assert bool((difference <= 2.0 ** -8 * (size + size.mean())).all()), float((difference / (size + size.mean())).max())
 
 
 @pytest.mark.gpu

@@ -63,10 +63,14 @@ def test_half_items_of_either_kind_of_list(stand_in):
 
 
 def test_every_attention_kernel_is_compared_with_the_oracle(stand_in):
-    """The packs of the GPU tests named in dispatch_packs reach every instance of the attention kernels that the library holds."""
+    """The packs of the GPU tests, those named in dispatch_packs and those of teams and shares, reach every instance of the attention
+    kernels that the library holds."""
+    import test_head_pieces
+    import test_teams
     from test_gpu_split_items import MANY_SHORT
     cases = [c[:4] for c in packs.PACKED + packs.PERSISTENT_PACKS] + [(packs.GEOMETRY, *c[:3]) for c in packs.BLOCKS]
     cases += packs.HALF_LONG_PACKS + packs.HALF_LONG_BLOCKS + packs.SHORT_PACKS + packs.SHORT_BLOCKS + [(MANY_SHORT, 16, 8, 104)]
+    cases += [c[:4] for c in test_head_pieces.PACKS + test_teams.PACKS]
     seen = {k for names in launched(stand_in, cases) for k in names}
     program = """
 name, names = ctypes.c_char_p(), []
@@ -76,9 +80,26 @@ for i in range(fake.fake_kernels(0, ctypes.byref(name))):
 out(names)
 """
     held = {rec.kernel(n) for n in rec.record(stand_in, program)[0]}
-    attention = {k for k in held if k[0] in HALVES}
-    assert len(attention) > 100
+    attention = {k for k in held if k[0] in HALVES or k[0] == "bwd_piece_sums_kernel"}
+    assert len(attention) > 100 and all(sum(mark in k[1] for k in attention) > 10 for mark in ("TwoTeams", "HeadPieces"))
     assert not attention - seen, sorted(attention - seen)
+
+
+def test_packs_of_shares_launch_the_form_that_they_declare(stand_in):
+    """Whole and half shares, at either tile width, with the list in the arguments and on the device."""
+    from test_head_pieces import ORDINARY, PACKS
+    forms = {1: set(), 2: set()}   # of single heads, of groups
+    for (lengths, hq, hkv, d, halves), names in zip(PACKS, launched(stand_in, [c[:4] for c in PACKS])):
+        in_arguments = names[-1][1][-1]
+        width = 64 if d <= 64 else 128
+        assert names[-2:] == [("bwd_dkv_kernel", (width, False, _steps(d), bool(halves), False, False, "HeadPieces", in_arguments)),
+                              ("bwd_piece_sums_kernel", (in_arguments,))], (lengths, d)
+        forms[1 if hq == hkv else 2].add((width, halves, in_arguments))
+    assert {(w, 0, a) for w in (64, 128) for a in (False, True)} <= forms[1] and {(w, 1, True) for w in (64, 128)} <= forms[1]
+    assert {(w, h, False) for w in (64, 128) for h in (0, 1)} <= forms[2] and (128, 1, True) in forms[2]
+    ordinary = [c for c in ORDINARY if c[0]]
+    for case, names in zip(ordinary, launched(stand_in, ordinary)):
+        assert names[-1][0] == "bwd_dkv_kernel" and "HeadPieces" not in names[-1][1], case
 
 
 def test_static_workspace_takes_the_same_kernels(stand_in):
@@ -152,7 +173,8 @@ plan = Plan(pack, hq, hkv, d)
 calls(); plan.backward(); out([c[1] for c in calls() if c[0] == "launch"])
 """
     (names,) = rec.record(stand_in, program, lengths, hq, hkv, d)
-    assert rec.kernel(names[-1])[0] == "bwd_dkv_kernel" and "HeadPieces" not in names[-1]
+    name, arguments = rec.kernel(names[-1])
+    assert name == "bwd_dkv_kernel" and "HeadPieces" not in arguments
 
 
 @pytest.mark.parametrize("lengths,heads,d,fwd,dq", [
@@ -167,5 +189,6 @@ plan = Plan(pack, h, h, d)
 calls(); plan.forward(); plan.backward(); out([c[1] for c in calls() if c[0] == "launch"])
 """
     (names,) = rec.record(stand_in, program, lengths, heads, d)
-    assert [rec.kernel(n)[0] for n in names[:2]] == ["fwd_kernel", "bwd_dq_kernel"]
-    assert ["TwoTeams" in n for n in names[:2]] == [fwd, dq]
+    kernels = [rec.kernel(n) for n in names[:2]]
+    assert [name for name, _ in kernels] == ["fwd_kernel", "bwd_dq_kernel"]
+    assert ["TwoTeams" in arguments for _, arguments in kernels] == [fwd, dq]
