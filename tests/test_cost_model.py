@@ -75,3 +75,29 @@ def test_an_estimate_costs_little_more_than_the_two_work_lists(lengths, hq, hkv)
         return min(times)
     # (1.3 to 1.5; building the forward's list once per pass and once more for the dK/dV pass 2.6 to 3)
     assert shortest(estimate) < 2.0 * shortest(lists)
+
+
+def test_refit_knows_the_forms_of_the_passes():
+    """Given the library's own predictions for measurements, the refit finds a model that gives them back: its features and formula are
+    the library's, passes of two teams and dealt-out items among them."""
+    import tempfile
+    from paper_2504_20490_amd import fit_cost_model as fit
+    packs = list(fit._packs(np.random.default_rng(7))) + list(fit._small_packs(np.random.default_rng(11)))
+    rows = []
+    for d in (64, 104, 128):
+        for lengths, hq, hkv in packs:
+            forward, _ = A.estimate_ms(_cu(lengths), hq, hkv, d)
+            rows.append((lengths, hq, hkv, d, {name: forward * 1e3 for name in fit.PASSES}))
+    with tempfile.TemporaryDirectory() as folder:
+        scheduler = fit._scheduler(folder)
+        features = np.stack([fit._features(scheduler, lengths, hq, hkv, d) for lengths, hq, hkv, d, _ in rows])
+    forward, dkv = fit._Passes(0, features, rows), fit._Passes(2, features, rows)
+    assert min((forward.teams == 2).sum(), (dkv.areas > 0).sum(), forward.plain.sum()) > 20
+    *_, errors = fit._fit(0, forward)
+    assert errors.max() < 1e-3
+    # the dK/dV pass from coefficients of its kind: the sums' cost is found again
+    table = np.tile([1.6, 13.0, 1.1], (len(fit.WIDTHS), 1))
+    shares = np.where(dkv.halves[:, None], [0.52, 0.70, 0.84], 1.0)
+    dkv.measured = dkv.time(0.0, table, shares) + np.where(dkv.areas > 0, 5.0 + 0.03 * dkv.areas, 0.0)
+    *_, sums, errors = fit._fit(2, dkv)
+    assert errors.max() < 0.02 and abs(sums[0] - 5.0) < 0.5 and abs(sums[1] - 0.03) < 0.005
