@@ -229,7 +229,8 @@ hspmd_status hspmd_attn_varlen_fwd(const hspmd_attn_plan* plan, const void* q, c
 
 /*
  * Backward (AttentionBwd): two launches on `stream` -- the dQ pass, which also computes the
- * row statistic D = rowsum(dO * O) of its rows and leaves it in the workspace; the dK/dV pass.
+ * row statistic D = rowsum(dO * O) of its rows and leaves it in the workspace; the dK/dV pass --
+ * and, where items of the dK/dV pass are dealt out, a third that adds up their sums.
  * Both passes recompute P from the stored lse.  No atomics: results are run-to-run bit-identical.
  *   o, d_o  bf16 [T, local_q_heads, head_dim], contiguous
  *   lse     fp32 [local_q_heads, T] as written by the forward
@@ -331,10 +332,11 @@ hspmd_status hspmd_attn_block_bwd_rope(const hspmd_attn_plan* plan, const void* 
  * Model: each pass walks its work list; an item weighs (inner steps x a step time + a fixed time per
  * item), a pass takes a launch time plus, smoothly joined, the longer of the weight of its heaviest XCD
  * queue divided by the workgroups resident per XCD and the time of its heaviest item alone; passes that
- * work on half items take a share of these; backward = dQ pass + dK/dV pass.  The coefficients are fitted
+ * work on half items or with two teams of waves take a share of these, and the sums of dealt-out dK/dV items
+ * a time of their own; backward = dQ pass + dK/dV pass.  The coefficients are fitted
  * per width class of head_dim (up to 64, 80, 96, 112, 128) to measured kernel times
  * (paper_2504_20490_amd/fit_cost_model.py refits them): forward and backward have a mean error of 7 and 5 %,
- * 95 % of the packs are within 20 and 13 %, all of them within 36 and 25 %.  Host-side plan creation is not included.
+ * 95 % of the packs are within 18 and 13 %, all of them within 35 and 23 %.  Host-side plan creation is not included.
  */
 hspmd_status hspmd_attn_estimate_ms(const int32_t* cu_seqlens, int32_t num_seqs, int32_t local_q_heads,
                                     int32_t local_kv_heads, int32_t head_dim, double* fwd_ms, double* bwd_ms);

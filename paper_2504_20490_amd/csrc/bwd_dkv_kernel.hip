@@ -419,7 +419,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 && !SPLIT ? 2 : 1)) void bwd_dkv
     // tiles: for each head of the group, q tiles first_qt .. n_qt-1 (rows at or below the diagonal: row r sees
     // key j iff j <= r + shift, so the tile's first key is seen by the rows from key0 - shift on)
     const int diagonal_qt = max(0, key0 - shift) / BQ;
-    // (a share has two tiles and more, so the second half of an item, which starts a tile further down, finds one in its first share too)
+    // (the second half of an item starts a tile further down.  A share of one head's tiles has three and more, so the half finds some in its
+    // first share too; other shares hold the whole range, and where that is one tile the item has no second half)
     const int first_qt = kPieces ? max(diagonal_qt, share_first) : diagonal_qt;
     const int n_qt = kPieces ? share_end : (L + BQ - 1) / BQ;
     const int per_head = max(0, n_qt - first_qt);

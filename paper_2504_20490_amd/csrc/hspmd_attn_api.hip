@@ -672,7 +672,7 @@ static hspmd_status varlen_bwd(const hspmd_attn_plan* plan, const void* q, const
         return fail(HSPMD_ERR_INVALID_ARG, "tensors and workspace must be 16-byte aligned");
     if (hspmd_status rc = check_strides(plan, q_token_stride, kv_token_stride)) return rc;
     if (workspace_bytes < statistics_bytes(plan))
-        return fail(HSPMD_ERR_WORKSPACE_TOO_SMALL, "workspace smaller than hspmd_attn_bwd_workspace_bytes(plan)");
+        return fail(HSPMD_ERR_WORKSPACE_TOO_SMALL, "workspace smaller than the row statistics, (2 * local_q_heads * total_tokens + 16) * 4 bytes");
     float scale = 0.f;
     if (hspmd_status rc = resolve_scale(softmax_scale, plan->head_dim, &scale)) return rc;
     hspmd::BwdParams p{};

@@ -12,8 +12,8 @@ namespace hspmd {
 
 // Work lists of small packs travel as the kernels' second argument: a refill then uploads nothing and a launch records no event
 // for it, and a workgroup reads its item together with the other arguments instead of behind a pointer among them.  A launch may
-// carry 4 KB of arguments (what the runtime appends to them not counted); beside the largest Params, 200 bytes, that is room for 240
-// slots (120 of the block variant).  Sequences of 17, 64 and 111 tokens, 2 heads, refill, forward and backward: 43.2 -> 23.8 us; two
+// carry 4 KB of arguments (what the runtime appends to them not counted); beside the largest Params, 224 bytes, and the 16 of
+// a marker like HeadPieces that is room for 240 slots (120 of the block variant), and all of it taken but for 16 bytes.  Sequences of 17, 64 and 111 tokens, 2 heads, refill, forward and backward: 43.2 -> 23.8 us; two
 // sequences of 2053 tokens on 8 heads, forward and backward 91.9 -> 86.6.
 constexpr int kArgumentBytes = 4096;
 constexpr int kListBytes = 3840;
