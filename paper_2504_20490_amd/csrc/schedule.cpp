@@ -472,12 +472,14 @@ bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t 
 // tokens, 1 to 8 KV heads and groups of 2 to 8, the 38 that this takes run in 0.74 of the time on average, 0.99 at worst; of 61 packs of 1000 to
 // 50000 tokens and 1 to 8 heads, most of one query head each, 18 in 0.75, 0.96 at worst.  The line is at 0.9 of the steps because idle time comes
 // back as clock: at 0.95 it also takes 32 heads on 8, 9 sequences of 103 .. 3079 321 / 322, and 10 on 5, head_dim 104, 8 of up to 12995 877 / 893.
-// Closer still, at 0.78, where the shares are whole items in one to two rounds and the items were halves: the estimate takes two workgroups
+// Closer still, at 0.77, where the shares are whole items in one to two rounds and the items were halves: the estimate takes two workgroups
 // that follow each other on a unit for the sum of their steps, and without its halves a long share starts last.  One sequence of 3596 tokens,
-// 16 heads on 8 111 / 124; 5438 tokens, 10 on 5, head_dim 80 82 / 89; 2332, 27 on 9 99 / 108; 3000, 16 on 8 87 / 90.  And where they are whole in more than
-// three rounds at head_dim above 112, whose whole items of several heads have a walk of their own that the shares lack: 13584 tokens, 40 on 5
-// 1324 / 1433; 25631, 21 on 3 2307 / 2405.  Of 900 packs of 256 to 40000 tokens, 1 to 16 KV heads and groups of 1 to 8 that the line at 0.9 takes 35
-// lost more than 1 %, with these two 5 (one 8 %); the 99 that they leave with their items would have taken 0.97 of the time on average.
+// 16 heads on 8 111 / 124; 5438 tokens, 10 on 5, head_dim 80 82 / 89; 2332, 27 on 9 99 / 108; 3000, 16 on 8 87 / 90.  At 0.72 for groups of more than
+// five heads, whose shares of two heads and more come out uneven (8622 to 9779 tokens among 17 sequences, 21 on 3, 1.02 to 1.09 of the time
+// on whole items).  And at the same lines where the shares are whole in more than three rounds at head_dim above 112, whose whole items of several
+// heads have a walk of their own that the shares lack: 13584 tokens, 40 on 5 1324 / 1433; 25631, 21 on 3 2307 / 2405.  Of 900 packs of 256 to
+// 40000 tokens, 1 to 16 KV heads and groups of 1 to 8 that the line at 0.9 takes 35 lost more than 1 %, with these 3 (35.1 / 36.4 the worst); the 105 that
+// they leave with their items would have taken 0.97 of the time on average.
 // Not against half items of single heads that are more than the units hold at once (5000, 3000 and 300 tokens, 3 heads 72 / 80; 16001 tokens, 2
 // heads 274 / 282).  Limits finer than a quarter of the mean only add sums; a limit of the mean leaves queues of 41 heavy shares on 32 units (8192
 // tokens, 16 on 4 617).
@@ -569,7 +571,7 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
     }
     if (best == 0) return false;
     // (see above)
-    if (!halves && least >= 0.78 * now && (whole_now ? head_dim > 112 && rounds > 3.0 : rounds > 1.15 && rounds < 2.3)) return false;
+    if (!halves && least >= (group > 5 ? 0.72 : 0.77) * now && (whole_now ? head_dim > 112 && rounds > 3.0 : rounds > 1.15 && rounds < 2.3)) return false;
 
     struct Share {
         int64_t cost;
