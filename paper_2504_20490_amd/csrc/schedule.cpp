@@ -476,10 +476,11 @@ bool persistent_dkv(Dispatch form, const PassLoad& load, int64_t slots, int32_t 
 // that follow each other on a unit for the sum of their steps, and without its halves a long share starts last.  One sequence of 3596 tokens,
 // 16 heads on 8 111 / 124; 5438 tokens, 10 on 5, head_dim 80 82 / 89; 2332, 27 on 9 99 / 108; 3000, 16 on 8 87 / 90.  At 0.72 for groups of more than
 // five heads, whose shares of two heads and more come out uneven (8622 to 9779 tokens among 17 sequences, 21 on 3, 1.02 to 1.09 of the time
-// on whole items).  And at the same lines where the shares are whole in more than three rounds at head_dim above 112, whose whole items of several
-// heads have a walk of their own that the shares lack: 13584 tokens, 40 on 5 1324 / 1433; 25631, 21 on 3 2307 / 2405.  Of 900 packs of 256 to
-// 40000 tokens, 1 to 16 KV heads and groups of 1 to 8 that the line at 0.9 takes 35 lost more than 1 %, with these 3 (35.1 / 36.4 the worst); the 105 that
-// they leave with their items would have taken 0.97 of the time on average.
+// on whole items).  Where the items were whole too, in more than three and a half rounds, at 0.87 (24268 tokens, 24 on 3, head_dim 104 1597 /
+// 1821; 36016, 20 on 4, 80 424 / 442), and for those groups at head_dim above 112, in more than three, at 0.8 (13584 tokens, 40 on 5 1324 /
+// 1433; 25631, 21 on 3 2307 / 2405; but 23554, 9 on 3 549 / 475).  Of 900 packs of 256 to
+// 40000 tokens, 1 to 16 KV heads and groups of 1 to 8 that the line at 0.9 takes 35 lost more than 1 %, with these 3 (35.1 / 36.4 the worst); the 107 that
+// they leave with their items would have taken 0.97 of the time on average.  Of 2568 that these lines take 10 lose more than 1 %; 0.68 on average.
 // Not against half items of single heads that are more than the units hold at once (5000, 3000 and 300 tokens, 3 heads 72 / 80; 16001 tokens, 2
 // heads 274 / 282).  Limits finer than a quarter of the mean only add sums; a limit of the mean leaves queues of 41 heavy shares on 32 units (8192
 // tokens, 16 on 4 617).
@@ -570,8 +571,12 @@ bool build_piece_list(const int32_t* cu, int32_t num_seqs, int32_t hq, int32_t h
         }
     }
     if (best == 0) return false;
-    // (see above)
-    if (!halves && least >= (group > 5 ? 0.72 : 0.77) * now && (whole_now ? head_dim > 112 && rounds > 3.0 : rounds > 1.15 && rounds < 2.3)) return false;
+    if (!halves) {   // (see above)
+        const double closer = group > 5 ? 0.72 : 0.77;
+        const double line = !whole_now ? (rounds > 1.15 && rounds < 2.3 ? closer : 0.9)
+                                       : group > 5 && head_dim > 112 && rounds > 3.0 ? 0.8 : rounds > 3.5 ? 0.87 : 0.9;
+        if (least >= line * now) return false;
+    }
 
     struct Share {
         int64_t cost;

@@ -150,7 +150,7 @@ for lengths in packs:
     assert sizes == sorted(sizes) and sizes[-1] <= 8 * hq * 65536 + 320 + (64 << 20)
 
 
-@pytest.mark.parametrize("long,short,count,hq,hkv,d", [(16000, 33, 2000, 4, 2, 104), (9000, 100, 578, 8, 1, 128), (5000, 1, 3000, 32, 4, 64)])
+@pytest.mark.parametrize("long,short,count,hq,hkv,d", [(16000, 33, 1000, 4, 2, 128), (9000, 100, 578, 8, 1, 128), (5000, 1, 3000, 32, 4, 64)])
 def test_sums_are_looked_for_among_the_items_that_have_some(stand_in, long, short, count, hq, hkv, d):
     """Few of a long list's items are dealt out: those of the long sequence."""
     program = """
@@ -165,7 +165,7 @@ calls(); plan.backward(); out([c for c in calls() if c[0] == "launch"])
 
 @pytest.mark.parametrize("lengths,hq,hkv,d", [
     ([3596], 16, 8, 128), ([2893, 2545], 10, 5, 80), ([3524], 16, 8, 96), ([2332], 27, 9, 128), ([1585, 482, 970], 20, 10, 104), ([3100], 16, 8, 128),
-    ([7158, 1551, 3781, 1094], 40, 5, 128), ([6735, 5618, 13278], 21, 3, 128), ([13846], 4, 2, 128),
+    ([7158, 1551, 3781, 1094], 40, 5, 128), ([6735, 5618, 13278], 21, 3, 128), ([13846], 4, 2, 128), ([5113, 5915, 5569, 7671], 24, 3, 104),
     ([1331, 426, 176, 433, 682, 390, 246, 77, 677, 287, 413, 341, 436, 509, 595, 487, 1391], 21, 3, 128)])
 def test_items_stay_whole_where_shares_would_take_longer(stand_in, lengths, hq, hkv, d):
     program = """
